@@ -23,11 +23,11 @@
 //                  no steering term), and record one (E, s) mass per 2048-logit chunk
 //                  in LDS.  A double-precision scan over the chunk masses locates the
 //                  chunk holding u*Z; only that chunk is read again to pick the token.
-//                  The full log-prob row is a second sweep, taken only on request.
 //                  Batches of at most 128 sequences share each recovery row between
 //                  several workgroups; the one that delivers its chunk masses last
 //                  draws the token (see accept_recover_kernel; hand-over by write-through
 //                  stores and an arrival counter, without cache-wide fences).
+//   recovery_logprob  the full log-prob rows, a second sweep over the rows at n_b, only on request.
 //
 // Precision: logits are widened exactly; sums of exponentials are accumulated in
 // fp32 (one rounding per term, pairwise across lanes), every per-row scalar
@@ -182,16 +182,21 @@ __device__ __forceinline__ Partial wave_combine(Acc a) {
 // first rejection, so the later positions of a sequence rejected early never need their rows.
 struct RowWindow {
     const int32_t* draft_len;  // NULL => K_b = k_max
-    const int32_t* alive;      // NULL => every sequence; else rows only where alive[b] != 0
+    const int32_t* state;      // NULL => every sequence; else rows only where state[b] == kInPlay
     int kmax, t_lo, t_hi;
 };
+
+// What the verdict kernel leaves per sequence: its first-rejection index (>= 0; final, Algorithm 1 has left its
+// loop), or one of
+constexpr int kInPlay = -1;   // nothing rejected so far and positions left to test
+constexpr int kFlagged = -2;  // length or a draft id out of range
 
 // Rows of sequence b inside the window.  A length outside [0, k_max] contributes none
 // (the sequence is flagged elsewhere).
 __device__ __forceinline__ int window_rows(const RowWindow& w, int b) {
     const int K = w.draft_len ? w.draft_len[b] : w.kmax;
     if (K < 0 || K > w.kmax) return 0;
-    if (w.alive && !w.alive[b]) return 0;
+    if (w.state && w.state[b] != kInPlay) return 0;
     return max(0, min(K, w.t_hi) - w.t_lo);
 }
 
@@ -348,14 +353,12 @@ struct RecArgs {
     const int32_t* off2;
     const Partial* partial1;
     const Partial* partial2;
-    const int32_t* alive;    // two passes: sequences whose later positions were scored; else NULL
-    const int32_t* flagged;  // two passes: bad length or draft id, found by the verdict kernel; else NULL
-    const int32_t* first_rej;  // two passes: first rejection inside the first window (verdict kernel)
+    const int32_t* state;    // two passes: what the verdict kernel found per sequence; else NULL
     int t1, rows1;
     int32_t* accepted_len;
     int32_t* next_token;
     float* next_token_logprob;
-    float* recovery_logprobs;
+    double* log2z;           // [B] log2 of the recovery row's normaliser, for the log-prob rows; else NULL
     float* draft_logprobs;
     long sb, st;
     int B, kmax, V;
@@ -751,8 +754,7 @@ __device__ __forceinline__ void ratio_test_block(const RecArgs& a, int b, int T0
 constexpr int kVerdictThreads = 64;  // one wave per sequence: a lane per (position, tensor) pair is plenty
 
 template <int DT>
-__global__ __launch_bounds__(kVerdictThreads) void verdict_kernel(const RecArgs a, int32_t* alive, int32_t* flagged,
-                                                              int32_t* first_rej) {
+__global__ __launch_bounds__(kVerdictThreads) void verdict_kernel(const RecArgs a, int32_t* state) {
     extern __shared__ double smem_d[];
     __shared__ int sh_n, sh_bad;
     const int b = blockIdx.x, tid = threadIdx.x;
@@ -775,12 +777,7 @@ __global__ __launch_bounds__(kVerdictThreads) void verdict_kernel(const RecArgs 
     __syncthreads();
     const int Kt = sh_bad ? 0 : min(K, a.t1);
     ratio_test_block<DT, kVerdictThreads>(a, b, 0, Kt, smem_d, &sh_n, &sh_bad);
-    if (tid == 0) {
-        const bool bad = sh_bad != 0;
-        alive[b] = (!bad && sh_n == Kt && K > a.t1) ? 1 : 0;
-        flagged[b] = bad ? 1 : 0;
-        first_rej[b] = sh_n;
-    }
+    if (tid == 0) state[b] = sh_bad ? kFlagged : (sh_n == Kt && K > a.t1 ? kInPlay : sh_n);
 }
 
 // Best candidate of the wave, left in every lane: larger value, then lower index.
@@ -802,7 +799,7 @@ __device__ __forceinline__ void wave_best(Best& best) {
 //   2b  wave 0: Eq. 7 on every position, first rejection by ballot
 //   3   all waves stream the three rows at the rejected (or bonus) position once, one (E, s)
 //       mass per 2048-logit chunk into LDS
-//   4   wave 0 draws the token; optionally all waves sweep the rows again to write log-probs
+//   4   wave 0 draws the token
 // Only workgroup barriers separate the steps; nothing crosses workgroups.
 //
 // SPLIT (small batches, where one workgroup per sequence leaves most of the chip idle): a.parts
@@ -815,7 +812,6 @@ template <int DT, int VEC, bool GREEDY, bool SPLIT, bool PLAIN, int NT>
 __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     extern __shared__ double smem_d[];
     __shared__ int sh_n, sh_bad, sh_last;
-    __shared__ double sh_log2Z;
     __shared__ double sh_best_v[kRecThreads / kWave];  // one slot per wave, or per part in the merge of a split row
     __shared__ long sh_best_i[kRecThreads / kWave];
 
@@ -829,19 +825,19 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     Partial* tab = reinterpret_cast<Partial*>(smem_d + 2 * kmax);   // [NC] chunk masses
 
     const int K = a.draft_len ? a.draft_len[b] : kmax;
-    const bool bad_len = (K < 0 || K > kmax) || (a.flagged && a.flagged[b]);
-    // Two-pass schedule: a sequence the verdict kernel saw rejected inside the first window keeps
-    // that first-rejection index (its later rows were never scored); a sequence still in play after
-    // that window is tested here on its remaining positions, any other over all K positions.
-    const bool in_play = a.alive && a.alive[b] && !bad_len;
-    const bool settled = a.alive && !in_play && !bad_len && K > a.t1;
+    const int state = a.state ? a.state[b] : kInPlay;
+    const bool bad_len = K < 0 || K > kmax || state == kFlagged;
+    // Two-pass schedule: a sequence the verdict kernel saw rejected (or at its end) inside the first window keeps
+    // that first-rejection index; a sequence still in play after that window is tested here on its remaining
+    // positions.  One pass: every sequence is tested here over all K positions.
+    const bool settled = state >= 0 && !bad_len;
     const int Kt = bad_len ? 0 : K;
     if (tid == 0) {
         sh_bad = bad_len ? 1 : 0;
-        sh_n = settled ? a.first_rej[b] : 0;
+        sh_n = settled ? state : 0;
     }
     __syncthreads();
-    if (!settled) ratio_test_block<DT, NT>(a, b, in_play ? a.t1 : 0, Kt, lp, &sh_n, &sh_bad);
+    if (!settled) ratio_test_block<DT, NT>(a, b, a.state ? a.t1 : 0, Kt, lp, &sh_n, &sh_bad);
     const bool bad = sh_bad != 0;
     if (a.draft_logprobs && part == 0) {  // valid positions from LDS, padded slots 0, a flagged sequence NaN throughout
         const float nanv = __int_as_float(0x7FC00000);
@@ -924,31 +920,79 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
             wave_best(best);
         }
         const double log2Z = sample_wave<DT, VEC, GREEDY, PLAIN>(a, b, n, lane, tab, g, sp, sm, nvec, tailc, nch, best);
-        if (lane == 0) sh_log2Z = log2Z;
+        if (a.log2z && lane == 0) a.log2z[b] = log2Z;
     }
-    if (a.recovery_logprobs) {
-        __syncthreads();
-        const double log2Z = sh_log2Z;
-        float* out = a.recovery_logprobs + (long)b * V;
-        for (long v = tid; v < nvec; v += NT) {
-            float hg[VEC], hp[VEC], hm[VEC];
-            unpack(ld_raw<DT, VEC>(g, v), hg);
-            if (PLAIN) {
+}
+
+// ------------------------------------------------------------------ kernel: log-prob rows
+
+struct LogprobArgs {
+    const void* G;
+    const void* recSp;
+    const void* recSm;
+    const int32_t* accepted_len;  // the row n_b of every sequence, -1 for a flagged one
+    const double* log2z;
+    float* out;                   // [B, V]
+    long sb, st;
+    int V;
+    int segs;                     // workgroups per row
+    double c, bc;
+};
+
+constexpr int kLogprobThreads = 256;
+constexpr int kLogprobUnroll = 2;  // vectors per tensor a thread has in flight
+
+// fp32 pair or quad stored at any element boundary (an odd vocabulary size starts its rows anywhere)
+__device__ __forceinline__ void st_f32x4(float* p, float x, float y, float z, float w) {
+    const f32x4 v = {x, y, z, w};
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
+}
+
+// log Softmax(h_rec / T) at row n_b, after accept_recover has left n_b and the row's log2-normaliser.
+// HBM-bound: three rows read and one fp32 row written per sequence.  It is a launch of its own because the
+// workgroup that draws a sequence's token is one of at most a few hundred, each tied to the rate of one
+// compute unit (16 sequences of V = 151936 bf16: 40 us of a 57 us recovery kernel); cut into segments of
+// two vectors a thread, the same sweep covers the chip.
+template <int DT, int VEC, bool PLAIN>
+__global__ __launch_bounds__(kLogprobThreads) void recovery_logprob_kernel(const LogprobArgs a) {
+    const int b = (int)blockIdx.x / a.segs, seg = (int)blockIdx.x - b * a.segs;
+    const int n = a.accepted_len[b];
+    if (n < 0) return;  // a flagged sequence's row is left unwritten
+    const double log2Z = a.log2z[b];
+    const long off = (long)b * a.sb + (long)n * a.st;
+    const void* g = row_ptr<DT>(a.G, off);
+    const void* sp = row_ptr<DT>(a.recSp, off);
+    const void* sm = row_ptr<DT>(a.recSm, off);
+    const long nvec = a.V / VEC;
+    float* out = a.out + (long)b * a.V;
+    const long v0 = (long)seg * (kLogprobThreads * kLogprobUnroll) + threadIdx.x;
+    typename RawT<DT, VEC>::type rg[kLogprobUnroll], rp[kLogprobUnroll], rm[kLogprobUnroll];
 #pragma unroll
-                for (int i = 0; i < VEC; ++i) hp[i] = hm[i] = 0.f;
-            } else {
-                unpack(ld_raw<DT, VEC>(sp, v), hp);
-                unpack(ld_raw<DT, VEC>(sm, v), hm);
+    for (int j = 0; j < kLogprobUnroll; ++j) {
+        const long v = v0 + j * kLogprobThreads;
+        if (v < nvec) {
+            rg[j] = ld_raw<DT, VEC>(g, v);
+            if (!PLAIN) {
+                rp[j] = ld_raw<DT, VEC>(sp, v);
+                rm[j] = ld_raw<DT, VEC>(sm, v);
             }
-#pragma unroll
-            for (int i = 0; i < VEC; ++i)
-                out[v * VEC + i] = (float)(kLn2 * (rec_y(hg[i], hp[i], hm[i], a.c, a.bc) - log2Z));
-        }
-        if (tid < tailc) {
-            const long e = nvec * VEC + tid;
-            out[e] = (float)(kLn2 * (rec_y(ld_elem<DT>(g, e), ld_steer<DT, PLAIN>(sp, e), ld_steer<DT, PLAIN>(sm, e), a.c, a.bc) - log2Z));
         }
     }
+#pragma unroll
+    for (int j = 0; j < kLogprobUnroll; ++j) {
+        const long v = v0 + j * kLogprobThreads;
+        if (v >= nvec) break;
+        float hg[VEC], hp[VEC], hm[VEC], o[VEC];
+        unpack(rg[j], hg);
+        unpack_steer<DT, VEC, PLAIN>(rp[j], rm[j], hp, hm);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) o[i] = (float)(kLn2 * (rec_y(hg[i], hp[i], hm[i], a.c, a.bc) - log2Z));
+#pragma unroll
+        for (int i = 0; i < VEC; i += 4) st_f32x4(out + v * VEC + i, o[i], o[i + 1], o[i + 2], o[i + 3]);
+    }
+    const long e = nvec * VEC + threadIdx.x;  // logits past the last full vector
+    if (seg == a.segs - 1 && e < a.V)
+        out[e] = (float)(kLn2 * (rec_y(ld_elem<DT>(g, e), ld_steer<DT, PLAIN>(sp, e), ld_steer<DT, PLAIN>(sm, e), a.c, a.bc) - log2Z));
 }
 
 __global__ void zero_u32_kernel(uint32_t* p, int n) {
@@ -963,7 +1007,7 @@ struct Plan {
     int NS2, slice_vecs2;  // second row pass
     int NSf, slice_vecsf;  // one pass over all k_max positions (taken when draft_logprobs is requested)
     int t1;          // positions in the first row pass; == k_max when the block is verified in one pass
-    size_t off_list2, off_alive, off_flagged, off_firstrej, off_partial;
+    size_t off_list2, off_log2z, off_state, off_partial;
     size_t off_arrive, off_part_best, off_chunk_tab;  // split recovery; only present for small batches
     size_t bytes;
 };
@@ -1044,9 +1088,8 @@ Plan make_plan(const ss_params* p) {
     const size_t B = (size_t)p->batch;
     size_t o = align_up((B + 1) * sizeof(int32_t), 256);  // row list of the first pass
     pl.off_list2 = o;    o += align_up((B + 1) * sizeof(int32_t), 256);      // row list of the second pass
-    pl.off_alive = o;    o += align_up((B ? B : 1) * sizeof(int32_t), 256);
-    pl.off_flagged = o;  o += align_up((B ? B : 1) * sizeof(int32_t), 256);
-    pl.off_firstrej = o; o += align_up((B ? B : 1) * sizeof(int32_t), 256);
+    pl.off_log2z = o;    o += 2 * align_up((B ? B : 1) * sizeof(int32_t), 256);  // one double per sequence
+    pl.off_state = o;    o += align_up((B ? B : 1) * sizeof(int32_t), 256);
     pl.off_partial = o;
     // sized for the one-pass schedule as well (a call that asks for draft_logprobs takes it): all
     // k_max positions at the finer of the two slicings
@@ -1090,13 +1133,12 @@ void launch_row_pass(LseArgs la, const RowWindow& win, int uniform_rows, int32_t
 }
 
 template <int DT, int VEC>
-hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, hipStream_t stream, hipEvent_t* ev) {
+hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* recovery_logprobs, hipStream_t stream,
+                      hipEvent_t* ev) {
     const int B = ra.B, kmax = ra.kmax, V = ra.V;
     int32_t* off1 = reinterpret_cast<int32_t*>(ws);
     int32_t* off2 = reinterpret_cast<int32_t*>(ws + pl.off_list2);
-    int32_t* alive = reinterpret_cast<int32_t*>(ws + pl.off_alive);
-    int32_t* flagged = reinterpret_cast<int32_t*>(ws + pl.off_flagged);
-    int32_t* first_rej = reinterpret_cast<int32_t*>(ws + pl.off_firstrej);
+    int32_t* state = reinterpret_cast<int32_t*>(ws + pl.off_state);
     Partial* partial1 = reinterpret_cast<Partial*>(ws + pl.off_partial);
     // the verdict's position-by-position log-probs are only complete in the one-pass schedule
     const int t1 = ra.draft_logprobs ? kmax : pl.t1;
@@ -1119,9 +1161,8 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, hipStrea
     ra.t1 = t1;
     ra.rows1 = ragged ? 0 : t1;
     ra.off1 = off1; ra.off2 = off2; ra.partial1 = partial1; ra.partial2 = partial2;
-    ra.alive = two_pass ? alive : nullptr;
-    ra.flagged = two_pass ? flagged : nullptr;
-    ra.first_rej = two_pass ? first_rej : nullptr;
+    ra.state = two_pass ? state : nullptr;
+    ra.log2z = recovery_logprobs ? reinterpret_cast<double*>(ws + pl.off_log2z) : nullptr;
     ra.NC = chunks_per_row(V, VEC);
     const int cus = device_cu_count();
     ra.parts = recovery_parts(B, ra.NC, cus);
@@ -1142,13 +1183,13 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, hipStrea
     mark(1);
     if (two_pass)
         hipLaunchKernelGGL((verdict_kernel<DT>), dim3((unsigned)B), dim3(kVerdictThreads), (size_t)2 * kmax * sizeof(double),
-                           stream, ra, alive, flagged, first_rej);
+                           stream, ra, state);
     mark(2);
     if (two_pass) {
         la.NS = pl.NS2;
         la.slice_vecs = pl.slice_vecs2;
         la.zero_n = 0;
-        launch_row_pass<DT, VEC>(la, RowWindow{ra.draft_len, alive, kmax, t1, kmax}, 0, off2, partial2,
+        launch_row_pass<DT, VEC>(la, RowWindow{ra.draft_len, state, kmax, t1, kmax}, 0, off2, partial2,
                                           (long)B * (kmax - t1), stream);
     }
     mark(3);
@@ -1172,6 +1213,18 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, hipStrea
     else
         hipLaunchKernelGGL(rec_kernels[(ra.greedy ? 1 : 0) | (split ? 2 : 0) | (ra.plain ? 4 : 0)], rec_grid,
                            dim3(kFull), smem, stream, ra);
+    if (recovery_logprobs) {
+        const long nvec = V / VEC, per = kLogprobThreads * kLogprobUnroll;
+        const int segs = nvec > per ? (int)((nvec + per - 1) / per) : 1;
+        const LogprobArgs pa{ra.G, ra.recSp, ra.recSm, ra.accepted_len, ra.log2z, recovery_logprobs, ra.sb, ra.st, V,
+                             segs, ra.c, ra.bc};
+        if (ra.plain)
+            hipLaunchKernelGGL((recovery_logprob_kernel<DT, VEC, true>), dim3((unsigned)(B * segs)),
+                               dim3(kLogprobThreads), 0, stream, pa);
+        else
+            hipLaunchKernelGGL((recovery_logprob_kernel<DT, VEC, false>), dim3((unsigned)(B * segs)),
+                               dim3(kLogprobThreads), 0, stream, pa);
+    }
     mark(4);
     const hipError_t launch_err = hipGetLastError();
     return launch_err != hipSuccess ? launch_err : ev_err;
@@ -1224,7 +1277,7 @@ ss_status verify_block_impl(const void* G, const void* S_ctx, const void* S_noct
     const bool steer = params->beta != 0.f;
     ra.G = G; ra.Sm = S_noctx; ra.recSp = steer ? S_ctx : G; ra.recSm = steer ? S_noctx : G; ra.draft = draft; ra.draft_len = draft_len; ra.uniforms = uniforms;
     ra.accepted_len = accepted_len; ra.next_token = next_token;
-    ra.next_token_logprob = next_token_logprob; ra.recovery_logprobs = recovery_logprobs;
+    ra.next_token_logprob = next_token_logprob;
     ra.draft_logprobs = draft_logprobs; ra.sb = sb; ra.st = st; ra.B = params->batch; ra.kmax = params->k_max;
     ra.V = params->vocab; ra.NS = pl.NS; ra.NS2 = pl.NS2; ra.NC = 0; ra.c = c;
     ra.bc = (double)params->beta * c; ra.ln_lambda = std::log((double)params->lambda);
@@ -1238,9 +1291,9 @@ ss_status verify_block_impl(const void* G, const void* S_ctx, const void* S_noct
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t err;
     if (params->dtype == SS_BF16) {
-        err = launch_all<SS_BF16, 8>(la, ra, pl, ws, s, ev);
+        err = launch_all<SS_BF16, 8>(la, ra, pl, ws, recovery_logprobs, s, ev);
     } else {
-        err = launch_all<SS_F32, 4>(la, ra, pl, ws, s, ev);
+        err = launch_all<SS_F32, 4>(la, ra, pl, ws, recovery_logprobs, s, ev);
     }
     return err == hipSuccess ? SS_OK : SS_ERR_DEVICE;
 }
