@@ -39,6 +39,20 @@ __device__ __forceinline__ int wave_max_i32(int v) {
     return max(max(a, b), max(c, d));
 }
 
+// The same inside each 16-lane row only; every lane of a row ends with its row's value.
+__device__ __forceinline__ int row_max_i32(int v) {
+    v = max(v, dpp_mov<kDppXor1>(v));
+    v = max(v, dpp_mov<kDppXor2>(v));
+    v = max(v, dpp_mov<kDppHalfMirror>(v));
+    return max(v, dpp_mov<kDppMirror>(v));
+}
+__device__ __forceinline__ float row_sum_f32(float x) {
+    x += __int_as_float(dpp_mov<kDppXor1>(__float_as_int(x)));
+    x += __int_as_float(dpp_mov<kDppXor2>(__float_as_int(x)));
+    x += __int_as_float(dpp_mov<kDppHalfMirror>(__float_as_int(x)));
+    return x + __int_as_float(dpp_mov<kDppMirror>(__float_as_int(x)));
+}
+
 __device__ __forceinline__ int wave_sum_i32(int v) {
     v += dpp_mov<kDppXor1>(v);
     v += dpp_mov<kDppXor2>(v);
@@ -88,11 +102,20 @@ __device__ __forceinline__ double wave_incl_scan_f64(double x) {
 
 // Exclusive companion of an inclusive scan result (lane 0 gets 0) and the wave total.
 __device__ __forceinline__ double wave_shift_up_f64(double incl) { return dpp_f64_or_zero<kDppWaveShr1, 0xF>(incl); }
-__device__ __forceinline__ double wave_last_f64(double incl) {
-    const long long b = __double_as_longlong(incl);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xFFFFFFFFll), 63);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+__device__ __forceinline__ double wave_readlane_f64(double x, int lane) {  // `lane` wave-uniform
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xFFFFFFFFll), lane);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double wave_last_f64(double incl) { return wave_readlane_f64(incl, 63); }
+
+// What this wave's lanes wrote to LDS is visible to its other lanes: LDS operations of one wave complete in
+// order, so only the compiler has to keep them in place.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __device__ __forceinline__ int first_lane(unsigned long long mask) { return __ffsll((long long)mask) - 1; }

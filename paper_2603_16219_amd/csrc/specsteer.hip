@@ -14,8 +14,8 @@
 //                  exclusive scan of the draft lengths that every workgroup rebuilds in
 //                  LDS at kernel start (prep_rows does it once in global memory for
 //                  batches too large for LDS).
-//   accept_recover one 16-wave workgroup per sequence.  Each (position, tensor) pair
-//                  gets a lane that merges the row's slice partials and gathers the draft
+//   accept_recover one workgroup per sequence, or several.  Each (position, tensor) pair
+//                  gets 16 lanes that merge the row's slice partials and gather the draft
 //                  token's logit; wave 0 applies the ratio test and finds the first
 //                  rejection with a ballot.  All waves then stream the three logit rows
 //                  of the rejected (or bonus) position once, forming the recovery
@@ -60,14 +60,15 @@ constexpr int kMinSliceVecs = kWave * kLseUnroll;  // smallest slice: one unroll
 constexpr int kMaxSliceVecs = SS_LSE_MAX_SLICE_VECS;  // 64 KiB of logits per slice
 constexpr int kMaxSlices = 64;
 constexpr int kMaxLdsBatch = 8192;          // ragged batches up to this size keep their row list in LDS
+// Arrival counters of different sequences lie 256 bytes apart: atomics on one cache line are served one after the
+// other, 7.4 ns each (4800 arrivals on 64 neighbouring counters: 36 us; 256 or 64 bytes apart: no queue).
+constexpr int kArriveStride = 64;
 constexpr int kChunkSteps = 4;              // recovery chunk = 4 wave-steps (2048 bf16 logits)
 constexpr int kEInit = -(1 << 29);          // "no logit seen yet" exponent reference
 constexpr float kEClamp = 5.0e8f;           // keeps (int)ceil(h*c) inside int32 for any finite h
 constexpr double kLn2 = 0.693147180559945309417232121458;
 constexpr double kLog2e = 1.442695040888963407359924681002;
 
-constexpr int kRecThreads = 1024;           // accept + recover: one 16-wave workgroup per sequence ...
-constexpr int kRecThreadsHalf = 512;        // ... or two 8-wave workgroups per CU when sequences outnumber the CUs
 
 struct Partial {
     int E;    // integer exponent reference of this slice
@@ -275,7 +276,7 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
     if (blockIdx.x == 0 && ragged && a.list_in_lds)
         for (int i = threadIdx.x; i <= a.B; i += kLseThreads) a.row_off[i] = lds_off[i];
     if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < a.zero_n; i += kLseThreads) a.zero_ptr[i] = 0u;
+        for (int i = threadIdx.x; i < a.zero_n; i += kLseThreads) a.zero_ptr[(long)i * kArriveStride] = 0u;
     const int R = ragged ? off[a.B] : a.B * a.uniform_rows;
     const long items = (long)R * 2 * a.NS;
     const long slice_units = a.slice_vecs;
@@ -373,10 +374,11 @@ struct RecArgs {
     int greedy;      // SS_FLAG_GREEDY
     int plain;       // beta == 0: no steering term, the specialist rows are not read by the recovery sweep
     // Split recovery (small batches): `parts` workgroups share the recovery row of one sequence.
-    int parts;
+    int parts, part_chunks;  // part i takes chunks [i * part_chunks, (i+1) * part_chunks)
     Partial* chunk_tab;   // [B][NC] chunk masses, filled by the parts
-    Best* part_best;      // [B][parts] greedy candidates of the parts
-    uint32_t* arrive;     // [B] parts that have delivered; cleared by the first row pass
+    double* best_v;       // [B][NC] greedy candidates of the waves: value ...
+    int32_t* best_i;      // [B][NC] ... and token
+    uint32_t* arrive;     // [B][kArriveStride] waves that have delivered; cleared by the first row pass
 };
 
 // Hand-over between workgroups that may run on different XCDs, whose L2 caches are not coherent with each
@@ -399,25 +401,28 @@ __device__ __forceinline__ Partial ld_dev_partial(const Partial* p) {
 // every memory operation this wave has issued so far has completed: s_waitcnt vmcnt(0) lgkmcnt(0)
 __device__ __forceinline__ void wait_stores() { __builtin_amdgcn_s_waitcnt(0x0070); }
 
-// log2 of sum_v 2^(h_v * c) for one row from its slice partials, by one lane: the partials are merged in
-// slice order (sixteen loads in flight at a time), so the result does not depend on who computes it.
-__device__ __forceinline__ double combine_partials_lane(const Partial* p, int ns, double rho) {
+// log2 of sum_v 2^(h_v * c) for one row from its slice partials, by the 16 lanes of one DPP row (`l` is the lane's
+// index in it, every lane returns the value): lane l takes slices l, l+16, ..., four loads in flight, and the 16
+// running pairs are merged by a fixed pattern, so the result does not depend on who computes it.  One lane per row
+// (all slices in turn) spends a round trip per 16 slices and some 60 clocks per merge: with the 38
+// slices of V = 151936 that was a third of the 4.5 us before the first rejection was known.
+__device__ __forceinline__ double combine_partials_row16(const Partial* p, int ns, double rho, int l) {
     int Em = kEInit;
     float S = 0.f;
-    for (int k0 = 0; k0 < ns; k0 += 16) {
-        Partial pv[16];
+    for (int k0 = l; k0 < ns; k0 += 64) {
+        Partial pv[4];
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (k0 + i < ns) pv[i] = p[k0 + i];
+        for (int i = 0; i < 4; ++i) pv[i] = k0 + 16 * i < ns ? p[k0 + 16 * i] : Partial{kEInit, 0.f};
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (k0 + i < ns) {
-                const int En = max(Em, pv[i].E);
-                S = ldexpf(S, Em - En) + ldexpf(pv[i].s, pv[i].E - En);
-                Em = En;
-            }
+        for (int i = 0; i < 4; ++i) {
+            const int En = max(Em, pv[i].E);
+            S = ldexpf(S, Em - En) + ldexpf(pv[i].s, pv[i].E - En);
+            Em = En;
+        }
     }
-    return (double)Em * (1.0 + rho) + log2((double)S);  // E*rho: see acc_add_f32
+    const int Er = row_max_i32(Em);
+    S = row_sum_f32(ldexpf(S, Em - Er));
+    return (double)Er * (1.0 + rho) + log2((double)S);  // E*rho: see acc_add_f32
 }
 
 // PLAIN (beta == 0): the recovery distribution is Softmax(h_LLM / T); the two specialist rows are
@@ -442,35 +447,33 @@ __device__ __forceinline__ float ld_steer(const void* row, long e) {
 // Probability terms 2^(y - E) of the logits one lane owns in recovery chunk c, laid out so that
 // a lane's logits are consecutive in the vocabulary: lane l holds vectors 4l..4l+3 of the chunk.
 // The pseudo-chunk c == nch holds the < VEC logits past the last full vector, one per lane.
-// cnt[j] says how many entries of p[j] are valid; first[j] is the vocabulary index of p[j][0].
+// Terms of logits that do not exist are 0.
 // PLAIN forms the terms as the sweep did, 2^(fma(h, c_hi, -E)) in fp32.
 template <int DT, int VEC, bool PLAIN>
 __device__ __forceinline__ void chunk_lane_terms(const void* g, const void* sp, const void* sm, long nvec, int tailc,
                                                  long nch, long c, int lane, double cc, double bc, float c_hi, int E,
-                                                 float (&p)[kChunkSteps][VEC], long (&first)[kChunkSteps],
-                                                 int (&cnt)[kChunkSteps]) {
+                                                 float (&p)[kChunkSteps][VEC]) {
     const double dE = (double)E;
     const float nE = -(float)E;
     typename RawT<DT, VEC>::type rg[kChunkSteps], rp[kChunkSteps], rm[kChunkSteps];
+    bool ok[kChunkSteps];
 #pragma unroll
     for (int j = 0; j < kChunkSteps; ++j) {
         const long v = c * (long)(kWave * kChunkSteps) + (long)lane * kChunkSteps + j;
-        cnt[j] = 0;
-        first[j] = v * VEC;
-        if (c < nch && v < nvec) {
+        ok[j] = c < nch && v < nvec;
+        if (ok[j]) {
             rg[j] = ld_raw<DT, VEC>(g, v);
             if (!PLAIN) {
                 rp[j] = ld_raw<DT, VEC>(sp, v);
                 rm[j] = ld_raw<DT, VEC>(sm, v);
             }
-            cnt[j] = VEC;
         }
     }
 #pragma unroll
     for (int j = 0; j < kChunkSteps; ++j) {
 #pragma unroll
         for (int i = 0; i < VEC; ++i) p[j][i] = 0.f;
-        if (cnt[j]) {
+        if (ok[j]) {
             float hg[VEC], hp[VEC], hm[VEC];
             unpack(rg[j], hg);
             unpack_steer<DT, VEC, PLAIN>(rp[j], rm[j], hp, hm);
@@ -481,12 +484,11 @@ __device__ __forceinline__ void chunk_lane_terms(const void* g, const void* sp, 
         }
     }
     if (c >= nch && lane < tailc) {
-        first[0] = nvec * VEC + lane;
-        cnt[0] = 1;
-        const float hg = ld_elem<DT>(g, first[0]);
+        const long e = nvec * VEC + lane;
+        const float hg = ld_elem<DT>(g, e);
         p[0][0] = PLAIN ? __builtin_amdgcn_exp2f(fmaf(hg, c_hi, nE))
-                        : __builtin_amdgcn_exp2f((float)(rec_y(hg, ld_steer<DT, PLAIN>(sp, first[0]),
-                                                               ld_steer<DT, PLAIN>(sm, first[0]), cc, bc) - dE));
+                        : __builtin_amdgcn_exp2f((float)(rec_y(hg, ld_steer<DT, PLAIN>(sp, e),
+                                                               ld_steer<DT, PLAIN>(sm, e), cc, bc) - dE));
     }
 }
 
@@ -570,10 +572,11 @@ __device__ __forceinline__ Partial chunk_mass(const void* g, const void* sp, con
 // Inverse-CDF draw for one sequence by one wave, from the chunk masses `tab` (LDS) of its
 // recovery row: a double-precision scan over the masses finds the chunk holding u*Z, and only
 // that chunk is read again to pick the token.  Returns log2 Z; writes the per-sequence outputs.
+// lane_terms: LDS for the terms of one lane.
 template <int DT, int VEC, bool GREEDY, bool PLAIN>
 __device__ __forceinline__ double sample_wave(const RecArgs& a, int b, int n, int lane, const Partial* tab,
                                               const void* g, const void* sp, const void* sm, long nvec, int tailc,
-                                              long nch, Best greedy_pick) {
+                                              long nch, Best greedy_pick, float* lane_terms) {
     const int NC = a.NC;
     const double us = (double)a.uniforms[(long)b * (a.kmax + 1) + a.kmax];
     // each lane owns a contiguous run of `per` chunks
@@ -625,7 +628,8 @@ __device__ __forceinline__ double sample_wave(const RecArgs& a, int b, int n, in
         take_last = true;
     }
 
-    // re-read that chunk with each lane holding consecutive logits: one scan over the lanes.  The terms are
+    // re-read that chunk with each lane holding consecutive logits: one scan over the lanes finds the lane that
+    // holds the token, one scan over that lane's logits the token.  The terms are
     // taken relative to the chunk's own exponent reference, 2^(y - Ec), so that the logits that carry the
     // chunk are normal fp32 numbers however far the chunk sits below the row's maximum; `sc` brings them
     // to the scale of the chunk table in double, exactly.
@@ -636,57 +640,47 @@ __device__ __forceinline__ double sample_wave(const RecArgs& a, int b, int n, in
     // is y_hi * (1 + rho), and the row's log2-sum moves by rho * E* to first order (see acc_add_f32)
     const double fix = PLAIN ? a.rho : 0.0;
     float p[kChunkSteps][VEC];
-    long first[kChunkSteps];
-    int cnt[kChunkSteps];
-    chunk_lane_terms<DT, VEC, PLAIN>(g, sp, sm, nvec, tailc, nch, cstar, lane, a.c, a.bc, a.c_hi, Ec, p, first, cnt);
-    double ls = 0.0;
-    long lastpos = -1;
+    chunk_lane_terms<DT, VEC, PLAIN>(g, sp, sm, nvec, tailc, nch, cstar, lane, a.c, a.bc, a.c_hi, Ec, p);
+    double lsj[kChunkSteps];
 #pragma unroll
     for (int j = 0; j < kChunkSteps; ++j) {
+        lsj[j] = 0.0;
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-            ls += (double)p[j][i] * sc;
-            if (i < cnt[j] && p[j][i] > 0.f) lastpos = first[j] + i;
+        for (int i = 0; i < VEC; ++i) lsj[j] += (double)p[j][i];
+    }
+    const double ls = (lsj[0] + lsj[1]) + (lsj[2] + lsj[3]);
+    const double incl_l = wave_incl_scan_f64(ls * sc);
+    const double start = wave_shift_up_f64(incl_l) + base;
+    const unsigned long long hmask = __ballot(!take_last && incl_l + base > target);
+    const unsigned long long pmask = __ballot(ls > 0.0);
+    // No lane reaches the target (rounding between the chunk table and the re-read, or take_last): the last
+    // logit of the chunk that still carries probability
+    const int L = hmask ? first_lane(hmask) : (pmask ? 63 - __clzll((long long)pmask) : 0);
+    constexpr int kOwn = kChunkSteps * VEC;  // consecutive logits a lane holds
+    if (lane == L) {
+#pragma unroll
+        for (int j = 0; j < kChunkSteps; ++j) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) lane_terms[j * VEC + i] = p[j][i];
         }
     }
-    double cw = wave_shift_up_f64(wave_incl_scan_f64(ls)) + base;
-    long mytok = -1;
-    float ptok = 0.f, plast = 0.f;
-#pragma unroll
-    for (int j = 0; j < kChunkSteps; ++j) {
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) {
-            cw += (double)p[j][i] * sc;
-            if (i < cnt[j] && p[j][i] > 0.f) plast = p[j][i];
-            if (!take_last && mytok < 0 && i < cnt[j] && cw > target) {
-                mytok = first[j] + i;
-                ptok = p[j][i];
-            }
-        }
-    }
-    long tok;
-    const unsigned long long hmask = __ballot(mytok >= 0);
-    if (hmask) {
-        const int L = first_lane(hmask);
-        tok = __shfl(mytok, L, kWave);
-        ptok = __shfl(ptok, L, kWave);
-    } else {
-        // rounding between the chunk table and the re-read (or take_last): the last logit of
-        // the chunk that still carries probability
-        long best = lastpos;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) best = max(best, __shfl_xor(best, d, kWave));
-        const unsigned long long omask = __ballot(lastpos == best && best >= 0);
-        // the chunk's largest logit is within one unit of Ec, so a positive term always exists unless
-        // the row holds something that is not a number; keep the index valid then
-        tok = omask ? best : min((long)cstar * (kWave * kChunkSteps * VEC), (long)a.V - 1);
-        ptok = omask ? __shfl(plast, first_lane(omask), kWave) : 1.f;
-    }
+    wave_lds_sync();
+    const float pl = lane < kOwn ? lane_terms[lane] : 0.f;
+    const double incl_i = wave_incl_scan_f64((double)pl * sc) + wave_readlane_f64(start, L);
+    const unsigned long long over = __ballot(hmask != 0ull && pl > 0.f && incl_i > target);
+    const unsigned long long pos = __ballot(pl > 0.f);
+    // the chunk's largest logit is within one unit of Ec, so a positive term always exists unless the row
+    // holds something that is not a number; keep the index valid then
+    const int i = over ? first_lane(over) : (pos ? 63 - __clzll((long long)pos) : 0);
+    const float ptok = pos ? __shfl(pl, i, kWave) : 1.f;
+    const long tok = cstar < nch ? min(((long)cstar * kWave + L) * kOwn + i, (long)a.V - 1) : nvec * VEC + min(L, tailc - 1);
     // the chosen logit's exponent back from its term: 2^(y - Ec) is a normal fp32 number with one
-    // ulp of error, so log2 of it is good to ~2e-7 whatever the magnitude of y
-    const double ytok_hi = dE + log2((double)ptok);
+    // ulp of error, so log2 of it is good to ~2e-7 whatever the magnitude of y.  Lane 0 takes the logarithm
+    // of the total, lane 1 that of the term.
+    const double lg = log2(lane == 0 ? total : (double)ptok);
+    const double ytok_hi = dE + wave_readlane_f64(lg, 1);
     const double ytok = ytok_hi + fix * ytok_hi;
-    const double log2Z = (double)Estar + log2(total) + fix * (double)Estar;
+    const double log2Z = (double)Estar + wave_readlane_f64(lg, 0) + fix * (double)Estar;
     if (lane == 0) {
         a.accepted_len[b] = n;
         a.next_token[b] = (int32_t)tok;
@@ -706,26 +700,30 @@ __device__ __forceinline__ const Partial* partials_of(const RecArgs& a, int b, i
     return a.partial2 + (r * 2 + x) * a.NS2;
 }
 
-// Phase 2 for one sequence by its workgroup of NT threads, on positions [T0, Kt) (those before T0
+// Phase 2 for one sequence by a workgroup of NT threads, on positions [T0, Kt) (those before T0
 // are known to have been accepted):
-//   2a  every (position, tensor) pair gets a lane: merge the row's slice partials, gather the draft
+//   2a  every (position, tensor) pair gets 16 lanes: merge the row's slice partials, gather the draft
 //       token's logit, leave log P(y_t) in lp[2t + x]        (two memory round trips in all)
 //   2b  wave 0: Eq. 7 on every position, first rejection by ballot -> *sh_n (Kt if none)
 // A draft id outside the vocabulary among those positions sets *sh_bad.  Ends with a barrier.
 template <int DT, int NT>
 __device__ __forceinline__ void ratio_test_block(const RecArgs& a, int b, int T0, int Kt, double* lp, int* sh_n,
                                                  int* sh_bad) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l = tid & 15;
     const int kmax = a.kmax, V = a.V;
-    for (int q = 2 * T0 + tid; q < 2 * Kt; q += NT) {
+    const float* un = a.uniforms + (long)b * (kmax + 1);
+    const float u0 = T0 + lane < Kt ? un[T0 + lane] : 0.f;  // wave 0's first block, on its way while the rows are merged
+    for (int q = 2 * T0 + (tid >> 4); q < 2 * Kt; q += NT / 16) {
         const int t = q >> 1, x = q & 1;
         const int y = a.draft[(long)b * kmax + t];
+        const double L = combine_partials_row16(partials_of(a, b, t, x), t < a.t1 ? a.NS : a.NS2, a.rho, l);
         const bool ok = (y >= 0 && y < V);
         const long off = (long)b * a.sb + (long)t * a.st;
         const float h = ok ? ld_elem<DT>(row_ptr<DT>(x ? a.Sm : a.G, off), y) : 0.f;
-        const double L = combine_partials_lane(partials_of(a, b, t, x), t < a.t1 ? a.NS : a.NS2, a.rho);
-        lp[q] = kLn2 * ((double)h * a.c - L);
-        if (!ok) *sh_bad = 1;
+        if (l == 0) {
+            lp[q] = kLn2 * ((double)h * a.c - L);
+            if (!ok) *sh_bad = 1;
+        }
     }
     __syncthreads();
     if (wave == 0) {
@@ -734,8 +732,9 @@ __device__ __forceinline__ void ratio_test_block(const RecArgs& a, int b, int T0
             const int t = t0 + lane;
             bool rej = false;
             if (t < Kt) {
+                const double u = (double)(t0 == T0 ? u0 : un[t]);
                 const double alpha = fmin(1.0, exp(lp[2 * t] - lp[2 * t + 1] - a.ln_lambda));  // Eq. 7
-                rej = !((double)a.uniforms[(long)b * (kmax + 1) + t] <= alpha);
+                rej = !(u <= alpha);
             }
             const unsigned long long rmask = __ballot(rej);
             if (rmask && first_rej == Kt) first_rej = t0 + first_lane(rmask);
@@ -751,7 +750,7 @@ __device__ __forceinline__ void ratio_test_block(const RecArgs& a, int b, int T0
 // rejection): its later rows are never scored and its first-rejection index is final.  Every
 // draft id of the sequence is range-checked here, so a sequence is flagged exactly as in the
 // one-pass schedule.
-constexpr int kVerdictThreads = 64;  // one wave per sequence: a lane per (position, tensor) pair is plenty
+constexpr int kVerdictThreads = 128;  // 16 lanes per (position, tensor) pair: a window of 4 positions in one round
 
 template <int DT>
 __global__ __launch_bounds__(kVerdictThreads) void verdict_kernel(const RecArgs a, int32_t* state) {
@@ -793,8 +792,8 @@ __device__ __forceinline__ void wave_best(Best& best) {
     }
 }
 
-// One workgroup (16 waves) per sequence, everything after the row pass in one launch:
-//   2a  every (position, tensor) pair gets a wave: merge its slice partials, gather the draft
+// Everything after the row pass in one launch, a workgroup of NT threads per sequence:
+//   2a  every (position, tensor) pair gets 16 lanes: merge its slice partials, gather the draft
 //       token's logit, leave log P(y_t) in LDS            (two memory round trips in all)
 //   2b  wave 0: Eq. 7 on every position, first rejection by ballot
 //   3   all waves stream the three rows at the rejected (or bonus) position once, one (E, s)
@@ -802,22 +801,21 @@ __device__ __forceinline__ void wave_best(Best& best) {
 //   4   wave 0 draws the token
 // Only workgroup barriers separate the steps; nothing crosses workgroups.
 //
-// SPLIT (small batches, where one workgroup per sequence leaves most of the chip idle): a.parts
-// workgroups share a sequence.  Each repeats steps 2a-2b (cheap), takes every a.parts-th group of
-// 16 chunks in step 3 and delivers its chunk masses to a table in global memory; the part that
+// a.parts > 1: that many workgroups share a sequence.  Each repeats steps 2a-2b, takes a.part_chunks
+// consecutive chunks in step 3 and delivers its chunk masses to a table in global memory; the part that
 // arrives last (an atomic counter per sequence, no workgroup ever waits for another) runs step 4
 // from the complete table.  The deliveries are made and counted by one wave with write-through stores
 // (st_dev, wait_stores), and the last part reads them with device-scope loads: no cache-wide fence.
-template <int DT, int VEC, bool GREEDY, bool SPLIT, bool PLAIN, int NT>
+template <int DT, int VEC, bool GREEDY, bool PLAIN, int NT>
 __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     extern __shared__ double smem_d[];
-    __shared__ int sh_n, sh_bad, sh_last;
-    __shared__ double sh_best_v[kRecThreads / kWave];  // one slot per wave, or per part in the merge of a split row
-    __shared__ long sh_best_i[kRecThreads / kWave];
+    __shared__ int sh_n, sh_bad;
+    __shared__ float sh_terms[kChunkSteps * VEC];
+    __shared__ double sh_best_v[NT / kWave];
+    __shared__ long sh_best_i[NT / kWave];
 
-    const int S = SPLIT ? a.parts : 1;
-    const int b = SPLIT ? (int)blockIdx.x / S : (int)blockIdx.x;
-    const int part = SPLIT ? (int)blockIdx.x - b * S : 0;
+    const int S = a.parts;
+    const int b = (int)blockIdx.x / S, part = (int)blockIdx.x - b * S;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NW = NT / kWave;
     const int kmax = a.kmax, V = a.V;
@@ -852,7 +850,6 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
         }
         return;
     }
-    __syncthreads();
     const int n = sh_n;
 
     // ---- 3
@@ -863,8 +860,10 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     const long nvec = V / VEC;
     const int tailc = V - (int)(nvec * VEC);
     const long nch = (nvec + kWave * kChunkSteps - 1) / (kWave * kChunkSteps);
+    const int NC = a.NC;
     Best best{-__builtin_huge_val(), 0x7FFFFFFFFFFFFFFFl};
-    for (int c = part * NW + wave; c < a.NC; c += NW * S) {
+    const int c0 = part * a.part_chunks, c1 = min(NC, c0 + a.part_chunks);
+    for (int c = c0 + wave; c < c1; c += NW) {
         const Partial p = chunk_mass<DT, VEC, GREEDY, PLAIN>(g, sp, sm, nvec, tailc, nch, c, lane, a.c, a.bc, a.beta, a.c_hi, best);
         if (lane == 0) tab[c] = p;
     }
@@ -876,52 +875,42 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
         }
     }
     __syncthreads();
-
-    if (SPLIT) {  // deliver this part; only the last part to arrive goes on
-        if (wave == 0) {
-            Partial* gtab = a.chunk_tab + (long)b * a.NC;
-            for (int c = lane; c < a.NC; c += kWave)
-                if ((c / NW) % S == part) st_dev_partial(gtab + c, tab[c]);
-            if (GREEDY) {
-                best.v = lane < NW ? sh_best_v[lane] : -__builtin_huge_val();
-                best.idx = lane < NW ? sh_best_i[lane] : 0x7FFFFFFFFFFFFFFFl;
-                wave_best(best);
-                if (lane == 0) {
-                    Best* o = a.part_best + (long)b * S + part;
-                    st_dev(reinterpret_cast<unsigned long long*>(&o->v), (unsigned long long)__double_as_longlong(best.v));
-                    st_dev(reinterpret_cast<unsigned long long*>(&o->idx), (unsigned long long)best.idx);
-                }
-            }
-            wait_stores();  // this wave's deliveries have reached memory before it is counted
-            unsigned prev = 0;
-            if (lane == 0) prev = __hip_atomic_fetch_add(a.arrive + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (lane == 0) sh_last = (prev == (unsigned)(S - 1)) ? 1 : 0;
+    if (wave != 0) return;
+    if (GREEDY) {
+        best.v = lane < NW ? sh_best_v[lane] : -__builtin_huge_val();
+        best.idx = lane < NW ? sh_best_i[lane] : 0x7FFFFFFFFFFFFFFFl;
+        wave_best(best);
+    }
+    if (S > 1) {  // deliver this part; only the last part to arrive goes on
+        Partial* gtab = a.chunk_tab + (long)b * NC;
+        for (int c = c0 + lane; c < c1; c += kWave) st_dev_partial(gtab + c, tab[c]);
+        if (GREEDY && lane == 0) {
+            st_dev(reinterpret_cast<unsigned long long*>(a.best_v + (long)b * NC + part),
+                   (unsigned long long)__double_as_longlong(best.v));
+            st_dev(a.best_i + (long)b * NC + part, (int32_t)min(best.idx, (long)V));
         }
-        __syncthreads();
-        if (!sh_last) return;
-        if (wave == 0) {
-            const Partial* gtab = a.chunk_tab + (long)b * a.NC;
-            for (int c = lane; c < a.NC; c += kWave) tab[c] = ld_dev_partial(gtab + c);
-            if (GREEDY && lane < S) {
-                const Best* o = a.part_best + (long)b * S + lane;
-                sh_best_v[lane] = __longlong_as_double((long long)ld_dev(reinterpret_cast<const unsigned long long*>(&o->v)));
-                sh_best_i[lane] = (long)ld_dev(reinterpret_cast<const unsigned long long*>(&o->idx));
+        wait_stores();  // this wave's deliveries have reached memory before it is counted
+        unsigned prev = 0;
+        if (lane == 0)
+            prev = __hip_atomic_fetch_add(a.arrive + (long)b * kArriveStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_readfirstlane((int)prev) != S - 1) return;
+        for (int c = lane; c < NC; c += kWave) tab[c] = ld_dev_partial(gtab + c);
+        if (GREEDY) {
+            best = Best{-__builtin_huge_val(), 0x7FFFFFFFFFFFFFFFl};
+            for (int i = lane; i < S; i += kWave) {
+                const double v = __longlong_as_double((long long)ld_dev(
+                    reinterpret_cast<const unsigned long long*>(a.best_v + (long)b * NC + i)));
+                const long idx = (long)ld_dev(a.best_i + (long)b * NC + i);
+                if (v > best.v || (v == best.v && idx < best.idx)) best = Best{v, idx};
             }
+            wave_best(best);
         }
-        __syncthreads();
+        wave_lds_sync();
     }
 
     // ---- 4
-    if (wave == 0) {
-        if (GREEDY) {
-            const int NB = SPLIT ? S : NW;
-            best.v = lane < NB ? sh_best_v[lane] : -__builtin_huge_val();
-            best.idx = lane < NB ? sh_best_i[lane] : 0x7FFFFFFFFFFFFFFFl;
-            wave_best(best);
-        }
-        const double log2Z = sample_wave<DT, VEC, GREEDY, PLAIN>(a, b, n, lane, tab, g, sp, sm, nvec, tailc, nch, best);
-        if (a.log2z && lane == 0) a.log2z[b] = log2Z;
-    }
+    const double log2Z = sample_wave<DT, VEC, GREEDY, PLAIN>(a, b, n, lane, tab, g, sp, sm, nvec, tailc, nch, best, sh_terms);
+    if (a.log2z && lane == 0) a.log2z[b] = log2Z;
 }
 
 // ------------------------------------------------------------------ kernel: log-prob rows
@@ -951,8 +940,8 @@ __device__ __forceinline__ void st_f32x4(float* p, float x, float y, float z, fl
 // log Softmax(h_rec / T) at row n_b, after accept_recover has left n_b and the row's log2-normaliser.
 // HBM-bound: three rows read and one fp32 row written per sequence.  It is a launch of its own because the
 // workgroup that draws a sequence's token is one of at most a few hundred, each tied to the rate of one
-// compute unit (16 sequences of V = 151936 bf16: 40 us of a 57 us recovery kernel); cut into segments of
-// two vectors a thread, the same sweep covers the chip.
+// compute unit; cut into segments of two vectors a thread, the sweep covers the chip (16 sequences of
+// V = 151936 bf16: 40 us of a 57 us recovery kernel before, 7 us as a launch of its own).
 template <int DT, int VEC, bool PLAIN>
 __global__ __launch_bounds__(kLogprobThreads) void recovery_logprob_kernel(const LogprobArgs a) {
     const int b = (int)blockIdx.x / a.segs, seg = (int)blockIdx.x - b * a.segs;
@@ -996,7 +985,7 @@ __global__ __launch_bounds__(kLogprobThreads) void recovery_logprob_kernel(const
 }
 
 __global__ void zero_u32_kernel(uint32_t* p, int n) {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0u;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) p[(long)i * kArriveStride] = 0u;
 }
 
 // ------------------------------------------------------------------ host side
@@ -1008,23 +997,38 @@ struct Plan {
     int NSf, slice_vecsf;  // one pass over all k_max positions (taken when draft_logprobs is requested)
     int t1;          // positions in the first row pass; == k_max when the block is verified in one pass
     size_t off_list2, off_log2z, off_state, off_partial;
-    size_t off_arrive, off_part_best, off_chunk_tab;  // split recovery; only present for small batches
+    bool split;      // the tables of a shared recovery row are there
+    size_t off_arrive, off_best_v, off_best_i, off_chunk_tab;
     size_t bytes;
 };
 
-// Small batches split each sequence's recovery row over several workgroups so that the sweep is
-// not tied to the rate of one compute unit per sequence: as many parts as there are compute units
-// per sequence, but a part is worth having only if it gets a full round of 16 chunks.
-constexpr int kSplitMaxBatch = 128;  // workspace is reserved for the split up to this batch (half of MI355X's 256 units)
-constexpr int kSplitMaxParts = 16;   // one LDS slot per part in the greedy merge
+constexpr int kSplitMaxBatch = 128;  // workspace is reserved for shared recovery rows up to this batch (half of MI355X's 256 units)
 
-int recovery_parts(int B, int NC, int cus) {
-    if (B < 1 || B > kSplitMaxBatch) return 1;
-    const int by_chunks = (NC + (kRecThreads / kWave) - 1) / (kRecThreads / kWave);
-    int parts = cus / B;
-    if (parts > by_chunks) parts = by_chunks;
-    if (parts > kSplitMaxParts) parts = kSplitMaxParts;
-    return parts < 1 ? 1 : parts;
+// Shape of the recovery launch: threads per workgroup, and chunks per part of a recovery row.
+//   - So few chunks that 4-wave workgroups with one chunk a wave leave at most 8 waves per compute unit: spread
+//     them like that, since a chunk's arithmetic (some 1.5 us alone on a SIMD) takes as long as four of them
+//     sharing one.  With 8 sequences of V = 151936 (75 chunks) the recovery kernel goes from 17.2 us (40
+//     workgroups of 16 waves) to 11.5; beyond that line the parts' repeated ratio tests weigh more than the
+//     spread gains (64 such sequences: 71.2 us a step in 19 parts, 69.9 in 3, 72.4 in 4 uneven ones).
+//   - At least two compute units per sequence: as many 16-wave parts as there are units per sequence, with
+//     equal rounds of 16 chunks.
+//   - Up to one sequence per unit: one 16-wave workgroup each.  More: 8-wave workgroups, two to a unit, so that the
+//     serial ends of one sequence (ratio test, token pick) overlap the sweep of another (300 sequences of
+//     V = 100000: 132 us a step against 137 in balanced parts and 140 with 16 waves).
+struct RecShape {
+    int threads, part_chunks;
+};
+
+RecShape recovery_shape(int B, int NC, int cus, bool split) {
+    if (split && (long)B * NC <= 8l * cus) return {256, 4};
+    if (split && B <= cus / 2) {
+        const int rows = (NC + 15) / 16;  // rounds of 16 chunks
+        const int most = cus / B < rows ? cus / B : rows;
+        const int rounds = (rows + most - 1) / most;
+        const int parts = (rows + rounds - 1) / rounds;
+        return {1024, (NC + parts - 1) / parts};
+    }
+    return {B <= cus ? 1024 : 512, NC};
 }
 
 // Two row passes pay off when the batch is large enough to be bandwidth-bound and long enough for
@@ -1075,7 +1079,8 @@ void slice_plan(long nvec, long row_tensors, int& NS, int& slice_vecs) {
     slice_vecs = (int)sv;
 }
 
-Plan make_plan(const ss_params* p) {
+// Bytes up to the tables of a shared recovery row, and the tables themselves when `split` is set.
+Plan lay_out(const ss_params* p, bool split) {
     Plan pl;
     pl.vec = p->dtype == SS_BF16 ? 8 : 4;
     const long nvec = (p->vocab + pl.vec - 1) / pl.vec;
@@ -1096,14 +1101,29 @@ Plan make_plan(const ss_params* p) {
     size_t ns_max = (size_t)(pl.NS > pl.NS2 ? pl.NS : pl.NS2);
     if ((size_t)pl.NSf > ns_max) ns_max = (size_t)pl.NSf;
     o += align_up(((size_t)p->batch * p->k_max * 2 + 1) * ns_max * sizeof(Partial), 256);
-    pl.off_arrive = pl.off_part_best = pl.off_chunk_tab = o;
-    if (p->batch >= 1 && p->batch <= kSplitMaxBatch) {
-        pl.off_arrive = o;     o += align_up(B * sizeof(uint32_t), 256);
-        pl.off_part_best = o;  o += align_up(B * kSplitMaxParts * sizeof(Best), 256);
-        pl.off_chunk_tab = o;  o += align_up(B * (size_t)chunks_per_row(p->vocab, pl.vec) * sizeof(Partial), 256);
+    const size_t NC = (size_t)chunks_per_row(p->vocab, pl.vec);
+    pl.split = split && p->batch >= 1 && p->batch <= kSplitMaxBatch;
+    pl.off_arrive = pl.off_best_v = pl.off_best_i = pl.off_chunk_tab = o;
+    if (pl.split) {
+        pl.off_arrive = o;     o += align_up(B * kArriveStride * sizeof(uint32_t), 256);
+        pl.off_best_v = o;     o += align_up(B * (NC < 32 ? 32 : NC) * sizeof(double), 256);
+        pl.off_best_i = o;     o += align_up(B * NC * sizeof(int32_t), 256);
+        pl.off_chunk_tab = o;  o += align_up(B * NC * sizeof(Partial), 256);
+    } else if (p->batch >= 1 && p->batch <= kSplitMaxBatch) {
+        // not used, and never more than the tables: which blocks fit the static scratch stays what it is
+        o += align_up(B * sizeof(uint32_t), 256) + align_up(B * 256, 256) + align_up(B * NC * sizeof(Partial), 256);
     }
     pl.bytes = o;
     return pl;
+}
+
+// The plan with the shared recovery row, unless only the plan without it fits the static scratch: which blocks
+// that entry point takes does not depend on the tables.
+Plan make_plan(const ss_params* p) {
+    const Plan pl = lay_out(p, true);
+    if (pl.bytes <= (size_t)SS_STATIC_SCRATCH_BYTES) return pl;
+    const Plan small = lay_out(p, false);
+    return small.bytes <= (size_t)SS_STATIC_SCRATCH_BYTES ? small : pl;
 }
 
 // One row pass over window `win`.  `uniform_rows` > 0 when every sequence has that many rows.
@@ -1164,19 +1184,21 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     ra.state = two_pass ? state : nullptr;
     ra.log2z = recovery_logprobs ? reinterpret_cast<double*>(ws + pl.off_log2z) : nullptr;
     ra.NC = chunks_per_row(V, VEC);
-    const int cus = device_cu_count();
-    ra.parts = recovery_parts(B, ra.NC, cus);
-    ra.arrive = reinterpret_cast<uint32_t*>(ws + pl.off_arrive);
-    ra.part_best = reinterpret_cast<Best*>(ws + pl.off_part_best);
-    ra.chunk_tab = reinterpret_cast<Partial*>(ws + pl.off_chunk_tab);
+    const RecShape shape = recovery_shape(B, ra.NC, device_cu_count(), pl.split);
+    ra.part_chunks = shape.part_chunks;
+    ra.parts = (ra.NC + ra.part_chunks - 1) / ra.part_chunks;
     const bool split = ra.parts > 1;
+    ra.arrive = reinterpret_cast<uint32_t*>(ws + pl.off_arrive);
+    ra.best_v = reinterpret_cast<double*>(ws + pl.off_best_v);
+    ra.best_i = reinterpret_cast<int32_t*>(ws + pl.off_best_i);
+    ra.chunk_tab = reinterpret_cast<Partial*>(ws + pl.off_chunk_tab);
     la.zero_ptr = ra.arrive;
     la.zero_n = split ? B : 0;
     const size_t smem = (size_t)2 * kmax * sizeof(double) + (size_t)ra.NC * sizeof(Partial);
 
     mark(0);
     if (kmax == 0 && split)  // no row pass to clear the arrival counters
-        hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(kSplitMaxBatch), 0, stream, ra.arrive, B);
+        hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(256), 0, stream, ra.arrive, B);
     if (kmax > 0)
         launch_row_pass<DT, VEC>(la, RowWindow{ragged ? ra.draft_len : nullptr, nullptr, kmax, 0, t1},
                                           ragged ? 0 : t1, off1, partial1, (long)B * t1, stream);
@@ -1196,23 +1218,15 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     // accept + recover: LDS holds the per-position log-probs and one mass per recovery chunk
     const dim3 rec_grid((unsigned)(B * ra.parts));
     using RecKernel = void (*)(RecArgs);
-    constexpr int kFull = kRecThreads, kHalf = kRecThreadsHalf;
-    static const RecKernel rec_kernels[8] = {  // index: greedy | split << 1 | plain << 2
-        accept_recover_kernel<DT, VEC, false, false, false, kFull>, accept_recover_kernel<DT, VEC, true, false, false, kFull>,
-        accept_recover_kernel<DT, VEC, false, true, false, kFull>,  accept_recover_kernel<DT, VEC, true, true, false, kFull>,
-        accept_recover_kernel<DT, VEC, false, false, true, kFull>,  accept_recover_kernel<DT, VEC, true, false, true, kFull>,
-        accept_recover_kernel<DT, VEC, false, true, true, kFull>,   accept_recover_kernel<DT, VEC, true, true, true, kFull>};
-    // With at least two sequences per compute unit, two 8-wave workgroups share a unit: the serial ends of one
-    // sequence (ratio test, token pick) then overlap the sweep of another.  Same waves per unit, same arithmetic.
-    static const RecKernel rec_kernels_half[4] = {  // index: greedy | plain << 1
-        accept_recover_kernel<DT, VEC, false, false, false, kHalf>, accept_recover_kernel<DT, VEC, true, false, false, kHalf>,
-        accept_recover_kernel<DT, VEC, false, false, true, kHalf>,  accept_recover_kernel<DT, VEC, true, false, true, kHalf>};
-    if (!split && B >= 2 * cus)
-        hipLaunchKernelGGL(rec_kernels_half[(ra.greedy ? 1 : 0) | (ra.plain ? 2 : 0)], rec_grid, dim3(kHalf), smem,
-                           stream, ra);
-    else
-        hipLaunchKernelGGL(rec_kernels[(ra.greedy ? 1 : 0) | (split ? 2 : 0) | (ra.plain ? 4 : 0)], rec_grid,
-                           dim3(kFull), smem, stream, ra);
+    static const RecKernel rec_kernels[3][4] = {  // [256, 512, 1024 threads][greedy | plain << 1]
+        {accept_recover_kernel<DT, VEC, false, false, 256>, accept_recover_kernel<DT, VEC, true, false, 256>,
+         accept_recover_kernel<DT, VEC, false, true, 256>, accept_recover_kernel<DT, VEC, true, true, 256>},
+        {accept_recover_kernel<DT, VEC, false, false, 512>, accept_recover_kernel<DT, VEC, true, false, 512>,
+         accept_recover_kernel<DT, VEC, false, true, 512>, accept_recover_kernel<DT, VEC, true, true, 512>},
+        {accept_recover_kernel<DT, VEC, false, false, 1024>, accept_recover_kernel<DT, VEC, true, false, 1024>,
+         accept_recover_kernel<DT, VEC, false, true, 1024>, accept_recover_kernel<DT, VEC, true, true, 1024>}};
+    hipLaunchKernelGGL(rec_kernels[shape.threads >> 9][(ra.greedy ? 1 : 0) | (ra.plain ? 2 : 0)], rec_grid,
+                       dim3((unsigned)shape.threads), smem, stream, ra);
     if (recovery_logprobs) {
         const long nvec = V / VEC, per = kLogprobThreads * kLogprobUnroll;
         const int segs = nvec > per ? (int)((nvec + per - 1) / per) : 1;
@@ -1286,7 +1300,7 @@ ss_status verify_block_impl(const void* G, const void* S_ctx, const void* S_noct
     ra.greedy = (params->flags & SS_FLAG_GREEDY) ? 1 : 0;
     ra.plain = steer ? 0 : 1;
     ra.c_hi = c_hi;
-    ra.parts = 1; ra.chunk_tab = nullptr; ra.part_best = nullptr; ra.arrive = nullptr;
+    ra.parts = 1; ra.part_chunks = 0; ra.chunk_tab = nullptr; ra.best_v = nullptr; ra.best_i = nullptr; ra.arrive = nullptr;
 
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t err;

@@ -45,13 +45,6 @@ __device__ __forceinline__ bool beats(double av, int ai, double bv, int bi) {
     return av > bv || (av == bv && ai < bi);
 }
 
-__device__ __forceinline__ double readlane_f64(double x, int lane) {
-    const long long b = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xFFFFFFFFll), lane);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
 struct TopArgs {
     const void* G;
     const void* Sm;
@@ -85,7 +78,7 @@ __device__ __forceinline__ void wave_insert(WaveTop& w, double cv, int ci, int l
         w.ev = cv;
         w.ei = ci;
     }
-    w.tau_v = readlane_f64(w.ev, topk - 1);
+    w.tau_v = wave_readlane_f64(w.ev, topk - 1);
     w.tau_i = __builtin_amdgcn_readlane(w.ei, topk - 1);
 }
 
@@ -101,7 +94,7 @@ __device__ __forceinline__ void wave_offer(WaveTop& w, unsigned long long m, dou
     while (m) {
         const int L = first_lane(m);
         m &= m - 1;
-        wave_insert(w, readlane_f64(hc, L), __builtin_amdgcn_readlane(idx, L), lane, topk);
+        wave_insert(w, wave_readlane_f64(hc, L), __builtin_amdgcn_readlane(idx, L), lane, topk);
     }
 }
 
@@ -159,10 +152,10 @@ __device__ void topk_by_insertion(const TopArgs& a, const void* g, const void* s
                 const int si = valid[j] ? idx0 : 0x7FFFFFFF - lane;
                 int rank = 0;
                 for (int L = 0; L < kWave; ++L)
-                    rank += beats(readlane_f64(sv, L), __builtin_amdgcn_readlane(si, L), sv, si) ? 1 : 0;
+                    rank += beats(wave_readlane_f64(sv, L), __builtin_amdgcn_readlane(si, L), sv, si) ? 1 : 0;
                 w.ev = permute_f64(sv, rank);
                 w.ei = __builtin_amdgcn_ds_permute(rank << 2, si);
-                w.tau_v = readlane_f64(w.ev, topk - 1);
+                w.tau_v = wave_readlane_f64(w.ev, topk - 1);
                 w.tau_i = __builtin_amdgcn_readlane(w.ei, topk - 1);
                 mine = true;
             }

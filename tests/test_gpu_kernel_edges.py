@@ -47,3 +47,36 @@ def test_logprob_rows_at_segment_edges(binding, oracle, dtype, vocab, beta):
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=beta, temperature=w.temperature)
     parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
     assert out["accepted_len"][2].item() == -1 and torch.all(out["recovery_logprobs"][2] == 7.0)  # left unwritten
+
+
+# The recovery launch: 4-wave workgroups of one chunk a wave while batch x chunks <= 8 x 256, then 16-wave parts of
+# equal rounds up to 128 sequences, then one workgroup of 16 waves per sequence up to 256 and of 8 beyond.  A chunk is
+# 256 vectors (2048 bf16, 1024 fp32 logits), the logits past the last vector are a chunk of their own.
+@pytest.mark.parametrize("greedy,beta", [(False, 0.8), (True, 0.8), (False, 0.0), (True, 0.0)])
+@pytest.mark.parametrize("dtype,batch,vocab", [
+    ("bf16", 1, 4 * 2048), ("bf16", 1, 4 * 2048 + 1), ("bf16", 3, 7 * 2048 + 9), ("f32", 2, 4 * 1024 + 1), ("f32", 5, 3),
+    ("bf16", 128, 16 * 2048), ("bf16", 128, 16 * 2048 + 5), ("f32", 100, 40 * 1024 + 3),
+    ("bf16", 129, 4100), ("bf16", 257, 4100)])
+def test_recovery_launch_shapes(binding, oracle, dtype, batch, vocab, greedy, beta):
+    w = recipe("c4", dtype, batch=batch, k_max=1, vocab=vocab)
+    inp = W.generate(w, "cuda", seq_chunk=64)
+    inp["draft_len"] = torch.randint(0, 2, (batch,), generator=torch.Generator("cuda").manual_seed(batch), device="cuda",
+                                     dtype=torch.int32)
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam,
+                               beta=beta, temperature=w.temperature, draft_len=inp["draft_len"], greedy=greedy,
+                               want_draft_logprobs=True)
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=beta, temperature=w.temperature, greedy=greedy,
+                            want_recovery_logprobs=False)
+    parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
+
+
+# Row-pass slices merged by 16 lanes: 1, 15 .. 17 and 64 slices (the most) of a row, with a remainder.
+@pytest.mark.parametrize("dtype,vocab", [("bf16", 2048), ("bf16", 15 * 2048 + 1), ("bf16", 16 * 2048), ("bf16", 17 * 2048 + 7),
+                                         ("bf16", 64 * 2048), ("f32", 63 * 1024 + 1)])
+def test_slice_merge_edges(binding, oracle, dtype, vocab):
+    w = recipe("c2", dtype, batch=2, k_max=9, vocab=vocab)
+    inp = W.generate(w, "cuda")
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam,
+                               beta=w.beta, temperature=w.temperature, want_draft_logprobs=True)
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, want_recovery_logprobs=False)
+    parity.compare(out, ora, inp["uniforms"], None)
