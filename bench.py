@@ -134,6 +134,17 @@ def bench_split(args, w, sets, dev) -> int:
     return 0
 
 
+def row_windows(t1, kmax, position_bytes) -> list:
+    """Bounds of the windows the library's row passes cover, from the length of the first one: a further window is
+    as long as all before it while it is worth its launch, else it takes the rest."""
+    bounds = [0, t1]
+    while bounds[-1] < kmax:
+        t = bounds[-1]
+        cut = position_bytes >= 240 << 20 or position_bytes * t >= 448 << 20
+        bounds.append(2 * t if cut and 2 * t + t // 2 < kmax else kmax)
+    return bounds
+
+
 def measure(binding, W, w, sets, dev, *, steps, warmup, mode="verify", full_rows=False, graph=False):
     """Time `steps` calls of the block on workload `w` (inputs already on the device) and the per-kernel stages
     of 20 further calls.  Returns the figures of one benchmark line; `state` holds what the parity check reuses."""
@@ -149,6 +160,7 @@ def measure(binding, W, w, sets, dev, *, steps, warmup, mode="verify", full_rows
                                  flags=(binding.SS_FLAG_GREEDY if mode == "greedy" else 0)
                                  | (binding.SS_FLAG_FULL_ROWS if full_rows else 0))
     t1 = binding.first_window(params)
+    bounds = row_windows(t1, kmax, 2 * B * V * esz)
     ws = torch.empty(max(256, binding.workspace_bytes(params)), dtype=torch.uint8, device=dev)
     acc = torch.empty(B, dtype=torch.int32, device=dev)
     tok = torch.empty(B, dtype=torch.int32, device=dev)
@@ -198,9 +210,9 @@ def measure(binding, W, w, sets, dev, *, steps, warmup, mode="verify", full_rows
         s = sets[i % len(sets)]
         K = s["draft_len"] if s["draft_len"] is not None else torch.full((B,), kmax, dtype=torch.int32, device=dev)
         n_bonus = int((acc == K).sum().item())
-        # rows the schedule scores: the first window for everyone, the rest for sequences not rejected inside it
-        in_play = (K > t1) & (acc >= t1)
-        rows = int(torch.clamp(K, max=t1).sum().item()) + int((K - t1)[in_play].sum().item())
+        # rows the schedule scores: the first window for everyone, each later one for the sequences still in play
+        rows = sum(int((torch.clamp(K, max=hi) - lo)[(K > lo) & (acc >= lo)].sum().item())
+                   for lo, hi in zip(bounds, bounds[1:]))
         rows_scored += rows / n_timed
         # row pass: two rows of V logits per scored position
         lse_bytes += 2.0 * rows * V * esz / n_timed
@@ -208,9 +220,10 @@ def measure(binding, W, w, sets, dev, *, steps, warmup, mode="verify", full_rows
         # G / S_noctx bonus rows of fully accepted sequences (a rejected row was already read by a row pass)
         step_bytes += (2.0 * rows + B + 2.0 * n_bonus) * V * esz / n_timed
         bonus_frac += n_bonus / B / n_timed
-    n_lse = 2 if (not rows_mode and t1 < kmax) else 1  # launches of the row-pass kernel per step
+    n_lse = 1 if rows_mode else len(bounds) - 1  # launches of the row-pass kernel per step
     # a stage that launches nothing still measures the ~5 us of its event pair: only passes that ran are counted
-    lse_ms = stage["row_pass1"] + (stage["row_pass2"] if n_lse == 2 else 0.0)
+    # (with more than two windows row_pass2 holds the verdicts between them too)
+    lse_ms = stage["row_pass1"] + (stage["row_pass2"] if n_lse >= 2 else 0.0)
     lse_gbs = lse_bytes / (lse_ms * 1e-3) / 1e9 if lse_ms > 0 else 0.0
     if rows_mode:
         # no row pass: the recovery sweep is the dominant (only) kernel; it reads 3 rows per row, 1 when beta = 0

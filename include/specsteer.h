@@ -84,9 +84,9 @@ typedef struct {
 /*
  * Algorithm 1 leaves its loop at the first rejection, so the rows of the later positions of a
  * rejected sequence never need scoring.  On large batches the block therefore scores the first
- * quarter of the positions for every sequence, applies the ratio test to them, and scores the
- * remaining positions only for the sequences that have not been rejected yet.  The outputs are
- * the same; only draft_logprobs (which asks for every position) forces the one-pass schedule.
+ * positions (specsteer_first_window of them) for every sequence, applies the ratio test to them, and scores the
+ * remaining positions, in one window or several, only for the sequences that have not been rejected yet.  The
+ * outputs are the same; only draft_logprobs (which asks for every position) forces the one-pass schedule.
  * SS_FLAG_FULL_ROWS forces it too: every valid row of G and S_noctx is then read.
  */
 #define SS_FLAG_FULL_ROWS 2u
@@ -184,8 +184,8 @@ ss_status specsteer_verify_block_static(const void *G, const void *S_ctx, const 
  * milliseconds of each stage to the host array stage_ms[SS_NUM_STAGES]:
  *   [SS_STAGE_ROW_PASS1] log-sum-exp pass over G and S_noctx, positions [0, first window),
  *   [SS_STAGE_VERDICT]   ratio test on those positions (0 in the one-pass schedule),
- *   [SS_STAGE_ROW_PASS2] log-sum-exp pass over the remaining positions of the sequences still in
- *                        play (0 in the one-pass schedule),
+ *   [SS_STAGE_ROW_PASS2] log-sum-exp passes over the remaining positions of the sequences still in
+ *                        play, with the ratio tests between them (0 in the one-pass schedule),
  *   [SS_STAGE_RECOVER]   ratio test, first rejection, recovery distribution, sampling and the
  *                        optional log-prob rows.
  * Creates and destroys its events inside the call, so it is not for latency-critical use.

@@ -179,7 +179,7 @@ __device__ __forceinline__ Partial wave_combine(Acc a) {
 // ------------------------------------------------------------------ row lists
 
 // Which rows a row pass covers: positions [t_lo, t_hi) of every sequence that is still in play.
-// The block is verified in at most two such windows (see the host side): Algorithm 1 stops at the
+// The block is verified in one or more such windows (see the host side): Algorithm 1 stops at the
 // first rejection, so the later positions of a sequence rejected early never need their rows.
 struct RowWindow {
     const int32_t* draft_len;  // NULL => K_b = k_max
@@ -347,15 +347,13 @@ struct RecArgs {
     const int32_t* draft;
     const int32_t* draft_len;
     const float* uniforms;
-    // Partials of positions [0, t1) come from the first row pass, those of [t1, k_max) from the
-    // second (t1 == k_max when there is only one pass).  off1 / off2 are the passes' row lists;
-    // rows1 > 0 means the first pass had that many rows for every sequence and no list.
-    const int32_t* off1;
-    const int32_t* off2;
-    const Partial* partial1;
-    const Partial* partial2;
-    const int32_t* state;    // two passes: what the verdict kernel found per sequence; else NULL
-    int t1, rows1;
+    // Slice partials of the window this launch tests: position t of sequence b has row
+    // (rows > 0 ? b * rows : off[b]) + t - t_lo in it.
+    const int32_t* off;
+    const Partial* partial;
+    int rows, NS;            // rows per sequence if all have the same, slices per row
+    int t_lo, t_hi;          // the window; t_hi == k_max for the last one
+    int32_t* state;          // several windows: what the verdicts so far have found; else NULL
     int32_t* accepted_len;
     int32_t* next_token;
     float* next_token_logprob;
@@ -363,7 +361,6 @@ struct RecArgs {
     float* draft_logprobs;
     long sb, st;
     int B, kmax, V;
-    int NS, NS2;     // slices per row in the first / second row pass
     int NC;          // chunks per row (full chunks + one pseudo-chunk for the logits past the last vector)
     double c;        // log2(e) / T
     double bc;       // beta * log2(e) / T
@@ -689,15 +686,10 @@ __device__ __forceinline__ double sample_wave(const RecArgs& a, int b, int n, in
     return log2Z;
 }
 
-// Slice partials of (sequence b, position t, tensor x): from the first row pass for t < t1, from the
-// second for t >= t1.
+// Slice partials of (sequence b, position t, tensor x), t in the window.
 __device__ __forceinline__ const Partial* partials_of(const RecArgs& a, int b, int t, int x) {
-    if (t < a.t1) {
-        const long r = (a.rows1 > 0 ? (long)b * a.rows1 : (long)a.off1[b]) + t;
-        return a.partial1 + (r * 2 + x) * a.NS;
-    }
-    const long r = (long)a.off2[b] + (t - a.t1);
-    return a.partial2 + (r * 2 + x) * a.NS2;
+    const long r = (a.rows > 0 ? (long)b * a.rows : (long)a.off[b]) + (t - a.t_lo);
+    return a.partial + (r * 2 + x) * a.NS;
 }
 
 // Phase 2 for one sequence by a workgroup of NT threads, on positions [T0, Kt) (those before T0
@@ -716,7 +708,7 @@ __device__ __forceinline__ void ratio_test_block(const RecArgs& a, int b, int T0
     for (int q = 2 * T0 + (tid >> 4); q < 2 * Kt; q += NT / 16) {
         const int t = q >> 1, x = q & 1;
         const int y = a.draft[(long)b * kmax + t];
-        const double L = combine_partials_row16(partials_of(a, b, t, x), t < a.t1 ? a.NS : a.NS2, a.rho, l);
+        const double L = combine_partials_row16(partials_of(a, b, t, x), a.NS, a.rho, l);
         const bool ok = (y >= 0 && y < V);
         const long off = (long)b * a.sb + (long)t * a.st;
         const float h = ok ? ld_elem<DT>(row_ptr<DT>(x ? a.Sm : a.G, off), y) : 0.f;
@@ -744,39 +736,40 @@ __device__ __forceinline__ void ratio_test_block(const RecArgs& a, int b, int T0
     __syncthreads();
 }
 
-// Between the two row passes: the ratio test on the positions of the first window,
-// [0, min(K_b, t1)), with exactly the arithmetic of the final kernel.  A sequence rejected there is
+// Between two row passes: the ratio test on the positions of the window just scored, [t_lo, min(K_b, t_hi)), of
+// every sequence still in play, with exactly the arithmetic of the final kernel.  A sequence rejected there is
 // finished as far as verification goes (Algorithm 1 breaks out of the loop at the first
-// rejection): its later rows are never scored and its first-rejection index is final.  Every
-// draft id of the sequence is range-checked here, so a sequence is flagged exactly as in the
+// rejection): its later rows are never scored and its first-rejection index is final.  After the first window
+// every draft id of the sequence is range-checked, so a sequence is flagged exactly as in the
 // one-pass schedule.
 constexpr int kVerdictThreads = 128;  // 16 lanes per (position, tensor) pair: a window of 4 positions in one round
 
 template <int DT>
-__global__ __launch_bounds__(kVerdictThreads) void verdict_kernel(const RecArgs a, int32_t* state) {
+__global__ __launch_bounds__(kVerdictThreads) void verdict_kernel(const RecArgs a) {
     extern __shared__ double smem_d[];
     __shared__ int sh_n, sh_bad;
     const int b = blockIdx.x, tid = threadIdx.x;
     const int kmax = a.kmax, V = a.V;
+    const bool first = a.t_lo == 0;
+    if (!first && a.state[b] != kInPlay) return;
     const int K = a.draft_len ? a.draft_len[b] : kmax;
     const bool bad_len = (K < 0 || K > kmax);
+    const int Kt = bad_len ? 0 : min(K, a.t_hi);
     if (tid == 0) {
         sh_bad = bad_len ? 1 : 0;
         sh_n = 0;
     }
     __syncthreads();
-    if (!bad_len) {
+    if (first && !bad_len) {  // ids behind the window; those inside it are checked with their rows
         bool oob = false;
-        for (int t = tid; t < K; t += kVerdictThreads) {
+        for (int t = Kt + tid; t < K; t += kVerdictThreads) {
             const int y = a.draft[(long)b * kmax + t];
             oob = oob || y < 0 || y >= V;
         }
         if (oob) sh_bad = 1;
     }
-    __syncthreads();
-    const int Kt = sh_bad ? 0 : min(K, a.t1);
-    ratio_test_block<DT, kVerdictThreads>(a, b, 0, Kt, smem_d, &sh_n, &sh_bad);
-    if (tid == 0) state[b] = sh_bad ? kFlagged : (sh_n == Kt && K > a.t1 ? kInPlay : sh_n);
+    ratio_test_block<DT, kVerdictThreads>(a, b, a.t_lo, Kt, smem_d, &sh_n, &sh_bad);
+    if (tid == 0) a.state[b] = sh_bad ? kFlagged : (sh_n == Kt && K > a.t_hi ? kInPlay : sh_n);
 }
 
 // Best candidate of the wave, left in every lane: larger value, then lower index.
@@ -825,9 +818,9 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     const int K = a.draft_len ? a.draft_len[b] : kmax;
     const int state = a.state ? a.state[b] : kInPlay;
     const bool bad_len = K < 0 || K > kmax || state == kFlagged;
-    // Two-pass schedule: a sequence the verdict kernel saw rejected (or at its end) inside the first window keeps
-    // that first-rejection index; a sequence still in play after that window is tested here on its remaining
-    // positions.  One pass: every sequence is tested here over all K positions.
+    // Several windows: a sequence a verdict kernel saw rejected (or at its end) keeps that first-rejection
+    // index; a sequence still in play is tested here on the positions of the last window.  One window: every
+    // sequence is tested here over all K positions.
     const bool settled = state >= 0 && !bad_len;
     const int Kt = bad_len ? 0 : K;
     if (tid == 0) {
@@ -835,7 +828,7 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
         sh_n = settled ? state : 0;
     }
     __syncthreads();
-    if (!settled) ratio_test_block<DT, NT>(a, b, a.state ? a.t1 : 0, Kt, lp, &sh_n, &sh_bad);
+    if (!settled) ratio_test_block<DT, NT>(a, b, a.t_lo, Kt, lp, &sh_n, &sh_bad);
     const bool bad = sh_bad != 0;
     if (a.draft_logprobs && part == 0) {  // valid positions from LDS, padded slots 0, a flagged sequence NaN throughout
         const float nanv = __int_as_float(0x7FC00000);
@@ -990,12 +983,18 @@ __global__ void zero_u32_kernel(uint32_t* p, int n) {
 
 // ------------------------------------------------------------------ host side
 
+constexpr int kMaxWindows = 12;  // first window of one position, each next one as long as all before it: 1024 positions
+
+struct Window {
+    int t_lo, t_hi;
+    int NS, slice_vecs;  // slices per row, vectors per slice
+};
+
 struct Plan {
     int vec;         // logits per 16-byte vector
-    int NS, slice_vecs;    // first row pass: slices per row, fast-width vectors per slice
-    int NS2, slice_vecs2;  // second row pass
-    int NSf, slice_vecsf;  // one pass over all k_max positions (taken when draft_logprobs is requested)
-    int t1;          // positions in the first row pass; == k_max when the block is verified in one pass
+    int windows;
+    Window win[kMaxWindows];
+    Window all;      // one pass over all k_max positions (taken when draft_logprobs is requested)
     size_t off_list2, off_log2z, off_state, off_partial;
     bool split;      // the tables of a shared recovery row are there
     size_t off_arrive, off_best_v, off_best_i, off_chunk_tab;
@@ -1031,17 +1030,30 @@ RecShape recovery_shape(int B, int NC, int cus, bool split) {
     return {B <= cus ? 1024 : 512, NC};
 }
 
-// Two row passes pay off when the batch is large enough to be bandwidth-bound and long enough for
-// a first rejection to cut rows: the first quarter of the positions is scored for everyone, the
-// rest only for the sequences that are still in play.
+// Several row passes pay off when the batch is large enough to be bandwidth-bound and long enough for
+// a first rejection to cut rows: a first window is scored for everyone, what follows only for the sequences that
+// are still in play.  A further window costs some 10 us (a verdict launch, and the ends of a row pass), the time of
+// 66 MB of rows.
+//   - From kEarlyExitMinBytes of rows: a first window of a quarter of the positions and one of the rest.
+//   - From kDoublingMinBytes a position, the rows behind one position are already worth a launch: windows of 1,
+//     1, 2, 4, ... positions.  512 sequences of 8 positions, V = 256000 bf16 (524 MB a position): 347 -> 287 us a
+//     step at acceptance 0.4, 590 -> 511 at 0.8; at V = 128256 (263 MB) 193 -> 173 and 303 -> 285.  At 140 MB a
+//     position (273 sequences, V = 128256) it turns: 184 -> 190 at acceptance 0.8.
+//   - From kNextWindowMinBytes in a window as long as all before it, the rest is cut in the same way: 256 ragged
+//     sequences of up to 16 positions, V = 128256 (windows of 4, 4 and 8 instead of 4 and 12) 167.8 -> 164.9 us.
 constexpr long kEarlyExitMinBytes = 512l << 20;
+constexpr long kDoublingMinBytes = 240l << 20;
+constexpr long kNextWindowMinBytes = 448l << 20;
+
+long position_bytes(const ss_params* p) {  // both tensors' rows of one position, all sequences
+    return 2l * p->batch * p->vocab * (p->dtype == SS_BF16 ? 2 : 4);
+}
 
 int first_window(const ss_params* p) {
     if (p->flags & SS_FLAG_FULL_ROWS) return p->k_max;
     if (p->k_max < 4) return p->k_max;
-    const long esz = p->dtype == SS_BF16 ? 2 : 4;
-    if ((long)p->batch * p->k_max * 2 * p->vocab * esz < kEarlyExitMinBytes) return p->k_max;
-    return p->k_max / 4;
+    if (position_bytes(p) * p->k_max < kEarlyExitMinBytes) return p->k_max;
+    return position_bytes(p) >= kDoublingMinBytes ? 1 : p->k_max / 4;
 }
 
 bool shape_ok(const ss_params* p) {
@@ -1064,19 +1076,19 @@ int chunks_per_row(int V, int vec) {
 // Slices per row for a pass expected to cover `row_tensors` (row, tensor) pairs: 64 KiB slices for
 // big passes, smaller ones (down to one unrolled group) when there are too few rows to give every
 // resident wave several slices -- a wave that gets one or two long slices cannot balance.
-void slice_plan(long nvec, long row_tensors, int& NS, int& slice_vecs) {
+void slice_plan(long nvec, long row_tensors, int most, Window& w) {
     long ns_lo = (nvec + kMaxSliceVecs - 1) / kMaxSliceVecs;
     long ns_hi = (nvec + kMinSliceVecs - 1) / kMinSliceVecs;
     long want = row_tensors > 0 ? (32768 + row_tensors - 1) / row_tensors : 1;
     long ns = want < ns_lo ? ns_lo : (want > ns_hi ? ns_hi : want);
-    if (ns > kMaxSlices) ns = kMaxSlices;
+    if (ns > most) ns = most;
     if (ns < 1) ns = 1;
     long sv = (nvec + ns - 1) / ns;
     sv = (sv + kMinSliceVecs - 1) / kMinSliceVecs * kMinSliceVecs;
     ns = (nvec + sv - 1) / sv;
     if (ns < 1) ns = 1;
-    NS = (int)ns;
-    slice_vecs = (int)sv;
+    w.NS = (int)ns;
+    w.slice_vecs = (int)sv;
 }
 
 // Bytes up to the tables of a shared recovery row, and the tables themselves when `split` is set.
@@ -1084,23 +1096,39 @@ Plan lay_out(const ss_params* p, bool split) {
     Plan pl;
     pl.vec = p->dtype == SS_BF16 ? 8 : 4;
     const long nvec = (p->vocab + pl.vec - 1) / pl.vec;
-    pl.t1 = first_window(p);
-    const long rows1 = (long)p->batch * pl.t1, rows2 = (long)p->batch * (p->k_max - pl.t1);
-    slice_plan(nvec, rows1 * 2, pl.NS, pl.slice_vecs);
-    // the second pass covers only the sequences still in play: typically a third of the padded rows
-    slice_plan(nvec, rows2 * 2 / 3, pl.NS2, pl.slice_vecs2);
-    slice_plan(nvec, (long)p->batch * p->k_max * 2, pl.NSf, pl.slice_vecsf);
+    // The space of the slice partials: that of one window of all positions and of two, the first a quarter of the
+    // positions, at the finest of their slicings.  The windows use it one after the other.
+    const int quarter = first_window(p) < p->k_max ? p->k_max / 4 : p->k_max;
+    const long rows1 = (long)p->batch * quarter, rows2 = (long)p->batch * (p->k_max - quarter);
+    Window two[2];
+    slice_plan(nvec, rows1 * 2, kMaxSlices, two[0]);
+    // a later window covers only the sequences still in play: typically a third of the padded rows
+    slice_plan(nvec, rows2 * 2 / 3, kMaxSlices, two[1]);
+    slice_plan(nvec, (long)p->batch * p->k_max * 2, kMaxSlices, pl.all);
+    pl.all.t_lo = 0;
+    pl.all.t_hi = p->k_max;
+    int ns_max = two[0].NS > two[1].NS ? two[0].NS : two[1].NS;
+    if (pl.all.NS > ns_max) ns_max = pl.all.NS;
+    pl.windows = 0;
+    for (int t = 0, hi = first_window(p);; hi = 2 * t) {
+        const bool cut = position_bytes(p) >= kDoublingMinBytes || position_bytes(p) * t >= kNextWindowMinBytes;
+        if (t > 0 && (!cut || hi + t / 2 >= p->k_max)) hi = p->k_max;  // no last window shorter than half the one before
+        Window& w = pl.win[pl.windows++];
+        const long rows = (long)p->batch * (hi - t);
+        const long most = hi > t ? (long)p->k_max * ns_max / (hi - t) : kMaxSlices;
+        slice_plan(nvec, t == 0 ? rows * 2 : rows * 2 / 3, most < kMaxSlices ? (int)most : kMaxSlices, w);
+        w.t_lo = t;
+        w.t_hi = hi;
+        if (hi >= p->k_max) break;
+        t = hi;
+    }
     const size_t B = (size_t)p->batch;
     size_t o = align_up((B + 1) * sizeof(int32_t), 256);  // row list of the first pass
     pl.off_list2 = o;    o += align_up((B + 1) * sizeof(int32_t), 256);      // row list of the second pass
     pl.off_log2z = o;    o += 2 * align_up((B ? B : 1) * sizeof(int32_t), 256);  // one double per sequence
     pl.off_state = o;    o += align_up((B ? B : 1) * sizeof(int32_t), 256);
     pl.off_partial = o;
-    // sized for the one-pass schedule as well (a call that asks for draft_logprobs takes it): all
-    // k_max positions at the finer of the two slicings
-    size_t ns_max = (size_t)(pl.NS > pl.NS2 ? pl.NS : pl.NS2);
-    if ((size_t)pl.NSf > ns_max) ns_max = (size_t)pl.NSf;
-    o += align_up(((size_t)p->batch * p->k_max * 2 + 1) * ns_max * sizeof(Partial), 256);
+    o += align_up(((size_t)p->batch * p->k_max * 2 + 1) * (size_t)ns_max * sizeof(Partial), 256);
     const size_t NC = (size_t)chunks_per_row(p->vocab, pl.vec);
     pl.split = split && p->batch >= 1 && p->batch <= kSplitMaxBatch;
     pl.off_arrive = pl.off_best_v = pl.off_best_i = pl.off_chunk_tab = o;
@@ -1128,11 +1156,13 @@ Plan make_plan(const ss_params* p) {
 
 // One row pass over window `win`.  `uniform_rows` > 0 when every sequence has that many rows.
 template <int DT, int VEC>
-void launch_row_pass(LseArgs la, const RowWindow& win, int uniform_rows, int32_t* row_off, Partial* partial,
-                     long max_rows, hipStream_t stream) {
+void launch_row_pass(LseArgs la, const Window& w, const RowWindow& win, int uniform_rows, int32_t* row_off, Partial* partial,
+                     hipStream_t stream) {
     const int B = la.B;
     const int cus = device_cu_count();
     la.win = win;
+    la.NS = w.NS;
+    la.slice_vecs = w.slice_vecs;
     la.uniform_rows = uniform_rows;
     la.row_off = row_off;
     la.partial = partial;
@@ -1141,7 +1171,7 @@ void launch_row_pass(LseArgs la, const RowWindow& win, int uniform_rows, int32_t
     const bool global_list = listed && B > kMaxLdsBatch;
     la.list_in_lds = (listed && !global_list) ? 1 : 0;
     if (global_list) hipLaunchKernelGGL(prep_rows_kernel, dim3(1), dim3(1024), 0, stream, win, B, row_off);
-    const long items = max_rows * 2 * la.NS;
+    const long items = (long)B * (w.t_hi - w.t_lo) * 2 * la.NS;
     if (items <= 0) return;
     const long per_wg = kLseThreads / kWave;
     long wgs = (items + per_wg - 1) / per_wg;
@@ -1156,32 +1186,22 @@ template <int DT, int VEC>
 hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* recovery_logprobs, hipStream_t stream,
                       hipEvent_t* ev) {
     const int B = ra.B, kmax = ra.kmax, V = ra.V;
-    int32_t* off1 = reinterpret_cast<int32_t*>(ws);
-    int32_t* off2 = reinterpret_cast<int32_t*>(ws + pl.off_list2);
+    int32_t* lists[2] = {reinterpret_cast<int32_t*>(ws), reinterpret_cast<int32_t*>(ws + pl.off_list2)};
     int32_t* state = reinterpret_cast<int32_t*>(ws + pl.off_state);
-    Partial* partial1 = reinterpret_cast<Partial*>(ws + pl.off_partial);
-    // the verdict's position-by-position log-probs are only complete in the one-pass schedule
-    const int t1 = ra.draft_logprobs ? kmax : pl.t1;
-    const bool two_pass = t1 < kmax;
+    Partial* partial = reinterpret_cast<Partial*>(ws + pl.off_partial);
+    // the verdicts' position-by-position log-probs are only complete in the one-pass schedule
+    const bool one_pass = ra.draft_logprobs != nullptr || pl.windows == 1;
+    const Window* wins = one_pass ? &pl.all : pl.win;
+    const int windows = one_pass ? 1 : pl.windows;
     hipError_t ev_err = hipSuccess;
     auto mark = [&](int i) {  // stage boundary of the timed entry point
         if (!ev) return;
         const hipError_t e = hipEventRecord(ev[i], stream);
         if (e != hipSuccess && ev_err == hipSuccess) ev_err = e;
     };
-    if (t1 != pl.t1) {  // one pass although the plan was made for two
-        la.NS = pl.NSf;
-        la.slice_vecs = pl.slice_vecsf;
-    }
-    Partial* partial2 = partial1 + (size_t)B * t1 * 2 * la.NS;
-    ra.NS = la.NS;
-    ra.NS2 = pl.NS2;
     const bool ragged = ra.draft_len != nullptr && kmax > 0;
-
-    ra.t1 = t1;
-    ra.rows1 = ragged ? 0 : t1;
-    ra.off1 = off1; ra.off2 = off2; ra.partial1 = partial1; ra.partial2 = partial2;
-    ra.state = two_pass ? state : nullptr;
+    ra.partial = partial;
+    ra.state = windows > 1 ? state : nullptr;
     ra.log2z = recovery_logprobs ? reinterpret_cast<double*>(ws + pl.off_log2z) : nullptr;
     ra.NC = chunks_per_row(V, VEC);
     const RecShape shape = recovery_shape(B, ra.NC, device_cu_count(), pl.split);
@@ -1199,20 +1219,23 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     mark(0);
     if (kmax == 0 && split)  // no row pass to clear the arrival counters
         hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(256), 0, stream, ra.arrive, B);
-    if (kmax > 0)
-        launch_row_pass<DT, VEC>(la, RowWindow{ragged ? ra.draft_len : nullptr, nullptr, kmax, 0, t1},
-                                          ragged ? 0 : t1, off1, partial1, (long)B * t1, stream);
-    mark(1);
-    if (two_pass)
-        hipLaunchKernelGGL((verdict_kernel<DT>), dim3((unsigned)B), dim3(kVerdictThreads), (size_t)2 * kmax * sizeof(double),
-                           stream, ra, state);
-    mark(2);
-    if (two_pass) {
-        la.NS = pl.NS2;
-        la.slice_vecs = pl.slice_vecs2;
+    for (int i = 0; i < windows; ++i) {
+        const Window& w = wins[i];
+        const bool listed = ragged || i > 0;
+        ra.off = lists[i > 0];
+        ra.rows = listed ? 0 : w.t_hi;
+        ra.NS = w.NS;
+        ra.t_lo = w.t_lo;
+        ra.t_hi = w.t_hi;
+        if (kmax > 0)
+            launch_row_pass<DT, VEC>(la, w, RowWindow{listed ? ra.draft_len : nullptr, i > 0 ? state : nullptr, kmax, w.t_lo, w.t_hi},
+                                     listed ? 0 : w.t_hi, lists[i > 0], partial, stream);
         la.zero_n = 0;
-        launch_row_pass<DT, VEC>(la, RowWindow{ra.draft_len, state, kmax, t1, kmax}, 0, off2, partial2,
-                                          (long)B * (kmax - t1), stream);
+        if (i == 0) mark(1);
+        if (i + 1 < windows)
+            hipLaunchKernelGGL((verdict_kernel<DT>), dim3((unsigned)B), dim3(kVerdictThreads),
+                               (size_t)2 * kmax * sizeof(double), stream, ra);
+        if (i == 0) mark(2);
     }
     mark(3);
     // accept + recover: LDS holds the per-position log-probs and one mass per recovery chunk
@@ -1284,7 +1307,7 @@ ss_status verify_block_impl(const void* G, const void* S_ctx, const void* S_noct
     la.G = G; la.Sm = S_noctx; la.row_off = nullptr; la.partial = nullptr; la.uniform_rows = 0;
     la.win = RowWindow{nullptr, nullptr, params->k_max, 0, params->k_max};
     la.sb = sb; la.st = st; la.B = params->batch; la.kmax = params->k_max; la.V = params->vocab;
-    la.NS = pl.NS; la.slice_vecs = pl.slice_vecs; la.list_in_lds = 0; la.c_hi = c_hi;
+    la.NS = 0; la.slice_vecs = 0; la.list_in_lds = 0; la.c_hi = c_hi;
     la.zero_ptr = nullptr; la.zero_n = 0;
 
     RecArgs ra;
@@ -1293,7 +1316,7 @@ ss_status verify_block_impl(const void* G, const void* S_ctx, const void* S_noct
     ra.accepted_len = accepted_len; ra.next_token = next_token;
     ra.next_token_logprob = next_token_logprob;
     ra.draft_logprobs = draft_logprobs; ra.sb = sb; ra.st = st; ra.B = params->batch; ra.kmax = params->k_max;
-    ra.V = params->vocab; ra.NS = pl.NS; ra.NS2 = pl.NS2; ra.NC = 0; ra.c = c;
+    ra.V = params->vocab; ra.NS = 0; ra.NC = 0; ra.c = c;
     ra.bc = (double)params->beta * c; ra.ln_lambda = std::log((double)params->lambda);
     ra.rho = (c - (double)c_hi) / (double)c_hi;
     ra.beta = (double)params->beta;

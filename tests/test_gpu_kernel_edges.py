@@ -80,3 +80,39 @@ def test_slice_merge_edges(binding, oracle, dtype, vocab):
                                beta=w.beta, temperature=w.temperature, want_draft_logprobs=True)
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, want_recovery_logprobs=False)
     parity.compare(out, ora, inp["uniforms"], None)
+
+
+# Windows of 1, 1, 2, ... positions from 240 MiB of rows a position on: 4, 5 and 6 positions end in windows of
+# 2, 3 (no short last window) and 2.  Every length occurs, and one flagged sequence of each kind.
+@pytest.mark.parametrize("k_max,greedy", [(4, False), (5, True), (6, False)])
+def test_doubling_windows_equal_the_one_pass_schedule(binding, oracle, k_max, greedy):
+    w = recipe("c2" if k_max == 6 else "c5", "bf16", batch=1000, k_max=k_max, vocab=63001)
+    inp = W.generate(w, "cuda", seq_chunk=40)
+    p = binding.make_params(w.batch, k_max, w.vocab, torch.bfloat16, lam=w.lam, beta=w.beta, temperature=w.temperature)
+    assert binding.first_window(p) == 1
+    lens = torch.randint(0, k_max + 1, (w.batch,), generator=torch.Generator("cuda").manual_seed(k_max), device="cuda",
+                         dtype=torch.int32)
+    lens[7], lens[8] = k_max + 1, -1
+    lens[9] = k_max
+    inp["draft"][9, k_max - 1] = w.vocab  # out of the vocabulary, behind the first window
+    inp["draft_len"] = lens
+    kw = dict(lam=w.lam, beta=w.beta, temperature=w.temperature, draft_len=lens, greedy=greedy)
+    args = [inp[k] for k in ("G", "S_ctx", "S_noctx", "draft", "uniforms")]
+    got = binding.verify_block(*args, **kw)
+    one = binding.verify_block(*args, full_rows=True, **kw)
+    for k in ("accepted_len", "next_token", "next_token_logprob"):
+        assert torch.equal(torch.nan_to_num(got[k]), torch.nan_to_num(one[k])), k
+    assert got["accepted_len"][7:10].tolist() == [-1, -1, -1]
+    n = got["accepted_len"]
+    seqs = torch.arange(0, w.batch, 20, device="cuda")
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, seqs=seqs, greedy=greedy,
+                            want_recovery_logprobs=False)
+    parity.compare(got, ora, inp["uniforms"], lens, seqs=seqs)
+    for lo in (1, 2):  # rows behind the window a sequence was rejected in are never read
+        out = (n >= 0) & (n < lo) & (lens > lo)
+        assert out.any()
+        for k in ("G", "S_noctx"):
+            inp[k][out, lo:] = float("nan")
+    again = binding.verify_block(*args, **kw)
+    for k in ("accepted_len", "next_token", "next_token_logprob"):
+        assert torch.equal(torch.nan_to_num(got[k]), torch.nan_to_num(again[k])), k

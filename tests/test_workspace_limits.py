@@ -18,10 +18,12 @@ def slices(nvec, row_tensors):
 
 
 def least_bytes(p):
-    """Two row lists, four words a sequence, slice partials of every position at the finest of the three slicings,
+    """Two row lists, four words a sequence, slice partials of every position at the finest of three slicings
+    (one window of all positions, or a quarter of them and the rest),
     and up to 128 sequences a counter, 256 bytes and 8 bytes a recovery chunk each."""
     vec = 8 if p.dtype == B.SS_BF16 else 4
-    nvec, t1 = -(-p.vocab // vec), B.first_window(p)
+    nvec = -(-p.vocab // vec)
+    t1 = p.k_max // 4 if B.first_window(p) < p.k_max else p.k_max
     ns = max(slices(nvec, 2 * p.batch * t1), slices(nvec, 2 * p.batch * (p.k_max - t1) // 3), slices(nvec, 2 * p.batch * p.k_max))
     total = 2 * up(4 * (p.batch + 1)) + 3 * up(4 * max(p.batch, 1)) + up((p.batch * p.k_max * 2 + 1) * ns * 8)
     if 1 <= p.batch <= 128:
