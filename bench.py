@@ -140,7 +140,7 @@ def row_windows(t1, kmax, position_bytes) -> list:
     bounds = [0, t1]
     while bounds[-1] < kmax:
         t = bounds[-1]
-        cut = position_bytes >= 240 << 20 or position_bytes * t >= 448 << 20
+        cut = position_bytes >= 240 << 20
         bounds.append(2 * t if cut and 2 * t + t // 2 < kmax else kmax)
     return bounds
 

@@ -1034,16 +1034,15 @@ RecShape recovery_shape(int B, int NC, int cus, bool split) {
 // a first rejection to cut rows: a first window is scored for everyone, what follows only for the sequences that
 // are still in play.  A further window costs some 10 us (a verdict launch, and the ends of a row pass), the time of
 // 66 MB of rows.
-//   - From kEarlyExitMinBytes of rows: a first window of a quarter of the positions and one of the rest.
+//   - From kEarlyExitMinBytes of rows: a first window of a quarter of the positions and one of the rest (256 ragged
+//     sequences of up to 16 positions, V = 128256: 4 and 12; cut into 4, 4 and 8 it gains 2 us of 168 at
+//     acceptance 0.8 and loses 10 where nearly everything is accepted).
 //   - From kDoublingMinBytes a position, the rows behind one position are already worth a launch: windows of 1,
 //     1, 2, 4, ... positions.  512 sequences of 8 positions, V = 256000 bf16 (524 MB a position): 347 -> 287 us a
 //     step at acceptance 0.4, 590 -> 511 at 0.8; at V = 128256 (263 MB) 193 -> 173 and 303 -> 285.  At 140 MB a
 //     position (273 sequences, V = 128256) it turns: 184 -> 190 at acceptance 0.8.
-//   - From kNextWindowMinBytes in a window as long as all before it, the rest is cut in the same way: 256 ragged
-//     sequences of up to 16 positions, V = 128256 (windows of 4, 4 and 8 instead of 4 and 12) 167.8 -> 164.9 us.
 constexpr long kEarlyExitMinBytes = 512l << 20;
 constexpr long kDoublingMinBytes = 240l << 20;
-constexpr long kNextWindowMinBytes = 448l << 20;
 
 long position_bytes(const ss_params* p) {  // both tensors' rows of one position, all sequences
     return 2l * p->batch * p->vocab * (p->dtype == SS_BF16 ? 2 : 4);
@@ -1111,8 +1110,7 @@ Plan lay_out(const ss_params* p, bool split) {
     if (pl.all.NS > ns_max) ns_max = pl.all.NS;
     pl.windows = 0;
     for (int t = 0, hi = first_window(p);; hi = 2 * t) {
-        const bool cut = position_bytes(p) >= kDoublingMinBytes || position_bytes(p) * t >= kNextWindowMinBytes;
-        if (t > 0 && (!cut || hi + t / 2 >= p->k_max)) hi = p->k_max;  // no last window shorter than half the one before
+        if (t > 0 && (position_bytes(p) < kDoublingMinBytes || hi + t / 2 >= p->k_max)) hi = p->k_max;  // no last window shorter than half the one before
         Window& w = pl.win[pl.windows++];
         const long rows = (long)p->batch * (hi - t);
         const long most = hi > t ? (long)p->k_max * ns_max / (hi - t) : kMaxSlices;
