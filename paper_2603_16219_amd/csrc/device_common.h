@@ -130,8 +130,10 @@ template <> struct RawT<SS_F32, 4> { using type = float4; };
 // them from displacing each other in L2 / Infinity Cache and measure ~12 % faster than plain
 // loads on a pure read of this size.
 // The vector types only promise element alignment (2 bytes for bf16, 4 for fp32): gfx950 under ROCm runs
-// with unaligned access enabled, so the same 16-byte load instruction serves rows that start anywhere
-// (an odd vocabulary size with dense rows) at the cost of an extra cache line per wave-load.
+// with unaligned access enabled, so the same 16-byte load instruction serves rows that start anywhere.
+// At any 4-byte boundary it runs at the full rate (a plain read of 231 MB in rows of V = 50258: 36.8 us, of V = 50256:
+// 36.6); off 4-byte boundaries, every other row of an odd bf16 vocabulary, it does not (V = 50257: 46.3 us).
+// Kernels therefore read such a row from one element before its start (odd_head) and mask that element.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4), aligned(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -160,6 +162,17 @@ __device__ __forceinline__ void unpack(const uint4& r, float (&h)[8]) {
 __device__ __forceinline__ void unpack(const float4& r, float (&h)[4]) {
     h[0] = r.x; h[1] = r.y; h[2] = r.z; h[3] = r.w;
 }
+
+// 1 for a bf16 row that starts off a 4-byte boundary and is not the first element of its tensor (elem_off > 0: the
+// element before it lies in the tensor too), else 0: how many elements before its start the row is read from.
+template <int DT>
+__device__ __forceinline__ int odd_head(const void* row, long elem_off) {
+    return DT == SS_BF16 && elem_off > 0 ? (int)((reinterpret_cast<uintptr_t>(row) >> 1) & 1) : 0;
+}
+// the vector that starts with such an element, with another value in its place
+__device__ __forceinline__ uint4 set_first(uint4 r, unsigned bf16) { r.x = (r.x & 0xFFFF0000u) | bf16; return r; }
+__device__ __forceinline__ float4 set_first(float4 r, unsigned) { return r; }  // fp32 rows have no such element
+constexpr unsigned kBf16NegInf = 0xFF80u;
 
 template <int DT>
 __device__ __forceinline__ float ld_elem(const void* row, long e) {

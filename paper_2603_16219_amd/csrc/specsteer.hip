@@ -280,8 +280,6 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
     const int R = ragged ? off[a.B] : a.B * a.uniform_rows;
     const long items = (long)R * 2 * a.NS;
     const long slice_units = a.slice_vecs;
-    const long nvec = a.V / VEC;
-    const int tailc = a.V - (int)(nvec * VEC);
     constexpr long kGroup = (long)kWave * kUnroll;
 
     for (long item = wave_global; item < items; item += waves_total) {
@@ -302,7 +300,13 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
             b = r / a.uniform_rows;
             t = a.win.t_lo + (r - b * a.uniform_rows);
         }
-        const void* row = row_ptr<DT>(x ? a.Sm : a.G, (long)b * a.sb + (long)t * a.st);
+        const long elem_off = (long)b * a.sb + (long)t * a.st;
+        const void* row = row_ptr<DT>(x ? a.Sm : a.G, elem_off);
+        const int head = __builtin_amdgcn_readfirstlane(odd_head<DT>(row, elem_off));
+        row = row_ptr<DT>(row, -(long)head);
+        const long nvec = (a.V + head) / VEC;
+        const int tailc = a.V + head - (int)(nvec * VEC);
+        const bool masked = head && k == 0;  // this slice starts with the element before the row
         const long v0 = (long)k * slice_units;
         const long v1 = min(nvec, v0 + slice_units);
         const long nfull = v1 > v0 ? (v1 - v0) / kGroup : 0;  // wave-uniform trip count
@@ -313,6 +317,7 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
             typename RawT<DT, VEC>::type raw[kUnroll];
 #pragma unroll
             for (int j = 0; j < kUnroll; ++j) raw[j] = ld_raw<DT, VEC>(row, v + (long)kWave * j);
+            if (masked && g == 0 && lane == 0) raw[0] = set_first(raw[0], kBf16NegInf);
             float h[kUnroll * VEC];
 #pragma unroll
             for (int j = 0; j < kUnroll; ++j) {
@@ -324,11 +329,13 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
             acc_add_f32<kUnroll * VEC>(acc, h, a.c_hi);
         }
         for (; v < v1; v += kWave) {
+            typename RawT<DT, VEC>::type raw = ld_raw<DT, VEC>(row, v);
+            if (masked && v == 0) raw = set_first(raw, kBf16NegInf);
             float hj[VEC];
-            unpack(ld_raw<DT, VEC>(row, v), hj);
+            unpack(raw, hj);
             acc_add_f32<VEC>(acc, hj, a.c_hi);
         }
-        if (k == a.NS - 1 && lane < tailc) {  // logits past the last full vector
+        if (k == a.NS - 1 && lane < tailc && !(head && nvec == 0 && lane == 0)) {  // logits past the last full vector
             float hj[1] = {ld_elem<DT>(row, nvec * VEC + lane)};
             acc_add_f32<1>(acc, hj, a.c_hi);
         }
@@ -361,7 +368,7 @@ struct RecArgs {
     float* draft_logprobs;
     long sb, st;
     int B, kmax, V;
-    int NC;          // chunks per row (full chunks + one pseudo-chunk for the logits past the last vector)
+    int NC;          // chunks per row at most (full chunks + one pseudo-chunk for the logits past the last vector)
     double c;        // log2(e) / T
     double bc;       // beta * log2(e) / T
     double beta;     // beta itself, for the greedy argmax of Eq. 8
@@ -448,7 +455,7 @@ __device__ __forceinline__ float ld_steer(const void* row, long e) {
 // PLAIN forms the terms as the sweep did, 2^(fma(h, c_hi, -E)) in fp32.
 template <int DT, int VEC, bool PLAIN>
 __device__ __forceinline__ void chunk_lane_terms(const void* g, const void* sp, const void* sm, long nvec, int tailc,
-                                                 long nch, long c, int lane, double cc, double bc, float c_hi, int E,
+                                                 int head, long nch, long c, int lane, double cc, double bc, float c_hi, int E,
                                                  float (&p)[kChunkSteps][VEC]) {
     const double dE = (double)E;
     const float nE = -(float)E;
@@ -480,6 +487,7 @@ __device__ __forceinline__ void chunk_lane_terms(const void* g, const void* sp, 
                                 : __builtin_amdgcn_exp2f((float)(rec_y(hg[i], hp[i], hm[i], cc, bc) - dE));
         }
     }
+    if (c == 0 && head && lane == 0) p[0][0] = 0.f;  // the element before the row
     if (c >= nch && lane < tailc) {
         const long e = nvec * VEC + lane;
         const float hg = ld_elem<DT>(g, e);
@@ -494,7 +502,7 @@ __device__ __forceinline__ void chunk_lane_terms(const void* g, const void* sp, 
 // row pass's route, one fp32 fma per logit with the rounded scale c_hi, repaired to first order by the caller.
 template <int DT, int VEC, bool GREEDY, bool PLAIN>
 __device__ __forceinline__ Partial chunk_mass(const void* g, const void* sp, const void* sm, long nvec, int tailc,
-                                              long nch, long c, int lane, double cc, double bc, double beta,
+                                              int head, long nch, long c, int lane, double cc, double bc, double beta,
                                               float c_hi, Best& best) {
     const float cf = (float)cc, bcf = (float)bc;
     Acc acc{kEInit, 0.f};
@@ -510,6 +518,13 @@ __device__ __forceinline__ Partial chunk_mass(const void* g, const void* sp, con
                     rp[j] = ld_raw<DT, VEC>(sp, v);
                     rm[j] = ld_raw<DT, VEC>(sm, v);
                 }
+            }
+        }
+        if (head && vbase == 0) {  // the element before the row: masked, no steering
+            rg[0] = set_first(rg[0], kBf16NegInf);
+            if (!PLAIN) {
+                rp[0] = set_first(rp[0], 0u);
+                rm[0] = set_first(rm[0], 0u);
             }
         }
         if (PLAIN && vbase + (long)(kChunkSteps - 1) * kWave < nvec) {  // a full chunk: one accumulate over its 4 vectors
@@ -573,8 +588,7 @@ __device__ __forceinline__ Partial chunk_mass(const void* g, const void* sp, con
 template <int DT, int VEC, bool GREEDY, bool PLAIN>
 __device__ __forceinline__ double sample_wave(const RecArgs& a, int b, int n, int lane, const Partial* tab,
                                               const void* g, const void* sp, const void* sm, long nvec, int tailc,
-                                              long nch, Best greedy_pick, float* lane_terms) {
-    const int NC = a.NC;
+                                              int head, long nch, int NC, Best greedy_pick, float* lane_terms) {
     const double us = (double)a.uniforms[(long)b * (a.kmax + 1) + a.kmax];
     // each lane owns a contiguous run of `per` chunks
     const int per = (NC + kWave - 1) / kWave;
@@ -637,7 +651,7 @@ __device__ __forceinline__ double sample_wave(const RecArgs& a, int b, int n, in
     // is y_hi * (1 + rho), and the row's log2-sum moves by rho * E* to first order (see acc_add_f32)
     const double fix = PLAIN ? a.rho : 0.0;
     float p[kChunkSteps][VEC];
-    chunk_lane_terms<DT, VEC, PLAIN>(g, sp, sm, nvec, tailc, nch, cstar, lane, a.c, a.bc, a.c_hi, Ec, p);
+    chunk_lane_terms<DT, VEC, PLAIN>(g, sp, sm, nvec, tailc, head, nch, cstar, lane, a.c, a.bc, a.c_hi, Ec, p);
     double lsj[kChunkSteps];
 #pragma unroll
     for (int j = 0; j < kChunkSteps; ++j) {
@@ -670,7 +684,8 @@ __device__ __forceinline__ double sample_wave(const RecArgs& a, int b, int n, in
     // holds something that is not a number; keep the index valid then
     const int i = over ? first_lane(over) : (pos ? 63 - __clzll((long long)pos) : 0);
     const float ptok = pos ? __shfl(pl, i, kWave) : 1.f;
-    const long tok = cstar < nch ? min(((long)cstar * kWave + L) * kOwn + i, (long)a.V - 1) : nvec * VEC + min(L, tailc - 1);
+    const long elem = cstar < nch ? ((long)cstar * kWave + L) * kOwn + i : nvec * VEC + L;
+    const long tok = min(max(elem - head, 0l), (long)a.V - 1);
     // the chosen logit's exponent back from its term: 2^(y - Ec) is a normal fp32 number with one
     // ulp of error, so log2 of it is good to ~2e-7 whatever the magnitude of y.  Lane 0 takes the logarithm
     // of the total, lane 1 that of the term.
@@ -850,14 +865,19 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     const void* g = row_ptr<DT>(a.G, off);
     const void* sp = row_ptr<DT>(a.recSp, off);
     const void* sm = row_ptr<DT>(a.recSm, off);
-    const long nvec = V / VEC;
-    const int tailc = V - (int)(nvec * VEC);
+    // Rows off 4-byte boundaries are read from one element before, if all three are and a vector is there to mask it in
+    const int head = V + 1 >= VEC ? odd_head<DT>(g, off) & odd_head<DT>(sp, off) & odd_head<DT>(sm, off) : 0;
+    g = row_ptr<DT>(g, -(long)head);
+    sp = row_ptr<DT>(sp, -(long)head);
+    sm = row_ptr<DT>(sm, -(long)head);
+    const long nvec = (V + head) / VEC;
+    const int tailc = V + head - (int)(nvec * VEC);
     const long nch = (nvec + kWave * kChunkSteps - 1) / (kWave * kChunkSteps);
-    const int NC = a.NC;
+    const int NC = (int)nch + (tailc ? 1 : 0);  // a.NC or one less
     Best best{-__builtin_huge_val(), 0x7FFFFFFFFFFFFFFFl};
     const int c0 = part * a.part_chunks, c1 = min(NC, c0 + a.part_chunks);
     for (int c = c0 + wave; c < c1; c += NW) {
-        const Partial p = chunk_mass<DT, VEC, GREEDY, PLAIN>(g, sp, sm, nvec, tailc, nch, c, lane, a.c, a.bc, a.beta, a.c_hi, best);
+        const Partial p = chunk_mass<DT, VEC, GREEDY, PLAIN>(g, sp, sm, nvec, tailc, head, nch, c, lane, a.c, a.bc, a.beta, a.c_hi, best);
         if (lane == 0) tab[c] = p;
     }
     if (GREEDY) {
@@ -873,14 +893,15 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
         best.v = lane < NW ? sh_best_v[lane] : -__builtin_huge_val();
         best.idx = lane < NW ? sh_best_i[lane] : 0x7FFFFFFFFFFFFFFFl;
         wave_best(best);
+        if (best.idx <= (long)V) best.idx -= head;
     }
     if (S > 1) {  // deliver this part; only the last part to arrive goes on
-        Partial* gtab = a.chunk_tab + (long)b * NC;
+        Partial* gtab = a.chunk_tab + (long)b * a.NC;
         for (int c = c0 + lane; c < c1; c += kWave) st_dev_partial(gtab + c, tab[c]);
         if (GREEDY && lane == 0) {
-            st_dev(reinterpret_cast<unsigned long long*>(a.best_v + (long)b * NC + part),
+            st_dev(reinterpret_cast<unsigned long long*>(a.best_v + (long)b * a.NC + part),
                    (unsigned long long)__double_as_longlong(best.v));
-            st_dev(a.best_i + (long)b * NC + part, (int32_t)min(best.idx, (long)V));
+            st_dev(a.best_i + (long)b * a.NC + part, (int32_t)min(best.idx, (long)V));
         }
         wait_stores();  // this wave's deliveries have reached memory before it is counted
         unsigned prev = 0;
@@ -892,8 +913,8 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
             best = Best{-__builtin_huge_val(), 0x7FFFFFFFFFFFFFFFl};
             for (int i = lane; i < S; i += kWave) {
                 const double v = __longlong_as_double((long long)ld_dev(
-                    reinterpret_cast<const unsigned long long*>(a.best_v + (long)b * NC + i)));
-                const long idx = (long)ld_dev(a.best_i + (long)b * NC + i);
+                    reinterpret_cast<const unsigned long long*>(a.best_v + (long)b * a.NC + i)));
+                const long idx = (long)ld_dev(a.best_i + (long)b * a.NC + i);
                 if (v > best.v || (v == best.v && idx < best.idx)) best = Best{v, idx};
             }
             wave_best(best);
@@ -902,7 +923,7 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     }
 
     // ---- 4
-    const double log2Z = sample_wave<DT, VEC, GREEDY, PLAIN>(a, b, n, lane, tab, g, sp, sm, nvec, tailc, nch, best, sh_terms);
+    const double log2Z = sample_wave<DT, VEC, GREEDY, PLAIN>(a, b, n, lane, tab, g, sp, sm, nvec, tailc, head, nch, NC, best, sh_terms);
     if (a.log2z && lane == 0) a.log2z[b] = log2Z;
 }
 
@@ -1066,10 +1087,16 @@ bool shape_ok(const ss_params* p) {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-int chunks_per_row(int V, int vec) {
-    const long nvec = V / vec;
+int chunks_of(int elems, int vec) {
+    const long nvec = elems / vec;
     const long nch = (nvec + kWave * kChunkSteps - 1) / (kWave * kChunkSteps);
-    return (int)nch + ((V % vec) ? 1 : 0);
+    return (int)nch + ((elems % vec) ? 1 : 0);
+}
+
+// Recovery chunks of a row; a bf16 row may be read from one element before its start.
+int chunks_per_row(int V, int vec) {
+    const int n = chunks_of(V, vec), m = vec == 8 ? chunks_of(V + 1, vec) : n;
+    return n > m ? n : m;
 }
 
 // Slices per row for a pass expected to cover `row_tensors` (row, tensor) pairs: 64 KiB slices for
@@ -1137,7 +1164,8 @@ Plan lay_out(const ss_params* p, bool split) {
         pl.off_chunk_tab = o;  o += align_up(B * NC * sizeof(Partial), 256);
     } else if (p->batch >= 1 && p->batch <= kSplitMaxBatch) {
         // not used, and never more than the tables: which blocks fit the static scratch stays what it is
-        o += align_up(B * sizeof(uint32_t), 256) + align_up(B * 256, 256) + align_up(B * NC * sizeof(Partial), 256);
+        o += align_up(B * sizeof(uint32_t), 256) + align_up(B * 256, 256) +
+             align_up(B * (size_t)chunks_of(p->vocab, pl.vec) * sizeof(Partial), 256);
     }
     pl.bytes = o;
     return pl;

@@ -116,3 +116,28 @@ def test_doubling_windows_equal_the_one_pass_schedule(binding, oracle, k_max, gr
     again = binding.verify_block(*args, **kw)
     for k in ("accepted_len", "next_token", "next_token_logprob"):
         assert torch.equal(torch.nan_to_num(got[k]), torch.nan_to_num(again[k])), k
+
+
+# bf16 rows off 4-byte boundaries are read from one element before their start, which is masked: an odd stride puts
+# every other row there.  The padding (and so the element before a row) is NaN.  Sizes around a vector, a chunk and
+# a slice; `shift` moves G alone (its rows then differ in parity from the specialists').
+@pytest.mark.parametrize("greedy,beta", [(False, 0.8), (True, 0.8), (False, 0.0)])
+@pytest.mark.parametrize("vocab,pad,shift", [(6, 1, 0), (7, 2, 0), (8, 1, 0), (9, 0, 0), (2047, 0, 0), (2048, 1, 0), (2049, 2, 0),
+                                             (16384, 3, 0), (16391, 0, 0), (16391, 0, 1), (16384, 3, 1), (9, 2, 1)])
+def test_rows_at_odd_elements(binding, oracle, vocab, pad, shift, greedy, beta):
+    w = recipe("c4", "bf16", batch=6, k_max=3, vocab=vocab + pad)
+    inp = W.generate(w, "cuda")
+    for k in ("G", "S_ctx", "S_noctx"):
+        inp[k][..., vocab:] = float("nan")
+        if k == "G" and shift:
+            flat = torch.full((inp[k].numel() + 1,), float("nan"), dtype=torch.bfloat16, device="cuda")
+            flat[1:].copy_(inp[k].reshape(-1))
+            inp[k] = flat[1:].view_as(inp[k])
+        inp[k] = inp[k][..., :vocab]
+    inp["draft"] = inp["draft"].clamp(max=vocab - 1)
+    inp["draft_len"] = torch.tensor([3, 0, 1, 2, 3, 2], dtype=torch.int32, device="cuda")
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam, beta=beta,
+                               temperature=w.temperature, draft_len=inp["draft_len"], greedy=greedy,
+                               want_recovery_logprobs=True, want_draft_logprobs=True)
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=beta, temperature=w.temperature, greedy=greedy)
+    parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
