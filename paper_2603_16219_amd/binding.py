@@ -35,6 +35,9 @@ class SSParams(ctypes.Structure):
     ]
 
 
+_DTYPES = {torch.float32: SS_F32, torch.bfloat16: SS_BF16}
+
+
 class SpecSteerError(RuntimeError):
     def __init__(self, status: int, message: str):
         super().__init__(f"specsteer status {status}: {message}")
@@ -88,7 +91,7 @@ def version() -> int:
 
 def make_params(batch: int, k_max: int, vocab: int, dtype: torch.dtype, *, lam: float, beta: float,
                 temperature: float, stride_b: int = 0, stride_t: int = 0, flags: int = 0) -> SSParams:
-    code = {torch.float32: SS_F32, torch.bfloat16: SS_BF16}.get(dtype)
+    code = _DTYPES.get(dtype)
     if code is None:
         raise TypeError(f"logits must be float32 or bfloat16, got {dtype}")
     return SSParams(batch, k_max, vocab, code, stride_b, stride_t, lam, beta, temperature, flags)
@@ -103,7 +106,21 @@ def workspace_bytes(params: SSParams) -> int:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _stream(device: torch.device) -> int:
+    """The handle of torch's current stream on `device` (torch.cuda.current_stream without its Stream object,
+    which takes as long to build as the smallest launch)."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if device.index is None else device.index)
+
+
+def _ready(t: torch.Tensor, device: torch.device, dtype: torch.dtype) -> torch.Tensor:
+    """`t` as a contiguous tensor of `dtype` on `device`; itself if it is one (a no-op .to().contiguous() costs
+    a microsecond, several of which are most of a small call)."""
+    if t.dtype is dtype and t.device == device and t.is_contiguous():
+        return t
+    return t.to(device=device, dtype=dtype).contiguous()
 
 
 STAGES = ("row_pass1", "verdict", "row_pass2", "recover")
@@ -116,13 +133,13 @@ def verify_block_raw(G, S_ctx, S_noctx, draft, draft_len, uniforms, params: SSPa
     With ``timed`` it calls specsteer_verify_block_timed (which waits for the stream) and returns
     the per-stage milliseconds as a dict."""
     if stream is None:
-        stream = torch.cuda.current_stream(G.device).cuda_stream
+        stream = _stream(G.device)
     args = [
         _ptr(G), _ptr(S_ctx), _ptr(S_noctx), _ptr(draft), _ptr(draft_len), _ptr(uniforms),
         ctypes.byref(params), _ptr(accepted_len), _ptr(next_token), _ptr(next_token_logprob),
         _ptr(recovery_logprobs), _ptr(draft_logprobs), _ptr(workspace),
         0 if workspace is None else workspace.numel() * workspace.element_size(),
-        ctypes.c_void_p(stream)]
+        stream]
     if timed:
         ms = (ctypes.c_float * len(STAGES))()
         rc = library().specsteer_verify_block_timed(*args, ctypes.cast(ms, ctypes.c_void_p))
@@ -142,11 +159,11 @@ def verify_block_static_raw(G, S_ctx, S_noctx, draft, draft_len, uniforms, param
     """Thin call of specsteer_verify_block_static: the block on the library's own scratch array, no
     workspace argument and no allocation anywhere in the call."""
     if stream is None:
-        stream = torch.cuda.current_stream(G.device).cuda_stream
+        stream = _stream(G.device)
     rc = library().specsteer_verify_block_static(
         _ptr(G), _ptr(S_ctx), _ptr(S_noctx), _ptr(draft), _ptr(draft_len), _ptr(uniforms), ctypes.byref(params),
         _ptr(accepted_len), _ptr(next_token), _ptr(next_token_logprob), _ptr(recovery_logprobs),
-        _ptr(draft_logprobs), ctypes.c_void_p(stream))
+        _ptr(draft_logprobs), stream)
     if rc != _STATUS_OK:
         raise SpecSteerError(rc, status_string(rc))
 
@@ -179,10 +196,10 @@ def verify_block(G: torch.Tensor, S_ctx: torch.Tensor, S_noctx: torch.Tensor, dr
         raise ValueError("specsteer_verify_block needs device tensors; there is no CPU path")
     if workspace is not None and (not workspace.is_cuda or not workspace.is_contiguous()):
         raise ValueError("workspace must be a contiguous device tensor")
-    draft = draft.to(device=dev, dtype=torch.int32).contiguous()
-    uniforms = uniforms.to(device=dev, dtype=torch.float32).contiguous()
+    draft = _ready(draft, dev, torch.int32)
+    uniforms = _ready(uniforms, dev, torch.float32)
     if draft_len is not None:
-        draft_len = draft_len.to(device=dev, dtype=torch.int32).contiguous()
+        draft_len = _ready(draft_len, dev, torch.int32)
     params = make_params(B, k_max, V, G.dtype, lam=lam, beta=beta, temperature=temperature,
                          stride_b=G.stride(0) if B > 1 else 0, stride_t=G.stride(1) if k1 > 1 else 0,
                          flags=(SS_FLAG_GREEDY if greedy else 0) | (SS_FLAG_FULL_ROWS if full_rows else 0))
@@ -212,11 +229,33 @@ def steer_rows(G: torch.Tensor, S_ctx: torch.Tensor, S_noctx: torch.Tensor, unif
     if G.dim() != 2 or uniforms.numel() != G.shape[0]:
         raise ValueError("rows must be [N, V] with one uniform per row")
     n, v = G.shape
-    out = verify_block(G.view(n, 1, v), S_ctx.view(n, 1, v), S_noctx.view(n, 1, v),
-                       torch.empty(n, 0, dtype=torch.int32, device=G.device), uniforms.reshape(n, 1),
-                       beta=beta, temperature=temperature, want_recovery_logprobs=want_logprobs, greedy=greedy)
-    return {"token": out["next_token"], "token_logprob": out["next_token_logprob"],
-            "logprobs": out["recovery_logprobs"]}
+    if not (G.shape == S_ctx.shape == S_noctx.shape):
+        S_ctx, S_noctx = S_ctx.view(n, v), S_noctx.view(n, v)
+    if not (G.dtype == S_ctx.dtype == S_noctx.dtype):
+        raise ValueError("logit tensors must share a dtype")
+    stride = G.stride()
+    lead = 0 if n > 1 else 1  # the row stride of a single row means nothing
+    if not (stride[lead:] == S_ctx.stride()[lead:] == S_noctx.stride()[lead:]) or stride[1] != 1:
+        raise ValueError("logit tensors must share strides, with the vocabulary contiguous")
+    if not (G.is_cuda and S_ctx.is_cuda and S_noctx.is_cuda):
+        raise ValueError("specsteer_verify_block needs device tensors; there is no CPU path")
+    dev = G.device
+    uniforms = _ready(uniforms, dev, torch.float32)
+    params = make_params(n, 0, v, G.dtype, lam=0.5, beta=beta, temperature=temperature,
+                         stride_b=stride[0] if n > 1 else 0, flags=SS_FLAG_GREEDY if greedy else 0)
+    # one allocation for the workspace and, behind it, the accepted lengths (all 0) that nobody asked for
+    need = (max(workspace_bytes(params), 256) + 255) // 256 * 256
+    workspace = torch.empty(need + 4 * n, dtype=torch.uint8, device=dev)
+    token = torch.empty(n, dtype=torch.int32, device=dev)
+    token_logprob = torch.empty(n, dtype=torch.float32, device=dev)
+    logprobs = torch.empty(n, v, dtype=torch.float32, device=dev) if want_logprobs else None
+    at = workspace.data_ptr()
+    rc = library().specsteer_verify_block(
+        G.data_ptr(), S_ctx.data_ptr(), S_noctx.data_ptr(), None, None, uniforms.data_ptr(), ctypes.byref(params),
+        at + need, token.data_ptr(), token_logprob.data_ptr(), _ptr(logprobs), None, at, need, _stream(dev))
+    if rc != _STATUS_OK:
+        raise SpecSteerError(rc, status_string(rc))
+    return {"token": token, "token_logprob": token_logprob, "logprobs": logprobs}
 
 
 def sample_rows(logits: torch.Tensor, uniforms: torch.Tensor, *, temperature: float = 1.0,
@@ -243,12 +282,12 @@ def cloud_topk(G: torch.Tensor, S_noctx: torch.Tensor, row: torch.Tensor, *, bet
         raise ValueError(f"row must be [B] = [{B}], got {tuple(row.shape)}")
     if not (G.is_cuda and S_noctx.is_cuda):
         raise ValueError("specsteer_cloud_topk needs device tensors; there is no CPU path")
-    row = row.to(device=G.device, dtype=torch.int32).contiguous()
+    row = _ready(row, G.device, torch.int32)
     idx = torch.empty(B, topk, dtype=torch.int32, device=G.device)
     val = torch.empty(B, topk, dtype=torch.float32, device=G.device)
     p = _split_params(G, beta, 1.0, False)
     rc = library().specsteer_cloud_topk(_ptr(G), _ptr(S_noctx), _ptr(row), ctypes.byref(p), topk, _ptr(idx), _ptr(val),
-                                        ctypes.c_void_p(torch.cuda.current_stream(G.device).cuda_stream))
+                                        _stream(G.device))
     if rc != _STATUS_OK:
         raise SpecSteerError(rc, status_string(rc))
     return idx, val
@@ -270,14 +309,14 @@ def edge_resample(index: torch.Tensor, value: torch.Tensor, S_ctx: torch.Tensor,
         raise ValueError(f"row and uniform must be [B] = [{B}]")
     if not (S_ctx.is_cuda and index.is_cuda and value.is_cuda):
         raise ValueError("specsteer_edge_resample needs device tensors; there is no CPU path")
-    row = row.to(device=dev, dtype=torch.int32).contiguous()
-    uniform = None if uniform is None else uniform.to(device=dev, dtype=torch.float32).contiguous()
+    row = _ready(row, dev, torch.int32)
+    uniform = None if uniform is None else _ready(uniform, dev, torch.float32)
     tok = torch.empty(B, dtype=torch.int32, device=dev)
     lp = torch.empty(B, dtype=torch.float32, device=dev)
     p = _split_params(S_ctx, beta, temperature, greedy)
     rc = library().specsteer_edge_resample(_ptr(index.contiguous()), _ptr(value.contiguous()), _ptr(S_ctx), _ptr(row),
                                            _ptr(uniform), ctypes.byref(p), index.shape[1], _ptr(tok), _ptr(lp),
-                                           ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream))
+                                           _stream(dev))
     if rc != _STATUS_OK:
         raise SpecSteerError(rc, status_string(rc))
     return {"next_token": tok, "next_token_logprob": lp}

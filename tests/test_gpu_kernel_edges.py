@@ -141,3 +141,31 @@ def test_rows_at_odd_elements(binding, oracle, vocab, pad, shift, greedy, beta):
                                want_recovery_logprobs=True, want_draft_logprobs=True)
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=beta, temperature=w.temperature, greedy=greedy)
     parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
+
+
+def test_row_modes_take_every_form_of_rows_the_block_takes(binding):
+    """steer_rows and sample_rows hand pointers over themselves: padded rows, a single row cut from a wider tensor,
+    specialist logits of another shape, uniforms of another type, shape or device must give what the block gives."""
+    w = recipe("c4", "bf16", batch=4, k_max=1, vocab=3001)
+    inp = W.generate(w, "cuda")
+    wide = {k: torch.cat([inp[k].view(8, 3001), torch.full((8, 7), float("nan"), dtype=torch.bfloat16, device="cuda")], 1)
+            for k in ("G", "S_ctx", "S_noctx")}
+    u = inp["uniforms"].reshape(8)
+    flat = [inp[k].view(8, 3001) for k in ("G", "S_ctx", "S_noctx")]
+    want = binding.verify_block(*(t.view(8, 1, 3001) for t in flat), torch.empty(8, 0, dtype=torch.int32, device="cuda"),
+                                u.view(8, 1), beta=0.7, temperature=0.9, want_recovery_logprobs=True)
+    kw = dict(beta=0.7, temperature=0.9, want_logprobs=True)
+    padded = [wide[k][:, :3001] for k in ("G", "S_ctx", "S_noctx")]
+    for rows, un in ((flat, u), (padded, u.double()), ([flat[0], inp["S_ctx"], inp["S_noctx"]], u.view(2, 4)), (flat, u.cpu())):
+        got = binding.steer_rows(*rows, un, **kw)
+        # padded rows start at other offsets: the sums of a row at an odd element are grouped differently
+        assert torch.equal(got["token"], want["next_token"])
+        assert torch.allclose(got["token_logprob"], want["next_token_logprob"], rtol=0, atol=2e-6)
+        assert torch.allclose(got["logprobs"], want["recovery_logprobs"], rtol=0, atol=4e-6)
+    one = binding.steer_rows(padded[0][3:4], flat[1][3:4], padded[2][3:4], u[3:4], **kw)
+    assert one["token"].item() == want["next_token"][3].item()
+    for bad in ((flat[0], flat[1], flat[2][:, ::2]), (flat[0], flat[1].float(), flat[2]), (flat[0], padded[1], flat[2])):
+        with pytest.raises((ValueError, RuntimeError)):
+            binding.steer_rows(*bad, u, **kw)
+    with pytest.raises(ValueError):
+        binding.steer_rows(*(t.cpu() for t in flat), u, **kw)
