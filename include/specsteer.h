@@ -25,7 +25,9 @@
  * each [B, k_max+1, V], vocabulary contiguous.  Row t is the next-token
  * distribution after the prefix plus draft tokens 0..t-1, so row t scores
  * draft[b][t] and row K_b is the bonus row.  Rows t > K_b, draft slots
- * t >= K_b and S_ctx rows other than n_b are never read.
+ * t >= K_b and S_ctx rows other than n_b are never read.  (A bf16 row
+ * at an odd element is fetched together with the one element before it in the
+ * tensor, whose value never matters.)
  *
  * Pointers marked "device" must be dereferenceable by the GPU the call runs
  * on; "host" pointers are read on the CPU during the call.  No entry point
@@ -113,8 +115,9 @@ size_t specsteer_workspace_bytes(const ss_params *params);
  *                      recovery distribution is Softmax(G/T) and S_ctx is not read.  Pointers
  *                      need element alignment only (SS_ERR_STRIDE otherwise) and any V works;
  *                      rows that start on 16-byte boundaries (base pointers 16-byte aligned,
- *                      strides multiples of 16 bytes) stream fastest, others cost about a
- *                      third more.
+ *                      strides multiples of 16 bytes) stream fastest, others take up to a
+ *                      tenth longer (a third where bf16 rows of the three tensors lie at odd
+ *                      and even elements).
  *   draft              device, [B, k_max] int32 token ids; slots t >= K_b ignored.
  *                      May be NULL when k_max == 0.
  *   draft_len          device, [B] int32 K_b, or NULL meaning K_b = k_max for all b.

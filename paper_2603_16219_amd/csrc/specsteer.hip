@@ -377,12 +377,12 @@ struct RecArgs {
     float c_hi;      // fl32(c)
     int greedy;      // SS_FLAG_GREEDY
     int plain;       // beta == 0: no steering term, the specialist rows are not read by the recovery sweep
-    // Split recovery (small batches): `parts` workgroups share the recovery row of one sequence.
+    // Small batches: `parts` workgroups share the recovery row of one sequence.
     int parts, part_chunks;  // part i takes chunks [i * part_chunks, (i+1) * part_chunks)
     Partial* chunk_tab;   // [B][NC] chunk masses, filled by the parts
-    double* best_v;       // [B][NC] greedy candidates of the waves: value ...
+    double* best_v;       // [B][NC] greedy candidates of the parts: value ...
     int32_t* best_i;      // [B][NC] ... and token
-    uint32_t* arrive;     // [B][kArriveStride] waves that have delivered; cleared by the first row pass
+    uint32_t* arrive;     // [B][kArriveStride] parts that have delivered; cleared by the first row pass
 };
 
 // Hand-over between workgroups that may run on different XCDs, whose L2 caches are not coherent with each
