@@ -169,3 +169,38 @@ def test_row_modes_take_every_form_of_rows_the_block_takes(binding):
             binding.steer_rows(*bad, u, **kw)
     with pytest.raises(ValueError):
         binding.steer_rows(*(t.cpu() for t in flat), u, **kw)
+
+
+def test_doubling_windows_inside_a_hip_graph(binding):
+    """The launches of several windows captured once and replayed on new drafts, lengths and uniforms, with eager
+    calls on the same workspace between the replays; every replay equals the direct call."""
+    w = recipe("c5", "bf16", batch=1000, k_max=5, vocab=63001)
+    inp = W.generate(w, "cuda", seq_chunk=40)
+    inp["draft_len"] = torch.randint(0, 6, (1000,), device="cuda", dtype=torch.int32)
+    p = binding.make_params(1000, 5, w.vocab, torch.bfloat16, lam=w.lam, beta=w.beta, temperature=w.temperature)
+    assert binding.first_window(p) == 1
+    ws = torch.empty(binding.workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    outs = [[torch.empty(1000, dtype=dt, device="cuda") for dt in (torch.int32, torch.int32, torch.float32)] for _ in range(2)]
+
+    def call(out):
+        binding.verify_block_raw(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["draft_len"], inp["uniforms"], p,
+                                 *out, None, None, ws)
+
+    call(outs[0])
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call(outs[0])
+    for rnd in range(4):
+        gen = torch.Generator("cuda").manual_seed(rnd)
+        inp["uniforms"].uniform_(generator=gen)
+        inp["draft_len"].random_(0, 6, generator=gen)
+        inp["draft"].copy_(inp["draft"].roll(1, 0))
+        for t in outs[0]:
+            t.fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        call(outs[1])
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(*outs)), rnd
+        assert torch.all(outs[0][0] >= 0)
