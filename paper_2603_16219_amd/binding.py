@@ -309,12 +309,15 @@ def edge_resample(index: torch.Tensor, value: torch.Tensor, S_ctx: torch.Tensor,
         raise ValueError(f"row and uniform must be [B] = [{B}]")
     if not (S_ctx.is_cuda and index.is_cuda and value.is_cuda):
         raise ValueError("specsteer_edge_resample needs device tensors; there is no CPU path")
+    # bound to names: a copy that nothing holds is freed before the call, and the next one may take its memory
+    index = _ready(index, dev, torch.int32)
+    value = _ready(value, dev, torch.float32)
     row = _ready(row, dev, torch.int32)
     uniform = None if uniform is None else _ready(uniform, dev, torch.float32)
     tok = torch.empty(B, dtype=torch.int32, device=dev)
     lp = torch.empty(B, dtype=torch.float32, device=dev)
     p = _split_params(S_ctx, beta, temperature, greedy)
-    rc = library().specsteer_edge_resample(_ptr(index.contiguous()), _ptr(value.contiguous()), _ptr(S_ctx), _ptr(row),
+    rc = library().specsteer_edge_resample(_ptr(index), _ptr(value), _ptr(S_ctx), _ptr(row),
                                            _ptr(uniform), ctypes.byref(p), index.shape[1], _ptr(tok), _ptr(lp),
                                            _stream(dev))
     if rc != _STATUS_OK:

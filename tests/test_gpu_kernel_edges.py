@@ -204,3 +204,17 @@ def test_doubling_windows_inside_a_hip_graph(binding):
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(*outs)), rnd
         assert torch.all(outs[0][0] >= 0)
+
+
+def test_edge_resample_on_columns_of_a_wider_payload(binding):
+    """The first 16 columns of a top-32 payload, handed over as a view, give what a copy of them gives."""
+    w = recipe("c4", "bf16", batch=9, k_max=2, vocab=4099)
+    inp = W.generate(w, "cuda")
+    row = torch.randint(0, 3, (9,), generator=torch.Generator("cuda").manual_seed(3), device="cuda", dtype=torch.int32)
+    idx, val = binding.cloud_topk(inp["G"], inp["S_noctx"], row, beta=w.beta, topk=32)
+    u = inp["uniforms"][:, -1].contiguous()
+    copies = idx[:, :16].contiguous(), val[:, :16].contiguous()
+    want = binding.edge_resample(*copies, inp["S_ctx"], row, u, beta=w.beta, temperature=w.temperature)
+    got = binding.edge_resample(idx[:, :16], val[:, :16], inp["S_ctx"], row, u, beta=w.beta, temperature=w.temperature)
+    for k in ("next_token", "next_token_logprob"):
+        assert torch.equal(got[k], want[k]), k
