@@ -123,6 +123,18 @@ def _ready(t: torch.Tensor, device: torch.device, dtype: torch.dtype) -> torch.T
     return t.to(device=device, dtype=dtype).contiguous()
 
 
+def _stride(rows: torch.Tensor, dim: int) -> int:
+    """The stride of dimension `dim` of the logits as the library takes it, where 0 means dense.  A dimension of one
+    has no stride worth passing on; one that repeats the same memory (an expanded tensor) would be read as dense,
+    past its end, and is refused like rows that overlap in part."""
+    if rows.shape[dim] <= 1:
+        return 0
+    stride = rows.stride(dim)
+    if stride == 0:
+        raise ValueError("logit rows must not repeat the same memory (an expanded tensor): pass a contiguous copy")
+    return stride
+
+
 STAGES = ("row_pass1", "verdict", "row_pass2", "recover")
 
 
@@ -201,7 +213,7 @@ def verify_block(G: torch.Tensor, S_ctx: torch.Tensor, S_noctx: torch.Tensor, dr
     if draft_len is not None:
         draft_len = _ready(draft_len, dev, torch.int32)
     params = make_params(B, k_max, V, G.dtype, lam=lam, beta=beta, temperature=temperature,
-                         stride_b=G.stride(0) if B > 1 else 0, stride_t=G.stride(1) if k1 > 1 else 0,
+                         stride_b=_stride(G, 0), stride_t=_stride(G, 1),
                          flags=(SS_FLAG_GREEDY if greedy else 0) | (SS_FLAG_FULL_ROWS if full_rows else 0))
     need = workspace_bytes(params)
     if workspace is None:
@@ -242,7 +254,7 @@ def steer_rows(G: torch.Tensor, S_ctx: torch.Tensor, S_noctx: torch.Tensor, unif
     dev = G.device
     uniforms = _ready(uniforms, dev, torch.float32)
     params = make_params(n, 0, v, G.dtype, lam=0.5, beta=beta, temperature=temperature,
-                         stride_b=stride[0] if n > 1 else 0, flags=SS_FLAG_GREEDY if greedy else 0)
+                         stride_b=_stride(G, 0), flags=SS_FLAG_GREEDY if greedy else 0)
     # one allocation for the workspace and, behind it, the accepted lengths (all 0) that nobody asked for
     need = (max(workspace_bytes(params), 256) + 255) // 256 * 256
     workspace = torch.empty(need + 4 * n, dtype=torch.uint8, device=dev)
@@ -268,7 +280,7 @@ def sample_rows(logits: torch.Tensor, uniforms: torch.Tensor, *, temperature: fl
 def _split_params(T: torch.Tensor, beta: float, temperature: float, greedy: bool) -> SSParams:
     B, k1, V = T.shape
     return make_params(B, k1 - 1, V, T.dtype, lam=0.5, beta=beta, temperature=temperature,
-                       stride_b=T.stride(0) if B > 1 else 0, stride_t=T.stride(1) if k1 > 1 else 0,
+                       stride_b=_stride(T, 0), stride_t=_stride(T, 1),
                        flags=SS_FLAG_GREEDY if greedy else 0)
 
 

@@ -87,3 +87,41 @@ def test_edge_resample_hands_over_the_payload_it_was_given(library, monkeypatch,
     binding.edge_resample(dev(index), dev(value), S, torch.zeros(B, dtype=torch.int32), torch.zeros(B))
     assert seen["copies"] == (0 if layout == "dense" else 2) and seen["dead"] == 0
     assert seen["index"] == want_i.reshape(-1).tolist() and seen["value"] == want_v.reshape(-1).tolist()
+
+
+def zero_stride_views():
+    """[4, 3, 8] logits of which one dimension repeats the same memory."""
+    return {"sequences": torch.zeros(1, 3, 8).expand(4, 3, 8), "positions": torch.zeros(4, 1, 8).expand(4, 3, 8),
+            "both": torch.zeros(8).expand(4, 3, 8)}
+
+
+@pytest.mark.parametrize("form", ["sequences", "positions", "both"])
+def test_rows_that_repeat_the_same_memory_are_refused(library, form):
+    """A stride of 0 means dense rows to the library, which would then read past the end of an expanded tensor."""
+    lib = library()
+    x = dev(zero_stride_views()[form])
+    row, draft = torch.zeros(4, dtype=torch.int32), torch.zeros(4, 2, dtype=torch.int32)
+    ids, val = dev(torch.zeros(4, 5, dtype=torch.int32)), dev(torch.zeros(4, 5))
+    for call in (lambda: binding.verify_block(x, x, x, draft, torch.zeros(4, 3), workspace=dev(torch.zeros(256))),
+                 lambda: binding.cloud_topk(x, x, row, topk=5),
+                 lambda: binding.edge_resample(ids, val, x, row, torch.zeros(4))):
+        with pytest.raises(ValueError, match="same memory"):
+            call()
+    rows = dev(torch.zeros(8).expand(4, 8))
+    for call in (lambda: binding.steer_rows(rows, rows, rows, torch.zeros(4)),
+                 lambda: binding.sample_rows(rows, torch.zeros(4))):
+        with pytest.raises(ValueError, match="same memory"):
+            call()
+    assert not any(name.startswith(("specsteer_verify", "specsteer_cloud", "specsteer_edge")) for name, _ in lib.calls)
+
+
+def test_a_zero_stride_of_a_dimension_of_one_is_no_repetition(library):
+    """Nothing is repeated along a dimension of one: its stride means nothing and is passed on as dense."""
+    lib = library()
+    one = dev(torch.zeros(8).as_strided((1, 1, 8), (0, 0, 1)))
+    row = torch.zeros(1, dtype=torch.int32)
+    binding.cloud_topk(one, one, row, topk=5)
+    binding.edge_resample(dev(torch.zeros(1, 5, dtype=torch.int32)), dev(torch.zeros(1, 5)), one, row, torch.zeros(1))
+    binding.sample_rows(dev(torch.zeros(8).as_strided((1, 8), (0, 1))), torch.zeros(1))
+    assert [n for n, _ in lib.calls] == ["specsteer_cloud_topk", "specsteer_edge_resample", "specsteer_workspace_bytes",
+                                         "specsteer_verify_block"]
