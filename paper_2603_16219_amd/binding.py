@@ -111,7 +111,9 @@ def _ptr(t: Optional[torch.Tensor]):
 
 def _stream(device: torch.device) -> int:
     """The handle of torch's current stream on `device` (torch.cuda.current_stream without its Stream object,
-    which takes as long to build as the smallest launch)."""
+    which takes as long to build as the smallest launch).  Like it, it refuses a device that is no GPU."""
+    if device.type != "cuda":
+        raise ValueError(f"logits must be on a GPU device, got {device}; there is no CPU path")
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if device.index is None else device.index)
 
 

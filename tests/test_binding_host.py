@@ -125,3 +125,21 @@ def test_a_zero_stride_of_a_dimension_of_one_is_no_repetition(library):
     binding.sample_rows(dev(torch.zeros(8).as_strided((1, 8), (0, 1))), torch.zeros(1))
     assert [n for n, _ in lib.calls] == ["specsteer_cloud_topk", "specsteer_edge_resample", "specsteer_workspace_bytes",
                                          "specsteer_verify_block"]
+
+
+@pytest.mark.parametrize("device", ["cpu", "meta"])
+@pytest.mark.parametrize("entry", ["verify_block_raw", "verify_block_static_raw"])
+def test_raw_entry_points_refuse_host_tensors(monkeypatch, device, entry):
+    """They check nothing else, but the stream they look up by themselves is that of the logits' device: logits on no
+    GPU end there, on a machine that has one too, before the kernel is handed a host address."""
+    lib = Recorder()
+    monkeypatch.setattr(binding, "library", lambda: lib)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda index: 0, raising=False)
+    x = torch.zeros(1, 2, 8, device=device)
+    p = binding.make_params(1, 1, 8, torch.float32, lam=0.5, beta=1.0, temperature=1.0)
+    out = [torch.zeros(1, dtype=torch.int32), torch.zeros(1, dtype=torch.int32), torch.zeros(1), None, None]
+    extra = [torch.zeros(256)] if entry == "verify_block_raw" else []
+    with pytest.raises(ValueError, match="device"):
+        getattr(binding, entry)(x, x, x, torch.zeros(1, 1, dtype=torch.int32), None, torch.zeros(1, 2), p, *out, *extra)
+    assert lib.calls == []
