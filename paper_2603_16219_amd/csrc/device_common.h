@@ -9,11 +9,10 @@
 
 #include <cstdint>
 
+#include "plan.h"  // kWave
 #include "specsteer.h"
 
 namespace {
-
-constexpr int kWave = 64;
 
 // ------------------------------------------------------------------ wave primitives
 

@@ -38,42 +38,16 @@
 #include <cstdint>
 
 #include "device_common.h"
+#include "plan.h"
 #include "specsteer.h"
 
 namespace {
 
 constexpr int kLseThreads = 256;            // 4 independent waves per workgroup
-// Launch-shape constants of the row pass; the defaults are the measured optimum on MI355X for
-// the B=256, V=128256 bf16 workload and can be overridden at build time for other sweeps.
-#ifndef SS_LSE_UNROLL
-#define SS_LSE_UNROLL 4
-#endif
-#ifndef SS_LSE_WG_PER_CU
-#define SS_LSE_WG_PER_CU 4
-#endif
-#ifndef SS_LSE_MAX_SLICE_VECS
-#define SS_LSE_MAX_SLICE_VECS 4096
-#endif
-constexpr int kLseUnroll = SS_LSE_UNROLL;   // 16-byte loads in flight per lane
-constexpr int kLseWgPerCu = SS_LSE_WG_PER_CU;  // persistent workgroups per CU
-constexpr int kMinSliceVecs = kWave * kLseUnroll;  // smallest slice: one unrolled group
-constexpr int kMaxSliceVecs = SS_LSE_MAX_SLICE_VECS;  // 64 KiB of logits per slice
-constexpr int kMaxSlices = 64;
-constexpr int kMaxLdsBatch = 8192;          // ragged batches up to this size keep their row list in LDS
-// Arrival counters of different sequences lie 256 bytes apart: atomics on one cache line are served one after the
-// other, 7.4 ns each (4800 arrivals on 64 neighbouring counters: 36 us; 256 or 64 bytes apart: no queue).
-constexpr int kArriveStride = 64;
-constexpr int kChunkSteps = 4;              // recovery chunk = 4 wave-steps (2048 bf16 logits)
 constexpr int kEInit = -(1 << 29);          // "no logit seen yet" exponent reference
 constexpr float kEClamp = 5.0e8f;           // keeps (int)ceil(h*c) inside int32 for any finite h
 constexpr double kLn2 = 0.693147180559945309417232121458;
 constexpr double kLog2e = 1.442695040888963407359924681002;
-
-
-struct Partial {
-    int E;    // integer exponent reference of this slice
-    float s;  // sum over the slice of 2^(h*c - E)
-};
 
 // ------------------------------------------------------------------ online sum of exponentials
 
@@ -1003,182 +977,6 @@ __global__ void zero_u32_kernel(uint32_t* p, int n) {
 }
 
 // ------------------------------------------------------------------ host side
-
-constexpr int kMaxWindows = 12;  // first window of one position, each next one as long as all before it: 1024 positions
-
-struct Window {
-    int t_lo, t_hi;
-    int NS, slice_vecs;  // slices per row, vectors per slice
-};
-
-struct Plan {
-    int vec;         // logits per 16-byte vector
-    int windows;
-    Window win[kMaxWindows];
-    Window all;      // one pass over all k_max positions (taken when draft_logprobs is requested)
-    size_t off_list2, off_log2z, off_state, off_partial;
-    bool split;      // the tables of a shared recovery row are there
-    size_t off_arrive, off_best_v, off_best_i, off_chunk_tab;
-    size_t bytes;
-};
-
-constexpr int kSplitMaxBatch = 128;  // workspace is reserved for shared recovery rows up to this batch (half of MI355X's 256 units)
-
-// Shape of the recovery launch: threads per workgroup, and chunks per part of a recovery row.
-//   - So few chunks that 4-wave workgroups with one chunk a wave leave at most 8 waves per compute unit: spread
-//     them like that, since a chunk's arithmetic (some 1.5 us alone on a SIMD) takes as long as four of them
-//     sharing one.  With 8 sequences of V = 151936 (75 chunks) the recovery kernel goes from 17.2 us (40
-//     workgroups of 16 waves) to 11.5; beyond that line the parts' repeated ratio tests weigh more than the
-//     spread gains (64 such sequences: 71.2 us a step in 19 parts, 69.9 in 3, 72.4 in 4 uneven ones).
-//   - At least two compute units per sequence: as many 16-wave parts as there are units per sequence, with
-//     equal rounds of 16 chunks.
-//   - Up to one sequence per unit: one 16-wave workgroup each.  More: 8-wave workgroups, two to a unit, so that the
-//     serial ends of one sequence (ratio test, token pick) overlap the sweep of another (300 sequences of
-//     V = 100000: 132 us a step against 137 in balanced parts and 140 with 16 waves).
-struct RecShape {
-    int threads, part_chunks;
-};
-
-RecShape recovery_shape(int B, int NC, int cus, bool split) {
-    if (split && (long)B * NC <= 8l * cus) return {256, 4};
-    if (split && B <= cus / 2) {
-        const int rows = (NC + 15) / 16;  // rounds of 16 chunks
-        const int most = cus / B < rows ? cus / B : rows;
-        const int rounds = (rows + most - 1) / most;
-        const int parts = (rows + rounds - 1) / rounds;
-        return {1024, (NC + parts - 1) / parts};
-    }
-    return {B <= cus ? 1024 : 512, NC};
-}
-
-// Several row passes pay off when the batch is large enough to be bandwidth-bound and long enough for
-// a first rejection to cut rows: a first window is scored for everyone, what follows only for the sequences that
-// are still in play.  A further window costs some 10 us (a verdict launch, and the ends of a row pass), the time of
-// 66 MB of rows.
-//   - From kEarlyExitMinBytes of rows: a first window of a quarter of the positions and one of the rest (256 ragged
-//     sequences of up to 16 positions, V = 128256: 4 and 12; cut into 4, 4 and 8 it gains 2 us of 168 at
-//     acceptance 0.8 and loses 10 where nearly everything is accepted).
-//   - From kDoublingMinBytes a position, the rows behind one position are already worth a launch: windows of 1,
-//     1, 2, 4, ... positions.  512 sequences of 8 positions, V = 256000 bf16 (524 MB a position): 347 -> 287 us a
-//     step at acceptance 0.4, 590 -> 511 at 0.8; at V = 128256 (263 MB) 193 -> 173 and 303 -> 285.  At 140 MB a
-//     position (273 sequences, V = 128256) it turns: 184 -> 190 at acceptance 0.8.
-constexpr long kEarlyExitMinBytes = 512l << 20;
-constexpr long kDoublingMinBytes = 240l << 20;
-
-long position_bytes(const ss_params* p) {  // both tensors' rows of one position, all sequences
-    return 2l * p->batch * p->vocab * (p->dtype == SS_BF16 ? 2 : 4);
-}
-
-int first_window(const ss_params* p) {
-    if (p->flags & SS_FLAG_FULL_ROWS) return p->k_max;
-    if (p->k_max < 4) return p->k_max;
-    if (position_bytes(p) * p->k_max < kEarlyExitMinBytes) return p->k_max;
-    return position_bytes(p) >= kDoublingMinBytes ? 1 : p->k_max / 4;
-}
-
-bool shape_ok(const ss_params* p) {
-    if (!p) return false;
-    if (p->batch < 0 || p->k_max < 0 || p->k_max > SS_MAX_K) return false;
-    if (p->vocab < 1 || p->vocab > SS_MAX_VOCAB) return false;
-    if (p->dtype != SS_F32 && p->dtype != SS_BF16) return false;
-    if ((long)p->batch * (p->k_max + 1) > (1l << 30)) return false;
-    return true;
-}
-
-size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
-
-int chunks_of(int elems, int vec) {
-    const long nvec = elems / vec;
-    const long nch = (nvec + kWave * kChunkSteps - 1) / (kWave * kChunkSteps);
-    return (int)nch + ((elems % vec) ? 1 : 0);
-}
-
-// Recovery chunks of a row; a bf16 row may be read from one element before its start.
-int chunks_per_row(int V, int vec) {
-    const int n = chunks_of(V, vec), m = vec == 8 ? chunks_of(V + 1, vec) : n;
-    return n > m ? n : m;
-}
-
-// Slices per row for a pass expected to cover `row_tensors` (row, tensor) pairs: 64 KiB slices for
-// big passes, smaller ones (down to one unrolled group) when there are too few rows to give every
-// resident wave several slices -- a wave that gets one or two long slices cannot balance.
-void slice_plan(long nvec, long row_tensors, int most, Window& w) {
-    long ns_lo = (nvec + kMaxSliceVecs - 1) / kMaxSliceVecs;
-    long ns_hi = (nvec + kMinSliceVecs - 1) / kMinSliceVecs;
-    long want = row_tensors > 0 ? (32768 + row_tensors - 1) / row_tensors : 1;
-    long ns = want < ns_lo ? ns_lo : (want > ns_hi ? ns_hi : want);
-    if (ns > most) ns = most;
-    if (ns < 1) ns = 1;
-    long sv = (nvec + ns - 1) / ns;
-    sv = (sv + kMinSliceVecs - 1) / kMinSliceVecs * kMinSliceVecs;
-    ns = (nvec + sv - 1) / sv;
-    if (ns < 1) ns = 1;
-    w.NS = (int)ns;
-    w.slice_vecs = (int)sv;
-}
-
-// Bytes up to the tables of a shared recovery row, and the tables themselves when `split` is set.
-Plan lay_out(const ss_params* p, bool split) {
-    Plan pl;
-    pl.vec = p->dtype == SS_BF16 ? 8 : 4;
-    const long nvec = (p->vocab + pl.vec - 1) / pl.vec;
-    // The space of the slice partials: that of one window of all positions and of two, the first a quarter of the
-    // positions, at the finest of their slicings.  The windows use it one after the other.
-    const int quarter = first_window(p) < p->k_max ? p->k_max / 4 : p->k_max;
-    const long rows1 = (long)p->batch * quarter, rows2 = (long)p->batch * (p->k_max - quarter);
-    Window two[2];
-    slice_plan(nvec, rows1 * 2, kMaxSlices, two[0]);
-    // a later window covers only the sequences still in play: typically a third of the padded rows
-    slice_plan(nvec, rows2 * 2 / 3, kMaxSlices, two[1]);
-    slice_plan(nvec, (long)p->batch * p->k_max * 2, kMaxSlices, pl.all);
-    pl.all.t_lo = 0;
-    pl.all.t_hi = p->k_max;
-    int ns_max = two[0].NS > two[1].NS ? two[0].NS : two[1].NS;
-    if (pl.all.NS > ns_max) ns_max = pl.all.NS;
-    pl.windows = 0;
-    for (int t = 0, hi = first_window(p);; hi = 2 * t) {
-        if (t > 0 && (position_bytes(p) < kDoublingMinBytes || hi + t / 2 >= p->k_max)) hi = p->k_max;  // no last window shorter than half the one before
-        Window& w = pl.win[pl.windows++];
-        const long rows = (long)p->batch * (hi - t);
-        const long most = hi > t ? (long)p->k_max * ns_max / (hi - t) : kMaxSlices;
-        slice_plan(nvec, t == 0 ? rows * 2 : rows * 2 / 3, most < kMaxSlices ? (int)most : kMaxSlices, w);
-        w.t_lo = t;
-        w.t_hi = hi;
-        if (hi >= p->k_max) break;
-        t = hi;
-    }
-    const size_t B = (size_t)p->batch;
-    size_t o = align_up((B + 1) * sizeof(int32_t), 256);  // row list of the first pass
-    pl.off_list2 = o;    o += align_up((B + 1) * sizeof(int32_t), 256);      // row list of the second pass
-    pl.off_log2z = o;    o += 2 * align_up((B ? B : 1) * sizeof(int32_t), 256);  // one double per sequence
-    pl.off_state = o;    o += align_up((B ? B : 1) * sizeof(int32_t), 256);
-    pl.off_partial = o;
-    o += align_up(((size_t)p->batch * p->k_max * 2 + 1) * (size_t)ns_max * sizeof(Partial), 256);
-    const size_t NC = (size_t)chunks_per_row(p->vocab, pl.vec);
-    pl.split = split && p->batch >= 1 && p->batch <= kSplitMaxBatch;
-    pl.off_arrive = pl.off_best_v = pl.off_best_i = pl.off_chunk_tab = o;
-    if (pl.split) {
-        pl.off_arrive = o;     o += align_up(B * kArriveStride * sizeof(uint32_t), 256);
-        pl.off_best_v = o;     o += align_up(B * (NC < 32 ? 32 : NC) * sizeof(double), 256);
-        pl.off_best_i = o;     o += align_up(B * NC * sizeof(int32_t), 256);
-        pl.off_chunk_tab = o;  o += align_up(B * NC * sizeof(Partial), 256);
-    } else if (p->batch >= 1 && p->batch <= kSplitMaxBatch) {
-        // not used, and never more than the tables: which blocks fit the static scratch stays what it is
-        o += align_up(B * sizeof(uint32_t), 256) + align_up(B * 256, 256) +
-             align_up(B * (size_t)chunks_of(p->vocab, pl.vec) * sizeof(Partial), 256);
-    }
-    pl.bytes = o;
-    return pl;
-}
-
-// The plan with the shared recovery row, unless only the plan without it fits the static scratch: which blocks
-// that entry point takes does not depend on the tables.
-Plan make_plan(const ss_params* p) {
-    const Plan pl = lay_out(p, true);
-    if (pl.bytes <= (size_t)SS_STATIC_SCRATCH_BYTES) return pl;
-    const Plan small = lay_out(p, false);
-    return small.bytes <= (size_t)SS_STATIC_SCRATCH_BYTES ? small : pl;
-}
 
 // One row pass over window `win`.  `uniform_rows` > 0 when every sequence has that many rows.
 template <int DT, int VEC>
