@@ -127,9 +127,21 @@ inline int chunks_of(int elems, int vec) {
     return (int)nch + ((elems % vec) ? 1 : 0);
 }
 
-// Recovery chunks of a row; a bf16 row may be read from one element before its start.
-inline int chunks_per_row(int V, int vec) {
-    const int n = chunks_of(V, vec), m = vec == 8 ? chunks_of(V + 1, vec) : n;
+// Whether the recovery sweep can meet a row that it reads from one element before its start: a bf16 row behind the
+// tensor's first, at an odd element in all three tensors (`bases`: bit 0 of each tensor's element address).
+inline bool odd_rows_possible(int vec, const unsigned (&bases)[3], int B, int kmax, long sb, long st) {
+    if (vec != 8 || (bases[0] & 1) != (bases[1] & 1) || (bases[0] & 1) != (bases[2] & 1)) return false;
+    return (bases[0] & 1) || (B > 1 && (sb & 1)) || (kmax > 0 && (st & 1));
+}
+
+// Most recovery chunks of a row; a row read from one element before its start has those of V + 1.  The launch is shaped
+// by what its rows really have: with V a multiple of 2048 the element more is a chunk more, and that chunk may start
+// another round of 16.  Counting it where no row is odd gave 64 sequences of V = 131072 3 parts of 22 chunks instead of 4 of
+// 16 (a step of 4 drafts 44.3 us, 43.3 without it; steering rows 18.1, 16.8), and 128 of V = 65536 two rounds instead of
+// one (43.8, 42.9; rows 17.9, 16.9).  The other way round once in ten sizes: 64 rows of V = 196608 21.9 in 4 parts of 25,
+// 22.4 in 3 of 32.  The workspace is laid out for either.
+inline int chunks_per_row(int V, int vec, bool odd_rows) {
+    const int n = chunks_of(V, vec), m = odd_rows ? chunks_of(V + 1, vec) : n;
     return n > m ? n : m;
 }
 
@@ -188,7 +200,7 @@ inline Plan lay_out(const ss_params* p, bool split) {
     pl.off_state = o;    o += align_up((B ? B : 1) * sizeof(int32_t), 256);
     pl.off_partial = o;
     o += align_up(((size_t)p->batch * p->k_max * 2 + 1) * (size_t)ns_max * sizeof(Partial), 256);
-    const size_t NC = (size_t)chunks_per_row(p->vocab, pl.vec);
+    const size_t NC = (size_t)chunks_per_row(p->vocab, pl.vec, pl.vec == 8);
     pl.split = split && p->batch >= 1 && p->batch <= kSplitMaxBatch;
     pl.off_arrive = pl.off_best_v = pl.off_best_i = pl.off_chunk_tab = o;
     if (pl.split) {

@@ -342,7 +342,7 @@ struct RecArgs {
     float* draft_logprobs;
     long sb, st;
     int B, kmax, V;
-    int NC;          // chunks per row at most (full chunks + one pseudo-chunk for the logits past the last vector)
+    int NC;          // most chunks of a row (full chunks + one pseudo-chunk for the logits past the last vector)
     double c;        // log2(e) / T
     double bc;       // beta * log2(e) / T
     double beta;     // beta itself, for the greedy argmax of Eq. 8
@@ -1006,6 +1006,9 @@ void launch_row_pass(LseArgs la, const Window& w, const RowWindow& win, int unif
                        stream, la);
 }
 
+template <int DT>
+unsigned elem_parity(const void* p) { return (unsigned)(reinterpret_cast<uintptr_t>(p) / (DT == SS_BF16 ? 2 : 4)) & 1u; }
+
 template <int DT, int VEC>
 hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* recovery_logprobs, hipStream_t stream,
                       hipEvent_t* ev) {
@@ -1027,7 +1030,8 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     ra.partial = partial;
     ra.state = windows > 1 ? state : nullptr;
     ra.log2z = recovery_logprobs ? reinterpret_cast<double*>(ws + pl.off_log2z) : nullptr;
-    ra.NC = chunks_per_row(V, VEC);
+    const unsigned bases[3] = {elem_parity<DT>(ra.G), elem_parity<DT>(ra.recSp), elem_parity<DT>(ra.recSm)};
+    ra.NC = chunks_per_row(V, VEC, odd_rows_possible(VEC, bases, B, kmax, ra.sb, ra.st));
     const RecShape shape = recovery_shape(B, ra.NC, device_cu_count(), pl.split);
     ra.part_chunks = shape.part_chunks;
     ra.parts = (ra.NC + ra.part_chunks - 1) / ra.part_chunks;

@@ -218,3 +218,20 @@ def test_edge_resample_on_columns_of_a_wider_payload(binding):
     got = binding.edge_resample(idx[:, :16], val[:, :16], inp["S_ctx"], row, u, beta=w.beta, temperature=w.temperature)
     for k in ("next_token", "next_token_logprob"):
         assert torch.equal(got[k], want[k]), k
+
+
+# Rows that are all odd although every stride is even (each tensor starts one element late), and the same rows at even
+# elements, on both sides of a whole number of chunks: the launch is planned with the chunks its rows have.
+@pytest.mark.parametrize("vocab", [4 * 2048 - 2, 4 * 2048, 4 * 2048 + 2])
+@pytest.mark.parametrize("late", [0, 1])
+def test_odd_bases_with_even_strides(binding, oracle, vocab, late):
+    w = recipe("c4", "bf16", batch=3, k_max=2, vocab=vocab)
+    inp = W.generate(w, "cuda")
+    for k in ("G", "S_ctx", "S_noctx"):
+        flat = torch.full((inp[k].numel() + 2,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        flat[late:late + inp[k].numel()].copy_(inp[k].reshape(-1))
+        inp[k] = flat[late:late + inp[k].numel()].view_as(inp[k])
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam, beta=w.beta,
+                               temperature=w.temperature, draft_len=inp["draft_len"], want_draft_logprobs=True)
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, want_recovery_logprobs=False)
+    parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
