@@ -134,13 +134,15 @@ def bench_split(args, w, sets, dev) -> int:
     return 0
 
 
-def row_windows(t1, kmax, position_bytes) -> list:
+def row_windows(t1, kmax, position_bytes, lam) -> list:
     """Bounds of the windows the library's row passes cover, from the length of the first one: a further window is
-    as long as all before it while it is worth its launch, else it takes the rest."""
+    as long as all before it while it is worth its launch, else it takes the rest.  The library's own rule
+    (csrc/plan.h) again; a test holds the two together."""
+    line = (480 if lam < 0.2 else 280 if lam < 0.4 or kmax < 6 else 240) << 20
     bounds = [0, t1]
     while bounds[-1] < kmax:
         t = bounds[-1]
-        cut = position_bytes >= 240 << 20
+        cut = position_bytes >= line
         bounds.append(2 * t if cut and 2 * t + t // 2 < kmax else kmax)
     return bounds
 
@@ -160,7 +162,7 @@ def measure(binding, W, w, sets, dev, *, steps, warmup, mode="verify", full_rows
                                  flags=(binding.SS_FLAG_GREEDY if mode == "greedy" else 0)
                                  | (binding.SS_FLAG_FULL_ROWS if full_rows else 0))
     t1 = binding.first_window(params)
-    bounds = row_windows(t1, kmax, 2 * B * V * esz)
+    bounds = row_windows(t1, kmax, 2 * B * V * esz, w.lam)
     ws = torch.empty(max(256, binding.workspace_bytes(params)), dtype=torch.uint8, device=dev)
     acc = torch.empty(B, dtype=torch.int32, device=dev)
     tok = torch.empty(B, dtype=torch.int32, device=dev)

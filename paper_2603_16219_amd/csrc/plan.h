@@ -92,12 +92,28 @@ inline RecShape recovery_shape(int B, int NC, int cus, bool split) {
 //   - From kEarlyExitMinBytes of rows: a first window of a quarter of the positions and one of the rest (256 ragged
 //     sequences of up to 16 positions, V = 128256: 4 and 12; cut into 4, 4 and 8 it gains 2 us of 168 at
 //     acceptance 0.8 and loses 10 where nearly everything is accepted).
-//   - From kDoublingMinBytes a position, the rows behind one position are already worth a launch: windows of 1,
-//     1, 2, 4, ... positions.  512 sequences of 8 positions, V = 256000 bf16 (524 MB a position): 347 -> 287 us a
-//     step at acceptance 0.4, 590 -> 511 at 0.8; at V = 128256 (263 MB) 193 -> 173 and 303 -> 285.  At 140 MB a
-//     position (273 sequences, V = 128256) it turns: 184 -> 190 at acceptance 0.8.
+//   - From doubling_min_bytes of rows a position, the rows behind one position are already worth a launch: windows of
+//     1, 1, 2, 4, ... positions.  512 sequences of 8 positions, V = 256000 bf16 (500 MiB a position): 362 -> 298 us a step
+//     at acceptance 0.4, 603 -> 525 at 0.8.
 constexpr long kEarlyExitMinBytes = 512l << 20;
-constexpr long kDoublingMinBytes = 240l << 20;
+
+// What doubling windows gain falls with the rows of a position, with the positions behind the first ones (fewer of
+// them in ragged drafts) and with the share that is accepted, of which the threshold lambda is what the host knows.
+// Microseconds a step in two windows -> in doubling ones (ragged drafts in brackets), 495 or 512 sequences, bf16, a recipe
+// of acceptance 0.8 at lambda 0.5:
+//   - 6 positions and more, from 240 MiB.  At 242 MiB 16 of them 408 -> 329 (297 -> 281), 8 294 -> 276 (213 -> 220), 6
+//     270 -> 250 (197 -> 205); at 280 MiB 8 of them 346 -> 307 (247 -> 243).  At 140 MB (273 sequences, V = 128256)
+//     184 -> 190.
+//   - 4 and 5 positions, from 280 MiB: 4 of them 244 -> 237 (194 -> 199), 5 270 -> 255 (204 -> 205); at 242 MiB 211 -> 214
+//     (168 -> 178) and 237 -> 237 (181 -> 191).
+//   - lambda below 0.4, from 280 MiB: at 0.3 8 positions 357 -> 339 (250 -> 258); at 242 MiB 313 -> 307 (222 -> 237).
+//   - lambda below 0.2, from 480 MiB: at 0.1 8 positions of 500 MiB 722 -> 676 (480 -> 468), of 375 MiB 528 -> 517 (356 -> 369),
+//     of 242 MiB 358 -> 368 (237 -> 262); at 0.01, where nearly everything is accepted, 794 -> 794 (514 -> 517), 585 -> 602
+//     (382 -> 406) and 386 -> 419 (251 -> 283), though a poorer specialist gains there too (500 MiB: 516 -> 425).
+inline long doubling_min_bytes(const ss_params* p) {
+    if (!(p->lambda >= 0.2f)) return 480l << 20;
+    return (p->lambda < 0.4f || p->k_max < 6 ? 280l : 240l) << 20;
+}
 
 inline long position_bytes(const ss_params* p) {  // both tensors' rows of one position, all sequences
     return 2l * p->batch * p->vocab * (p->dtype == SS_BF16 ? 2 : 4);
@@ -107,7 +123,7 @@ inline int first_window(const ss_params* p) {
     if (p->flags & SS_FLAG_FULL_ROWS) return p->k_max;
     if (p->k_max < 4) return p->k_max;
     if (position_bytes(p) * p->k_max < kEarlyExitMinBytes) return p->k_max;
-    return position_bytes(p) >= kDoublingMinBytes ? 1 : p->k_max / 4;
+    return position_bytes(p) >= doubling_min_bytes(p) ? 1 : p->k_max / 4;
 }
 
 inline bool shape_ok(const ss_params* p) {
@@ -183,7 +199,7 @@ inline Plan lay_out(const ss_params* p, bool split) {
     if (pl.all.NS > ns_max) ns_max = pl.all.NS;
     pl.windows = 0;
     for (int t = 0, hi = first_window(p);; hi = 2 * t) {
-        if (t > 0 && (position_bytes(p) < kDoublingMinBytes || hi + t / 2 >= p->k_max)) hi = p->k_max;  // no last window shorter than half the one before
+        if (t > 0 && (position_bytes(p) < doubling_min_bytes(p) || hi + t / 2 >= p->k_max)) hi = p->k_max;  // no last window shorter than half the one before
         Window& w = pl.win[pl.windows++];
         const long rows = (long)p->batch * (hi - t);
         const long most = hi > t ? (long)p->k_max * ns_max / (hi - t) : kMaxSlices;

@@ -82,11 +82,12 @@ def test_slice_merge_edges(binding, oracle, dtype, vocab):
     parity.compare(out, ora, inp["uniforms"], None)
 
 
-# Windows of 1, 1, 2, ... positions from 240 MiB of rows a position on: 4, 5 and 6 positions end in windows of
-# 2, 3 (no short last window) and 2.  Every length occurs, and one flagged sequence of each kind.
-@pytest.mark.parametrize("k_max,greedy", [(4, False), (5, True), (6, False)])
+# Windows of 1, 1, 2, ... positions, at the fewest bytes a position that get them (240 MiB, 280 with 4 and 5
+# positions): 4, 5, 6 and 8 positions end in windows of 2, 3 (no short last window), 2 and 4.  Every length occurs, and one
+# flagged sequence of each kind.
+@pytest.mark.parametrize("k_max,greedy", [(4, False), (5, True), (6, False), (8, False)])
 def test_doubling_windows_equal_the_one_pass_schedule(binding, oracle, k_max, greedy):
-    w = recipe("c2" if k_max == 6 else "c5", "bf16", batch=1000, k_max=k_max, vocab=63001)
+    w = recipe("c2" if k_max == 6 else "c5", "bf16", batch=1000, k_max=k_max, vocab=73401 if k_max < 6 else 63001)
     inp = W.generate(w, "cuda", seq_chunk=40)
     p = binding.make_params(w.batch, k_max, w.vocab, torch.bfloat16, lam=w.lam, beta=w.beta, temperature=w.temperature)
     assert binding.first_window(p) == 1
@@ -174,7 +175,7 @@ def test_row_modes_take_every_form_of_rows_the_block_takes(binding):
 def test_doubling_windows_inside_a_hip_graph(binding):
     """The launches of several windows captured once and replayed on new drafts, lengths and uniforms, with eager
     calls on the same workspace between the replays; every replay equals the direct call."""
-    w = recipe("c5", "bf16", batch=1000, k_max=5, vocab=63001)
+    w = recipe("c5", "bf16", batch=1000, k_max=5, vocab=73401)
     inp = W.generate(w, "cuda", seq_chunk=40)
     inp["draft_len"] = torch.randint(0, 6, (1000,), device="cuda", dtype=torch.int32)
     p = binding.make_params(1000, 5, w.vocab, torch.bfloat16, lam=w.lam, beta=w.beta, temperature=w.temperature)

@@ -2,8 +2,12 @@
 import os
 import random
 import subprocess
+import sys
 
 import pytest
+import torch
+
+from paper_2603_16219_amd import binding
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2603_16219_amd", "csrc")
@@ -20,15 +24,21 @@ int main() {
             unsigned a[3]; int vec, B, k; long sb, st;
             if (std::scanf("%d %u %u %u %d %d %ld %ld", &vec, a, a + 1, a + 2, &B, &k, &sb, &st) != 8) return 1;
             std::printf("%d\n", odd_rows_possible(vec, a, B, k, sb, st) ? 1 : 0);
-        } else {  // B kmax V dtype flags cus odd
-            ss_params p = {}; int cus, odd;
-            if (std::scanf("%d %d %d %d %u %d %d", &p.batch, &p.k_max, &p.vocab, &p.dtype, &p.flags, &cus, &odd) != 7) return 1;
-            p.lambda = p.beta = p.temperature = 1.f;
-            const Plan pl = make_plan(&p);
+            continue;
+        }
+        ss_params p = {};  // B kmax V dtype flags lambda, then what is asked
+        if (std::scanf("%d %d %d %d %u %f", &p.batch, &p.k_max, &p.vocab, &p.dtype, &p.flags, &p.lambda) != 6) return 1;
+        p.beta = p.temperature = 1.f;
+        const Plan pl = make_plan(&p);
+        if (!std::strcmp(what, "parts")) {  // cus odd
+            int cus, odd;
+            if (std::scanf("%d %d", &cus, &odd) != 2) return 1;
             const int nc = chunks_per_row(p.vocab, pl.vec, odd != 0);
             const RecShape s = recovery_shape(p.batch, nc, cus, pl.split);
-            std::printf("%d %d %d %d", nc, s.threads, s.part_chunks, pl.windows);
-            for (int i = 0; i < pl.windows; ++i) std::printf(" %d %d", pl.win[i].t_lo, pl.win[i].t_hi);
+            std::printf("%d %d %d\n", nc, s.threads, s.part_chunks);
+        } else {  // the workspace, the space of the slice partials, and for every window its end and its slices a row
+            std::printf("%ld %ld", (long)pl.bytes, (long)(pl.off_arrive - pl.off_partial) / (long)sizeof(Partial));
+            for (int i = 0; i < pl.windows; ++i) std::printf(" %d %d", pl.win[i].t_hi, pl.win[i].NS);
             std::printf("\n");
         }
     }
@@ -59,7 +69,7 @@ BF16 = 1
 
 def shape(planner, batch, vocab, dtype, odd):
     """(chunks of a row, threads of a workgroup, chunks of a part)"""
-    return planner([f"plan {batch} 1 {vocab} {dtype} 0 {CUS} {odd}"])[0][:3]
+    return planner([f"parts {batch} 1 {vocab} {dtype} 0 0.5 {CUS} {odd}"])[0]
 
 
 # A chunk is 256 vectors (2048 bf16 logits); rows that start at even elements have exactly V / 2048 of them here.
@@ -103,3 +113,53 @@ def test_odd_rows_are_expected_exactly_where_the_kernel_can_meet_one(planner):
             assert g == some or (g and not some and line.split()[2] == "1"), line
         assert g or not some or vec == 4, line
     assert 500 < sum(got) < 3500
+
+
+def windows(planner, calls):
+    """For every (batch, k_max, vocab, lambda) on bf16 the ends of the row windows."""
+    return [list(g[2::2]) for g in planner([f"windows {b} {k} {v} {BF16} 0 {lam}" for b, k, v, lam in calls])]
+
+
+# 512 sequences: a position is 2 KiB a logit: 240 MiB of rows at V = 122880, 280 MiB at 143360, 480 MiB at 245760.
+@pytest.mark.parametrize("k_max,vocab,lam,want", [
+    (8, 122880, 0.4, [1, 2, 4, 8]), (8, 122879, 0.5, [2, 8]), (6, 122880, 0.5, [1, 2, 4, 6]), (7, 122879, 0.5, [1, 7]),
+    (16, 122880, 0.5, [1, 2, 4, 8, 16]), (12, 122880, 1.0, [1, 2, 4, 8, 12]), (12, 122879, 0.5, [3, 12]),
+    (5, 143360, 0.5, [1, 2, 5]), (5, 143359, 0.5, [1, 5]), (4, 143360, 0.5, [1, 2, 4]), (4, 143359, 0.5, [1, 4]),  # few
+    (8, 143360, 0.2, [1, 2, 4, 8]), (8, 143359, 0.39, [2, 8]), (4, 143360, 0.2, [1, 2, 4]),   # more accepted: later
+    (8, 245760, 0.01, [1, 2, 4, 8]), (8, 245759, 0.01, [2, 8]), (16, 245759, 0.1, [4, 16]), (4, 245759, 0.19, [1, 4]),
+    (3, 256000, 0.5, [3]), (1024, 256000, 0.5, [2 ** i for i in range(11)])])
+def test_windows_start_with_one_position_where_that_pays(planner, k_max, vocab, lam, want):
+    assert windows(planner, [(512, k_max, vocab, lam)]) == [want]
+
+
+def random_calls(n, seed):
+    rng = random.Random(seed)
+    return [(int(2 ** rng.uniform(0, 11)), rng.choice([0, 1, 3, 4, 5, 6, 7, 8, 11, 12, 13, 16, 33, 200]),
+             int(2 ** rng.uniform(5, 20)), rng.choice([0.01, 0.1, 0.3, 0.5, 1.0])) for _ in range(n)]
+
+
+def test_windows_cover_the_positions_and_fit_the_space_of_the_partials(planner):
+    calls = random_calls(4000, 11)
+    lines = [f"windows {b} {k} {v} {BF16} 0 {lam}" for b, k, v, lam in calls]
+    same = planner([f"windows {b} {k} {v} {BF16} 0 0.5" for b, k, v, _ in calls])
+    many = 0
+    for (b, k, v, lam), g, other in zip(calls, planner(lines), same):
+        ends, slices = g[2::2], g[3::2]
+        assert ends[-1] == k and (k == 0 or all(x < y for x, y in zip((0,) + ends, ends)))
+        assert all(b * (hi - lo) * 2 * ns <= g[1] for lo, hi, ns in zip((0,) + ends, ends, slices)), (b, k, v, lam)
+        assert g[0] == other[0]  # the workspace does not depend on lambda
+        many += len(ends) > 2
+    assert many > 100
+
+
+def test_the_benchmark_counts_the_rows_of_the_windows_the_library_scores(planner):
+    sys.path.insert(0, ROOT)
+    import bench
+
+    calls = [c for c in random_calls(4000, 12) if c[1] > 0]
+    calls += [(512, k, v, lam) for k in (4, 5, 6, 8, 12, 16) for v in (122879, 122880, 143359, 143360, 245759, 245760)
+              for lam in (0.1, 0.19, 0.2, 0.39, 0.4, 0.5)]
+    for (b, k, v, lam), ends in zip(calls, windows(planner, calls)):
+        p = binding.make_params(b, k, v, torch.bfloat16, lam=lam, beta=1.0, temperature=1.0)
+        assert binding.first_window(p) == ends[0]
+        assert bench.row_windows(ends[0], k, 4 * b * v, lam) == [0, *ends], (b, k, v, lam)
