@@ -379,12 +379,12 @@ __device__ __forceinline__ Partial ld_dev_partial(const Partial* p) {
 // every memory operation this wave has issued so far has completed: s_waitcnt vmcnt(0) lgkmcnt(0)
 __device__ __forceinline__ void wait_stores() { __builtin_amdgcn_s_waitcnt(0x0070); }
 
-// log2 of sum_v 2^(h_v * c) for one row from its slice partials, by the 16 lanes of one DPP row (`l` is the lane's
-// index in it, every lane returns the value): lane l takes slices l, l+16, ..., four loads in flight, and the 16
+// The slice partials of one row merged by the 16 lanes of one DPP row (`l` is the lane's index in it, every lane
+// returns the pair): lane l takes slices l, l+16, ..., four loads in flight, and the 16
 // running pairs are merged by a fixed pattern, so the result does not depend on who computes it.  One lane per row
 // (all slices in turn) spends a round trip per 16 slices and some 60 clocks per merge: with the 38
 // slices of V = 151936 that was a third of the 4.5 us before the first rejection was known.
-__device__ __forceinline__ double combine_partials_row16(const Partial* p, int ns, double rho, int l) {
+__device__ __forceinline__ Partial merge_partials_row16(const Partial* p, int ns, int l) {
     int Em = kEInit;
     float S = 0.f;
     for (int k0 = l; k0 < ns; k0 += 64) {
@@ -399,8 +399,12 @@ __device__ __forceinline__ double combine_partials_row16(const Partial* p, int n
         }
     }
     const int Er = row_max_i32(Em);
-    S = row_sum_f32(ldexpf(S, Em - Er));
-    return (double)Er * (1.0 + rho) + log2((double)S);  // E*rho: see acc_add_f32
+    return Partial{Er, row_sum_f32(ldexpf(S, Em - Er))};
+}
+
+// log2 of sum_v 2^(h_v * c) for one row from its merged partials
+__device__ __forceinline__ double row_log2(Partial p, double rho) {
+    return (double)p.E * (1.0 + rho) + log2((double)p.s);  // E*rho: see acc_add_f32
 }
 
 // PLAIN (beta == 0): the recovery distribution is Softmax(h_LLM / T); the two specialist rows are
@@ -684,7 +688,7 @@ __device__ __forceinline__ const Partial* partials_of(const RecArgs& a, int b, i
 // Phase 2 for one sequence by a workgroup of NT threads, on positions [T0, Kt) (those before T0
 // are known to have been accepted):
 //   2a  every (position, tensor) pair gets 16 lanes: merge the row's slice partials, gather the draft
-//       token's logit, leave log P(y_t) in lp[2t + x]        (two memory round trips in all)
+//       token's logit, leave log P(y_t) in lp[2t + x]        (two memory round trips)
 //   2b  wave 0: Eq. 7 on every position, first rejection by ballot -> *sh_n (Kt if none)
 // A draft id outside the vocabulary among those positions sets *sh_bad.  Ends with a barrier.
 template <int DT, int NT>
@@ -694,16 +698,35 @@ __device__ __forceinline__ void ratio_test_block(const RecArgs& a, int b, int T0
     const int kmax = a.kmax, V = a.V;
     const float* un = a.uniforms + (long)b * (kmax + 1);
     const float u0 = T0 + lane < Kt ? un[T0 + lane] : 0.f;  // wave 0's first block, on its way while the rows are merged
-    for (int q = 2 * T0 + (tid >> 4); q < 2 * Kt; q += NT / 16) {
+    const auto logprob = [&](int q, int y, Partial row) {  // log P(y) at (position, tensor) pair q
         const int t = q >> 1, x = q & 1;
-        const int y = a.draft[(long)b * kmax + t];
-        const double L = combine_partials_row16(partials_of(a, b, t, x), a.NS, a.rho, l);
         const bool ok = (y >= 0 && y < V);
         const long off = (long)b * a.sb + (long)t * a.st;
         const float h = ok ? ld_elem<DT>(row_ptr<DT>(x ? a.Sm : a.G, off), y) : 0.f;
-        if (l == 0) {
-            lp[q] = kLn2 * ((double)h * a.c - L);
-            if (!ok) *sh_bad = 1;
+        if (!ok) *sh_bad = 1;
+        return kLn2 * ((double)h * a.c - row_log2(row, a.rho));
+    };
+    const int* draft = a.draft + (long)b * kmax;
+    const int q0 = 2 * T0 + (tid >> 4);
+    if (2 * (Kt - T0) <= NT / 16) {
+        if (q0 < 2 * Kt) {
+            const int y = draft[q0 >> 1];
+            const double v = logprob(q0, y, merge_partials_row16(partials_of(a, b, q0 >> 1, q0 & 1), a.NS, l));
+            if (l == 0) lp[q0] = v;
+        }
+    } else {
+        // More pairs than groups of sixteen lanes: only the merging goes in rounds, its result waits in the pair's slot of
+        // lp, and the gathers and logarithms follow once, a lane to every pair.  With all of it in the rounds each of
+        // them cost 0.9 us of dependent loads: 27 positions tested by 4 waves took 4, and one sequence of 128 positions,
+        // V = 40000, 24.1 us a step where it takes 20.7.
+        for (int q = q0; q < 2 * Kt; q += NT / 16) {
+            const Partial m = merge_partials_row16(partials_of(a, b, q >> 1, q & 1), a.NS, l);
+            if (l == 0) lp[q] = __hiloint2double(m.E, __float_as_int(m.s));
+        }
+        __syncthreads();
+        for (int q = 2 * T0 + tid; q < 2 * Kt; q += NT) {
+            const Partial m{__double2hiint(lp[q]), __int_as_float(__double2loint(lp[q]))};
+            lp[q] = logprob(q, draft[q >> 1], m);
         }
     }
     __syncthreads();
@@ -731,10 +754,11 @@ __device__ __forceinline__ void ratio_test_block(const RecArgs& a, int b, int T0
 // rejection): its later rows are never scored and its first-rejection index is final.  After the first window
 // every draft id of the sequence is range-checked, so a sequence is flagged exactly as in the
 // one-pass schedule.
-constexpr int kVerdictThreads = 128;  // 16 lanes per (position, tensor) pair: a window of 4 positions in one round
-
-template <int DT>
-__global__ __launch_bounds__(kVerdictThreads) void verdict_kernel(const RecArgs a) {
+//
+// NT = 128, two waves, test a window of up to 8 positions (4 without rounds); 512 a longer one (of 32 positions: 20 sequences of 128
+// drafts, V = 65536, 50.4 -> 47.3 us a step).
+template <int DT, int NT>
+__global__ __launch_bounds__(NT) void verdict_kernel(const RecArgs a) {
     extern __shared__ double smem_d[];
     __shared__ int sh_n, sh_bad;
     const int b = blockIdx.x, tid = threadIdx.x;
@@ -751,13 +775,13 @@ __global__ __launch_bounds__(kVerdictThreads) void verdict_kernel(const RecArgs 
     __syncthreads();
     if (first && !bad_len) {  // ids behind the window; those inside it are checked with their rows
         bool oob = false;
-        for (int t = Kt + tid; t < K; t += kVerdictThreads) {
+        for (int t = Kt + tid; t < K; t += NT) {
             const int y = a.draft[(long)b * kmax + t];
             oob = oob || y < 0 || y >= V;
         }
         if (oob) sh_bad = 1;
     }
-    ratio_test_block<DT, kVerdictThreads>(a, b, a.t_lo, Kt, smem_d, &sh_n, &sh_bad);
+    ratio_test_block<DT, NT>(a, b, a.t_lo, Kt, smem_d, &sh_n, &sh_bad);
     if (tid == 0) a.state[b] = sh_bad ? kFlagged : (sh_n == Kt && K > a.t_hi ? kInPlay : sh_n);
 }
 
@@ -1060,9 +1084,11 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
                                      listed ? 0 : w.t_hi, lists[i > 0], partial, stream);
         la.zero_n = 0;
         if (i == 0) mark(1);
-        if (i + 1 < windows)
-            hipLaunchKernelGGL((verdict_kernel<DT>), dim3((unsigned)B), dim3(kVerdictThreads),
+        if (i + 1 < windows) {
+            const bool few = w.t_hi - w.t_lo <= 8;
+            hipLaunchKernelGGL((few ? verdict_kernel<DT, 128> : verdict_kernel<DT, 512>), dim3((unsigned)B), dim3(few ? 128 : 512),
                                (size_t)2 * kmax * sizeof(double), stream, ra);
+        }
         if (i == 0) mark(2);
     }
     mark(3);

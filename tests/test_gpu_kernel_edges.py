@@ -236,3 +236,28 @@ def test_odd_bases_with_even_strides(binding, oracle, vocab, late):
                                temperature=w.temperature, draft_len=inp["draft_len"], want_draft_logprobs=True)
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, want_recovery_logprobs=False)
     parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
+
+
+# Ratio test: 16 lanes to a (position, tensor) pair.  As many pairs as a workgroup has such groups (8 positions with 4 waves, 32
+# with 16) and one position more, which takes rounds; verdicts of 5 .. 8 (two waves) and of more positions (eight).
+@pytest.mark.parametrize("batch,k_max,vocab", [(2, 8, 3001), (2, 9, 3001), (2, 32, 3001), (2, 33, 3001), (2, 32, 40001), (2, 33, 40001),
+                                               (300, 16, 801), (300, 17, 801), (64, 20, 104900), (64, 36, 58301)])
+def test_ratio_test_rounds(binding, oracle, batch, k_max, vocab):
+    w = recipe("c3", "bf16", batch=batch, k_max=k_max, vocab=vocab)
+    inp = W.generate(w, "cuda", seq_chunk=16)
+    gen = torch.Generator("cuda").manual_seed(k_max)
+    lens = torch.randint(0, k_max + 1, (batch,), generator=gen, device="cuda", dtype=torch.int32)
+    lens[0] = k_max
+    lens[-1] = k_max
+    inp["draft"][-1, k_max - 1] = vocab  # flagged by the last position
+    inp["draft_len"] = lens
+    args = [inp[k] for k in ("G", "S_ctx", "S_noctx", "draft", "uniforms")]
+    kw = dict(lam=w.lam, beta=w.beta, temperature=w.temperature, draft_len=lens)
+    got = binding.verify_block(*args, **kw)
+    one = binding.verify_block(*args, full_rows=True, want_draft_logprobs=True, **kw)
+    for k in ("accepted_len", "next_token", "next_token_logprob"):
+        assert torch.equal(torch.nan_to_num(got[k]), torch.nan_to_num(one[k])), k
+    assert got["accepted_len"][-1].item() == -1
+    seqs = torch.arange(0, batch, max(1, batch // 8), device="cuda")
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, seqs=seqs, want_recovery_logprobs=False)
+    parity.compare(one, ora, inp["uniforms"], lens, seqs=seqs)
