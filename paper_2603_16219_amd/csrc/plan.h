@@ -64,6 +64,13 @@ constexpr int kSplitMaxBatch = 128;  // workspace is reserved for shared recover
 //     sharing one.  With 8 sequences of V = 151936 (75 chunks) the recovery kernel goes from 17.2 us (40
 //     workgroups of 16 waves) to 11.5; beyond that line the parts' repeated ratio tests weigh more than the
 //     spread gains (64 such sequences: 71.2 us a step in 19 parts, 69.9 in 3, 72.4 in 4 uneven ones).
+//     Not where one 16-wave workgroup takes the row in a round and the hand-over between parts, or the ratio test by
+//     fewer waves, costs more (us a step of 8 sequences, 16 waves -> spread): from 5 to 8 chunks (4 drafts, V = 6166
+//     11.4 -> 12.7, V = 14400 12.8 -> 13.4; 10 chunks 14.5 -> 14.1); up to 16 with no draft, where the counters cost a
+//     launch of their own (rows of V = 6166, 14400 or 32768 11.8 -> 14.8), or with more than 16 drafts (V = 20000, 20
+//     drafts: 17.0 -> 17.4, 32 18.4 -> 18.9); a single part of 4 waves with more than 8 drafts (V = 2000, 12 drafts: 12.1 ->
+//     12.4).  Beyond 16 chunks up to 32 drafts (V = 151936: 24 drafts 27.1 -> 24.8, 32 30.8 -> 29.1; one sequence of V = 40000,
+//     48 drafts: 17.1 -> 17.9).
 //   - At least two compute units per sequence: as many 16-wave parts as there are units per sequence, with
 //     equal rounds of 16 chunks.
 //   - Up to one sequence per unit: one 16-wave workgroup each.  More: 8-wave workgroups, two to a unit, so that the
@@ -73,8 +80,9 @@ struct RecShape {
     int threads, part_chunks;
 };
 
-inline RecShape recovery_shape(int B, int NC, int cus, bool split) {
-    if (split && (long)B * NC <= 8l * cus) return {256, 4};
+inline RecShape recovery_shape(int B, int NC, int kmax, int cus, bool split) {
+    const bool spread = NC <= 4 ? kmax <= 8 : NC <= 16 ? NC > 8 && kmax > 0 && kmax <= 16 : kmax <= 32;
+    if (split && spread && (long)B * NC <= 8l * cus) return {256, 4};
     if (split && B <= cus / 2) {
         const int rows = (NC + 15) / 16;  // rounds of 16 chunks
         const int most = cus / B < rows ? cus / B : rows;

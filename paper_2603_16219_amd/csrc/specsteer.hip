@@ -1056,7 +1056,7 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     ra.log2z = recovery_logprobs ? reinterpret_cast<double*>(ws + pl.off_log2z) : nullptr;
     const unsigned bases[3] = {elem_parity<DT>(ra.G), elem_parity<DT>(ra.recSp), elem_parity<DT>(ra.recSm)};
     ra.NC = chunks_per_row(V, VEC, odd_rows_possible(VEC, bases, B, kmax, ra.sb, ra.st));
-    const RecShape shape = recovery_shape(B, ra.NC, device_cu_count(), pl.split);
+    const RecShape shape = recovery_shape(B, ra.NC, kmax, device_cu_count(), pl.split);
     ra.part_chunks = shape.part_chunks;
     ra.parts = (ra.NC + ra.part_chunks - 1) / ra.part_chunks;
     const bool split = ra.parts > 1;

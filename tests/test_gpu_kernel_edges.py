@@ -49,7 +49,8 @@ def test_logprob_rows_at_segment_edges(binding, oracle, dtype, vocab, beta):
     assert out["accepted_len"][2].item() == -1 and torch.all(out["recovery_logprobs"][2] == 7.0)  # left unwritten
 
 
-# The recovery launch: 4-wave workgroups of one chunk a wave while batch x chunks <= 8 x 256, then 16-wave parts of
+# The recovery launch: 4-wave workgroups of one chunk a wave while batch x chunks <= 8 x 256 (a single workgroup of 16 waves
+# for 5 .. 8 chunks), then 16-wave parts of
 # equal rounds up to 128 sequences, then one workgroup of 16 waves per sequence up to 256 and of 8 beyond.  A chunk is
 # 256 vectors (2048 bf16, 1024 fp32 logits), the logits past the last vector are a chunk of their own.
 @pytest.mark.parametrize("greedy,beta", [(False, 0.8), (True, 0.8), (False, 0.0), (True, 0.0)])
@@ -261,3 +262,18 @@ def test_ratio_test_rounds(binding, oracle, batch, k_max, vocab):
     seqs = torch.arange(0, batch, max(1, batch // 8), device="cuda")
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, seqs=seqs, want_recovery_logprobs=False)
     parity.compare(one, ora, inp["uniforms"], lens, seqs=seqs)
+
+
+# The same launch by chunks and drafts: up to 16 chunks it is one workgroup or several by the number of drafts, beyond them
+# two 16-wave parts (33 drafts).  No draft leaves the counters to a launch of their own.
+@pytest.mark.parametrize("dtype,k_max,chunks", [("bf16", 0, 4), ("bf16", 0, 9), ("bf16", 0, 16), ("f32", 0, 17), ("bf16", 9, 4), ("f32", 8, 8),
+                                                ("bf16", 16, 9), ("bf16", 17, 16), ("bf16", 32, 17), ("f32", 33, 17)])
+@pytest.mark.parametrize("greedy", [False, True])
+def test_recovery_launch_by_chunks_and_drafts(binding, oracle, dtype, k_max, chunks, greedy):
+    w = recipe("c3", dtype, batch=3, k_max=k_max, vocab=chunks * (2048 if dtype == "bf16" else 1024))
+    inp = W.generate(w, "cuda")
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam, beta=w.beta,
+                               temperature=w.temperature, greedy=greedy, want_draft_logprobs=True)
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, greedy=greedy,
+                            want_recovery_logprobs=False)
+    parity.compare(out, ora, inp["uniforms"], None)

@@ -34,7 +34,7 @@ int main() {
             int cus, odd;
             if (std::scanf("%d %d", &cus, &odd) != 2) return 1;
             const int nc = chunks_per_row(p.vocab, pl.vec, odd != 0);
-            const RecShape s = recovery_shape(p.batch, nc, cus, pl.split);
+            const RecShape s = recovery_shape(p.batch, nc, p.k_max, cus, pl.split);
             std::printf("%d %d %d\n", nc, s.threads, s.part_chunks);
         } else {  // the workspace, the space of the slice partials, and for every window its end and its slices a row
             std::printf("%ld %ld", (long)pl.bytes, (long)(pl.off_arrive - pl.off_partial) / (long)sizeof(Partial));
@@ -67,9 +67,9 @@ def planner(tmp_path_factory):
 BF16 = 1
 
 
-def shape(planner, batch, vocab, dtype, odd):
+def shape(planner, batch, vocab, dtype, odd, k_max=1):
     """(chunks of a row, threads of a workgroup, chunks of a part)"""
-    return planner([f"parts {batch} 1 {vocab} {dtype} 0 0.5 {CUS} {odd}"])[0]
+    return planner([f"parts {batch} {k_max} {vocab} {dtype} 0 0.5 {CUS} {odd}"])[0]
 
 
 # A chunk is 256 vectors (2048 bf16 logits); rows that start at even elements have exactly V / 2048 of them here.
@@ -83,6 +83,15 @@ def shape(planner, batch, vocab, dtype, odd):
 def test_recovery_parts_follow_the_chunks_the_rows_have(planner, batch, vocab, threads, part_chunks):
     chunks = -(-vocab // 2048)
     assert shape(planner, batch, vocab, BF16, 0) == (chunks, threads, part_chunks)
+
+
+# Rows that one 16-wave workgroup takes in a round, and long drafts: spread over 4-wave workgroups only where that pays.
+@pytest.mark.parametrize("chunks,k_max,spread", [
+    (1, 0, True), (4, 8, True), (4, 9, False), (5, 1, False), (8, 8, False), (9, 0, False), (9, 1, True), (16, 0, False),
+    (16, 16, True), (16, 17, False), (17, 0, True), (17, 32, True), (17, 33, False)])
+def test_recovery_of_few_chunks_is_spread_only_where_that_pays(planner, chunks, k_max, spread):
+    n, threads, part = shape(planner, 8, chunks * 2048, BF16, 0, k_max)
+    assert n == chunks and (threads, part) == ((256, 4) if spread else (1024, 9 if chunks > 16 else chunks))
 
 
 def test_a_row_read_from_one_element_before_may_have_a_chunk_more(planner):
