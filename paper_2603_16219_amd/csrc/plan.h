@@ -93,6 +93,18 @@ inline RecShape recovery_shape(int B, int NC, int kmax, int cus, bool split) {
     return {B <= cus ? 1024 : 512, NC};
 }
 
+// Whether the recovery launch writes the requested log-prob rows itself, its row in one part, or a launch of their own does.
+// A launch costs 2.5 us of host time, which is what such small calls take; the workgroup that drew the token takes longer
+// over its row than the chip does, which counts the sooner, the more drafted rows the call has.  By the bytes of a row, three
+// read and one written (us a call, a launch of its own -> inside; bf16, 4 drafts): one sequence of V = 1000 20.1 -> 17.8, of
+// V = 32000 20.4 -> 18.7, of V = 40000 20.5 -> 20.9; 2 of V = 32000 22.2 -> 19.8, of V = 40000 20.7 -> 23.0; 4 of V = 32000
+// 20.4 -> 21.0; 8 of V = 24000 20.7 -> 19.1 (16 drafts 21.7 -> 21.7); 16 of V = 20000 22.0 -> 20.7 (16 drafts 22.1 -> 23.2);
+// 100 of V = 16384 23.9 -> 23.2, 600 of them 72.6 -> 67.4.
+inline bool logprobs_in_recovery(int B, int kmax, int V, int esz) {
+    const long drafts = (long)B * kmax, row = (long)V * (3 * esz + 4);
+    return row <= (B <= 16 && drafts <= 128 ? (drafts <= 4 ? 384l : drafts <= 8 ? 320l : 256l) : 164l) << 10;
+}
+
 // Several row passes pay off when the batch is large enough to be bandwidth-bound and long enough for
 // a first rejection to cut rows: a first window is scored for everyone, what follows only for the sequences that
 // are still in play.  A further window costs some 10 us (a verdict launch, and the ends of a row pass), the time of

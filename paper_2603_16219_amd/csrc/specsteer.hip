@@ -338,7 +338,8 @@ struct RecArgs {
     int32_t* accepted_len;
     int32_t* next_token;
     float* next_token_logprob;
-    double* log2z;           // [B] log2 of the recovery row's normaliser, for the log-prob rows; else NULL
+    double* log2z;           // [B] log2 of the recovery row's normaliser, for a launch that writes the log-prob rows; else NULL
+    float* recovery_logprobs;  // [B, V] log-prob rows if this launch writes them itself; else NULL
     float* draft_logprobs;
     long sb, st;
     int B, kmax, V;
@@ -798,6 +799,55 @@ __device__ __forceinline__ void wave_best(Best& best) {
     }
 }
 
+// ------------------------------------------------------------------ log-prob rows
+
+constexpr int kLogprobThreads = 256;
+constexpr int kLogprobUnroll = 2;  // vectors per tensor a thread has in flight
+
+// fp32 pair or quad stored at any element boundary (an odd vocabulary size starts its rows anywhere)
+__device__ __forceinline__ void st_f32x4(float* p, float x, float y, float z, float w) {
+    const f32x4 v = {x, y, z, w};
+    __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
+}
+
+constexpr int kNoTail = 0x7FFFFFFF;
+
+// log Softmax(h_rec / T) of kLogprobUnroll vectors of a row, v and those `step` behind it, and of logit `tail` past the last
+// full vector, where there is one.
+template <int DT, int VEC, bool PLAIN>
+__device__ __forceinline__ void write_logprobs(const void* g, const void* sp, const void* sm, float* out, int V, long v0,
+                                               int step, int tail, double c, double bc, double log2Z) {
+    const long nvec = V / VEC;
+    typename RawT<DT, VEC>::type rg[kLogprobUnroll], rp[kLogprobUnroll], rm[kLogprobUnroll];
+#pragma unroll
+    for (int j = 0; j < kLogprobUnroll; ++j) {
+        const long v = v0 + j * step;
+        if (v < nvec) {
+            rg[j] = ld_raw<DT, VEC>(g, v);
+            if (!PLAIN) {
+                rp[j] = ld_raw<DT, VEC>(sp, v);
+                rm[j] = ld_raw<DT, VEC>(sm, v);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kLogprobUnroll; ++j) {
+        const long v = v0 + j * step;
+        if (v >= nvec) break;
+        float hg[VEC], hp[VEC], hm[VEC], o[VEC];
+        unpack(rg[j], hg);
+        unpack_steer<DT, VEC, PLAIN>(rp[j], rm[j], hp, hm);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) o[i] = (float)(kLn2 * (rec_y(hg[i], hp[i], hm[i], c, bc) - log2Z));
+#pragma unroll
+        for (int i = 0; i < VEC; i += 4) st_f32x4(out + v * VEC + i, o[i], o[i + 1], o[i + 2], o[i + 3]);
+    }
+    if (tail < V - nvec * VEC) {
+        const long e = nvec * VEC + tail;
+        out[e] = (float)(kLn2 * (rec_y(ld_elem<DT>(g, e), ld_steer<DT, PLAIN>(sp, e), ld_steer<DT, PLAIN>(sm, e), c, bc) - log2Z));
+    }
+}
+
 // Everything after the row pass in one launch, a workgroup of NT threads per sequence:
 //   2a  every (position, tensor) pair gets 16 lanes: merge its slice partials, gather the draft
 //       token's logit, leave log P(y_t) in LDS            (two memory round trips in all)
@@ -805,6 +855,7 @@ __device__ __forceinline__ void wave_best(Best& best) {
 //   3   all waves stream the three rows at the rejected (or bonus) position once, one (E, s)
 //       mass per 2048-logit chunk into LDS
 //   4   wave 0 draws the token
+//   5   all waves write the log-prob row, where it is short enough (logprobs_in_recovery)
 // Only workgroup barriers separate the steps; nothing crosses workgroups.
 //
 // a.parts > 1: that many workgroups share a sequence.  Each repeats steps 2a-2b, takes a.part_chunks
@@ -819,6 +870,7 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     __shared__ float sh_terms[kChunkSteps * VEC];
     __shared__ double sh_best_v[NT / kWave];
     __shared__ long sh_best_i[NT / kWave];
+    __shared__ double sh_log2z;
 
     const int S = a.parts;
     const int b = (int)blockIdx.x / S, part = (int)blockIdx.x - b * S;
@@ -885,44 +937,59 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
             sh_best_i[wave] = best.idx;
         }
     }
+    const bool rows = a.recovery_logprobs != nullptr;
     __syncthreads();
-    if (wave != 0) return;
-    if (GREEDY) {
-        best.v = lane < NW ? sh_best_v[lane] : -__builtin_huge_val();
-        best.idx = lane < NW ? sh_best_i[lane] : 0x7FFFFFFFFFFFFFFFl;
-        wave_best(best);
-        if (best.idx <= (long)V) best.idx -= head;
-    }
-    if (S > 1) {  // deliver this part; only the last part to arrive goes on
-        Partial* gtab = a.chunk_tab + (long)b * a.NC;
-        for (int c = c0 + lane; c < c1; c += kWave) st_dev_partial(gtab + c, tab[c]);
-        if (GREEDY && lane == 0) {
-            st_dev(reinterpret_cast<unsigned long long*>(a.best_v + (long)b * a.NC + part),
-                   (unsigned long long)__double_as_longlong(best.v));
-            st_dev(a.best_i + (long)b * a.NC + part, (int32_t)min(best.idx, (long)V));
-        }
-        wait_stores();  // this wave's deliveries have reached memory before it is counted
-        unsigned prev = 0;
-        if (lane == 0)
-            prev = __hip_atomic_fetch_add(a.arrive + (long)b * kArriveStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (__builtin_amdgcn_readfirstlane((int)prev) != S - 1) return;
-        for (int c = lane; c < NC; c += kWave) tab[c] = ld_dev_partial(gtab + c);
+    if (wave == 0) {
         if (GREEDY) {
-            best = Best{-__builtin_huge_val(), 0x7FFFFFFFFFFFFFFFl};
-            for (int i = lane; i < S; i += kWave) {
-                const double v = __longlong_as_double((long long)ld_dev(
-                    reinterpret_cast<const unsigned long long*>(a.best_v + (long)b * a.NC + i)));
-                const long idx = (long)ld_dev(a.best_i + (long)b * a.NC + i);
-                if (v > best.v || (v == best.v && idx < best.idx)) best = Best{v, idx};
-            }
+            best.v = lane < NW ? sh_best_v[lane] : -__builtin_huge_val();
+            best.idx = lane < NW ? sh_best_i[lane] : 0x7FFFFFFFFFFFFFFFl;
             wave_best(best);
+            if (best.idx <= (long)V) best.idx -= head;
         }
-        wave_lds_sync();
-    }
+        if (S > 1) {  // deliver this part; only the last part to arrive goes on
+            Partial* gtab = a.chunk_tab + (long)b * a.NC;
+            for (int c = c0 + lane; c < c1; c += kWave) st_dev_partial(gtab + c, tab[c]);
+            if (GREEDY && lane == 0) {
+                st_dev(reinterpret_cast<unsigned long long*>(a.best_v + (long)b * a.NC + part),
+                       (unsigned long long)__double_as_longlong(best.v));
+                st_dev(a.best_i + (long)b * a.NC + part, (int32_t)min(best.idx, (long)V));
+            }
+            wait_stores();  // this wave's deliveries have reached memory before it is counted
+            unsigned prev = 0;
+            if (lane == 0)
+                prev = __hip_atomic_fetch_add(a.arrive + (long)b * kArriveStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (__builtin_amdgcn_readfirstlane((int)prev) != S - 1) return;
+            for (int c = lane; c < NC; c += kWave) tab[c] = ld_dev_partial(gtab + c);
+            if (GREEDY) {
+                best = Best{-__builtin_huge_val(), 0x7FFFFFFFFFFFFFFFl};
+                for (int i = lane; i < S; i += kWave) {
+                    const double v = __longlong_as_double((long long)ld_dev(
+                        reinterpret_cast<const unsigned long long*>(a.best_v + (long)b * a.NC + i)));
+                    const long idx = (long)ld_dev(a.best_i + (long)b * a.NC + i);
+                    if (v > best.v || (v == best.v && idx < best.idx)) best = Best{v, idx};
+                }
+                wave_best(best);
+            }
+            wave_lds_sync();
+        }
 
-    // ---- 4
-    const double log2Z = sample_wave<DT, VEC, GREEDY, PLAIN>(a, b, n, lane, tab, g, sp, sm, nvec, tailc, head, nch, NC, best, sh_terms);
-    if (a.log2z && lane == 0) a.log2z[b] = log2Z;
+        // ---- 4
+        const double log2Z = sample_wave<DT, VEC, GREEDY, PLAIN>(a, b, n, lane, tab, g, sp, sm, nvec, tailc, head, nch, NC, best, sh_terms);
+        if (lane == 0) {
+            if (a.log2z) a.log2z[b] = log2Z;
+            sh_log2z = log2Z;
+        }
+    }
+    if (!rows) return;
+
+    // ---- 5 (only with the row in one part)
+    __syncthreads();
+    const long nv = V / VEC;
+    g = row_ptr<DT>(a.G, off);
+    sp = row_ptr<DT>(a.recSp, off);
+    sm = row_ptr<DT>(a.recSm, off);
+    for (long v = tid; v < nv || v == tid; v += NT * kLogprobUnroll)
+        write_logprobs<DT, VEC, PLAIN>(g, sp, sm, a.recovery_logprobs + (long)b * V, V, v, NT, v == tid ? tid : kNoTail, a.c, a.bc, sh_log2z);
 }
 
 // ------------------------------------------------------------------ kernel: log-prob rows
@@ -940,17 +1007,8 @@ struct LogprobArgs {
     double c, bc;
 };
 
-constexpr int kLogprobThreads = 256;
-constexpr int kLogprobUnroll = 2;  // vectors per tensor a thread has in flight
-
-// fp32 pair or quad stored at any element boundary (an odd vocabulary size starts its rows anywhere)
-__device__ __forceinline__ void st_f32x4(float* p, float x, float y, float z, float w) {
-    const f32x4 v = {x, y, z, w};
-    __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
-}
-
 // log Softmax(h_rec / T) at row n_b, after accept_recover has left n_b and the row's log2-normaliser.
-// HBM-bound: three rows read and one fp32 row written per sequence.  It is a launch of its own because the
+// HBM-bound: three rows read and one fp32 row written per sequence.  A launch of its own but for short rows, because the
 // workgroup that draws a sequence's token is one of at most a few hundred, each tied to the rate of one
 // compute unit; cut into segments of two vectors a thread, the sweep covers the chip (16 sequences of
 // V = 151936 bf16: 40 us of a 57 us recovery kernel before, 7 us as a launch of its own).
@@ -959,41 +1017,10 @@ __global__ __launch_bounds__(kLogprobThreads) void recovery_logprob_kernel(const
     const int b = (int)blockIdx.x / a.segs, seg = (int)blockIdx.x - b * a.segs;
     const int n = a.accepted_len[b];
     if (n < 0) return;  // a flagged sequence's row is left unwritten
-    const double log2Z = a.log2z[b];
     const long off = (long)b * a.sb + (long)n * a.st;
-    const void* g = row_ptr<DT>(a.G, off);
-    const void* sp = row_ptr<DT>(a.recSp, off);
-    const void* sm = row_ptr<DT>(a.recSm, off);
-    const long nvec = a.V / VEC;
-    float* out = a.out + (long)b * a.V;
-    const long v0 = (long)seg * (kLogprobThreads * kLogprobUnroll) + threadIdx.x;
-    typename RawT<DT, VEC>::type rg[kLogprobUnroll], rp[kLogprobUnroll], rm[kLogprobUnroll];
-#pragma unroll
-    for (int j = 0; j < kLogprobUnroll; ++j) {
-        const long v = v0 + j * kLogprobThreads;
-        if (v < nvec) {
-            rg[j] = ld_raw<DT, VEC>(g, v);
-            if (!PLAIN) {
-                rp[j] = ld_raw<DT, VEC>(sp, v);
-                rm[j] = ld_raw<DT, VEC>(sm, v);
-            }
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < kLogprobUnroll; ++j) {
-        const long v = v0 + j * kLogprobThreads;
-        if (v >= nvec) break;
-        float hg[VEC], hp[VEC], hm[VEC], o[VEC];
-        unpack(rg[j], hg);
-        unpack_steer<DT, VEC, PLAIN>(rp[j], rm[j], hp, hm);
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) o[i] = (float)(kLn2 * (rec_y(hg[i], hp[i], hm[i], a.c, a.bc) - log2Z));
-#pragma unroll
-        for (int i = 0; i < VEC; i += 4) st_f32x4(out + v * VEC + i, o[i], o[i + 1], o[i + 2], o[i + 3]);
-    }
-    const long e = nvec * VEC + threadIdx.x;  // logits past the last full vector
-    if (seg == a.segs - 1 && e < a.V)
-        out[e] = (float)(kLn2 * (rec_y(ld_elem<DT>(g, e), ld_steer<DT, PLAIN>(sp, e), ld_steer<DT, PLAIN>(sm, e), a.c, a.bc) - log2Z));
+    write_logprobs<DT, VEC, PLAIN>(row_ptr<DT>(a.G, off), row_ptr<DT>(a.recSp, off), row_ptr<DT>(a.recSm, off),
+                                   a.out + (long)b * a.V, a.V, (long)seg * (kLogprobThreads * kLogprobUnroll) + threadIdx.x,
+                                   kLogprobThreads, seg == a.segs - 1 ? (int)threadIdx.x : kNoTail, a.c, a.bc, a.log2z[b]);
 }
 
 __global__ void zero_u32_kernel(uint32_t* p, int n) {
@@ -1053,10 +1080,13 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     const bool ragged = ra.draft_len != nullptr && kmax > 0;
     ra.partial = partial;
     ra.state = windows > 1 ? state : nullptr;
-    ra.log2z = recovery_logprobs ? reinterpret_cast<double*>(ws + pl.off_log2z) : nullptr;
     const unsigned bases[3] = {elem_parity<DT>(ra.G), elem_parity<DT>(ra.recSp), elem_parity<DT>(ra.recSm)};
     ra.NC = chunks_per_row(V, VEC, odd_rows_possible(VEC, bases, B, kmax, ra.sb, ra.st));
-    const RecShape shape = recovery_shape(B, ra.NC, kmax, device_cu_count(), pl.split);
+    RecShape shape = recovery_shape(B, ra.NC, kmax, device_cu_count(), pl.split);
+    const bool rows_inside = recovery_logprobs && logprobs_in_recovery(B, kmax, V, DT == SS_BF16 ? 2 : 4);
+    if (rows_inside && shape.part_chunks < ra.NC) shape = RecShape{1024, ra.NC};
+    ra.recovery_logprobs = rows_inside ? recovery_logprobs : nullptr;
+    ra.log2z = recovery_logprobs && !rows_inside ? reinterpret_cast<double*>(ws + pl.off_log2z) : nullptr;
     ra.part_chunks = shape.part_chunks;
     ra.parts = (ra.NC + ra.part_chunks - 1) / ra.part_chunks;
     const bool split = ra.parts > 1;
@@ -1104,7 +1134,7 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
          accept_recover_kernel<DT, VEC, false, true, 1024>, accept_recover_kernel<DT, VEC, true, true, 1024>}};
     hipLaunchKernelGGL(rec_kernels[shape.threads >> 9][(ra.greedy ? 1 : 0) | (ra.plain ? 2 : 0)], rec_grid,
                        dim3((unsigned)shape.threads), smem, stream, ra);
-    if (recovery_logprobs) {
+    if (recovery_logprobs && !rows_inside) {
         const long nvec = V / VEC, per = kLogprobThreads * kLogprobUnroll;
         const int segs = nvec > per ? (int)((nvec + per - 1) / per) : 1;
         const LogprobArgs pa{ra.G, ra.recSp, ra.recSm, ra.accepted_len, ra.log2z, recovery_logprobs, ra.sb, ra.st, V,

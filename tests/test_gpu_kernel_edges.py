@@ -24,11 +24,14 @@ def recipe(name, dtype, **size):
     return dataclasses.replace(W.scaled(W.WORKLOADS[name], name=f"{name}-{dtype}-{size}", **size), dtype=dtype)
 
 
-# The log-prob rows are cut into segments of 512 vectors (4096 bf16 or 2048 fp32 logits): one segment exactly,
+# Short log-prob rows are written by the recovery launch (5 sequences: up to 256 KiB a row, 26214 bf16 or 16384 fp32 logits),
+# longer ones by a launch of their own, cut into segments of 512 vectors (4096 bf16 or 2048 fp32 logits): whole segments,
 # one logit more and less, a last segment that holds only the logits past the last vector, less than a vector.
 @pytest.mark.parametrize("beta", [0.0, 0.8])
 @pytest.mark.parametrize("dtype,vocab", [("bf16", 4096), ("bf16", 4097), ("bf16", 8191), ("bf16", 3), ("f32", 2048),
-                                         ("f32", 2049), ("f32", 6143), ("f32", 3)])
+                                         ("f32", 2049), ("f32", 6143), ("f32", 3),
+                                         ("bf16", 26214), ("bf16", 26215), ("bf16", 28671), ("bf16", 28672), ("bf16", 28673),
+                                         ("f32", 16384), ("f32", 16385), ("f32", 18431), ("f32", 18432), ("f32", 18433)])
 def test_logprob_rows_at_segment_edges(binding, oracle, dtype, vocab, beta):
     w = recipe("c4", dtype, batch=5, k_max=3, vocab=vocab)
     inp = W.generate(w, "cuda")

@@ -20,6 +20,12 @@ PROGRAM = r"""
 int main() {
     char what[16];
     while (std::scanf("%15s", what) == 1) {
+        if (!std::strcmp(what, "rows")) {  // B kmax V esz
+            int B, k, V, esz;
+            if (std::scanf("%d %d %d %d", &B, &k, &V, &esz) != 4) return 1;
+            std::printf("%d\n", logprobs_in_recovery(B, k, V, esz) ? 1 : 0);
+            continue;
+        }
         if (!std::strcmp(what, "odd")) {  // vec base base base B kmax sb st
             unsigned a[3]; int vec, B, k; long sb, st;
             if (std::scanf("%d %u %u %u %d %d %ld %ld", &vec, a, a + 1, a + 2, &B, &k, &sb, &st) != 8) return 1;
@@ -92,6 +98,16 @@ def test_recovery_parts_follow_the_chunks_the_rows_have(planner, batch, vocab, t
 def test_recovery_of_few_chunks_is_spread_only_where_that_pays(planner, chunks, k_max, spread):
     n, threads, part = shape(planner, 8, chunks * 2048, BF16, 0, k_max)
     assert n == chunks and (threads, part) == ((256, 4) if spread else (1024, 9 if chunks > 16 else chunks))
+
+
+# Small calls that ask for log-prob rows spend their time on the host: the rows of few and short sequences come without a
+# launch of their own.
+@pytest.mark.parametrize("batch,k_max,vocab,esz,inside", [
+    (1, 4, 32000, 2, 1), (1, 4, 40000, 2, 0), (1, 4, 24000, 4, 1), (1, 8, 24000, 4, 0), (2, 4, 32000, 2, 1), (2, 8, 32000, 2, 0),
+    (4, 4, 32000, 2, 0), (4, 4, 24000, 2, 1), (16, 8, 16384, 4, 1), (16, 9, 16384, 4, 0), (17, 4, 16384, 4, 0), (1, 0, 24576, 4, 1),
+    (600, 16, 16384, 2, 1), (600, 4, 20000, 2, 0), (16, 8, 151936, 2, 0)])
+def test_short_logprob_rows_come_without_a_launch_of_their_own(planner, batch, k_max, vocab, esz, inside):
+    assert planner([f"rows {batch} {k_max} {vocab} {esz}"]) == [(inside,)]
 
 
 def test_a_row_read_from_one_element_before_may_have_a_chunk_more(planner):
