@@ -112,9 +112,12 @@ def _ptr(t: Optional[torch.Tensor]):
 def _stream(device: torch.device) -> int:
     """The handle of torch's current stream on `device` (torch.cuda.current_stream without its Stream object,
     which takes as long to build as the smallest launch).  Like it, it refuses a device that is no GPU."""
-    if device.type != "cuda":
-        raise ValueError(f"logits must be on a GPU device, got {device}; there is no CPU path")
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if device.index is None else device.index)
+    index = device.index
+    if index is None:  # never so for the device of a GPU tensor, always for that of a host tensor
+        if device.type != "cuda":
+            raise ValueError(f"logits must be on a GPU device, got {device}; there is no CPU path")
+        index = torch.cuda.current_device()
+    return torch._C._cuda_getCurrentRawStream(index)
 
 
 def _ready(t: torch.Tensor, device: torch.device, dtype: torch.dtype) -> torch.Tensor:
@@ -125,16 +128,10 @@ def _ready(t: torch.Tensor, device: torch.device, dtype: torch.dtype) -> torch.T
     return t.to(device=device, dtype=dtype).contiguous()
 
 
-def _stride(rows: torch.Tensor, dim: int) -> int:
-    """The stride of dimension `dim` of the logits as the library takes it, where 0 means dense.  A dimension of one
-    has no stride worth passing on; one that repeats the same memory (an expanded tensor) would be read as dense,
-    past its end, and is refused like rows that overlap in part."""
-    if rows.shape[dim] <= 1:
-        return 0
-    stride = rows.stride(dim)
-    if stride == 0:
-        raise ValueError("logit rows must not repeat the same memory (an expanded tensor): pass a contiguous copy")
-    return stride
+def _refuse_repeated_rows() -> None:
+    """A stride of 0 means dense rows to the library, which would read an expanded tensor past its end; it is refused
+    like rows that overlap in part."""
+    raise ValueError("logit rows must not repeat the same memory (an expanded tensor): pass a contiguous copy")
 
 
 STAGES = ("row_pass1", "verdict", "row_pass2", "recover")
@@ -194,7 +191,8 @@ def verify_block(G: torch.Tensor, S_ctx: torch.Tensor, S_noctx: torch.Tensor, dr
         raise ValueError("logit tensors must share a [B, k_max+1, V] shape")
     if not (G.dtype == S_ctx.dtype == S_noctx.dtype):
         raise ValueError("logit tensors must share a dtype")
-    if not (G.stride() == S_ctx.stride() == S_noctx.stride()) or G.stride(2) != 1:
+    stride = G.stride()
+    if not (stride == S_ctx.stride() == S_noctx.stride()) or stride[2] != 1:
         raise ValueError("logit tensors must share strides, with the vocabulary contiguous")
     B, k1, V = G.shape
     k_max = k1 - 1
@@ -214,8 +212,10 @@ def verify_block(G: torch.Tensor, S_ctx: torch.Tensor, S_noctx: torch.Tensor, dr
     uniforms = _ready(uniforms, dev, torch.float32)
     if draft_len is not None:
         draft_len = _ready(draft_len, dev, torch.int32)
+    if (B > 1 and stride[0] == 0) or (k1 > 1 and stride[1] == 0):
+        _refuse_repeated_rows()
     params = make_params(B, k_max, V, G.dtype, lam=lam, beta=beta, temperature=temperature,
-                         stride_b=_stride(G, 0), stride_t=_stride(G, 1),
+                         stride_b=stride[0] if B > 1 else 0, stride_t=stride[1] if k1 > 1 else 0,
                          flags=(SS_FLAG_GREEDY if greedy else 0) | (SS_FLAG_FULL_ROWS if full_rows else 0))
     need = workspace_bytes(params)
     if workspace is None:
@@ -253,10 +253,12 @@ def steer_rows(G: torch.Tensor, S_ctx: torch.Tensor, S_noctx: torch.Tensor, unif
         raise ValueError("logit tensors must share strides, with the vocabulary contiguous")
     if not (G.is_cuda and S_ctx.is_cuda and S_noctx.is_cuda):
         raise ValueError("specsteer_verify_block needs device tensors; there is no CPU path")
+    if n > 1 and stride[0] == 0:
+        _refuse_repeated_rows()
     dev = G.device
     uniforms = _ready(uniforms, dev, torch.float32)
     params = make_params(n, 0, v, G.dtype, lam=0.5, beta=beta, temperature=temperature,
-                         stride_b=_stride(G, 0), flags=SS_FLAG_GREEDY if greedy else 0)
+                         stride_b=stride[0] if n > 1 else 0, flags=SS_FLAG_GREEDY if greedy else 0)
     # one allocation for the workspace and, behind it, the accepted lengths (all 0) that nobody asked for
     need = (max(workspace_bytes(params), 256) + 255) // 256 * 256
     workspace = torch.empty(need + 4 * n, dtype=torch.uint8, device=dev)
@@ -281,8 +283,11 @@ def sample_rows(logits: torch.Tensor, uniforms: torch.Tensor, *, temperature: fl
 
 def _split_params(T: torch.Tensor, beta: float, temperature: float, greedy: bool) -> SSParams:
     B, k1, V = T.shape
+    stride_b, stride_t, _ = T.stride()
+    if (B > 1 and stride_b == 0) or (k1 > 1 and stride_t == 0):
+        _refuse_repeated_rows()
     return make_params(B, k1 - 1, V, T.dtype, lam=0.5, beta=beta, temperature=temperature,
-                       stride_b=_stride(T, 0), stride_t=_stride(T, 1),
+                       stride_b=stride_b if B > 1 else 0, stride_t=stride_t if k1 > 1 else 0,
                        flags=SS_FLAG_GREEDY if greedy else 0)
 
 
@@ -324,8 +329,8 @@ def edge_resample(index: torch.Tensor, value: torch.Tensor, S_ctx: torch.Tensor,
     if not (S_ctx.is_cuda and index.is_cuda and value.is_cuda):
         raise ValueError("specsteer_edge_resample needs device tensors; there is no CPU path")
     # bound to names: a copy that nothing holds is freed before the call, and the next one may take its memory
-    index = _ready(index, dev, torch.int32)
-    value = _ready(value, dev, torch.float32)
+    index = index.contiguous()
+    value = value.contiguous()
     row = _ready(row, dev, torch.int32)
     uniform = None if uniform is None else _ready(uniform, dev, torch.float32)
     tok = torch.empty(B, dtype=torch.int32, device=dev)
