@@ -95,7 +95,7 @@ typedef struct {
 
 /*
  * Number of leading positions per sequence that the first row pass of specsteer_verify_block
- * scores for these params (host call).  Equal to k_max when the block is verified in one pass
+ * scores for these params, lambda among them (host call).  Equal to k_max when the block is verified in one pass
  * (small batches, k_max < 4, SS_FLAG_FULL_ROWS; a non-NULL draft_logprobs has the same effect at
  * call time).  Returns -1 for invalid params.
  */
@@ -103,7 +103,7 @@ int specsteer_first_window(const ss_params *params);
 
 /*
  * Bytes of device scratch specsteer_verify_block needs for these params
- * (depends on batch, k_max, vocab and dtype only).  Returns 0 if params is
+ * (depends on batch, k_max, vocab, dtype and SS_FLAG_FULL_ROWS only).  Returns 0 if params is
  * NULL or its shape fields are invalid.  Host call, no GPU work.
  */
 size_t specsteer_workspace_bytes(const ss_params *params);
@@ -116,8 +116,8 @@ size_t specsteer_workspace_bytes(const ss_params *params);
  *                      need element alignment only (SS_ERR_STRIDE otherwise) and any V works;
  *                      rows that start on 16-byte boundaries (base pointers 16-byte aligned,
  *                      strides multiples of 16 bytes) stream fastest, others take up to a
- *                      tenth longer (a third where bf16 rows of the three tensors lie at odd
- *                      and even elements).
+ *                      tenth longer (a third over bf16 rows at odd elements where the three
+ *                      tensors differ in that, and where recovery_logprobs is asked for).
  *   draft              device, [B, k_max] int32 token ids; slots t >= K_b ignored.
  *                      May be NULL when k_max == 0.
  *   draft_len          device, [B] int32 K_b, or NULL meaning K_b = k_max for all b.
@@ -219,6 +219,7 @@ ss_status specsteer_verify_block_timed(const void *G, const void *S_ctx, const v
  *   out_value  device, [B, topk] fp32  h_cloud of those tokens rounded to fp32; -inf in unused slots
  *   row        device, [B] int32 in [0, k_max] (normally accepted_len of specsteer_verify_block);
  *              a negative or too large entry marks a flagged sequence: all ids -1, values -inf.
+ * bf16 rows at odd elements take a third longer than others.
  * Uses batch, k_max, vocab, dtype, strides, beta of params (host); 1 <= topk <= SS_MAX_TOPK
  * (the paper uses 32).  No workspace.  Argument errors as for specsteer_verify_block.
  *

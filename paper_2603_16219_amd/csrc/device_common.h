@@ -132,7 +132,8 @@ template <> struct RawT<SS_F32, 4> { using type = float4; };
 // with unaligned access enabled, so the same 16-byte load instruction serves rows that start anywhere.
 // At any 4-byte boundary it runs at the full rate (a plain read of 231 MB in rows of V = 50258: 36.8 us, of V = 50256:
 // 36.6); off 4-byte boundaries, every other row of an odd bf16 vocabulary, it does not (V = 50257: 46.3 us).
-// Kernels therefore read such a row from one element before its start (odd_head) and mask that element.
+// The row pass and the recovery sweep therefore read such a row from one element before its start (odd_head) and mask that
+// element; the log-prob rows and the cloud top-k read it as it is, at the lower rate.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4), aligned(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4), aligned(4)));
 

@@ -111,7 +111,10 @@ inline bool logprobs_in_recovery(int B, int kmax, int V, int esz) {
 // 66 MB of rows.
 //   - From kEarlyExitMinBytes of rows: a first window of a quarter of the positions and one of the rest (256 ragged
 //     sequences of up to 16 positions, V = 128256: 4 and 12; cut into 4, 4 and 8 it gains 2 us of 168 at
-//     acceptance 0.8 and loses 10 where nearly everything is accepted).
+//     acceptance 0.8 and loses 10 where nearly everything is accepted).  Below it a second window pays or not by what is
+//     accepted, which the host does not know: 64 sequences of 8 positions, V = 151936 (311 MB), 69.1 us a step in one window,
+//     67.4 in 4 and 4, 70.5 in 2 and 6 at acceptance 0.8; 69.9, 52.5 and 46.6 at 0.4; 69.1, 78.1 and 79.7 where nearly
+//     everything is accepted.
 //   - From doubling_min_bytes of rows a position, the rows behind one position are already worth a launch: windows of
 //     1, 1, 2, 4, ... positions.  512 sequences of 8 positions, V = 256000 bf16 (500 MiB a position): 362 -> 298 us a step
 //     at acceptance 0.4, 603 -> 525 at 0.8.
