@@ -22,7 +22,8 @@
 //                  exponent in double (in fp32, as the row pass does, when beta == 0 leaves
 //                  no steering term), and record one (E, s) mass per 2048-logit chunk
 //                  in LDS.  A double-precision scan over the chunk masses locates the
-//                  chunk holding u*Z; only that chunk is read again to pick the token.
+//                  chunk holding u*Z; only that chunk is read again, by four waves, to pick the
+//                  token.
 //                  Batches of at most 128 sequences share each recovery row between
 //                  several workgroups; the one that delivers its chunk masses last
 //                  draws the token (see accept_recover_kernel; hand-over by write-through
@@ -427,55 +428,6 @@ __device__ __forceinline__ float ld_steer(const void* row, long e) {
     return PLAIN ? 0.f : ld_elem<DT>(row, e);
 }
 
-// Probability terms 2^(y - E) of the logits one lane owns in recovery chunk c, laid out so that
-// a lane's logits are consecutive in the vocabulary: lane l holds vectors 4l..4l+3 of the chunk.
-// The pseudo-chunk c == nch holds the < VEC logits past the last full vector, one per lane.
-// Terms of logits that do not exist are 0.
-// PLAIN forms the terms as the sweep did, 2^(fma(h, c_hi, -E)) in fp32.
-template <int DT, int VEC, bool PLAIN>
-__device__ __forceinline__ void chunk_lane_terms(const void* g, const void* sp, const void* sm, long nvec, int tailc,
-                                                 int head, long nch, long c, int lane, double cc, double bc, float c_hi, int E,
-                                                 float (&p)[kChunkSteps][VEC]) {
-    const double dE = (double)E;
-    const float nE = -(float)E;
-    typename RawT<DT, VEC>::type rg[kChunkSteps], rp[kChunkSteps], rm[kChunkSteps];
-    bool ok[kChunkSteps];
-#pragma unroll
-    for (int j = 0; j < kChunkSteps; ++j) {
-        const long v = c * (long)(kWave * kChunkSteps) + (long)lane * kChunkSteps + j;
-        ok[j] = c < nch && v < nvec;
-        if (ok[j]) {
-            rg[j] = ld_raw<DT, VEC>(g, v);
-            if (!PLAIN) {
-                rp[j] = ld_raw<DT, VEC>(sp, v);
-                rm[j] = ld_raw<DT, VEC>(sm, v);
-            }
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < kChunkSteps; ++j) {
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) p[j][i] = 0.f;
-        if (ok[j]) {
-            float hg[VEC], hp[VEC], hm[VEC];
-            unpack(rg[j], hg);
-            unpack_steer<DT, VEC, PLAIN>(rp[j], rm[j], hp, hm);
-#pragma unroll
-            for (int i = 0; i < VEC; ++i)
-                p[j][i] = PLAIN ? __builtin_amdgcn_exp2f(fmaf(hg[i], c_hi, nE))
-                                : __builtin_amdgcn_exp2f((float)(rec_y(hg[i], hp[i], hm[i], cc, bc) - dE));
-        }
-    }
-    if (c == 0 && head && lane == 0) p[0][0] = 0.f;  // the element before the row
-    if (c >= nch && lane < tailc) {
-        const long e = nvec * VEC + lane;
-        const float hg = ld_elem<DT>(g, e);
-        p[0][0] = PLAIN ? __builtin_amdgcn_exp2f(fmaf(hg, c_hi, nE))
-                        : __builtin_amdgcn_exp2f((float)(rec_y(hg, ld_steer<DT, PLAIN>(sp, e),
-                                                               ld_steer<DT, PLAIN>(sm, e), cc, bc) - dE));
-    }
-}
-
 // (E, s) mass of recovery chunk c, by one wave: sum over the chunk of 2^(y - E).  With a steering term the
 // exponent is formed in double (acc_add_rec); PLAIN (beta == 0) has only h_LLM * c to form and takes the
 // row pass's route, one fp32 fma per logit with the rounded scale c_hi, repaired to first order by the caller.
@@ -560,122 +512,197 @@ __device__ __forceinline__ Partial chunk_mass(const void* g, const void* sp, con
     return wave_combine(acc);
 }
 
-// Inverse-CDF draw for one sequence by one wave, from the chunk masses `tab` (LDS) of its
-// recovery row: a double-precision scan over the masses finds the chunk holding u*Z, and only
-// that chunk is read again to pick the token.  Returns log2 Z; writes the per-sequence outputs.
-// lane_terms: LDS for the terms of one lane.
-template <int DT, int VEC, bool GREEDY, bool PLAIN>
-__device__ __forceinline__ double sample_wave(const RecArgs& a, int b, int n, int lane, const Partial* tab,
-                                              const void* g, const void* sp, const void* sm, long nvec, int tailc,
-                                              int head, long nch, int NC, Best greedy_pick, float* lane_terms) {
-    const double us = (double)a.uniforms[(long)b * (a.kmax + 1) + a.kmax];
-    // each lane owns a contiguous run of `per` chunks
-    const int per = (NC + kWave - 1) / kWave;
-    const int lo = min(lane * per, NC), hi = min(lo + per, NC);
-    int Em = kEInit;
-    for (int c = lo; c < hi; ++c) Em = max(Em, tab[c].E);
-    const int Estar = wave_max_i32(Em);
-    double lsum = 0.0;
-    for (int c = lo; c < hi; ++c) lsum += ldexp((double)tab[c].s, tab[c].E - Estar);
-    const double incl = wave_incl_scan_f64(lsum);
-    const double total = wave_last_f64(incl);
-    if (GREEDY) {  // the token is already known; only the normaliser is needed
-        const double log2Z = (double)Estar + log2(total) + (PLAIN ? a.rho : 0.0) * (double)Estar;
-        const long tok = min(max(greedy_pick.idx, 0l), (long)a.V - 1);
-        if (lane == 0) {
-            a.accepted_len[b] = n;
-            a.next_token[b] = (int32_t)tok;
-            if (a.next_token_logprob) a.next_token_logprob[b] = (float)(kLn2 * (greedy_pick.v * a.c - log2Z));
-        }
-        return log2Z;
-    }
-    const double excl = wave_shift_up_f64(incl);
-    const double target = us * total;
+// log2 of the recovery row's normaliser from the base-2 scale and the sum of the chunk masses on it.  PLAIN sums were
+// formed with the rounded scale c_hi: an exponent comes back as y_hi = h * c_hi, the true one is y_hi * (1 + rho), and the
+// row's log2-sum moves by rho * E* to first order (see acc_add_f32).
+template <bool PLAIN>
+__device__ __forceinline__ double mass_log2(const RecArgs& a, int Estar, double total) {
+    return (double)Estar + log2(total) + (PLAIN ? a.rho : 0.0) * (double)Estar;
+}
 
-    int cfound = -1, clast = -1;
-    double cbase = 0.0, cum = excl;
-    for (int c = lo; c < hi; ++c) {
-        const double m = ldexp((double)tab[c].s, tab[c].E - Estar);
-        if (m > 0.0) clast = c;
-        const double cum2 = cum + m;
-        if (cfound < 0 && cum2 > target) {
-            cfound = c;
-            cbase = cum;
+// The chunk masses of a recovery row (`tab`, LDS) as one wave sees them: lane l owns a run of `per` consecutive chunks,
+// the first kHeld of them in registers, which is all of them up to V = 524288 bf16.
+struct ChunkScan {
+    static constexpr int kHeld = 4;
+    int lo, hi, Estar;
+    double held[kHeld];      // masses of chunks lo .. lo + 3 on the scale 2^Estar; 0 past the run
+    double incl, total;      // mass up to the end of this lane's run, and of the row
+    const Partial* tab;
+
+    __device__ __forceinline__ double mass(int c) const { return ldexp((double)tab[c].s, tab[c].E - Estar); }
+    __device__ __forceinline__ ChunkScan(const Partial* t, int NC, int lane) : tab(t) {
+        const int per = (NC + kWave - 1) / kWave;
+        lo = min(lane * per, NC);
+        hi = min(lo + per, NC);
+        Partial p[kHeld];
+        int Em = kEInit;
+#pragma unroll
+        for (int i = 0; i < kHeld; ++i) {
+            p[i] = lo + i < hi ? tab[lo + i] : Partial{kEInit, 0.f};
+            Em = max(Em, p[i].E);
         }
-        cum = cum2;
+        for (int c = lo + kHeld; c < hi; ++c) Em = max(Em, tab[c].E);
+        Estar = wave_max_i32(Em);
+        double sum = 0.0;
+#pragma unroll
+        for (int i = 0; i < kHeld; ++i) {
+            held[i] = ldexp((double)p[i].s, p[i].E - Estar);
+            sum += held[i];
+        }
+        for (int c = lo + kHeld; c < hi; ++c) sum += mass(c);
+        incl = wave_incl_scan_f64(sum);
+        total = wave_last_f64(incl);
     }
-    const unsigned long long fmask = __ballot(cfound >= 0);
-    int cstar;
-    double base;
+};
+
+constexpr int kDrawWaves = 4;  // a chunk is one vector of each of the first 4 waves' lanes
+
+// Inverse-CDF draw for one sequence by a workgroup, from the chunk masses `tab` (LDS) of its recovery row: a
+// double-precision scan over the masses finds the chunk holding u*Z, and only that chunk is read again to pick the token,
+// a vector a lane of the first four waves.  Every one of them scans the masses for itself, so that they meet only
+// once, over the sums of their quarters.  What bounds it is the chain of dependent steps, in which the chip is idle: by
+// one wave, with four vectors a lane and a logarithm of the token's term, the part behind the table took 3.6 us (8
+// sequences of V = 151936), now 2.7.  A step of one sequence 11.4 -> 11.1 us, of 8 20.3 -> 19.8, 512 steered rows of
+// V = 128256 67.0 -> 66.1, 4352 of them 501 -> 498.
+// Returns log2 Z to the first four waves; one lane writes the per-sequence outputs.
+template <int DT, int VEC, bool PLAIN>
+__device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, double us, int wave, int lane, const Partial* tab,
+                                             const void* g, const void* sp, const void* sm, long nvec, int tailc,
+                                             int head, long nch, int NC, double* sh_sum, int* sh_any) {
+    double incl_l = 0.0, base = 0.0, target = 0.0, dE = 0.0, sc = 0.0, ls = 0.0, log2Z = 0.0;
+    float p[VEC], hg[VEC], hp[VEC], hm[VEC];
+    long first = 0;          // vocabulary index of this lane's first logit, counted from the row as it is read
     bool take_last = false;  // the uniform is not below the total mass (u >= 1 or not a number)
-    if (fmask) {
-        const int L = first_lane(fmask);
-        cstar = __shfl(cfound, L, kWave);
-        base = __shfl(cbase, L, kWave);
-    } else {
-        cstar = max(wave_max_i32(clast), 0);
-        base = 0.0;
-        take_last = true;
-    }
-
-    // re-read that chunk with each lane holding consecutive logits: one scan over the lanes finds the lane that
-    // holds the token, one scan over that lane's logits the token.  The terms are
-    // taken relative to the chunk's own exponent reference, 2^(y - Ec), so that the logits that carry the
-    // chunk are normal fp32 numbers however far the chunk sits below the row's maximum; `sc` brings them
-    // to the scale of the chunk table in double, exactly.
-    const int Ec = tab[cstar].E;
-    const double dE = (double)Ec;
-    const double sc = ldexp(1.0, Ec - Estar);
-    // PLAIN sums were formed with the rounded scale c_hi: exponents come back as y_hi = h * c_hi, the true one
-    // is y_hi * (1 + rho), and the row's log2-sum moves by rho * E* to first order (see acc_add_f32)
-    const double fix = PLAIN ? a.rho : 0.0;
-    float p[kChunkSteps][VEC];
-    chunk_lane_terms<DT, VEC, PLAIN>(g, sp, sm, nvec, tailc, head, nch, cstar, lane, a.c, a.bc, a.c_hi, Ec, p);
-    double lsj[kChunkSteps];
+    if (wave < kDrawWaves) {
+        const ChunkScan cs(tab, NC, lane);
+        target = us * cs.total;
+        int cfound = -1, clast = -1;
+        double cbase = 0.0, cum = wave_shift_up_f64(cs.incl);
+        const auto meet = [&](int c, double m) {
+            if (m > 0.0) clast = c;
+            const double cum2 = cum + m;
+            if (cfound < 0 && cum2 > target) {
+                cfound = c;
+                cbase = cum;
+            }
+            cum = cum2;
+        };
 #pragma unroll
-    for (int j = 0; j < kChunkSteps; ++j) {
-        lsj[j] = 0.0;
+        for (int i = 0; i < ChunkScan::kHeld; ++i)
+            if (cs.lo + i < cs.hi) meet(cs.lo + i, cs.held[i]);
+        for (int c = cs.lo + ChunkScan::kHeld; c < cs.hi; ++c) meet(c, cs.mass(c));
+        const unsigned long long fmask = __ballot(cfound >= 0);
+        int cstar;
+        if (fmask) {
+            const int L = first_lane(fmask);
+            cstar = __builtin_amdgcn_readlane(cfound, L);
+            base = wave_readlane_f64(cbase, L);
+        } else {
+            cstar = max(wave_max_i32(clast), 0);
+            take_last = true;
+        }
+        // The terms are taken relative to the chunk's own exponent reference, 2^(y - Ec), so that the logits that carry
+        // the chunk are normal fp32 numbers however far the chunk sits below the row's maximum; `sc` brings them to the
+        // scale of the chunk table in double, exactly.
+        const int Ec = tab[cstar].E;
+        dE = (double)Ec;
+        const float nE = -(float)Ec;
+        sc = ldexp(1.0, Ec - cs.Estar);
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) lsj[j] += (double)p[j][i];
-    }
-    const double ls = (lsj[0] + lsj[1]) + (lsj[2] + lsj[3]);
-    const double incl_l = wave_incl_scan_f64(ls * sc);
-    const double start = wave_shift_up_f64(incl_l) + base;
-    const unsigned long long hmask = __ballot(!take_last && incl_l + base > target);
-    const unsigned long long pmask = __ballot(ls > 0.0);
-    // No lane reaches the target (rounding between the chunk table and the re-read, or take_last): the last
-    // logit of the chunk that still carries probability
-    const int L = hmask ? first_lane(hmask) : (pmask ? 63 - __clzll((long long)pmask) : 0);
-    constexpr int kOwn = kChunkSteps * VEC;  // consecutive logits a lane holds
-    if (lane == L) {
+        for (int i = 0; i < VEC; ++i) p[i] = 0.f;
+        const long v = (long)cstar * (kWave * kChunkSteps) + wave * kWave + lane;
+        const bool full = cstar < nch && v < nvec;
+        typename RawT<DT, VEC>::type rg{}, rp{}, rm{};
+        if (full) {
+            rg = ld_raw<DT, VEC>(g, v);
+            if (!PLAIN) {
+                rp = ld_raw<DT, VEC>(sp, v);
+                rm = ld_raw<DT, VEC>(sm, v);
+            }
+        }
+        log2Z = mass_log2<PLAIN>(a, cs.Estar, cs.total);  // while the chunk is on its way
+        int have = full ? VEC : 0;  // logits this lane holds
+        first = v * VEC;
+        unpack(rg, hg);
+        unpack_steer<DT, VEC, PLAIN>(rp, rm, hp, hm);
+        if (cstar >= nch) {         // the logits past the last full vector, one a lane
+            first = nvec * VEC + lane;
+            if (wave == 0 && lane < tailc) {
+                have = 1;
+                hg[0] = ld_elem<DT>(g, first);
+                hp[0] = ld_steer<DT, PLAIN>(sp, first);
+                hm[0] = ld_steer<DT, PLAIN>(sm, first);
+            }
+        }
 #pragma unroll
-        for (int j = 0; j < kChunkSteps; ++j) {
+        for (int i = 0; i < VEC; ++i)
+            if (i < have)
+                p[i] = PLAIN ? __builtin_amdgcn_exp2f(fmaf(hg[i], a.c_hi, nE))
+                             : __builtin_amdgcn_exp2f((float)(rec_y(hg[i], hp[i], hm[i], a.c, a.bc) - dE));
+        if (head && first == 0) p[0] = 0.f;  // the element before the row
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) lane_terms[j * VEC + i] = p[j][i];
+        for (int i = 0; i < VEC; i += 2) ls += (double)p[i] + (double)p[i + 1];
+        incl_l = wave_incl_scan_f64(ls * sc);
+        const unsigned long long pm = __ballot(ls > 0.0);
+        if (lane == 63) {
+            sh_sum[wave] = incl_l;
+            sh_any[wave] = pm != 0ull;
         }
     }
-    wave_lds_sync();
-    const float pl = lane < kOwn ? lane_terms[lane] : 0.f;
-    const double incl_i = wave_incl_scan_f64((double)pl * sc) + wave_readlane_f64(start, L);
-    const unsigned long long over = __ballot(hmask != 0ull && pl > 0.f && incl_i > target);
-    const unsigned long long pos = __ballot(pl > 0.f);
-    // the chunk's largest logit is within one unit of Ec, so a positive term always exists unless the row
-    // holds something that is not a number; keep the index valid then
-    const int i = over ? first_lane(over) : (pos ? 63 - __clzll((long long)pos) : 0);
-    const float ptok = pos ? __shfl(pl, i, kWave) : 1.f;
-    const long elem = cstar < nch ? ((long)cstar * kWave + L) * kOwn + i : nvec * VEC + L;
-    const long tok = min(max(elem - head, 0l), (long)a.V - 1);
-    // the chosen logit's exponent back from its term: 2^(y - Ec) is a normal fp32 number with one
-    // ulp of error, so log2 of it is good to ~2e-7 whatever the magnitude of y.  Lane 0 takes the logarithm
-    // of the total, lane 1 that of the term.
-    const double lg = log2(lane == 0 ? total : (double)ptok);
-    const double ytok_hi = dE + wave_readlane_f64(lg, 1);
-    const double ytok = ytok_hi + fix * ytok_hi;
-    const double log2Z = (double)Estar + wave_readlane_f64(lg, 0) + fix * (double)Estar;
+    __syncthreads();
+    if (wave >= kDrawWaves) return 0.0;
+    // The wave whose quarter reaches the target.  If none does (rounding between the chunk table and the re-read, or
+    // take_last): the last logit of the chunk that still carries probability.
+    int wsel = -1, wlast = 0;
+    double start = base;
+#pragma unroll
+    for (int w = 0; w < kDrawWaves; ++w) {
+        const double sum = sh_sum[w];
+        if (sh_any[w]) wlast = w;
+        if (wsel < 0) {
+            if (!take_last && start + sum > target) wsel = w; else start += sum;
+        }
+    }
+    const bool found = wsel >= 0;
+    if (wave == (found ? wsel : wlast)) {
+        const unsigned long long over = __ballot(found && start + incl_l > target), pm = __ballot(ls > 0.0);
+        const int L = over ? first_lane(over) : (pm ? 63 - __clzll((long long)pm) : 0);
+        double cum = wave_shift_up_f64(incl_l) + start;
+        if (lane == L) {
+            int at = 0;
+            bool done = false;
+            float tg = hg[0], tp = hp[0], tm = hm[0];
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                cum += (double)p[i] * sc;
+                if (!done && p[i] > 0.f) {  // the last of them stands if none reaches the target
+                    at = i;
+                    tg = hg[i];
+                    tp = hp[i];
+                    tm = hm[i];
+                    done = found && cum > target;
+                }
+            }
+            const double y = pm ? (PLAIN ? (double)tg * a.c : rec_y(tg, tp, tm, a.c, a.bc)) : dE;
+            a.accepted_len[b] = n;
+            // the chunk's largest logit is within one unit of Ec, so a positive term always exists unless the row holds
+            // something that is not a number; keep the index valid then
+            a.next_token[b] = (int32_t)min(max(first + at - head, 0l), (long)a.V - 1);
+            if (a.next_token_logprob) a.next_token_logprob[b] = (float)(kLn2 * (y - log2Z));
+        }
+    }
+    return log2Z;
+}
+
+// The same for greedy decoding, by one wave: the token is known, only the normaliser is needed.
+template <bool PLAIN>
+__device__ __forceinline__ double greedy_token(const RecArgs& a, int b, int n, int lane, const Partial* tab, int NC, Best pick) {
+    const ChunkScan cs(tab, NC, lane);
+    const double log2Z = mass_log2<PLAIN>(a, cs.Estar, cs.total);
     if (lane == 0) {
         a.accepted_len[b] = n;
-        a.next_token[b] = (int32_t)tok;
-        if (a.next_token_logprob) a.next_token_logprob[b] = (float)(kLn2 * (ytok - log2Z));
+        a.next_token[b] = (int32_t)min(max(pick.idx, 0l), (long)a.V - 1);
+        if (a.next_token_logprob) a.next_token_logprob[b] = (float)(kLn2 * (pick.v * a.c - log2Z));
     }
     return log2Z;
 }
@@ -854,7 +881,7 @@ __device__ __forceinline__ void write_logprobs(const void* g, const void* sp, co
 //   2b  wave 0: Eq. 7 on every position, first rejection by ballot
 //   3   all waves stream the three rows at the rejected (or bonus) position once, one (E, s)
 //       mass per 2048-logit chunk into LDS
-//   4   wave 0 draws the token
+//   4   the first four waves draw the token (greedy: wave 0)
 //   5   all waves write the log-prob row, where it is short enough (logprobs_in_recovery)
 // Only workgroup barriers separate the steps; nothing crosses workgroups.
 //
@@ -867,7 +894,8 @@ template <int DT, int VEC, bool GREEDY, bool PLAIN, int NT>
 __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     extern __shared__ double smem_d[];
     __shared__ int sh_n, sh_bad;
-    __shared__ float sh_terms[kChunkSteps * VEC];
+    __shared__ double sh_sum[kDrawWaves];
+    __shared__ int sh_any[kDrawWaves], sh_last;
     __shared__ double sh_best_v[NT / kWave];
     __shared__ long sh_best_i[NT / kWave];
     __shared__ double sh_log2z;
@@ -880,6 +908,7 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     double* lp = smem_d;                                            // [kmax][2] log P_LLM, log P_SLM^-
     Partial* tab = reinterpret_cast<Partial*>(smem_d + 2 * kmax);   // [NC] chunk masses
 
+    const double us = GREEDY ? 0.0 : (double)a.uniforms[(long)b * (kmax + 1) + kmax];  // read here, where nothing waits for it
     const int K = a.draft_len ? a.draft_len[b] : kmax;
     const int state = a.state ? a.state[b] : kInPlay;
     const bool bad_len = K < 0 || K > kmax || state == kFlagged;
@@ -937,17 +966,16 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
             sh_best_i[wave] = best.idx;
         }
     }
-    const bool rows = a.recovery_logprobs != nullptr;
     __syncthreads();
-    if (wave == 0) {
-        if (GREEDY) {
-            best.v = lane < NW ? sh_best_v[lane] : -__builtin_huge_val();
-            best.idx = lane < NW ? sh_best_i[lane] : 0x7FFFFFFFFFFFFFFFl;
-            wave_best(best);
-            if (best.idx <= (long)V) best.idx -= head;
-        }
-        if (S > 1) {  // deliver this part; only the last part to arrive goes on
-            Partial* gtab = a.chunk_tab + (long)b * a.NC;
+    if (GREEDY && wave == 0) {
+        best.v = lane < NW ? sh_best_v[lane] : -__builtin_huge_val();
+        best.idx = lane < NW ? sh_best_i[lane] : 0x7FFFFFFFFFFFFFFFl;
+        wave_best(best);
+        if (best.idx <= (long)V) best.idx -= head;
+    }
+    if (S > 1) {  // deliver this part; only the last part to arrive goes on
+        Partial* gtab = a.chunk_tab + (long)b * a.NC;
+        if (wave == 0) {
             for (int c = c0 + lane; c < c1; c += kWave) st_dev_partial(gtab + c, tab[c]);
             if (GREEDY && lane == 0) {
                 st_dev(reinterpret_cast<unsigned long long*>(a.best_v + (long)b * a.NC + part),
@@ -955,32 +983,36 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
                 st_dev(a.best_i + (long)b * a.NC + part, (int32_t)min(best.idx, (long)V));
             }
             wait_stores();  // this wave's deliveries have reached memory before it is counted
-            unsigned prev = 0;
             if (lane == 0)
-                prev = __hip_atomic_fetch_add(a.arrive + (long)b * kArriveStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (__builtin_amdgcn_readfirstlane((int)prev) != S - 1) return;
-            for (int c = lane; c < NC; c += kWave) tab[c] = ld_dev_partial(gtab + c);
-            if (GREEDY) {
-                best = Best{-__builtin_huge_val(), 0x7FFFFFFFFFFFFFFFl};
-                for (int i = lane; i < S; i += kWave) {
-                    const double v = __longlong_as_double((long long)ld_dev(
-                        reinterpret_cast<const unsigned long long*>(a.best_v + (long)b * a.NC + i)));
-                    const long idx = (long)ld_dev(a.best_i + (long)b * a.NC + i);
-                    if (v > best.v || (v == best.v && idx < best.idx)) best = Best{v, idx};
-                }
-                wave_best(best);
-            }
-            wave_lds_sync();
+                sh_last = __hip_atomic_fetch_add(a.arrive + (long)b * kArriveStride, 1u, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT) == (unsigned)S - 1u;
         }
+        __syncthreads();
+        if (!sh_last) return;
+        for (int c = tid; c < NC; c += NT) tab[c] = ld_dev_partial(gtab + c);
+        if (GREEDY && wave == 0) {
+            best = Best{-__builtin_huge_val(), 0x7FFFFFFFFFFFFFFFl};
+            for (int i = lane; i < S; i += kWave) {
+                const double v = __longlong_as_double((long long)ld_dev(
+                    reinterpret_cast<const unsigned long long*>(a.best_v + (long)b * a.NC + i)));
+                const long idx = (long)ld_dev(a.best_i + (long)b * a.NC + i);
+                if (v > best.v || (v == best.v && idx < best.idx)) best = Best{v, idx};
+            }
+            wave_best(best);
+        }
+        __syncthreads();
+    }
 
-        // ---- 4
-        const double log2Z = sample_wave<DT, VEC, GREEDY, PLAIN>(a, b, n, lane, tab, g, sp, sm, nvec, tailc, head, nch, NC, best, sh_terms);
-        if (lane == 0) {
+    // ---- 4
+    if (!GREEDY || wave == 0) {
+        const double log2Z = GREEDY ? greedy_token<PLAIN>(a, b, n, lane, tab, NC, best)
+                                    : draw_token<DT, VEC, PLAIN>(a, b, n, us, wave, lane, tab, g, sp, sm, nvec, tailc, head, nch, NC, sh_sum, sh_any);
+        if (tid == 0) {
             if (a.log2z) a.log2z[b] = log2Z;
             sh_log2z = log2Z;
         }
     }
-    if (!rows) return;
+    if (!a.recovery_logprobs) return;
 
     // ---- 5 (only with the row in one part)
     __syncthreads();

@@ -74,6 +74,30 @@ def test_recovery_launch_shapes(binding, oracle, dtype, batch, vocab, greedy, be
     parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
 
 
+# The draw reads its chunk by four waves, a vector a lane: a token at the first and last logit of a lane, a wave's quarter and
+# a chunk and among the logits past the last vector, each with a uniform in the middle of its interval; uniforms of 0, of 1 and not
+# a number, where the last token with positive probability (`keep` - 1) lies in an earlier quarter than the chunk's last.
+@pytest.mark.parametrize("beta", [0.0, 0.8])
+@pytest.mark.parametrize("dtype,vocab,keep", [("bf16", 2048, 2048), ("bf16", 2 * 2048 + 5, 2 * 2048 + 5), ("bf16", 4096, 4096 - 700),
+                                              ("f32", 1024, 300), ("f32", 3 * 1024 + 3, 3 * 1024 + 2)])
+def test_draw_at_the_edges_of_lanes_waves_and_chunks(binding, dtype, vocab, keep, beta):
+    vec = 8 if dtype == "bf16" else 4
+    gen = torch.Generator("cuda").manual_seed(vocab + keep)
+    row = torch.randn(3, vocab, generator=gen, device="cuda").mul_(0.25).to(W.torch_dtype(dtype))
+    row[0, keep:] = float("-inf")
+    h = row[0].double() + beta * (row[1].double() - row[2].double())
+    lp = torch.log_softmax(h, -1)
+    cdf = torch.cumsum(lp.exp(), -1)
+    edges = [e + d for e in (0, vec, 63 * vec, 64 * vec, 128 * vec, 192 * vec, 256 * vec, 512 * vec, keep) for d in (-1, 0)]
+    want = torch.tensor([e for e in edges if 0 <= e < keep] + [0, keep - 1, keep - 1], device="cuda")
+    u = (cdf[want] - 0.5 * lp[want].exp()).float()
+    u[-3:] = torch.tensor([0.0, 1.0, float("nan")])
+    rows = [r.expand(len(want), vocab).contiguous() for r in row]
+    out = binding.steer_rows(rows[0], rows[1], rows[2], u, beta=beta)
+    assert torch.equal(out["token"].long(), want)
+    assert (out["token_logprob"].double() - lp[want]).abs().max() <= 1e-5
+
+
 # Row-pass slices merged by 16 lanes: 1, 15 .. 17 and 64 slices (the most) of a row, with a remainder.
 @pytest.mark.parametrize("dtype,vocab", [("bf16", 2048), ("bf16", 15 * 2048 + 1), ("bf16", 16 * 2048), ("bf16", 17 * 2048 + 7),
                                          ("bf16", 64 * 2048), ("f32", 63 * 1024 + 1)])
