@@ -66,8 +66,8 @@ constexpr int kSplitMaxBatch = 128;  // workspace is reserved for shared recover
 //     spread gains (64 such sequences: 71.2 us a step in 19 parts, 69.9 in 3, 72.4 in 4 uneven ones).
 //     Not where one 16-wave workgroup takes the row in a round and the hand-over between parts, or the ratio test by
 //     fewer waves, costs more (us a step of 8 sequences, 16 waves -> spread): from 5 to 8 chunks (4 drafts, V = 6166
-//     11.4 -> 12.7, V = 14400 12.8 -> 13.4; 10 chunks 14.5 -> 14.1); up to 16 with no draft, where the counters cost a
-//     launch of their own (rows of V = 6166, 14400 or 32768 11.8 -> 14.8), or with more than 16 drafts (V = 20000, 20
+//     11.4 -> 12.7, V = 14400 12.8 -> 13.4; 10 chunks 14.5 -> 14.1); up to 16 with no draft, where parts cost a
+//     launch of their own (rows of V = 6166, 14400 or 32768 11.4 -> 14.5, the host's time), or with more than 16 drafts (V = 20000, 20
 //     drafts: 17.0 -> 17.4, 32 18.4 -> 18.9); a single part of 4 waves with more than 8 drafts (V = 2000, 12 drafts: 12.1 ->
 //     12.4).  Beyond 16 chunks up to 32 drafts (V = 151936: 24 drafts 27.1 -> 24.8, 32 30.8 -> 29.1; one sequence of V = 40000,
 //     48 drafts: 17.1 -> 17.9).
@@ -91,6 +91,23 @@ inline RecShape recovery_shape(int B, int NC, int kmax, int cus, bool split) {
         return {1024, (NC + parts - 1) / parts};
     }
     return {B <= cus ? 1024 : 512, NC};
+}
+
+// Whether rows without a draft that recovery_shape would cut into parts are taken whole by one 16-wave workgroup each.  Parts
+// cost a second launch, and of calls this small the host's 2.3 us for it and what it spends on the way are what bounds them: 14.3 us in
+// two launches whatever the size, 11.4 in one until the rate of one compute unit (or, with a steering term, its
+// arithmetic) takes over.  Us a call in two launches -> in one, by chunks of a row:
+//   - sampled rows, bf16: 32 rows of 64 chunks 14.2 -> 11.7, of 76 13.4 -> 13.3, of 80 14.2 -> 14.5; 64 of 75 (V = 151936) 14.6 ->
+//     13.4; 128 of 76 14.1 -> 14.0, of 80 14.3 -> 15.1; 8 of 80 13.6 -> 13.4, of 88 14.3 -> 14.2.
+//   - sampled rows, fp32: 8 of 112 14.2 -> 12.4, of 149 14.2 -> 15.2; 32 of 100 14.3 -> 12.9, of 112 14.2 -> 14.2; 64 of 100
+//     14.4 -> 13.6, of 112 14.4 -> 14.9; 128 of 92 14.3 -> 14.2, of 100 14.3 -> 14.8.
+//   - steered rows, bf16: 8 of 28 14.3 -> 12.9, of 30 14.3 -> 14.4; 32 of 25 14.3 -> 13.5, of 32 14.5 -> 15.6; 128 of 24
+//     14.3 -> 13.7, of 26 14.4 -> 14.7.
+//   - steered rows, fp32: 8 of 36 14.3 -> 12.5; 32 of 33 14.2 -> 13.6, of 36 14.2 -> 14.4; 128 of 28 14.4 -> 13.6, of 30 14.4 -> 14.6.
+inline bool rows_in_one_launch(int B, int NC, int dtype, bool plain, bool greedy) {
+    if (greedy) return false;
+    if (plain) return NC <= (dtype == SS_BF16 ? (B <= 8 ? 84 : 76) : B <= 8 ? 120 : B <= 64 ? 104 : 92);
+    return NC <= (dtype == SS_BF16 ? (B <= 8 ? 28 : 24) : B <= 32 ? 34 : 28);
 }
 
 // Whether the recovery launch writes the requested log-prob rows itself, its row in one part, or a launch of their own does.

@@ -428,13 +428,39 @@ __device__ __forceinline__ float ld_steer(const void* row, long e) {
     return PLAIN ? 0.f : ld_elem<DT>(row, e);
 }
 
+// The three rows of sequence b at position n as the recovery sweep reads them.
+template <int DT, int VEC>
+struct RecRow {
+    const void *g, *sp, *sm;
+    int head;        // 1: read from one element before the row
+    long nvec, nch;  // full vectors and the chunks they make
+    int tailc, NC;   // logits past them, and chunks with those: a.NC or one less
+    __device__ __forceinline__ RecRow(const RecArgs& a, int b, int n) {
+        const long off = (long)b * a.sb + (long)n * a.st;
+        g = row_ptr<DT>(a.G, off);
+        sp = row_ptr<DT>(a.recSp, off);
+        sm = row_ptr<DT>(a.recSm, off);
+        // Rows off 4-byte boundaries are read from one element before, if all three are and a vector is there to mask it in
+        head = a.V + 1 >= VEC ? odd_head<DT>(g, off) & odd_head<DT>(sp, off) & odd_head<DT>(sm, off) : 0;
+        g = row_ptr<DT>(g, -(long)head);
+        sp = row_ptr<DT>(sp, -(long)head);
+        sm = row_ptr<DT>(sm, -(long)head);
+        nvec = (a.V + head) / VEC;
+        tailc = a.V + head - (int)(nvec * VEC);
+        nch = (nvec + kWave * kChunkSteps - 1) / (kWave * kChunkSteps);
+        NC = (int)nch + (tailc ? 1 : 0);
+    }
+};
+
 // (E, s) mass of recovery chunk c, by one wave: sum over the chunk of 2^(y - E).  With a steering term the
 // exponent is formed in double (acc_add_rec); PLAIN (beta == 0) has only h_LLM * c to form and takes the
 // row pass's route, one fp32 fma per logit with the rounded scale c_hi, repaired to first order by the caller.
 template <int DT, int VEC, bool GREEDY, bool PLAIN>
-__device__ __forceinline__ Partial chunk_mass(const void* g, const void* sp, const void* sm, long nvec, int tailc,
-                                              int head, long nch, long c, int lane, double cc, double bc, double beta,
+__device__ __forceinline__ Partial chunk_mass(const RecRow<DT, VEC>& row, long c, int lane, double cc, double bc, double beta,
                                               float c_hi, Best& best) {
+    const void *g = row.g, *sp = row.sp, *sm = row.sm;
+    const long nvec = row.nvec, nch = row.nch;
+    const int tailc = row.tailc, head = row.head;
     const float cf = (float)cc, bcf = (float)bc;
     Acc acc{kEInit, 0.f};
     if (c < nch) {
@@ -512,6 +538,40 @@ __device__ __forceinline__ Partial chunk_mass(const void* g, const void* sp, con
     return wave_combine(acc);
 }
 
+// The masses of two full chunks of a row without steering, with the loads of both on their way at once.  Bound by latency: a wave with
+// one chunk has 4 loads in flight, and sixteen such waves draw 33 GB/s through a compute unit.  64 rows of V = 151936 bf16 in
+// one 16-wave workgroup each: 14.3 us a call with single chunks, 13.4 with pairs, V = 131072 13.3 -> 12.2.  Not with 8
+// waves, two workgroups to a unit (512 rows: 28.8 -> 29.3).
+template <int DT, int VEC, bool GREEDY>
+__device__ __forceinline__ void chunk_pair_mass(const RecRow<DT, VEC>& row, const long (&c)[2], int lane, float c_hi, Best& best, Partial (&out)[2]) {
+    typename RawT<DT, VEC>::type r[2][kChunkSteps];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int j = 0; j < kChunkSteps; ++j) r[q][j] = ld_raw<DT, VEC>(row.g, (c[q] * kChunkSteps + j) * kWave + lane);
+    if (row.head && c[0] == 0 && lane == 0) r[0][0] = set_first(r[0][0], kBf16NegInf);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        Acc acc{kEInit, 0.f};
+        float h[kChunkSteps * VEC];
+#pragma unroll
+        for (int j = 0; j < kChunkSteps; ++j) {
+            float hj[VEC];
+            unpack(r[q][j], hj);
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                h[j * VEC + i] = hj[i];
+                if (GREEDY && (double)hj[i] > best.v) {
+                    best.v = (double)hj[i];
+                    best.idx = ((c[q] * kChunkSteps + j) * kWave + lane) * VEC + i;
+                }
+            }
+        }
+        acc_add_f32<kChunkSteps * VEC>(acc, h, c_hi);
+        out[q] = wave_combine(acc);
+    }
+}
+
 // log2 of the recovery row's normaliser from the base-2 scale and the sum of the chunk masses on it.  PLAIN sums were
 // formed with the rounded scale c_hi: an exponent comes back as y_hi = h * c_hi, the true one is y_hi * (1 + rho), and the
 // row's log2-sum moves by rho * E* to first order (see acc_add_f32).
@@ -555,6 +615,7 @@ struct ChunkScan {
     }
 };
 
+constexpr int kMassWaves = 4;
 constexpr int kDrawWaves = 4;  // a chunk is one vector of each of the first 4 waves' lanes
 
 // Inverse-CDF draw for one sequence by a workgroup, from the chunk masses `tab` (LDS) of its recovery row: a
@@ -567,8 +628,10 @@ constexpr int kDrawWaves = 4;  // a chunk is one vector of each of the first 4 w
 // Returns log2 Z to the first four waves; one lane writes the per-sequence outputs.
 template <int DT, int VEC, bool PLAIN>
 __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, double us, int wave, int lane, const Partial* tab,
-                                             const void* g, const void* sp, const void* sm, long nvec, int tailc,
-                                             int head, long nch, int NC, double* sh_sum, int* sh_any) {
+                                             const RecRow<DT, VEC>& row, double* sh_sum, int* sh_any) {
+    const void *g = row.g, *sp = row.sp, *sm = row.sm;
+    const long nvec = row.nvec, nch = row.nch;
+    const int tailc = row.tailc, head = row.head, NC = row.NC;
     double incl_l = 0.0, base = 0.0, target = 0.0, dE = 0.0, sc = 0.0, ls = 0.0, log2Z = 0.0;
     float p[VEC], hg[VEC], hp[VEC], hm[VEC];
     long first = 0;          // vocabulary index of this lane's first logit, counted from the row as it is read
@@ -922,7 +985,7 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
         sh_n = settled ? state : 0;
     }
     __syncthreads();
-    if (!settled) ratio_test_block<DT, NT>(a, b, a.t_lo, Kt, lp, &sh_n, &sh_bad);
+    if (!settled && kmax > 0) ratio_test_block<DT, NT>(a, b, a.t_lo, Kt, lp, &sh_n, &sh_bad);
     const bool bad = sh_bad != 0;
     if (a.draft_logprobs && part == 0) {  // valid positions from LDS, padded slots 0, a flagged sequence NaN throughout
         const float nanv = __int_as_float(0x7FC00000);
@@ -940,23 +1003,23 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     const int n = sh_n;
 
     // ---- 3
-    const long off = (long)b * a.sb + (long)n * a.st;
-    const void* g = row_ptr<DT>(a.G, off);
-    const void* sp = row_ptr<DT>(a.recSp, off);
-    const void* sm = row_ptr<DT>(a.recSm, off);
-    // Rows off 4-byte boundaries are read from one element before, if all three are and a vector is there to mask it in
-    const int head = V + 1 >= VEC ? odd_head<DT>(g, off) & odd_head<DT>(sp, off) & odd_head<DT>(sm, off) : 0;
-    g = row_ptr<DT>(g, -(long)head);
-    sp = row_ptr<DT>(sp, -(long)head);
-    sm = row_ptr<DT>(sm, -(long)head);
-    const long nvec = (V + head) / VEC;
-    const int tailc = V + head - (int)(nvec * VEC);
-    const long nch = (nvec + kWave * kChunkSteps - 1) / (kWave * kChunkSteps);
-    const int NC = (int)nch + (tailc ? 1 : 0);  // a.NC or one less
+    const RecRow<DT, VEC> row(a, b, n);
     Best best{-__builtin_huge_val(), 0x7FFFFFFFFFFFFFFFl};
-    const int c0 = part * a.part_chunks, c1 = min(NC, c0 + a.part_chunks);
-    for (int c = c0 + wave; c < c1; c += NW) {
-        const Partial p = chunk_mass<DT, VEC, GREEDY, PLAIN>(g, sp, sm, nvec, tailc, head, nch, c, lane, a.c, a.bc, a.beta, a.c_hi, best);
+    const int c0 = part * a.part_chunks, c1 = min(row.NC, c0 + a.part_chunks);
+    int c = c0 + wave;
+    if (PLAIN && NT == 1024) {
+        for (; c + NW < c1 && (long)(c + NW + 1) * (kWave * kChunkSteps) <= row.nvec; c += 2 * NW) {
+            Partial p[2];
+            const long pair[2] = {c, c + NW};
+            chunk_pair_mass<DT, VEC, GREEDY>(row, pair, lane, a.c_hi, best, p);
+            if (lane == 0) {
+                tab[c] = p[0];
+                tab[c + NW] = p[1];
+            }
+        }
+    }
+    for (; c < c1; c += NW) {
+        const Partial p = chunk_mass<DT, VEC, GREEDY, PLAIN>(row, c, lane, a.c, a.bc, a.beta, a.c_hi, best);
         if (lane == 0) tab[c] = p;
     }
     if (GREEDY) {
@@ -971,7 +1034,7 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
         best.v = lane < NW ? sh_best_v[lane] : -__builtin_huge_val();
         best.idx = lane < NW ? sh_best_i[lane] : 0x7FFFFFFFFFFFFFFFl;
         wave_best(best);
-        if (best.idx <= (long)V) best.idx -= head;
+        if (best.idx <= (long)V) best.idx -= row.head;
     }
     if (S > 1) {  // deliver this part; only the last part to arrive goes on
         Partial* gtab = a.chunk_tab + (long)b * a.NC;
@@ -989,7 +1052,7 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
         }
         __syncthreads();
         if (!sh_last) return;
-        for (int c = tid; c < NC; c += NT) tab[c] = ld_dev_partial(gtab + c);
+        for (int c = tid; c < row.NC; c += NT) tab[c] = ld_dev_partial(gtab + c);
         if (GREEDY && wave == 0) {
             best = Best{-__builtin_huge_val(), 0x7FFFFFFFFFFFFFFFl};
             for (int i = lane; i < S; i += kWave) {
@@ -1005,8 +1068,8 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
 
     // ---- 4
     if (!GREEDY || wave == 0) {
-        const double log2Z = GREEDY ? greedy_token<PLAIN>(a, b, n, lane, tab, NC, best)
-                                    : draw_token<DT, VEC, PLAIN>(a, b, n, us, wave, lane, tab, g, sp, sm, nvec, tailc, head, nch, NC, sh_sum, sh_any);
+        const double log2Z = GREEDY ? greedy_token<PLAIN>(a, b, n, lane, tab, row.NC, best)
+                                    : draw_token<DT, VEC, PLAIN>(a, b, n, us, wave, lane, tab, row, sh_sum, sh_any);
         if (tid == 0) {
             if (a.log2z) a.log2z[b] = log2Z;
             sh_log2z = log2Z;
@@ -1016,12 +1079,75 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
 
     // ---- 5 (only with the row in one part)
     __syncthreads();
-    const long nv = V / VEC;
-    g = row_ptr<DT>(a.G, off);
-    sp = row_ptr<DT>(a.recSp, off);
-    sm = row_ptr<DT>(a.recSm, off);
+    const long nv = V / VEC, off = (long)b * a.sb + (long)n * a.st;
+    const void *g = row_ptr<DT>(a.G, off), *sp = row_ptr<DT>(a.recSp, off), *sm = row_ptr<DT>(a.recSm, off);
     for (long v = tid; v < nv || v == tid; v += NT * kLogprobUnroll)
         write_logprobs<DT, VEC, PLAIN>(g, sp, sm, a.recovery_logprobs + (long)b * V, V, v, NT, v == tid ? tid : kNoTail, a.c, a.bc, sh_log2z);
+}
+
+// ------------------------------------------------------------------ kernels: few rows without drafts
+
+// k_max == 0 and the row in several parts: with no row pass to clear arrival counters, the masses and the draw are two
+// launches instead of a fill, a sweep with a hand-over and a draw by the last part, whose chain of round trips was what
+// bound it (64 steered rows of V = 131072 17.1 -> 15.1 us a call, of V = 196608 22.0 -> 18.6; 101 sampled rows of V = 151552 17.9
+// -> 14.4, which is the host's time).
+//
+// The masses of kMassWaves chunks of a row, one a wave, and greedy candidates with them: as many workgroups as there are
+// chunks for, without a serial part, so that all loads are on their way at once.
+template <int DT, int VEC, bool GREEDY, bool PLAIN>
+__global__ __launch_bounds__(kMassWaves * kWave) void row_mass_kernel(const RecArgs a) {
+    const int b = (int)blockIdx.x / a.parts, part = (int)blockIdx.x - b * a.parts;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const RecRow<DT, VEC> row(a, b, 0);
+    const int c = part * kMassWaves + wave;
+    if (c >= row.NC) return;
+    Best best{-__builtin_huge_val(), 0x7FFFFFFFFFFFFFFFl};
+    const Partial p = chunk_mass<DT, VEC, GREEDY, PLAIN>(row, c, lane, a.c, a.bc, a.beta, a.c_hi, best);
+    const long at = (long)b * a.NC + c;
+    if (GREEDY) wave_best(best);
+    if (lane == 0) {
+        a.chunk_tab[at] = p;
+        if (GREEDY) {
+            a.best_v[at] = best.v;
+            a.best_i[at] = (int32_t)min(best.idx - (best.idx <= (long)a.V ? row.head : 0), (long)a.V);
+        }
+    }
+}
+
+// The token of a row from its masses.
+template <int DT, int VEC, bool GREEDY, bool PLAIN>
+__global__ __launch_bounds__(kDrawWaves * kWave) void row_draw_kernel(const RecArgs a) {
+    extern __shared__ double smem_d[];
+    __shared__ double sh_sum[kDrawWaves];
+    __shared__ int sh_any[kDrawWaves];
+    const int b = (int)blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    Partial* tab = reinterpret_cast<Partial*>(smem_d);
+    const double us = GREEDY ? 0.0 : (double)a.uniforms[b];
+    const RecRow<DT, VEC> row(a, b, 0);
+    const long at = (long)b * a.NC;
+    for (int c = tid; c < row.NC; c += kDrawWaves * kWave) tab[c] = a.chunk_tab[at + c];
+    Best best{-__builtin_huge_val(), 0x7FFFFFFFFFFFFFFFl};
+    if (GREEDY && wave == 0) {
+        for (int c = lane; c < row.NC; c += kWave) {
+            const double v = a.best_v[at + c];
+            const long idx = (long)a.best_i[at + c];
+            if (v > best.v || (v == best.v && idx < best.idx)) best = Best{v, idx};
+        }
+        wave_best(best);
+    }
+    if (a.draft_len && a.draft_len[b] != 0) {  // no draft can have a length
+        if (tid == 0) {
+            a.accepted_len[b] = -1;
+            a.next_token[b] = -1;
+            if (a.next_token_logprob) a.next_token_logprob[b] = __int_as_float(0x7FC00000);
+        }
+        return;
+    }
+    __syncthreads();
+    if (GREEDY && wave > 0) return;
+    const double log2Z = GREEDY ? greedy_token<PLAIN>(a, b, 0, lane, tab, row.NC, best)
+                                : draw_token<DT, VEC, PLAIN>(a, b, 0, us, wave, lane, tab, row, sh_sum, sh_any);
+    if (tid == 0 && a.log2z) a.log2z[b] = log2Z;
 }
 
 // ------------------------------------------------------------------ kernel: log-prob rows
@@ -1053,10 +1179,6 @@ __global__ __launch_bounds__(kLogprobThreads) void recovery_logprob_kernel(const
     write_logprobs<DT, VEC, PLAIN>(row_ptr<DT>(a.G, off), row_ptr<DT>(a.recSp, off), row_ptr<DT>(a.recSm, off),
                                    a.out + (long)b * a.V, a.V, (long)seg * (kLogprobThreads * kLogprobUnroll) + threadIdx.x,
                                    kLogprobThreads, seg == a.segs - 1 ? (int)threadIdx.x : kNoTail, a.c, a.bc, a.log2z[b]);
-}
-
-__global__ void zero_u32_kernel(uint32_t* p, int n) {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) p[(long)i * kArriveStride] = 0u;
 }
 
 // ------------------------------------------------------------------ host side
@@ -1115,6 +1237,7 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     const unsigned bases[3] = {elem_parity<DT>(ra.G), elem_parity<DT>(ra.recSp), elem_parity<DT>(ra.recSm)};
     ra.NC = chunks_per_row(V, VEC, odd_rows_possible(VEC, bases, B, kmax, ra.sb, ra.st));
     RecShape shape = recovery_shape(B, ra.NC, kmax, device_cu_count(), pl.split);
+    if (kmax == 0 && shape.part_chunks < ra.NC && rows_in_one_launch(B, ra.NC, DT, ra.plain != 0, ra.greedy != 0)) shape = RecShape{1024, ra.NC};
     const bool rows_inside = recovery_logprobs && logprobs_in_recovery(B, kmax, V, DT == SS_BF16 ? 2 : 4);
     if (rows_inside && shape.part_chunks < ra.NC) shape = RecShape{1024, ra.NC};
     ra.recovery_logprobs = rows_inside ? recovery_logprobs : nullptr;
@@ -1131,8 +1254,6 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     const size_t smem = (size_t)2 * kmax * sizeof(double) + (size_t)ra.NC * sizeof(Partial);
 
     mark(0);
-    if (kmax == 0 && split)  // no row pass to clear the arrival counters
-        hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(256), 0, stream, ra.arrive, B);
     for (int i = 0; i < windows; ++i) {
         const Window& w = wins[i];
         const bool listed = ragged || i > 0;
@@ -1164,8 +1285,18 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
          accept_recover_kernel<DT, VEC, false, true, 512>, accept_recover_kernel<DT, VEC, true, true, 512>},
         {accept_recover_kernel<DT, VEC, false, false, 1024>, accept_recover_kernel<DT, VEC, true, false, 1024>,
          accept_recover_kernel<DT, VEC, false, true, 1024>, accept_recover_kernel<DT, VEC, true, true, 1024>}};
-    hipLaunchKernelGGL(rec_kernels[shape.threads >> 9][(ra.greedy ? 1 : 0) | (ra.plain ? 2 : 0)], rec_grid,
-                       dim3((unsigned)shape.threads), smem, stream, ra);
+    const int kind = (ra.greedy ? 1 : 0) | (ra.plain ? 2 : 0);
+    if (kmax == 0 && split) {
+        static const RecKernel mass[4] = {row_mass_kernel<DT, VEC, false, false>, row_mass_kernel<DT, VEC, true, false>,
+                                          row_mass_kernel<DT, VEC, false, true>, row_mass_kernel<DT, VEC, true, true>};
+        static const RecKernel draw[4] = {row_draw_kernel<DT, VEC, false, false>, row_draw_kernel<DT, VEC, true, false>,
+                                          row_draw_kernel<DT, VEC, false, true>, row_draw_kernel<DT, VEC, true, true>};
+        ra.parts = (ra.NC + kMassWaves - 1) / kMassWaves;
+        hipLaunchKernelGGL(mass[kind], dim3((unsigned)(B * ra.parts)), dim3(kMassWaves * kWave), 0, stream, ra);
+        hipLaunchKernelGGL(draw[kind], dim3((unsigned)B), dim3(kDrawWaves * kWave), smem, stream, ra);
+    } else {
+        hipLaunchKernelGGL(rec_kernels[shape.threads >> 9][kind], rec_grid, dim3((unsigned)shape.threads), smem, stream, ra);
+    }
     if (recovery_logprobs && !rows_inside) {
         const long nvec = V / VEC, per = kLogprobThreads * kLogprobUnroll;
         const int segs = nvec > per ? (int)((nvec + per - 1) / per) : 1;

@@ -74,6 +74,29 @@ def test_recovery_launch_shapes(binding, oracle, dtype, batch, vocab, greedy, be
     parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
 
 
+# Up to 128 rows without a draft: one launch while a 16-wave workgroup takes its row fast enough, with pairs of chunks where there is no
+# steering term, else a launch for the chunk masses, four chunks a workgroup, and one for the draw.  Whole chunks and
+# workgroups, pairs with and without a chunk over, one logit more, odd rows, a row that has a length (flagged).
+@pytest.mark.parametrize("greedy,beta", [(False, 0.8), (True, 0.8), (False, 0.0), (True, 0.0)])
+@pytest.mark.parametrize("dtype,batch,vocab", [("bf16", 1, 20 * 2048), ("bf16", 3, 16 * 2048 + 1), ("bf16", 128, 17 * 2048 + 9),
+                                               ("bf16", 4, 32 * 2048), ("bf16", 9, 76 * 2048), ("bf16", 9, 77 * 2048 - 3),
+                                               ("f32", 9, 104 * 1024 + 1), ("bf16", 9, 33 * 2048 + 1),
+                                               ("f32", 2, 17 * 1024), ("f32", 37, 300 * 1024 + 3), ("bf16", 64, 75 * 2048 - 5)])
+def test_rows_without_drafts_in_one_launch_and_in_two(binding, oracle, dtype, batch, vocab, greedy, beta):
+    w = recipe("c4", dtype, batch=batch, k_max=0, vocab=vocab)
+    inp = W.generate(w, "cuda", seq_chunk=64)
+    inp["draft_len"] = torch.zeros(batch, dtype=torch.int32, device="cuda")
+    if batch > 2:
+        inp["draft_len"][batch - 2] = 1
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam,
+                               beta=beta, temperature=w.temperature, draft_len=inp["draft_len"], greedy=greedy,
+                               want_recovery_logprobs=batch < 64)
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=beta, temperature=w.temperature, greedy=greedy,
+                            want_recovery_logprobs=batch < 64)
+    parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
+    assert batch <= 2 or out["accepted_len"][batch - 2].item() == -1
+
+
 # The draw reads its chunk by four waves, a vector a lane: a token at the first and last logit of a lane, a wave's quarter and
 # a chunk and among the logits past the last vector, each with a uniform in the middle of its interval; uniforms of 0, of 1 and not
 # a number, where the last token with positive probability (`keep` - 1) lies in an earlier quarter than the chunk's last.
