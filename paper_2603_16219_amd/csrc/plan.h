@@ -104,8 +104,12 @@ inline RecShape recovery_shape(int B, int NC, int kmax, int cus, bool split) {
 //   - steered rows, bf16: 8 of 28 14.3 -> 12.9, of 30 14.3 -> 14.4; 32 of 25 14.3 -> 13.5, of 32 14.5 -> 15.6; 128 of 24
 //     14.3 -> 13.7, of 26 14.4 -> 14.7.
 //   - steered rows, fp32: 8 of 36 14.3 -> 12.5; 32 of 33 14.2 -> 13.6, of 36 14.2 -> 14.4; 128 of 28 14.4 -> 13.6, of 30 14.4 -> 14.6.
+//   - greedy, where every logit is compared too: bf16 rows without a steering term 8 of 52 13.4 -> 12.2, 128 of 52 14.2 -> 13.1,
+//     32 of 60 13.5 -> 13.8; fp32 64 of 92 14.3 -> 13.9, of 104 14.2 -> 14.8; steered bf16 128 of 20 14.3 -> 13.9, 32 of 22 14.2 ->
+//     14.5; steered fp32 as sampled.
 inline bool rows_in_one_launch(int B, int NC, int dtype, bool plain, bool greedy) {
-    if (greedy) return false;
+    if (greedy && plain) return NC <= (dtype == SS_BF16 ? 56 : B <= 64 ? 92 : 84);
+    if (greedy) return NC <= (dtype == SS_BF16 ? 20 : B <= 32 ? 32 : 28);
     if (plain) return NC <= (dtype == SS_BF16 ? (B <= 8 ? 84 : 76) : B <= 8 ? 120 : B <= 64 ? 104 : 92);
     return NC <= (dtype == SS_BF16 ? (B <= 8 ? 28 : 24) : B <= 32 ? 34 : 28);
 }

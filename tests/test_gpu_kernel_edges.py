@@ -97,6 +97,25 @@ def test_rows_without_drafts_in_one_launch_and_in_two(binding, oracle, dtype, ba
     assert batch <= 2 or out["accepted_len"][batch - 2].item() == -1
 
 
+# Greedy picks carry a lane's best logit as its place in a vector: the largest logit (twice, the first of them counts) at the first and
+# the last place of a vector, a lane's run, a wave and the row; the largest of a row whose logits are all negative zeros and zeros.
+@pytest.mark.parametrize("beta", [0.0, 0.8])
+@pytest.mark.parametrize("dtype,vocab", [("bf16", 9), ("bf16", 16 * 2048 + 1), ("bf16", 40 * 2048 + 7), ("f32", 70 * 1024 + 2)])
+def test_greedy_picks_the_first_of_the_largest(binding, dtype, vocab, beta):
+    vec = 8 if dtype == "bf16" else 4
+    edges = sorted({e % vocab for e in (0, 1, vec - 1, vec, 63 * vec, 64 * vec - 1, 256 * vec - 1, 256 * vec, 4096 * vec, vocab - 1)})
+    gen = torch.Generator("cuda").manual_seed(vocab)
+    rows = [torch.randn(len(edges) + 1, vocab, generator=gen, device="cuda").to(W.torch_dtype(dtype)) for _ in range(3)]
+    for i, e in enumerate(edges):
+        for r, v in zip(rows, (40.0, 1.0, 1.0)):
+            r[i, e], r[i, vocab - 1] = v, v
+    for r in rows:
+        r[-1] = -0.0
+        r[-1, vocab // 2:] = 0.0
+    out = binding.steer_rows(*rows, torch.zeros(len(edges) + 1, device="cuda"), beta=beta, greedy=True)
+    assert out["token"].tolist() == [*edges, 0]
+
+
 # The draw reads its chunk by four waves, a vector a lane: a token at the first and last logit of a lane, a wave's quarter and
 # a chunk and among the logits past the last vector, each with a uniform in the middle of its interval; uniforms of 0, of 1 and not
 # a number, where the last token with positive probability (`keep` - 1) lies in an earlier quarter than the chunk's last.
