@@ -270,25 +270,35 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
         for (int i = threadIdx.x; i <= a.B; i += kLseThreads) a.row_off[i] = lds_off[i];
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < a.zero_n; i += kLseThreads) a.zero_ptr[(long)i * kArriveStride] = 0u;
-    const int R = ragged ? off[a.B] : a.B * a.uniform_rows;
-    const long items = (long)R * 2 * a.NS;
+    const int R = ragged ? __builtin_amdgcn_readfirstlane(off[a.B]) : a.B * a.uniform_rows;
     const long slice_units = a.slice_vecs;
     constexpr long kGroup = (long)kWave * kUnroll;
 
-    for (long item = wave_global; item < items; item += waves_total) {
-        const int k = (int)(item % a.NS);
-        const long rx = item / a.NS;
-        const int x = (int)(rx & 1);
-        const int r = (int)(rx >> 1);
-        int b, t;
+    // The wave's items are waves_total apart: slice and row go on from those before without a division, and the sequence of
+    // a ragged batch's row is looked up from the last one on, 64 at a time.  Divisions in 64 bits and a search by halves, eight
+    // dependent reads of LDS, stood before the first load of every item, which counts where items are short: 16 sequences of up to
+    // 8 positions 26.2 -> 25.1 us a step, 40 ragged ones 31.6 -> 30.4, 300 131.5 -> 129.5, 256 of V = 128256 168.5 -> 166.6.
+    const unsigned NS = (unsigned)a.NS;
+    unsigned k_ = (unsigned)wave_global % NS, rx = (unsigned)wave_global / NS;
+    const unsigned dk = (unsigned)waves_total % NS, drx = (unsigned)waves_total / NS;
+    int b = 0, off_b = 0;  // ragged: the sequence of the row before, and its first row
+    for (; rx < 2u * (unsigned)R; k_ += dk, rx += drx) {
+        if (k_ >= NS) {
+            k_ -= NS;
+            if (++rx >= 2u * (unsigned)R) break;
+        }
+        const int k = (int)k_, x = (int)(rx & 1u), r = (int)(rx >> 1);
+        int t;
         if (ragged) {
-            int lo = 0, hi = a.B;  // largest b with off[b] <= r; off[B] = R > r
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (off[mid] <= r) lo = mid; else hi = mid;
+            for (;;) {  // the largest b with off[b] <= r; off[B] = R > r
+                const int o = off[min(b + 1 + lane, a.B)];
+                const int n = __popcll(__ballot(o <= r));
+                if (n == 0) break;
+                b += n;
+                off_b = __builtin_amdgcn_readlane(o, n - 1);
+                if (n < kWave) break;
             }
-            b = lo;
-            t = a.win.t_lo + (r - off[b]);
+            t = a.win.t_lo + (r - off_b);
         } else {
             b = r / a.uniform_rows;
             t = a.win.t_lo + (r - b * a.uniform_rows);
@@ -333,7 +343,7 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
             acc_add_f32<1>(acc, hj, a.c_hi);
         }
         const Partial p = wave_combine(acc);
-        if (lane == 0) a.partial[item] = p;
+        if (lane == 0) a.partial[(long)rx * a.NS + k] = p;
     }
 }
 

@@ -140,6 +140,23 @@ def test_draw_at_the_edges_of_lanes_waves_and_chunks(binding, dtype, vocab, keep
     assert (out["token_logprob"].double() - lp[want]).abs().max() <= 1e-5
 
 
+# A ragged batch's rows are looked up 64 sequences at a time from the last row's on: runs of 61 .. 129 sequences without a row
+# between two that have some, at the start and at the end; rows of one slice and of several, fewer of them than waves and more.
+@pytest.mark.parametrize("vocab", [40, 33 * 2048 + 3])
+@pytest.mark.parametrize("full", [(0, 63, 64, 126, 255), (64, 129, 258, 300), (130, 131), (0,), (299,)])
+def test_row_lookup_over_sequences_without_rows(binding, oracle, vocab, full):
+    w = recipe("c4", "bf16", batch=301, k_max=4, vocab=vocab)
+    inp = W.generate(w, "cuda", seq_chunk=64)
+    lens = torch.zeros(301, dtype=torch.int32, device="cuda")
+    for i, b in enumerate(full):
+        lens[b] = 1 + i % 4
+    inp["draft_len"] = lens
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam, beta=w.beta,
+                               temperature=w.temperature, draft_len=lens, want_draft_logprobs=True)
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, want_recovery_logprobs=False)
+    parity.compare(out, ora, inp["uniforms"], lens)
+
+
 # Row-pass slices merged by 16 lanes: 1, 15 .. 17 and 64 slices (the most) of a row, with a remainder.
 @pytest.mark.parametrize("dtype,vocab", [("bf16", 2048), ("bf16", 15 * 2048 + 1), ("bf16", 16 * 2048), ("bf16", 17 * 2048 + 7),
                                          ("bf16", 64 * 2048), ("f32", 63 * 1024 + 1)])
