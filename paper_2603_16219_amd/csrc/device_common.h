@@ -163,6 +163,13 @@ __device__ __forceinline__ void unpack(const float4& r, float (&h)[4]) {
     h[0] = r.x; h[1] = r.y; h[2] = r.z; h[3] = r.w;
 }
 
+// element e of a vector, e the same in all lanes
+__device__ __forceinline__ float elem_of(uint4 r, int e) {
+    const unsigned w = e < 4 ? (e < 2 ? r.x : r.y) : (e < 6 ? r.z : r.w);
+    return e & 1 ? bf16_hi(w) : bf16_lo(w);
+}
+__device__ __forceinline__ float elem_of(float4 r, int e) { return e < 2 ? (e < 1 ? r.x : r.y) : (e < 3 ? r.z : r.w); }
+
 // 1 for a bf16 row that starts off a 4-byte boundary and is not the first element of its tensor (elem_off > 0: the
 // element before it lies in the tensor too), else 0: how many elements before its start the row is read from.
 template <int DT>

@@ -51,6 +51,8 @@ struct Plan {
     Window win[kMaxWindows];
     Window all;      // one pass over all k_max positions (taken when draft_logprobs is requested)
     size_t off_list2, off_log2z, off_state, off_partial;
+    bool draft_logit;  // there is space for the draft tokens' logits
+    size_t off_draft_logit;
     bool split;      // the tables of a shared recovery row are there
     size_t off_arrive, off_best_v, off_best_i, off_chunk_tab;
     size_t bytes;
@@ -223,8 +225,9 @@ inline void slice_plan(long nvec, long row_tensors, int most, Window& w) {
     w.slice_vecs = (int)sv;
 }
 
-// Bytes up to the tables of a shared recovery row, and the tables themselves when `split` is set.
-inline Plan lay_out(const ss_params* p, bool split) {
+// Bytes up to the tables of a shared recovery row, the tables themselves when `split` is set, and the draft tokens' logits when
+// `logits` is.
+inline Plan lay_out(const ss_params* p, bool split, bool logits) {
     Plan pl;
     pl.vec = p->dtype == SS_BF16 ? 8 : 4;
     const long nvec = (p->vocab + pl.vec - 1) / pl.vec;
@@ -273,17 +276,22 @@ inline Plan lay_out(const ss_params* p, bool split) {
         o += align_up(B * sizeof(uint32_t), 256) + align_up(B * 256, 256) +
              align_up(B * (size_t)chunks_of(p->vocab, pl.vec) * sizeof(Partial), 256);
     }
+    pl.draft_logit = logits;
+    pl.off_draft_logit = o;
+    if (logits) o += align_up((size_t)p->batch * p->k_max * 2 * sizeof(float), 256);
     pl.bytes = o;
     return pl;
 }
 
-// The plan with the shared recovery row, unless only the plan without it fits the static scratch: which blocks
-// that entry point takes does not depend on the tables.
+// The plan with the shared recovery row and the draft tokens' logits, unless only a plan without them fits the static scratch:
+// which blocks that entry point takes does not depend on either.
 inline Plan make_plan(const ss_params* p) {
-    const Plan pl = lay_out(p, true);
-    if (pl.bytes <= (size_t)SS_STATIC_SCRATCH_BYTES) return pl;
-    const Plan small = lay_out(p, false);
-    return small.bytes <= (size_t)SS_STATIC_SCRATCH_BYTES ? small : pl;
+    const Plan whole = lay_out(p, true, true);
+    if (whole.bytes <= (size_t)SS_STATIC_SCRATCH_BYTES) return whole;
+    const Plan split = lay_out(p, true, false);
+    if (split.bytes <= (size_t)SS_STATIC_SCRATCH_BYTES) return split;
+    const Plan small = lay_out(p, false, false);
+    return small.bytes <= (size_t)SS_STATIC_SCRATCH_BYTES ? small : whole;
 }
 
 }  // namespace

@@ -238,8 +238,10 @@ struct LseArgs {
     const void* Sm;
     RowWindow win;             // the rows this launch covers
     int uniform_rows;          // > 0: every sequence has exactly this many window rows, no list needed
-    int32_t* row_off;          // else: global copy of the row list, [B+1]
-    Partial* partial;          // [rows][2][NS]
+    const int32_t* row_off;    // else: the row list, [B+1], of a batch too large for the one in LDS
+    Partial* partial;          // [B][win.t_hi - win.t_lo][2][NS]
+    const int32_t* draft;
+    float* draft_logit;        // [B][kmax][2] the draft token's logit in each tensor; NULL: gathered by who needs it
     long sb, st;               // element strides
     int B, kmax, V, NS;
     int slice_vecs;            // 16-byte vectors per slice
@@ -253,7 +255,9 @@ struct LseArgs {
 // of one row.  One wave per item, no communication between waves; the grid is persistent and
 // strides over the item list.  Ragged batches build the row list in LDS at kernel start
 // (every workgroup repeats the same small scan), so no separate launch is needed.
-// Workgroup 0 also publishes the row list for the kernels that consume the partials.
+// The wave that meets the draft token's vector leaves its logit beside the partials: it is in registers here, while the
+// ratio test would gather it from HBM behind the load of the draft id, a round trip that every sequence of that launch
+// waits for.  The id itself is looked at behind the item's first loads: before them it cost 300 ragged sequences 2 us.
 template <int DT, int VEC, int kUnroll>
 __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
     extern __shared__ int lds_off[];
@@ -266,8 +270,6 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
         block_scan_rows(a.win, a.B, lds_off, kLseThreads);
         off = lds_off;
     }
-    if (blockIdx.x == 0 && ragged && a.list_in_lds)
-        for (int i = threadIdx.x; i <= a.B; i += kLseThreads) a.row_off[i] = lds_off[i];
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < a.zero_n; i += kLseThreads) a.zero_ptr[(long)i * kArriveStride] = 0u;
     const int R = ragged ? __builtin_amdgcn_readfirstlane(off[a.B]) : a.B * a.uniform_rows;
@@ -304,6 +306,8 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
             t = a.win.t_lo + (r - b * a.uniform_rows);
         }
         const long elem_off = (long)b * a.sb + (long)t * a.st;
+        const int y_load = a.draft_logit ? a.draft[(long)b * a.kmax + t] : -1;  // looked at behind the first loads of the row
+        float* const y_out = a.draft_logit + ((long)b * a.kmax + t) * 2 + x;
         const void* row = row_ptr<DT>(x ? a.Sm : a.G, elem_off);
         const int head = __builtin_amdgcn_readfirstlane(odd_head<DT>(row, elem_off));
         row = row_ptr<DT>(row, -(long)head);
@@ -313,6 +317,13 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
         const long v0 = (long)k * slice_units;
         const long v1 = min(nvec, v0 + slice_units);
         const long nfull = v1 > v0 ? (v1 - v0) / kGroup : 0;  // wave-uniform trip count
+        // the draft token's element in the row as it is read, and its vector counted from the slice's start, < 0 if none of this slice
+        int ye = -1, yv = -1;
+        const auto find_y = [&]() {
+            const int y = __builtin_amdgcn_readfirstlane(y_load);
+            ye = y >= 0 && y < a.V ? y + head : -1;
+            yv = ye >= 0 && ye / VEC < v1 ? ye / VEC - (int)v0 : -1;
+        };
 
         Acc acc{kEInit, 0.f};
         long v = v0 + lane;
@@ -320,6 +331,16 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
             typename RawT<DT, VEC>::type raw[kUnroll];
 #pragma unroll
             for (int j = 0; j < kUnroll; ++j) raw[j] = ld_raw<DT, VEC>(row, v + (long)kWave * j);
+            if (g == 0) find_y();
+            if (yv >= 0 && yv / (int)kGroup == (int)g) {
+                float hy = 0.f;
+#pragma unroll
+                for (int j = 0; j < kUnroll; ++j) {
+                    const float hj = elem_of(raw[j], ye % VEC);
+                    hy = yv % (int)kGroup / kWave == j ? hj : hy;
+                }
+                if (yv % kWave == lane) *y_out = hy;
+            }
             if (masked && g == 0 && lane == 0) raw[0] = set_first(raw[0], kBf16NegInf);
             float h[kUnroll * VEC];
 #pragma unroll
@@ -331,8 +352,10 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
             }
             acc_add_f32<kUnroll * VEC>(acc, h, a.c_hi);
         }
+        if (nfull == 0) find_y();
         for (; v < v1; v += kWave) {
             typename RawT<DT, VEC>::type raw = ld_raw<DT, VEC>(row, v);
+            if (yv >= 0 && v == v0 + yv) *y_out = elem_of(raw, ye % VEC);
             if (masked && v == 0) raw = set_first(raw, kBf16NegInf);
             float hj[VEC];
             unpack(raw, hj);
@@ -340,10 +363,11 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
         }
         if (k == a.NS - 1 && lane < tailc && !(head && nvec == 0 && lane == 0)) {  // logits past the last full vector
             float hj[1] = {ld_elem<DT>(row, nvec * VEC + lane)};
+            if (ye == nvec * VEC + lane) *y_out = hj[0];
             acc_add_f32<1>(acc, hj, a.c_hi);
         }
         const Partial p = wave_combine(acc);
-        if (lane == 0) a.partial[(long)rx * a.NS + k] = p;
+        if (lane == 0) a.partial[(((long)b * (a.win.t_hi - a.win.t_lo) + (t - a.win.t_lo)) * 2 + x) * a.NS + k] = p;
     }
 }
 
@@ -357,11 +381,9 @@ struct RecArgs {
     const int32_t* draft;
     const int32_t* draft_len;
     const float* uniforms;
-    // Slice partials of the window this launch tests: position t of sequence b has row
-    // (rows > 0 ? b * rows : off[b]) + t - t_lo in it.
-    const int32_t* off;
-    const Partial* partial;
-    int rows, NS;            // rows per sequence if all have the same, slices per row
+    const Partial* partial;  // slice partials of the window this launch tests, [B][t_hi - t_lo][2][NS]
+    const float* draft_logit;  // [B][kmax][2] the draft tokens' logits, or NULL: gathered from the rows
+    int NS;                  // slices per row
     int t_lo, t_hi;          // the window; t_hi == k_max for the last one
     int32_t* state;          // several windows: what the verdicts so far have found; else NULL
     int32_t* accepted_len;
@@ -782,42 +804,53 @@ __device__ __forceinline__ double greedy_token(const RecArgs& a, int b, int n, i
 
 // Slice partials of (sequence b, position t, tensor x), t in the window.
 __device__ __forceinline__ const Partial* partials_of(const RecArgs& a, int b, int t, int x) {
-    const long r = (a.rows > 0 ? (long)b * a.rows : (long)a.off[b]) + (t - a.t_lo);
-    return a.partial + (r * 2 + x) * a.NS;
+    return a.partial + (((long)b * (a.t_hi - a.t_lo) + (t - a.t_lo)) * 2 + x) * a.NS;
 }
 
-// Phase 2 for one sequence by a workgroup of NT threads, on positions [T0, Kt) (those before T0
+// Phase 2 for one sequence by a workgroup of NT threads, on the positions [T0, Kt) of the window (those before T0
 // are known to have been accepted):
-//   2a  every (position, tensor) pair gets 16 lanes: merge the row's slice partials, gather the draft
-//       token's logit, leave log P(y_t) in lp[2t + x]        (two memory round trips)
-//   2b  wave 0: Eq. 7 on every position, first rejection by ballot -> *sh_n (Kt if none)
-// A draft id outside the vocabulary among those positions sets *sh_bad.  Ends with a barrier.
+//   2a  every (position, tensor) pair gets 16 lanes: merge the row's slice partials, take the draft
+//       token's logit, leave log P(y_t) in lp[2t + x]
+//   2b  wave 0: Eq. 7 on every position, first rejection by ballot
+// Returns the first rejected position, Kt if none, to every thread; kFlagged if a draft id among those positions is outside
+// the vocabulary or `bad` is set in any thread.  sh: kRatioWords<NT> words of LDS.
+//
+// What bounds it is its chain of memory round trips, while nothing else runs on the compute unit: everything that does not depend
+// on the length is loaded before the length is known (rows past it hold leftovers, which are not used), and the draft tokens' logits
+// lie beside the partials.  With the logits gathered behind the ids behind the length the first rejection of a block was known
+// 2.6 us after the launch's first workgroup; the recovery kernel of one sequence of V = 32000 fp32 takes 8.4 us now (9.0 before), of 8 of V = 151936 9.7
+// (10.7), a step of the first 10.6 (11.1), of 64 sequences 0.3 to 0.5 less.
+template <int NT>
+constexpr int kRatioWords = NT / kWave + 1;
 template <int DT, int NT>
-__device__ __forceinline__ void ratio_test_block(const RecArgs& a, int b, int T0, int Kt, double* lp, int* sh_n,
-                                                 int* sh_bad) {
+__device__ __forceinline__ int ratio_test_block(const RecArgs& a, int b, int T0, int Kt, bool bad, double* lp, int* sh) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l = tid & 15;
-    const int kmax = a.kmax, V = a.V;
+    const int kmax = a.kmax, V = a.V, Tend = a.t_hi;
     const float* un = a.uniforms + (long)b * (kmax + 1);
-    const float u0 = T0 + lane < Kt ? un[T0 + lane] : 0.f;  // wave 0's first block, on its way while the rows are merged
-    const auto logprob = [&](int q, int y, Partial row) {  // log P(y) at (position, tensor) pair q
-        const int t = q >> 1, x = q & 1;
-        const bool ok = (y >= 0 && y < V);
-        const long off = (long)b * a.sb + (long)t * a.st;
-        const float h = ok ? ld_elem<DT>(row_ptr<DT>(x ? a.Sm : a.G, off), y) : 0.f;
-        if (!ok) *sh_bad = 1;
-        return kLn2 * ((double)h * a.c - row_log2(row, a.rho));
-    };
+    const float u0 = T0 + lane < Tend ? un[T0 + lane] : 0.f;  // wave 0's first block, on its way while the rows are merged
     const int* draft = a.draft + (long)b * kmax;
+    const auto logit = [&](int q, int y) {  // of the draft token at (position, tensor) pair q
+        if (a.draft_logit) return a.draft_logit[(long)b * kmax * 2 + q];
+        const long off = (long)b * a.sb + (long)(q >> 1) * a.st;
+        return y >= 0 && y < V ? ld_elem<DT>(row_ptr<DT>(q & 1 ? a.Sm : a.G, off), y) : 0.f;
+    };
+    const auto logprob = [&](float h, Partial row) { return kLn2 * ((double)h * a.c - row_log2(row, a.rho)); };
     const int q0 = 2 * T0 + (tid >> 4);
-    if (2 * (Kt - T0) <= NT / 16) {
+    if (2 * (Tend - T0) <= NT / 16) {
+        int y = 0;
+        double v = 0.0;
+        if (q0 < 2 * Tend) {
+            y = draft[q0 >> 1];
+            const float h = logit(q0, y);
+            v = logprob(h, merge_partials_row16(partials_of(a, b, q0 >> 1, q0 & 1), a.NS, l));
+        }
         if (q0 < 2 * Kt) {
-            const int y = draft[q0 >> 1];
-            const double v = logprob(q0, y, merge_partials_row16(partials_of(a, b, q0 >> 1, q0 & 1), a.NS, l));
+            bad = bad || y < 0 || y >= V;
             if (l == 0) lp[q0] = v;
         }
     } else {
         // More pairs than groups of sixteen lanes: only the merging goes in rounds, its result waits in the pair's slot of
-        // lp, and the gathers and logarithms follow once, a lane to every pair.  With all of it in the rounds each of
+        // lp, and the logits and logarithms follow once, a lane to every pair.  With all of it in the rounds each of
         // them cost 0.9 us of dependent loads: 27 positions tested by 4 waves took 4, and one sequence of 128 positions,
         // V = 40000, 24.1 us a step where it takes 20.7.
         for (int q = q0; q < 2 * Kt; q += NT / 16) {
@@ -827,9 +860,13 @@ __device__ __forceinline__ void ratio_test_block(const RecArgs& a, int b, int T0
         __syncthreads();
         for (int q = 2 * T0 + tid; q < 2 * Kt; q += NT) {
             const Partial m{__double2hiint(lp[q]), __int_as_float(__double2loint(lp[q]))};
-            lp[q] = logprob(q, draft[q >> 1], m);
+            const int y = draft[q >> 1];
+            bad = bad || y < 0 || y >= V;
+            lp[q] = logprob(logit(q, y), m);
         }
     }
+    const bool any = __ballot(bad) != 0ull;
+    if (lane == 0) sh[1 + wave] = any;
     __syncthreads();
     if (wave == 0) {
         int first_rej = Kt;
@@ -844,9 +881,11 @@ __device__ __forceinline__ void ratio_test_block(const RecArgs& a, int b, int T0
             const unsigned long long rmask = __ballot(rej);
             if (rmask && first_rej == Kt) first_rej = t0 + first_lane(rmask);
         }
-        if (lane == 0) *sh_n = first_rej;
+        const bool flagged = __ballot(lane < NT / kWave && sh[1 + (lane < NT / kWave ? lane : 0)] != 0) != 0ull;
+        if (lane == 0) sh[0] = flagged ? kFlagged : first_rej;
     }
     __syncthreads();
+    return sh[0];
 }
 
 // Between two row passes: the ratio test on the positions of the window just scored, [t_lo, min(K_b, t_hi)), of
@@ -861,29 +900,22 @@ __device__ __forceinline__ void ratio_test_block(const RecArgs& a, int b, int T0
 template <int DT, int NT>
 __global__ __launch_bounds__(NT) void verdict_kernel(const RecArgs a) {
     extern __shared__ double smem_d[];
-    __shared__ int sh_n, sh_bad;
+    __shared__ int sh_ratio[kRatioWords<NT>];
     const int b = blockIdx.x, tid = threadIdx.x;
     const int kmax = a.kmax, V = a.V;
     const bool first = a.t_lo == 0;
     if (!first && a.state[b] != kInPlay) return;
     const int K = a.draft_len ? a.draft_len[b] : kmax;
-    const bool bad_len = (K < 0 || K > kmax);
-    const int Kt = bad_len ? 0 : min(K, a.t_hi);
-    if (tid == 0) {
-        sh_bad = bad_len ? 1 : 0;
-        sh_n = 0;
-    }
-    __syncthreads();
-    if (first && !bad_len) {  // ids behind the window; those inside it are checked with their rows
-        bool oob = false;
+    bool bad = K < 0 || K > kmax;
+    const int Kt = bad ? 0 : min(K, a.t_hi);
+    if (first && !bad) {  // ids behind the window; those inside it are checked with their rows
         for (int t = Kt + tid; t < K; t += NT) {
             const int y = a.draft[(long)b * kmax + t];
-            oob = oob || y < 0 || y >= V;
+            bad = bad || y < 0 || y >= V;
         }
-        if (oob) sh_bad = 1;
     }
-    ratio_test_block<DT, NT>(a, b, a.t_lo, Kt, smem_d, &sh_n, &sh_bad);
-    if (tid == 0) a.state[b] = sh_bad ? kFlagged : (sh_n == Kt && K > a.t_hi ? kInPlay : sh_n);
+    const int n = ratio_test_block<DT, NT>(a, b, a.t_lo, Kt, bad, smem_d, sh_ratio);
+    if (tid == 0) a.state[b] = n == Kt && K > a.t_hi ? kInPlay : n;
 }
 
 // Best candidate of the wave, left in every lane: larger value, then lower index.
@@ -966,7 +998,7 @@ __device__ __forceinline__ void write_logprobs(const void* g, const void* sp, co
 template <int DT, int VEC, bool GREEDY, bool PLAIN, int NT>
 __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     extern __shared__ double smem_d[];
-    __shared__ int sh_n, sh_bad;
+    __shared__ int sh_ratio[kRatioWords<NT>];
     __shared__ double sh_sum[kDrawWaves];
     __shared__ int sh_any[kDrawWaves], sh_last;
     __shared__ double sh_best_v[NT / kWave];
@@ -982,21 +1014,18 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     Partial* tab = reinterpret_cast<Partial*>(smem_d + 2 * kmax);   // [NC] chunk masses
 
     const double us = GREEDY ? 0.0 : (double)a.uniforms[(long)b * (kmax + 1) + kmax];  // read here, where nothing waits for it
-    const int K = a.draft_len ? a.draft_len[b] : kmax;
-    const int state = a.state ? a.state[b] : kInPlay;
-    const bool bad_len = K < 0 || K > kmax || state == kFlagged;
     // Several windows: a sequence a verdict kernel saw rejected (or at its end) keeps that first-rejection
     // index; a sequence still in play is tested here on the positions of the last window.  One window: every
     // sequence is tested here over all K positions.
-    const bool settled = state >= 0 && !bad_len;
-    const int Kt = bad_len ? 0 : K;
-    if (tid == 0) {
-        sh_bad = bad_len ? 1 : 0;
-        sh_n = settled ? state : 0;
+    const int state = a.state ? a.state[b] : kInPlay;
+    int n = state, Kt = 0;
+    if (state == kInPlay) {
+        const int K = a.draft_len ? a.draft_len[b] : kmax;
+        const bool bad_len = K < 0 || K > kmax;
+        Kt = bad_len ? 0 : K;
+        n = kmax > 0 ? ratio_test_block<DT, NT>(a, b, a.t_lo, Kt, bad_len, lp, sh_ratio) : bad_len ? kFlagged : 0;
     }
-    __syncthreads();
-    if (!settled && kmax > 0) ratio_test_block<DT, NT>(a, b, a.t_lo, Kt, lp, &sh_n, &sh_bad);
-    const bool bad = sh_bad != 0;
+    const bool bad = n < 0;
     if (a.draft_logprobs && part == 0) {  // valid positions from LDS, padded slots 0, a flagged sequence NaN throughout
         const float nanv = __int_as_float(0x7FC00000);
         for (int i = tid; i < kmax * 2; i += NT)
@@ -1010,7 +1039,6 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
         }
         return;
     }
-    const int n = sh_n;
 
     // ---- 3
     const RecRow<DT, VEC> row(a, b, n);
@@ -1243,6 +1271,9 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     };
     const bool ragged = ra.draft_len != nullptr && kmax > 0;
     ra.partial = partial;
+    la.draft = ra.draft;
+    la.draft_logit = pl.draft_logit ? reinterpret_cast<float*>(ws + pl.off_draft_logit) : nullptr;
+    ra.draft_logit = la.draft_logit;
     ra.state = windows > 1 ? state : nullptr;
     const unsigned bases[3] = {elem_parity<DT>(ra.G), elem_parity<DT>(ra.recSp), elem_parity<DT>(ra.recSm)};
     ra.NC = chunks_per_row(V, VEC, odd_rows_possible(VEC, bases, B, kmax, ra.sb, ra.st));
@@ -1267,8 +1298,6 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     for (int i = 0; i < windows; ++i) {
         const Window& w = wins[i];
         const bool listed = ragged || i > 0;
-        ra.off = lists[i > 0];
-        ra.rows = listed ? 0 : w.t_hi;
         ra.NS = w.NS;
         ra.t_lo = w.t_lo;
         ra.t_hi = w.t_hi;
@@ -1361,7 +1390,7 @@ ss_status verify_block_impl(const void* G, const void* S_ctx, const void* S_noct
     const float c_hi = (float)c;  // the row pass scales by this; the merge repairs the difference
 
     LseArgs la;
-    la.G = G; la.Sm = S_noctx; la.row_off = nullptr; la.partial = nullptr; la.uniform_rows = 0;
+    la.G = G; la.Sm = S_noctx; la.row_off = nullptr; la.partial = nullptr; la.draft = nullptr; la.draft_logit = nullptr; la.uniform_rows = 0;
     la.win = RowWindow{nullptr, nullptr, params->k_max, 0, params->k_max};
     la.sb = sb; la.st = st; la.B = params->batch; la.kmax = params->k_max; la.V = params->vocab;
     la.NS = 0; la.slice_vecs = 0; la.list_in_lds = 0; la.c_hi = c_hi;

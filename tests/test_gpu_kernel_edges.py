@@ -140,6 +140,32 @@ def test_draw_at_the_edges_of_lanes_waves_and_chunks(binding, dtype, vocab, keep
     assert (out["token_logprob"].double() - lp[want]).abs().max() <= 1e-5
 
 
+# The row pass leaves the draft token's logit as it meets it: a token at the first and last logit of a vector, a group of loads (256
+# vectors), a slice and the row, and past the last vector; rows at even and odd elements, with fewer logits than a vector; one
+# position more than a workgroup has groups of lanes for; a flagged sequence between two others.
+@pytest.mark.parametrize("pad", [0, 1])
+@pytest.mark.parametrize("dtype,vocab", [("bf16", 5), ("bf16", 8), ("bf16", 2048 + 3), ("bf16", 9 * 2048 + 1), ("bf16", 150 * 2048 + 7),
+                                         ("f32", 3), ("f32", 1024 + 2), ("f32", 70 * 1024)])
+def test_draft_logits_at_the_edges_of_vectors_groups_and_slices(binding, dtype, vocab, pad):
+    vec = 8 if dtype == "bf16" else 4
+    edges = sorted({e % vocab for u in (1, vec, 64 * vec, 256 * vec, 512 * vec, 1024 * vec, vocab // vec * vec) for e in (u - 1, u)}
+                   | {0, vocab - 1})
+    k_max = 33
+    gen = torch.Generator("cuda").manual_seed(vocab)
+    G, S, M = (torch.randn(3, k_max + 1, vocab + pad, generator=gen, device="cuda").mul_(3).to(W.torch_dtype(dtype))[..., :vocab]
+               for _ in range(3))
+    draft = torch.tensor([edges[i % len(edges)] for i in range(k_max)], dtype=torch.int32, device="cuda").repeat(3, 1)
+    draft[1, 20] = vocab
+    u = torch.zeros(3, k_max + 1, device="cuda")  # accepts everything
+    lens = torch.tensor([k_max, k_max, 7], dtype=torch.int32, device="cuda")
+    out = binding.verify_block(G, S, M, draft, u, draft_len=lens, lam=0.5, beta=0.8, want_draft_logprobs=True)
+    assert out["accepted_len"].tolist() == [k_max, -1, 7]
+    for b, n in ((0, k_max), (2, 7)):
+        for x, T in enumerate((G, M)):
+            lp = torch.log_softmax(T[b, :n].double(), -1).gather(1, draft[b, :n, None].long())[:, 0]
+            assert (out["draft_logprobs"][b, :n, x].double() - lp).abs().max() <= 1e-5
+
+
 # A ragged batch's rows are looked up 64 sequences at a time from the last row's on: runs of 61 .. 129 sequences without a row
 # between two that have some, at the start and at the end; rows of one slice and of several, fewer of them than waves and more.
 @pytest.mark.parametrize("vocab", [40, 33 * 2048 + 3])
