@@ -99,6 +99,18 @@ __device__ __forceinline__ double wave_incl_scan_f64(double x) {
     return x;
 }
 
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp_i32_or_zero(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xF, false); }
+__device__ __forceinline__ int wave_incl_scan_i32(int x) {
+    x += dpp_i32_or_zero<kDppRowShr1, 0xF>(x);
+    x += dpp_i32_or_zero<kDppRowShr2, 0xF>(x);
+    x += dpp_i32_or_zero<kDppRowShr4, 0xF>(x);
+    x += dpp_i32_or_zero<kDppRowShr8, 0xF>(x);
+    x += dpp_i32_or_zero<kDppRowBcast15, 0xA>(x);
+    x += dpp_i32_or_zero<kDppRowBcast31, 0xC>(x);
+    return x;
+}
+
 // Exclusive companion of an inclusive scan result (lane 0 gets 0) and the wave total.
 __device__ __forceinline__ double wave_shift_up_f64(double incl) { return dpp_f64_or_zero<kDppWaveShr1, 0xF>(incl); }
 __device__ __forceinline__ double wave_readlane_f64(double x, int lane) {  // `lane` wave-uniform

@@ -213,6 +213,10 @@ __device__ void topk_by_insertion(const TopArgs& a, const void* g, const void* s
 //      candidate buffer in LDS (typically 100-200 entries);
 //   D  each candidate counts the candidates that precede it in the payload order; ranks below k
 //      write themselves to the payload.
+// A is bound by HBM at 256 rows (131 MB in 18 us) and by the unit's own rate below; B to D are a chain of short steps that all rows
+// take at the same time.  With the group maxima read one behind the other, a counter bumped for every hit and one candidate at a
+// time ranked, 256 rows of V = 128256 took 33.0 us for both halves of the split, now 31.9 (top-64 36.9 -> 34.8); 64 rows 25.7 ->
+// 24.6, 16 of V = 151936 25.2 -> 23.3.  Eight vectors in flight a lane instead of four: 64 rows 1.3 us slower, 512 3.5.
 constexpr int kTopSlots = 16;  // one vector per group up to 16 K vectors per row
 constexpr int kTopCap = 1024;  // candidate buffer entries; more means a degenerate row -> exact slow path
 constexpr int kTopTodo = 2048; // (lane, group) pairs queued for the exact re-read
@@ -331,11 +335,21 @@ __global__ __launch_bounds__(kTopThreads) void cloud_topk_kernel(const TopArgs a
     // The (lane, group) pairs to revisit are few and scattered: they are queued first and then
     // dealt out one per thread, so that all of them are fetched in the same round trip.
     const int nslots = (Q + gsz - 1) / gsz;
-    for (int s = 0; s < nslots; ++s) {
-        if (gm[s * kTopThreads + tid] >= screen) {
-            const int pos = atomicAdd(&todo_count, 1);
-            if (pos < kTopTodo) todo[pos] = s * kTopThreads + tid;
-        }
+    // All of a lane's maxima are read in one round, and a wave bumps the counter once.
+    unsigned hits = 0;
+    float mx[kTopSlots];
+#pragma unroll
+    for (int s = 0; s < kTopSlots; ++s) mx[s] = gm[s * kTopThreads + tid];
+#pragma unroll
+    for (int s = 0; s < kTopSlots; ++s) hits |= (s < nslots && mx[s] >= screen ? 1u : 0u) << s;
+    const int mine = __popc(hits);
+    const int upto = wave_incl_scan_i32(mine), all = __builtin_amdgcn_readlane(upto, 63);
+    if (all) {
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&todo_count, all);
+        int pos = __builtin_amdgcn_readfirstlane(base) + upto - mine;
+        for (; hits; hits &= hits - 1, ++pos)
+            if (pos < kTopTodo) todo[pos] = (__ffs((int)hits) - 1) * kTopThreads + tid;
     }
     __syncthreads();
     const int ntodo = todo_count;
@@ -344,22 +358,27 @@ __global__ __launch_bounds__(kTopThreads) void cloud_topk_kernel(const TopArgs a
         topk_by_insertion<DT, VEC>(a, g, sm, oi, ov, c_v, c_i);
         return;
     }
-    for (int e = tid; e < ntodo; e += kTopThreads) {
-        const int s = todo[e] / kTopThreads, owner = todo[e] % kTopThreads;
-        const int qend = min(Q, (s + 1) * gsz);
-        for (int q = s * gsz; q < qend; q += 2) {  // two vectors of both rows per round trip
+    for (int e0 = wave * kWave; e0 < ntodo; e0 += kTopThreads) {  // wave-uniform
+        const bool mine = e0 + lane < ntodo;
+        const int td = mine ? todo[e0 + lane] : 0;
+        const int s = td / kTopThreads, owner = td % kTopThreads;
+        const int qend = mine ? min(Q, (s + 1) * gsz) : 0;
+        for (int d = 0; d < gsz; d += 2) {  // two vectors of both rows per round trip
             typename RawT<DT, VEC>::type rg[2], rm[2];
             long v[2];
             bool ok[2];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                v[j] = (long)(q + j) * kTopThreads + owner;
-                ok[j] = q + j < qend && v[j] < nvec;
+                const int q = s * gsz + d + j;
+                v[j] = (long)q * kTopThreads + owner;
+                ok[j] = q < qend && v[j] < nvec;
                 if (ok[j]) {
                     rg[j] = ld_raw<DT, VEC>(g, v[j]);
                     rm[j] = ld_raw<DT, VEC>(sm, v[j]);
                 }
             }
+            double hc[2][VEC];
+            unsigned hits = 0;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 if (!ok[j]) continue;
@@ -367,8 +386,29 @@ __global__ __launch_bounds__(kTopThreads) void cloud_topk_kernel(const TopArgs a
                 unpack(rg[j], hg);
                 unpack(rm[j], hm);
 #pragma unroll
+                for (int i = 0; i < VEC; ++i) {
+                    hc[j][i] = cloud_logit(hg[i], hm[i], a.beta);
+                    hits |= (hc[j][i] >= tau_d ? 1u : 0u) << (j * VEC + i);
+                }
+            }
+            // one counter bump a wave: a bump a logit took eight rounds of LDS atomics
+            const int n = __popc(hits);
+            const int incl = wave_incl_scan_i32(n), total = __builtin_amdgcn_readlane(incl, 63);
+            if (total == 0) continue;
+            int base = 0;
+            if (lane == 0) base = atomicAdd(&cand_count, total);
+            int pos = __builtin_amdgcn_readfirstlane(base) + incl - n;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+#pragma unroll
                 for (int i = 0; i < VEC; ++i)
-                    offer(cloud_logit(hg[i], hm[i], a.beta), (int)(v[j] * VEC) + i);
+                    if (hits >> (j * VEC + i) & 1u) {
+                        if (pos < kTopCap) {
+                            c_v[pos] = hc[j][i];
+                            c_i[pos] = (int)(v[j] * VEC) + i;
+                        }
+                        ++pos;
+                    }
             }
         }
     }
@@ -386,7 +426,8 @@ __global__ __launch_bounds__(kTopThreads) void cloud_topk_kernel(const TopArgs a
 
     // ---- D: rank among the candidates = position in the payload.  A wave takes every 16th
     // candidate; its lanes hold the candidate list in registers (the first 256 entries, normally
-    // all of it) and count, together, how many entries precede the wave's candidate.
+    // all of it) and count, together, how many entries precede the wave's candidate; two candidates at a time, their counts in
+    // one word.
     constexpr int kHold = 4;
     double hv[kHold];
     int hi[kHold];
@@ -396,17 +437,29 @@ __global__ __launch_bounds__(kTopThreads) void cloud_topk_kernel(const TopArgs a
         hv[j] = u < M ? c_v[u] : -__builtin_huge_val();
         hi[j] = u < M ? c_i[u] : 0x7FFFFFFF;
     }
-    for (int i = wave; i < M; i += kTopWaves) {
-        const double mv = c_v[i];
-        const int mi = c_i[i];
-        int cnt = 0;
+    for (int i = wave; i < M; i += 2 * kTopWaves) {
+        const bool two = i + kTopWaves < M;
+        const int i2 = two ? i + kTopWaves : i;
+        const double mv = c_v[i], mv2 = c_v[i2];
+        const int mi = c_i[i], mi2 = c_i[i2];
+        int cnt = 0, cnt2 = 0;
 #pragma unroll
-        for (int j = 0; j < kHold; ++j) cnt += beats(hv[j], hi[j], mv, mi) ? 1 : 0;
-        for (int u = lane + kWave * kHold; u < M; u += kWave) cnt += beats(c_v[u], c_i[u], mv, mi) ? 1 : 0;
-        const int rank = wave_sum_i32(cnt);
+        for (int j = 0; j < kHold; ++j) {
+            cnt += beats(hv[j], hi[j], mv, mi) ? 1 : 0;
+            cnt2 += beats(hv[j], hi[j], mv2, mi2) ? 1 : 0;
+        }
+        for (int u = lane + kWave * kHold; u < M; u += kWave) {
+            cnt += beats(c_v[u], c_i[u], mv, mi) ? 1 : 0;
+            cnt2 += beats(c_v[u], c_i[u], mv2, mi2) ? 1 : 0;
+        }
+        const int both = wave_sum_i32(cnt | cnt2 << 16), rank = both & 0xFFFF, rank2 = both >> 16;
         if (lane == 0 && rank < topk) {
             oi[rank] = mi;
             ov[rank] = (float)mv;
+        }
+        if (lane == 0 && two && rank2 < topk) {
+            oi[rank2] = mi2;
+            ov[rank2] = (float)mv2;
         }
     }
 }

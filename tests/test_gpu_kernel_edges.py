@@ -389,3 +389,26 @@ def test_recovery_launch_by_chunks_and_drafts(binding, oracle, dtype, k_max, chu
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, greedy=greedy,
                             want_recovery_logprobs=False)
     parity.compare(out, ora, inp["uniforms"], None)
+
+
+# The cloud top-k queues what reaches its bound wave by wave: as many equal largest logits as its buffers hold (256 in registers,
+# 1024 candidates, 2048 vectors) and one more or less, next to each other, a vector apart and all in the lanes of one wave.
+@pytest.mark.parametrize("spread", ["dense", "vectors", "one wave"])
+@pytest.mark.parametrize("dtype,count", [("bf16", 31), ("bf16", 255), ("bf16", 257), ("bf16", 1024), ("bf16", 1025), ("f32", 1023),
+                                         ("f32", 2048), ("f32", 2049)])
+def test_topk_of_equal_logits_fills_its_buffers(binding, dtype, count, spread):
+    vec, vocab, k = (8, 70007, 64) if dtype == "bf16" else (4, 50001, 64)
+    at = torch.arange(count, device="cuda")
+    if spread == "vectors":
+        at = at * vec % (vocab - vec) + at * vec // (vocab - vec)
+    elif spread == "one wave":  # 64 lanes x vec logits, 1024 vectors on for the next ones
+        at = at % (64 * vec) + at // (64 * vec) * 1024 * vec
+    at = at[at < vocab].unique()
+    gen = torch.Generator("cuda").manual_seed(count)
+    G = torch.rand(2, 1, vocab, generator=gen, device="cuda").mul_(3).to(W.torch_dtype(dtype))
+    M = torch.zeros_like(G)
+    G[0, 0, at] = 5.0
+    h = (G.double() - 0.5 * M.double())[:, 0]
+    value, index = torch.sort(h, dim=-1, descending=True, stable=True)
+    got_i, got_v = binding.cloud_topk(G, M, torch.zeros(2, dtype=torch.int32, device="cuda"), beta=0.5, topk=k)
+    assert torch.equal(got_i.long(), index[:, :k]) and torch.equal(got_v, value[:, :k].float())
