@@ -405,6 +405,8 @@ struct RecArgs {
     int plain;       // beta == 0: no steering term, the specialist rows are not read by the recovery sweep
     // Small batches: `parts` workgroups share the recovery row of one sequence.
     int parts, part_chunks;  // part i takes chunks [i * part_chunks, (i+1) * part_chunks)
+    int defer;            // the parts only deliver: row_draw_kernel draws, and writes the log-prob rows in segs workgroups a row
+    int segs;
     Partial* chunk_tab;   // [B][NC] chunk masses, filled by the parts
     double* best_v;       // [B][NC] greedy candidates of the parts: value ...
     int32_t* best_i;      // [B][NC] ... and token
@@ -945,10 +947,10 @@ __device__ __forceinline__ void st_f32x4(float* p, float x, float y, float z, fl
 constexpr int kNoTail = 0x7FFFFFFF;
 
 // log Softmax(h_rec / T) of kLogprobUnroll vectors of a row, v and those `step` behind it, and of logit `tail` past the last
-// full vector, where there is one.
-template <int DT, int VEC, bool PLAIN>
+// full vector, where there is one.  log2_z() gives the row's normaliser, asked for while the vectors are on their way.
+template <int DT, int VEC, bool PLAIN, typename F>
 __device__ __forceinline__ void write_logprobs(const void* g, const void* sp, const void* sm, float* out, int V, long v0,
-                                               int step, int tail, double c, double bc, double log2Z) {
+                                               int step, int tail, double c, double bc, F log2_z) {
     const long nvec = V / VEC;
     typename RawT<DT, VEC>::type rg[kLogprobUnroll], rp[kLogprobUnroll], rm[kLogprobUnroll];
 #pragma unroll
@@ -962,6 +964,7 @@ __device__ __forceinline__ void write_logprobs(const void* g, const void* sp, co
             }
         }
     }
+    const double log2Z = log2_z();
 #pragma unroll
     for (int j = 0; j < kLogprobUnroll; ++j) {
         const long v = v0 + j * step;
@@ -988,6 +991,7 @@ __device__ __forceinline__ void write_logprobs(const void* g, const void* sp, co
 //       mass per 2048-logit chunk into LDS
 //   4   the first four waves draw the token (greedy: wave 0)
 //   5   all waves write the log-prob row, where it is short enough (logprobs_in_recovery)
+// a.defer: steps 4 and 5 are row_draw_kernel's.
 // Only workgroup barriers separate the steps; nothing crosses workgroups.
 //
 // a.parts > 1: that many workgroups share a sequence.  Each repeats steps 2a-2b, takes a.part_chunks
@@ -1074,6 +1078,17 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
         wave_best(best);
         if (best.idx <= V) best.idx -= row.head;
     }
+    if (a.defer) {
+        for (int c = c0 + tid; c < c1; c += NT) a.chunk_tab[(long)b * a.NC + c] = tab[c];
+        if (tid == 0) {
+            if (GREEDY) {
+                a.best_v[(long)b * a.NC + part] = best.v;
+                a.best_i[(long)b * a.NC + part] = min(best.idx, V);
+            }
+            if (part == 0) a.accepted_len[b] = n;
+        }
+        return;
+    }
     if (S > 1) {  // deliver this part; only the last part to arrive goes on
         Partial* gtab = a.chunk_tab + (long)b * a.NC;
         if (wave == 0) {
@@ -1120,7 +1135,7 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     const long nv = V / VEC, off = (long)b * a.sb + (long)n * a.st;
     const void *g = row_ptr<DT>(a.G, off), *sp = row_ptr<DT>(a.recSp, off), *sm = row_ptr<DT>(a.recSm, off);
     for (long v = tid; v < nv || v == tid; v += NT * kLogprobUnroll)
-        write_logprobs<DT, VEC, PLAIN>(g, sp, sm, a.recovery_logprobs + (long)b * V, V, v, NT, v == tid ? tid : kNoTail, a.c, a.bc, sh_log2z);
+        write_logprobs<DT, VEC, PLAIN>(g, sp, sm, a.recovery_logprobs + (long)b * V, V, v, NT, v == tid ? tid : kNoTail, a.c, a.bc, [&] { return sh_log2z; });
 }
 
 // ------------------------------------------------------------------ kernels: few rows without drafts
@@ -1141,7 +1156,7 @@ __global__ __launch_bounds__(kMassWaves * kWave) void row_mass_kernel(const RecA
     if (c >= row.NC) return;
     Best best{-__builtin_huge_val(), kNoBest};
     const Partial p = chunk_mass<DT, VEC, GREEDY, PLAIN>(row, c, lane, a.c, a.bc, a.beta, a.c_hi, best);
-    const long at = (long)b * a.NC + c;
+    const long at = (long)b * a.NC + c;  // greedy candidates: one a chunk
     if (GREEDY) wave_best(best);
     if (lane == 0) {
         a.chunk_tab[at] = p;
@@ -1152,40 +1167,58 @@ __global__ __launch_bounds__(kMassWaves * kWave) void row_mass_kernel(const RecA
     }
 }
 
-// The token of a row from its masses.
+// The token of a row from its masses, and with a.segs > 0 its log-prob row: one workgroup draws, the others write a segment each, so
+// that the draw's chain of steps and the sweep over the row run side by side.  Each of them forms the row's
+// normaliser from the masses itself, while its logits are on their way.  Behind a draw by the last part, a launch of its own for
+// the rows took 16 sequences of V = 151936 to 33.8 us a call, 31.9 now (two launches of 7 and 12 us became 9 and 8); 32 of
+// V = 128256 47.6 -> 44.8, 64 of V = 151936 89.8 -> 87.1.
 template <int DT, int VEC, bool GREEDY, bool PLAIN>
-__global__ __launch_bounds__(kDrawWaves * kWave) void row_draw_kernel(const RecArgs a) {
+__global__ __launch_bounds__(kLogprobThreads) void row_draw_kernel(const RecArgs a) {
+    static_assert(kLogprobThreads == kDrawWaves * kWave, "a vector a lane of the drawing waves");
     extern __shared__ double smem_d[];
     __shared__ double sh_sum[kDrawWaves];
     __shared__ int sh_any[kDrawWaves];
-    const int b = (int)blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    Partial* tab = reinterpret_cast<Partial*>(smem_d);
-    const double us = GREEDY ? 0.0 : (double)a.uniforms[b];
-    const RecRow<DT, VEC> row(a, b, 0);
-    const long at = (long)b * a.NC;
-    for (int c = tid; c < row.NC; c += kDrawWaves * kWave) tab[c] = a.chunk_tab[at + c];
-    Best best{-__builtin_huge_val(), kNoBest};
-    if (GREEDY && wave == 0) {
-        for (int c = lane; c < row.NC; c += kWave) {
-            const double v = a.best_v[at + c];
-            const int idx = a.best_i[at + c];
-            if (v > best.v || (v == best.v && idx < best.idx)) best = Best{v, idx};
-        }
-        wave_best(best);
-    }
-    if (a.draft_len && a.draft_len[b] != 0) {  // no draft can have a length
-        if (tid == 0) {
+    const int b = (int)blockIdx.x / (a.segs + 1), seg = (int)blockIdx.x - b * (a.segs + 1) - 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, kmax = a.kmax;
+    const double us = GREEDY || seg >= 0 ? 0.0 : (double)a.uniforms[(long)b * (kmax + 1) + kmax];
+    // the row: what the ratio test has found, or the only one there is (no draft can have a length)
+    const int n = kmax > 0 ? a.accepted_len[b] : a.draft_len && a.draft_len[b] != 0 ? -1 : 0;
+    if (n < 0) {  // flagged: the log-prob row is left unwritten
+        if (kmax == 0 && seg < 0 && tid == 0) {
             a.accepted_len[b] = -1;
             a.next_token[b] = -1;
             if (a.next_token_logprob) a.next_token_logprob[b] = __int_as_float(0x7FC00000);
         }
         return;
     }
+    const RecRow<DT, VEC> row(a, b, n);
+    const long at = (long)b * a.NC;
+    if (seg >= 0) {
+        const long off = (long)b * a.sb + (long)n * a.st;
+        write_logprobs<DT, VEC, PLAIN>(row_ptr<DT>(a.G, off), row_ptr<DT>(a.recSp, off), row_ptr<DT>(a.recSm, off),
+                                       a.recovery_logprobs + (long)b * a.V, a.V, (long)seg * (kLogprobThreads * kLogprobUnroll) + tid,
+                                       kLogprobThreads, seg == a.segs - 1 ? tid : kNoTail, a.c, a.bc, [&] {
+                                           const ChunkScan cs(a.chunk_tab + at, row.NC, lane);
+                                           return mass_log2<PLAIN>(a, cs.Estar, cs.total);
+                                       });
+        return;
+    }
+    Partial* tab = reinterpret_cast<Partial*>(smem_d);
+    for (int c = tid; c < row.NC; c += kLogprobThreads) tab[c] = a.chunk_tab[at + c];
+    Best best{-__builtin_huge_val(), kNoBest};
+    if (GREEDY && wave == 0) {
+        const int cands = kmax > 0 ? a.parts : row.NC;  // one a part, or one a chunk
+        for (int i = lane; i < cands; i += kWave) {
+            const double v = a.best_v[at + i];
+            const int idx = a.best_i[at + i];
+            if (v > best.v || (v == best.v && idx < best.idx)) best = Best{v, idx};
+        }
+        wave_best(best);
+    }
     __syncthreads();
     if (GREEDY && wave > 0) return;
-    const double log2Z = GREEDY ? greedy_token<PLAIN>(a, b, 0, lane, tab, row.NC, best)
-                                : draw_token<DT, VEC, PLAIN>(a, b, 0, us, wave, lane, tab, row, sh_sum, sh_any);
-    if (tid == 0 && a.log2z) a.log2z[b] = log2Z;
+    if (GREEDY) greedy_token<PLAIN>(a, b, n, lane, tab, row.NC, best);
+    else draw_token<DT, VEC, PLAIN>(a, b, n, us, wave, lane, tab, row, sh_sum, sh_any);
 }
 
 // ------------------------------------------------------------------ kernel: log-prob rows
@@ -1216,7 +1249,7 @@ __global__ __launch_bounds__(kLogprobThreads) void recovery_logprob_kernel(const
     const long off = (long)b * a.sb + (long)n * a.st;
     write_logprobs<DT, VEC, PLAIN>(row_ptr<DT>(a.G, off), row_ptr<DT>(a.recSp, off), row_ptr<DT>(a.recSm, off),
                                    a.out + (long)b * a.V, a.V, (long)seg * (kLogprobThreads * kLogprobUnroll) + threadIdx.x,
-                                   kLogprobThreads, seg == a.segs - 1 ? (int)threadIdx.x : kNoTail, a.c, a.bc, a.log2z[b]);
+                                   kLogprobThreads, seg == a.segs - 1 ? (int)threadIdx.x : kNoTail, a.c, a.bc, [&] { return a.log2z[b]; });
 }
 
 // ------------------------------------------------------------------ host side
@@ -1325,28 +1358,32 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
         {accept_recover_kernel<DT, VEC, false, false, 1024>, accept_recover_kernel<DT, VEC, true, false, 1024>,
          accept_recover_kernel<DT, VEC, false, true, 1024>, accept_recover_kernel<DT, VEC, true, true, 1024>}};
     const int kind = (ra.greedy ? 1 : 0) | (ra.plain ? 2 : 0);
-    if (kmax == 0 && split) {
+    const long per = kLogprobThreads * kLogprobUnroll;  // vectors of a segment of a log-prob row
+    const int segs = V / VEC > per ? (int)((V / VEC + per - 1) / per) : 1;
+    const bool rows_apart = recovery_logprobs && !rows_inside;
+    ra.defer = split && (kmax == 0 || rows_apart) ? 1 : 0;
+    if (ra.defer) {
         static const RecKernel mass[4] = {row_mass_kernel<DT, VEC, false, false>, row_mass_kernel<DT, VEC, true, false>,
                                           row_mass_kernel<DT, VEC, false, true>, row_mass_kernel<DT, VEC, true, true>};
         static const RecKernel draw[4] = {row_draw_kernel<DT, VEC, false, false>, row_draw_kernel<DT, VEC, true, false>,
                                           row_draw_kernel<DT, VEC, false, true>, row_draw_kernel<DT, VEC, true, true>};
-        ra.parts = (ra.NC + kMassWaves - 1) / kMassWaves;
-        hipLaunchKernelGGL(mass[kind], dim3((unsigned)(B * ra.parts)), dim3(kMassWaves * kWave), 0, stream, ra);
-        hipLaunchKernelGGL(draw[kind], dim3((unsigned)B), dim3(kDrawWaves * kWave), smem, stream, ra);
+        if (kmax == 0) {
+            ra.parts = (ra.NC + kMassWaves - 1) / kMassWaves;
+            hipLaunchKernelGGL(mass[kind], dim3((unsigned)(B * ra.parts)), dim3(kMassWaves * kWave), 0, stream, ra);
+        } else {
+            hipLaunchKernelGGL(rec_kernels[shape.threads >> 9][kind], rec_grid, dim3((unsigned)shape.threads), smem, stream, ra);
+        }
+        ra.segs = rows_apart ? segs : 0;
+        ra.recovery_logprobs = recovery_logprobs;
+        hipLaunchKernelGGL(draw[kind], dim3((unsigned)(B * (ra.segs + 1))), dim3(kLogprobThreads), smem, stream, ra);
     } else {
         hipLaunchKernelGGL(rec_kernels[shape.threads >> 9][kind], rec_grid, dim3((unsigned)shape.threads), smem, stream, ra);
-    }
-    if (recovery_logprobs && !rows_inside) {
-        const long nvec = V / VEC, per = kLogprobThreads * kLogprobUnroll;
-        const int segs = nvec > per ? (int)((nvec + per - 1) / per) : 1;
-        const LogprobArgs pa{ra.G, ra.recSp, ra.recSm, ra.accepted_len, ra.log2z, recovery_logprobs, ra.sb, ra.st, V,
-                             segs, ra.c, ra.bc};
-        if (ra.plain)
-            hipLaunchKernelGGL((recovery_logprob_kernel<DT, VEC, true>), dim3((unsigned)(B * segs)),
-                               dim3(kLogprobThreads), 0, stream, pa);
-        else
-            hipLaunchKernelGGL((recovery_logprob_kernel<DT, VEC, false>), dim3((unsigned)(B * segs)),
-                               dim3(kLogprobThreads), 0, stream, pa);
+        if (rows_apart) {
+            const LogprobArgs pa{ra.G, ra.recSp, ra.recSm, ra.accepted_len, ra.log2z, recovery_logprobs, ra.sb, ra.st, V,
+                                 segs, ra.c, ra.bc};
+            hipLaunchKernelGGL((ra.plain ? recovery_logprob_kernel<DT, VEC, true> : recovery_logprob_kernel<DT, VEC, false>),
+                               dim3((unsigned)(B * segs)), dim3(kLogprobThreads), 0, stream, pa);
+        }
     }
     mark(4);
     const hipError_t launch_err = hipGetLastError();
@@ -1409,6 +1446,7 @@ ss_status verify_block_impl(const void* G, const void* S_ctx, const void* S_noct
     ra.greedy = (params->flags & SS_FLAG_GREEDY) ? 1 : 0;
     ra.plain = steer ? 0 : 1;
     ra.c_hi = c_hi;
+    ra.defer = 0; ra.segs = 0;
     ra.parts = 1; ra.part_chunks = 0; ra.chunk_tab = nullptr; ra.best_v = nullptr; ra.best_i = nullptr; ra.arrive = nullptr;
 
     hipStream_t s = static_cast<hipStream_t>(stream);

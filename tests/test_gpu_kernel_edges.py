@@ -52,6 +52,22 @@ def test_logprob_rows_at_segment_edges(binding, oracle, dtype, vocab, beta):
     assert out["accepted_len"][2].item() == -1 and torch.all(out["recovery_logprobs"][2] == 7.0)  # left unwritten
 
 
+# Log-prob rows of a recovery row in several parts: the parts only deliver, and one launch draws and writes the rows.
+@pytest.mark.parametrize("greedy,beta", [(False, 0.8), (True, 0.8), (False, 0.0), (True, 0.0)])
+@pytest.mark.parametrize("dtype,batch,vocab", [("bf16", 4, 20 * 2048 + 5), ("bf16", 40, 75 * 2048 - 1), ("f32", 3, 65 * 1024),
+                                               ("f32", 7, 260 * 1024 + 1)])
+def test_logprob_rows_beside_the_draw(binding, oracle, dtype, batch, vocab, greedy, beta):
+    w = recipe("c4", dtype, batch=batch, k_max=3, vocab=vocab)
+    inp = W.generate(w, "cuda", seq_chunk=16)
+    inp["draft_len"] = torch.tensor([i % 4 for i in range(batch)], dtype=torch.int32, device="cuda")
+    inp["draft_len"][1] = 4  # flagged
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam, beta=beta,
+                               temperature=w.temperature, draft_len=inp["draft_len"], greedy=greedy, want_recovery_logprobs=True)
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=beta, temperature=w.temperature, greedy=greedy)
+    parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
+    assert out["accepted_len"][1].item() == -1
+
+
 # The recovery launch: 4-wave workgroups of one chunk a wave while batch x chunks <= 8 x 256 (a single workgroup of 16 waves
 # for 5 .. 8 chunks), then 16-wave parts of
 # equal rounds up to 128 sequences, then one workgroup of 16 waves per sequence up to 256 and of 8 beyond.  A chunk is
