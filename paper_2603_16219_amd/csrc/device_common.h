@@ -206,6 +206,14 @@ __device__ __forceinline__ const void* row_ptr(const void* base, long elem_off) 
 
 // ------------------------------------------------------------------ host helpers
 
+// One launch.  hipLaunchKernel itself takes 2.1 us of host time here whatever the kernel, the launch syntax and
+// hipLaunchKernelGGL, which pass the configuration through a stack of the runtime's, 2.3.  An error stays for hipGetLastError.
+template <typename... P>
+void launch(void (*kernel)(P...), dim3 grid, dim3 block, size_t lds, hipStream_t stream, P... args) {
+    void* ptrs[] = {static_cast<void*>(&args)...};
+    (void)hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, ptrs, lds, stream);
+}
+
 // Compute units of the current device (MI355X: 256), looked up once per device; callers on
 // several host threads may race to fill an entry, all with the same value.
 inline int device_cu_count() {

@@ -1270,7 +1270,7 @@ void launch_row_pass(LseArgs la, const Window& w, const RowWindow& win, int unif
     // the row list is built in LDS by the row pass unless the batch is too large for it
     const bool global_list = listed && B > kMaxLdsBatch;
     la.list_in_lds = (listed && !global_list) ? 1 : 0;
-    if (global_list) hipLaunchKernelGGL(prep_rows_kernel, dim3(1), dim3(1024), 0, stream, win, B, row_off);
+    if (global_list) launch(prep_rows_kernel, dim3(1), dim3(1024), 0, stream, win, B, row_off);
     const long items = (long)B * (w.t_hi - w.t_lo) * 2 * la.NS;
     if (items <= 0) return;
     const long per_wg = kLseThreads / kWave;
@@ -1278,7 +1278,7 @@ void launch_row_pass(LseArgs la, const Window& w, const RowWindow& win, int unif
     const long cap = (long)cus * kLseWgPerCu;
     if (wgs > cap) wgs = cap;
     const size_t lds = la.list_in_lds ? (size_t)(B + 1) * sizeof(int) : 0;
-    hipLaunchKernelGGL((row_lse_kernel<DT, VEC, kLseUnroll>), dim3((unsigned)wgs), dim3(kLseThreads), lds,
+    launch(row_lse_kernel<DT, VEC, kLseUnroll>, dim3((unsigned)wgs), dim3(kLseThreads), lds,
                        stream, la);
 }
 
@@ -1341,7 +1341,7 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
         if (i == 0) mark(1);
         if (i + 1 < windows) {
             const bool few = w.t_hi - w.t_lo <= 8;
-            hipLaunchKernelGGL((few ? verdict_kernel<DT, 128> : verdict_kernel<DT, 512>), dim3((unsigned)B), dim3(few ? 128 : 512),
+            launch(few ? verdict_kernel<DT, 128> : verdict_kernel<DT, 512>, dim3((unsigned)B), dim3(few ? 128 : 512),
                                (size_t)2 * kmax * sizeof(double), stream, ra);
         }
         if (i == 0) mark(2);
@@ -1369,19 +1369,19 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
                                           row_draw_kernel<DT, VEC, false, true>, row_draw_kernel<DT, VEC, true, true>};
         if (kmax == 0) {
             ra.parts = (ra.NC + kMassWaves - 1) / kMassWaves;
-            hipLaunchKernelGGL(mass[kind], dim3((unsigned)(B * ra.parts)), dim3(kMassWaves * kWave), 0, stream, ra);
+            launch(mass[kind], dim3((unsigned)(B * ra.parts)), dim3(kMassWaves * kWave), 0, stream, ra);
         } else {
-            hipLaunchKernelGGL(rec_kernels[shape.threads >> 9][kind], rec_grid, dim3((unsigned)shape.threads), smem, stream, ra);
+            launch(rec_kernels[shape.threads >> 9][kind], rec_grid, dim3((unsigned)shape.threads), smem, stream, ra);
         }
         ra.segs = rows_apart ? segs : 0;
         ra.recovery_logprobs = recovery_logprobs;
-        hipLaunchKernelGGL(draw[kind], dim3((unsigned)(B * (ra.segs + 1))), dim3(kLogprobThreads), smem, stream, ra);
+        launch(draw[kind], dim3((unsigned)(B * (ra.segs + 1))), dim3(kLogprobThreads), smem, stream, ra);
     } else {
-        hipLaunchKernelGGL(rec_kernels[shape.threads >> 9][kind], rec_grid, dim3((unsigned)shape.threads), smem, stream, ra);
+        launch(rec_kernels[shape.threads >> 9][kind], rec_grid, dim3((unsigned)shape.threads), smem, stream, ra);
         if (rows_apart) {
             const LogprobArgs pa{ra.G, ra.recSp, ra.recSm, ra.accepted_len, ra.log2z, recovery_logprobs, ra.sb, ra.st, V,
                                  segs, ra.c, ra.bc};
-            hipLaunchKernelGGL((ra.plain ? recovery_logprob_kernel<DT, VEC, true> : recovery_logprob_kernel<DT, VEC, false>),
+            launch(ra.plain ? recovery_logprob_kernel<DT, VEC, true> : recovery_logprob_kernel<DT, VEC, false>,
                                dim3((unsigned)(B * segs)), dim3(kLogprobThreads), 0, stream, pa);
         }
     }

@@ -567,9 +567,9 @@ ss_status specsteer_cloud_topk(const void* G, const void* S_noctx, const int32_t
     hipStream_t s = static_cast<hipStream_t>(stream);
     const dim3 grid((unsigned)params->batch), block(kTopThreads);
     if (params->dtype == SS_BF16)
-        hipLaunchKernelGGL((cloud_topk_kernel<SS_BF16, 8>), grid, block, 0, s, a);
+        launch(cloud_topk_kernel<SS_BF16, 8>, grid, block, 0, s, a);
     else
-        hipLaunchKernelGGL((cloud_topk_kernel<SS_F32, 4>), grid, block, 0, s, a);
+        launch(cloud_topk_kernel<SS_F32, 4>, grid, block, 0, s, a);
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_DEVICE;
 }
 
@@ -591,8 +591,8 @@ ss_status specsteer_edge_resample(const int32_t* index, const float* value, cons
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int per = kEdgeThreads / kWave;
     const dim3 grid((unsigned)((params->batch + per - 1) / per)), block(kEdgeThreads);
-    if (params->dtype == SS_BF16) hipLaunchKernelGGL((edge_resample_kernel<SS_BF16>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((edge_resample_kernel<SS_F32>), grid, block, 0, s, a);
+    if (params->dtype == SS_BF16) launch(edge_resample_kernel<SS_BF16>, grid, block, 0, s, a);
+    else launch(edge_resample_kernel<SS_F32>, grid, block, 0, s, a);
     return hipGetLastError() == hipSuccess ? SS_OK : SS_ERR_DEVICE;
 }
 
