@@ -73,8 +73,9 @@ constexpr int kSplitMaxBatch = 128;  // workspace is reserved for shared recover
 //     drafts: 17.0 -> 17.4, 32 18.4 -> 18.9); a single part of 4 waves with more than 8 drafts (V = 2000, 12 drafts: 12.1 ->
 //     12.4).  Beyond 16 chunks up to 32 drafts (V = 151936: 24 drafts 27.1 -> 24.8, 32 30.8 -> 29.1; one sequence of V = 40000,
 //     48 drafts: 17.1 -> 17.9).
-//   - At least two compute units per sequence: as many 16-wave parts as there are units per sequence, with
-//     equal rounds of 16 chunks.
+//   - At least two compute units per sequence: as many 16-wave parts as there are units per sequence, and no more than rounds of
+//     16 chunks (80 sequences of V = 100000, 49 chunks: 38.5 us a step in 2 equal parts of two rounds, 36.9 in 3 of 17, 36.2 with
+//     the chunk over dealt out in quarters).
 //   - Up to one sequence per unit: one 16-wave workgroup each.  More: 8-wave workgroups, two to a unit, so that the
 //     serial ends of one sequence (ratio test, token pick) overlap the sweep of another (300 sequences of
 //     V = 100000: 132 us a step against 137 in balanced parts and 140 with 16 waves).
@@ -88,9 +89,7 @@ inline RecShape recovery_shape(int B, int NC, int kmax, int cus, bool split) {
     if (split && B <= cus / 2) {
         const int rows = (NC + 15) / 16;  // rounds of 16 chunks
         const int most = cus / B < rows ? cus / B : rows;
-        const int rounds = (rows + most - 1) / most;
-        const int parts = (rows + rounds - 1) / rounds;
-        return {1024, (NC + parts - 1) / parts};
+        return {1024, (NC + most - 1) / most};
     }
     return {B <= cus ? 1024 : 512, NC};
 }

@@ -504,22 +504,22 @@ struct RecRow {
     }
 };
 
-// (E, s) mass of recovery chunk c, by one wave: sum over the chunk of 2^(y - E).  With a steering term the
+// (E, s) mass of recovery chunk c, or of STEPS of its steps from step0 on, by one wave: sum over the chunk of 2^(y - E).  With a steering term the
 // exponent is formed in double (acc_add_rec); PLAIN (beta == 0) has only h_LLM * c to form and takes the
 // row pass's route, one fp32 fma per logit with the rounded scale c_hi, repaired to first order by the caller.
-template <int DT, int VEC, bool GREEDY, bool PLAIN>
+template <int DT, int VEC, bool GREEDY, bool PLAIN, int STEPS = kChunkSteps>
 __device__ __forceinline__ Partial chunk_mass(const RecRow<DT, VEC>& row, long c, int lane, double cc, double bc, double beta,
-                                              float c_hi, Best& best) {
+                                              float c_hi, Best& best, int step0 = 0) {
     const void *g = row.g, *sp = row.sp, *sm = row.sm;
     const long nvec = row.nvec, nch = row.nch;
     const int tailc = row.tailc, head = row.head;
     const float cf = (float)cc, bcf = (float)bc;
     Acc acc{kEInit, 0.f};
     if (c < nch) {
-        const long vbase = c * (long)(kWave * kChunkSteps) + lane;
-        typename RawT<DT, VEC>::type rg[kChunkSteps], rp[kChunkSteps], rm[kChunkSteps];
+        const long vbase = (c * kChunkSteps + step0) * kWave + lane;
+        typename RawT<DT, VEC>::type rg[STEPS], rp[STEPS], rm[STEPS];
 #pragma unroll
-        for (int j = 0; j < kChunkSteps; ++j) {
+        for (int j = 0; j < STEPS; ++j) {
             const long v = vbase + (long)j * kWave;
             if (v < nvec) {
                 rg[j] = ld_raw<DT, VEC>(g, v);
@@ -536,20 +536,20 @@ __device__ __forceinline__ Partial chunk_mass(const RecRow<DT, VEC>& row, long c
                 rm[0] = set_first(rm[0], 0u);
             }
         }
-        if (PLAIN && vbase + (long)(kChunkSteps - 1) * kWave < nvec) {  // a full chunk: one accumulate over its 4 vectors
-            float h[kChunkSteps * VEC];
+        if (PLAIN && vbase + (long)(STEPS - 1) * kWave < nvec) {  // all of it there: one accumulate over its vectors
+            float h[STEPS * VEC];
 #pragma unroll
-            for (int j = 0; j < kChunkSteps; ++j) {
+            for (int j = 0; j < STEPS; ++j) {
                 float hj[VEC];
                 unpack(rg[j], hj);
                 if (GREEDY) best_of<VEC>(best, hj, (int)(vbase + (long)j * kWave) * VEC);
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) h[j * VEC + i] = hj[i];
             }
-            acc_add_f32<kChunkSteps * VEC>(acc, h, c_hi);
+            acc_add_f32<STEPS * VEC>(acc, h, c_hi);
         } else {
 #pragma unroll
-            for (int j = 0; j < kChunkSteps; ++j) {
+            for (int j = 0; j < STEPS; ++j) {
                 const long v = vbase + (long)j * kWave;
                 if (v < nvec) {
                     float hg[VEC], hp[VEC], hm[VEC];
@@ -564,7 +564,7 @@ __device__ __forceinline__ Partial chunk_mass(const RecRow<DT, VEC>& row, long c
                 }
             }
         }
-    } else if (lane < tailc) {
+    } else if (lane < tailc && step0 == 0) {
         const long e = nvec * VEC + lane;
         const float hg[1] = {ld_elem<DT>(g, e)}, hp[1] = {ld_steer<DT, PLAIN>(sp, e)}, hm[1] = {ld_steer<DT, PLAIN>(sm, e)};
         if (PLAIN) {
@@ -1003,6 +1003,7 @@ template <int DT, int VEC, bool GREEDY, bool PLAIN, int NT>
 __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     extern __shared__ double smem_d[];
     __shared__ int sh_ratio[kRatioWords<NT>];
+    __shared__ Partial sh_part[NT == 1024 ? NT / kWave : 1];
     __shared__ double sh_sum[kDrawWaves];
     __shared__ int sh_any[kDrawWaves], sh_last;
     __shared__ double sh_best_v[NT / kWave];
@@ -1048,9 +1049,16 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     const RecRow<DT, VEC> row(a, b, n);
     Best best{-__builtin_huge_val(), kNoBest};
     const int c0 = part * a.part_chunks, c1 = min(row.NC, c0 + a.part_chunks);
+    // Shared rows: chunks left over for a last round of at most half the waves are dealt out in halves or quarters, so that the round
+    // takes as much less.  64 sequences of V = 151936, 75 chunks, in 4 parts of 16 whole chunks and 3 in quarters: 67.7 us a step, with the
+    // 3 whole 68.2, in the 3 parts of 25 that leave a quarter of the units idle 68.9; 80 of V = 100000 36.2, 36.9 and 38.5; 100 of V =
+    // 151936 in 2 parts of 32 and 6 in halves 63.9, whole 64.6.
+    const int over = NT == 1024 && S > 1 && c1 > c0 ? (c1 - c0) % NW : 0;
+    const int ways = over == 0 || 2 * over > NW ? 1 : 4 * over > NW ? 2 : 4;
+    const int cw = ways > 1 ? c1 - over : c1;  // whole chunks end here
     int c = c0 + wave;
     if (PLAIN && NT == 1024) {
-        for (; c + NW < c1 && (long)(c + NW + 1) * (kWave * kChunkSteps) <= row.nvec; c += 2 * NW) {
+        for (; c + NW < cw && (long)(c + NW + 1) * (kWave * kChunkSteps) <= row.nvec; c += 2 * NW) {
             Partial p[2];
             const long pair[2] = {c, c + NW};
             chunk_pair_mass<DT, VEC, GREEDY>(row, pair, lane, a.c_hi, best, p);
@@ -1060,10 +1068,27 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
             }
         }
     }
-    for (; c < c1; c += NW) {
+    for (; c < cw; c += NW) {
         const Partial p = chunk_mass<DT, VEC, GREEDY, PLAIN>(row, c, lane, a.c, a.bc, a.beta, a.c_hi, best);
         if (lane == 0) tab[c] = p;
     }
+    if (NT == 1024 && ways > 1 && wave < over * ways) {
+        const int cs = cw + wave / ways, step0 = wave % ways * (kChunkSteps / ways);
+        const Partial p = ways == 2
+            ? chunk_mass<DT, VEC, GREEDY, PLAIN, kChunkSteps / 2>(row, cs, lane, a.c, a.bc, a.beta, a.c_hi, best, step0)
+            : chunk_mass<DT, VEC, GREEDY, PLAIN, kChunkSteps / 4>(row, cs, lane, a.c, a.bc, a.beta, a.c_hi, best, step0);
+        if (lane == 0) sh_part[wave] = p;
+    }
+    const auto mass = [&](int c) {  // of a chunk of this part
+        if (NT != 1024 || c < cw) return tab[c];
+        Partial m = sh_part[(c - cw) * ways];
+        for (int i = 1; i < ways; ++i) {
+            const Partial q = sh_part[(c - cw) * ways + i];
+            const int E = max(m.E, q.E);
+            m = Partial{E, ldexpf(m.s, m.E - E) + ldexpf(q.s, q.E - E)};
+        }
+        return m;
+    };
     if (GREEDY) {
         wave_best(best);
         if (lane == 0) {
@@ -1079,7 +1104,7 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
         if (best.idx <= V) best.idx -= row.head;
     }
     if (a.defer) {
-        for (int c = c0 + tid; c < c1; c += NT) a.chunk_tab[(long)b * a.NC + c] = tab[c];
+        for (int c = c0 + tid; c < c1; c += NT) a.chunk_tab[(long)b * a.NC + c] = mass(c);
         if (tid == 0) {
             if (GREEDY) {
                 a.best_v[(long)b * a.NC + part] = best.v;
@@ -1092,7 +1117,7 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     if (S > 1) {  // deliver this part; only the last part to arrive goes on
         Partial* gtab = a.chunk_tab + (long)b * a.NC;
         if (wave == 0) {
-            for (int c = c0 + lane; c < c1; c += kWave) st_dev_partial(gtab + c, tab[c]);
+            for (int c = c0 + lane; c < c1; c += kWave) st_dev_partial(gtab + c, mass(c));
             if (GREEDY && lane == 0) {
                 st_dev(reinterpret_cast<unsigned long long*>(a.best_v + (long)b * a.NC + part),
                        (unsigned long long)__double_as_longlong(best.v));

@@ -199,6 +199,22 @@ def test_row_lookup_over_sequences_without_rows(binding, oracle, vocab, full):
     parity.compare(out, ora, inp["uniforms"], lens)
 
 
+# Shared rows whose parts have 1 .. 9 chunks over after whole rounds of 16, dealt out in quarters (1 .. 4), halves (5 .. 8) or whole: of
+# the last part, which may have fewer, the logits past the last vector and a last chunk of one vector among them.
+@pytest.mark.parametrize("greedy,beta", [(False, 0.8), (True, 0.8), (False, 0.0)])
+@pytest.mark.parametrize("dtype,batch,chunks,more", [("bf16", 64, 75, -5), ("bf16", 64, 67, 8), ("bf16", 100, 42, 0), ("bf16", 127, 43, 1),
+                                                     ("bf16", 128, 36, 9), ("f32", 128, 49, 2), ("f32", 90, 35, 4)])
+def test_chunks_over_are_dealt_out(binding, oracle, dtype, batch, chunks, more, greedy, beta):
+    vocab = chunks * (2048 if dtype == "bf16" else 1024) + more
+    w = recipe("c4", dtype, batch=batch, k_max=2, vocab=vocab)
+    inp = W.generate(w, "cuda", seq_chunk=32)
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam, beta=beta,
+                               temperature=w.temperature, draft_len=inp["draft_len"], greedy=greedy)
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=beta, temperature=w.temperature, greedy=greedy,
+                            want_recovery_logprobs=False)
+    parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
+
+
 # Row-pass slices merged by 16 lanes: 1, 15 .. 17 and 64 slices (the most) of a row, with a remainder.
 @pytest.mark.parametrize("dtype,vocab", [("bf16", 2048), ("bf16", 15 * 2048 + 1), ("bf16", 16 * 2048), ("bf16", 17 * 2048 + 7),
                                          ("bf16", 64 * 2048), ("f32", 63 * 1024 + 1)])
