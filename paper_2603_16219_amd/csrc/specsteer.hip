@@ -649,20 +649,62 @@ struct ChunkScan {
     }
 };
 
+// The chunk that holds the share u of a row's mass.
+struct Found {
+    int c, Estar, last;          // last: u is not below the total (u >= 1 or not a number); c is then the last chunk with any mass
+    double base, target, total;  // mass before the chunk, u's share and all of it, on the scale 2^Estar
+};
+__device__ __forceinline__ Found find_chunk(const Partial* tab, int NC, int lane, double us) {
+    const ChunkScan cs(tab, NC, lane);
+    Found f;
+    f.Estar = cs.Estar;
+    f.total = cs.total;
+    f.target = us * cs.total;
+    f.last = 0;
+    f.base = 0.0;
+    int cfound = -1, clast = -1;
+    double cbase = 0.0, cum = wave_shift_up_f64(cs.incl);
+    const auto meet = [&](int c, double m) {
+        if (m > 0.0) clast = c;
+        const double cum2 = cum + m;
+        if (cfound < 0 && cum2 > f.target) {
+            cfound = c;
+            cbase = cum;
+        }
+        cum = cum2;
+    };
+#pragma unroll
+    for (int i = 0; i < ChunkScan::kHeld; ++i)
+        if (cs.lo + i < cs.hi) meet(cs.lo + i, cs.held[i]);
+    for (int c = cs.lo + ChunkScan::kHeld; c < cs.hi; ++c) meet(c, cs.mass(c));
+    const unsigned long long fmask = __ballot(cfound >= 0);
+    if (fmask) {
+        const int L = first_lane(fmask);
+        f.c = __builtin_amdgcn_readlane(cfound, L);
+        f.base = wave_readlane_f64(cbase, L);
+    } else {
+        f.c = max(wave_max_i32(clast), 0);
+        f.last = 1;
+    }
+    return f;
+}
+
 constexpr int kMassWaves = 4;
 constexpr int kDrawWaves = 4;  // a chunk is one vector of each of the first 4 waves' lanes
 
 // Inverse-CDF draw for one sequence by a workgroup, from the chunk masses `tab` (LDS) of its recovery row: a
 // double-precision scan over the masses finds the chunk holding u*Z, and only that chunk is read again to pick the token,
-// a vector a lane of the first four waves.  Every one of them scans the masses for itself, so that they meet only
-// once, over the sums of their quarters.  What bounds it is the chain of dependent steps, in which the chip is idle: by
+// a vector a lane of the first four waves.  Every one of them scans the masses for itself, so that they meet only once, over the sums
+// of their quarters; with ONE_SCAN, in the workgroups of many rows that share a unit's vector ALUs, one does it for all and the
+// normaliser's logarithm is left to the wave that needs it (1290 sampled rows of V = 42298 24.4 -> 23.7 us, 1224 of V = 56960 27.7 -> 27.1).
+// What bounds it is the chain of dependent steps, in which the chip is idle: by
 // one wave, with four vectors a lane and a logarithm of the token's term, the part behind the table took 3.6 us (8
 // sequences of V = 151936), now 2.7.  A step of one sequence 11.4 -> 11.1 us, of 8 20.3 -> 19.8, 512 steered rows of
 // V = 128256 67.0 -> 66.1, 4352 of them 501 -> 498.
 // Returns log2 Z to the first four waves; one lane writes the per-sequence outputs.
-template <int DT, int VEC, bool PLAIN>
+template <int DT, int VEC, bool PLAIN, bool ONE_SCAN>
 __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, double us, int wave, int lane, const Partial* tab,
-                                             const RecRow<DT, VEC>& row, double* sh_sum, int* sh_any) {
+                                             const RecRow<DT, VEC>& row, double* sh_sum, int* sh_any, Found* sh_found) {
     const void *g = row.g, *sp = row.sp, *sm = row.sm;
     const long nvec = row.nvec, nch = row.nch;
     const int tailc = row.tailc, head = row.head, NC = row.NC;
@@ -670,41 +712,25 @@ __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, dou
     float p[VEC], hg[VEC], hp[VEC], hm[VEC];
     long first = 0;          // vocabulary index of this lane's first logit, counted from the row as it is read
     bool take_last = false;  // the uniform is not below the total mass (u >= 1 or not a number)
+    Found at;
+    if (ONE_SCAN ? wave == 0 : wave < kDrawWaves) at = find_chunk(tab, NC, lane, us);
+    if (ONE_SCAN) {
+        if (wave == 0 && lane == 0) *sh_found = at;
+        __syncthreads();
+        at = *sh_found;
+    }
     if (wave < kDrawWaves) {
-        const ChunkScan cs(tab, NC, lane);
-        target = us * cs.total;
-        int cfound = -1, clast = -1;
-        double cbase = 0.0, cum = wave_shift_up_f64(cs.incl);
-        const auto meet = [&](int c, double m) {
-            if (m > 0.0) clast = c;
-            const double cum2 = cum + m;
-            if (cfound < 0 && cum2 > target) {
-                cfound = c;
-                cbase = cum;
-            }
-            cum = cum2;
-        };
-#pragma unroll
-        for (int i = 0; i < ChunkScan::kHeld; ++i)
-            if (cs.lo + i < cs.hi) meet(cs.lo + i, cs.held[i]);
-        for (int c = cs.lo + ChunkScan::kHeld; c < cs.hi; ++c) meet(c, cs.mass(c));
-        const unsigned long long fmask = __ballot(cfound >= 0);
-        int cstar;
-        if (fmask) {
-            const int L = first_lane(fmask);
-            cstar = __builtin_amdgcn_readlane(cfound, L);
-            base = wave_readlane_f64(cbase, L);
-        } else {
-            cstar = max(wave_max_i32(clast), 0);
-            take_last = true;
-        }
+        const int cstar = at.c;
+        target = at.target;
+        base = at.base;
+        take_last = at.last;
         // The terms are taken relative to the chunk's own exponent reference, 2^(y - Ec), so that the logits that carry
         // the chunk are normal fp32 numbers however far the chunk sits below the row's maximum; `sc` brings them to the
         // scale of the chunk table in double, exactly.
         const int Ec = tab[cstar].E;
         dE = (double)Ec;
         const float nE = -(float)Ec;
-        sc = ldexp(1.0, Ec - cs.Estar);
+        sc = ldexp(1.0, Ec - at.Estar);
 #pragma unroll
         for (int i = 0; i < VEC; ++i) p[i] = 0.f;
         const long v = (long)cstar * (kWave * kChunkSteps) + wave * kWave + lane;
@@ -717,7 +743,7 @@ __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, dou
                 rm = ld_raw<DT, VEC>(sm, v);
             }
         }
-        log2Z = mass_log2<PLAIN>(a, cs.Estar, cs.total);  // while the chunk is on its way
+        if (!ONE_SCAN) log2Z = mass_log2<PLAIN>(a, at.Estar, at.total);  // while the chunk is on its way
         int have = full ? VEC : 0;  // logits this lane holds
         first = v * VEC;
         unpack(rg, hg);
@@ -764,6 +790,7 @@ __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, dou
     if (wave == (found ? wsel : wlast)) {
         const unsigned long long over = __ballot(found && start + incl_l > target), pm = __ballot(ls > 0.0);
         const int L = over ? first_lane(over) : (pm ? 63 - __clzll((long long)pm) : 0);
+        if (ONE_SCAN) log2Z = mass_log2<PLAIN>(a, at.Estar, at.total);
         double cum = wave_shift_up_f64(incl_l) + start;
         if (lane == L) {
             int at = 0;
@@ -788,7 +815,7 @@ __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, dou
             if (a.next_token_logprob) a.next_token_logprob[b] = (float)(kLn2 * (y - log2Z));
         }
     }
-    return log2Z;
+    return ONE_SCAN && wave == 0 && (a.log2z || a.recovery_logprobs) ? mass_log2<PLAIN>(a, at.Estar, at.total) : log2Z;
 }
 
 // The same for greedy decoding, by one wave: the token is known, only the normaliser is needed.
@@ -1006,6 +1033,7 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     __shared__ Partial sh_part[NT == 1024 ? NT / kWave : 1];
     __shared__ double sh_sum[kDrawWaves];
     __shared__ int sh_any[kDrawWaves], sh_last;
+    __shared__ Found sh_found;
     __shared__ double sh_best_v[NT / kWave];
     __shared__ int sh_best_i[NT / kWave];
     __shared__ double sh_log2z;
@@ -1145,9 +1173,12 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     }
 
     // ---- 4
+    // The waves that do not draw end here where nothing is left for them (a barrier waits for the surviving waves only), so that the
+    // next workgroup can start (1290 sampled rows of V = 42298 24.4 -> 24.3 us).
+    if (wave >= kDrawWaves && !a.recovery_logprobs) return;
     if (!GREEDY || wave == 0) {
         const double log2Z = GREEDY ? greedy_token<PLAIN>(a, b, n, lane, tab, row.NC, best)
-                                    : draw_token<DT, VEC, PLAIN>(a, b, n, us, wave, lane, tab, row, sh_sum, sh_any);
+                                    : draw_token<DT, VEC, PLAIN, NT == 512>(a, b, n, us, wave, lane, tab, row, sh_sum, sh_any, &sh_found);
         if (tid == 0) {
             if (a.log2z) a.log2z[b] = log2Z;
             sh_log2z = log2Z;
@@ -1243,7 +1274,7 @@ __global__ __launch_bounds__(kLogprobThreads) void row_draw_kernel(const RecArgs
     __syncthreads();
     if (GREEDY && wave > 0) return;
     if (GREEDY) greedy_token<PLAIN>(a, b, n, lane, tab, row.NC, best);
-    else draw_token<DT, VEC, PLAIN>(a, b, n, us, wave, lane, tab, row, sh_sum, sh_any);
+    else draw_token<DT, VEC, PLAIN, false>(a, b, n, us, wave, lane, tab, row, sh_sum, sh_any, nullptr);
 }
 
 // ------------------------------------------------------------------ kernel: log-prob rows
