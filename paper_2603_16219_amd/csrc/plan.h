@@ -65,7 +65,8 @@ constexpr int kSplitMaxBatch = 128;  // workspace is reserved for shared recover
 //     them like that, since a chunk's arithmetic (some 1.5 us alone on a SIMD) takes as long as four of them
 //     sharing one.  With 8 sequences of V = 151936 (75 chunks) the recovery kernel goes from 17.2 us (40
 //     workgroups of 16 waves) to 11.5; beyond that line the parts' repeated ratio tests weigh more than the
-//     spread gains (64 such sequences: 71.2 us a step in 19 parts, 69.9 in 3, 72.4 in 4 uneven ones).
+//     spread gains (64 such sequences: 69.4 us a step in 19 parts,
+//     68.0 in 4).
 //     Not where one 16-wave workgroup takes the row in a round and the hand-over between parts, or the ratio test by
 //     fewer waves, costs more (us a step of 8 sequences, 16 waves -> spread): from 5 to 8 chunks (4 drafts, V = 6166
 //     11.4 -> 12.7, V = 14400 12.8 -> 13.4; 10 chunks 14.5 -> 14.1); up to 16 with no draft, where parts cost a

@@ -15,8 +15,8 @@
 //                  LDS at kernel start (prep_rows does it once in global memory for
 //                  batches too large for LDS).
 //   accept_recover one workgroup per sequence, or several.  Each (position, tensor) pair
-//                  gets 16 lanes that merge the row's slice partials and gather the draft
-//                  token's logit; wave 0 applies the ratio test and finds the first
+//                  gets 16 lanes that merge the row's slice partials and take the draft
+//                  token's logit, left there by the row pass; wave 0 applies the ratio test and finds the first
 //                  rejection with a ballot.  All waves then stream the three logit rows
 //                  of the rejected (or bonus) position once, forming the recovery
 //                  exponent in double (in fp32, as the row pass does, when beta == 0 leaves
@@ -28,7 +28,9 @@
 //                  several workgroups; the one that delivers its chunk masses last
 //                  draws the token (see accept_recover_kernel; hand-over by write-through
 //                  stores and an arrival counter, without cache-wide fences).
-//   recovery_logprob  the full log-prob rows, a second sweep over the rows at n_b, only on request.
+//   row_mass, row_draw  the same without drafts, for rows too long for one workgroup each: the chunk masses, and the draw;
+//                  row_draw also writes the full log-prob rows beside the draw, on request
+//   recovery_logprob  the full log-prob rows where no workgroup shares a recovery row, a second sweep over the rows at n_b
 //
 // Precision: logits are widened exactly; sums of exponentials are accumulated in
 // fp32 (one rounding per term, pairwise across lanes), every per-row scalar
