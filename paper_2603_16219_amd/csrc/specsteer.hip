@@ -699,10 +699,9 @@ constexpr int kDrawWaves = 4;  // a chunk is one vector of each of the first 4 w
 // a vector a lane of the first four waves.  Every one of them scans the masses for itself, so that they meet only once, over the sums
 // of their quarters; with ONE_SCAN, in the workgroups of many rows that share a unit's vector ALUs, one does it for all and the
 // normaliser's logarithm is left to the wave that needs it (1290 sampled rows of V = 42298 24.4 -> 23.7 us, 1224 of V = 56960 27.7 -> 27.1).
-// What bounds it is the chain of dependent steps, in which the chip is idle: by
-// one wave, with four vectors a lane and a logarithm of the token's term, the part behind the table took 3.6 us (8
-// sequences of V = 151936), now 2.7.  A step of one sequence 11.4 -> 11.1 us, of 8 20.3 -> 19.8, 512 steered rows of
-// V = 128256 67.0 -> 66.1, 4352 of them 501 -> 498.
+// What bounds it is the chain of dependent steps, in which the chip is idle: by one wave, with four vectors a lane, the part
+// behind the table took 3.6 us (8 sequences of V = 151936), now 2.9.  512 steered rows of V = 128256 67.0 -> 66.1 us, 4352 of them
+// 501 -> 498.
 // Returns log2 Z to the first four waves; one lane writes the per-sequence outputs.
 template <int DT, int VEC, bool PLAIN, bool ONE_SCAN>
 __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, double us, int wave, int lane, const Partial* tab,
@@ -711,7 +710,7 @@ __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, dou
     const long nvec = row.nvec, nch = row.nch;
     const int tailc = row.tailc, head = row.head, NC = row.NC;
     double incl_l = 0.0, base = 0.0, target = 0.0, dE = 0.0, sc = 0.0, ls = 0.0, log2Z = 0.0;
-    float p[VEC], hg[VEC], hp[VEC], hm[VEC];
+    float p[VEC];
     long first = 0;          // vocabulary index of this lane's first logit, counted from the row as it is read
     bool take_last = false;  // the uniform is not below the total mass (u >= 1 or not a number)
     Found at;
@@ -746,6 +745,7 @@ __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, dou
             }
         }
         if (!ONE_SCAN) log2Z = mass_log2<PLAIN>(a, at.Estar, at.total);  // while the chunk is on its way
+        float hg[VEC], hp[VEC], hm[VEC];
         int have = full ? VEC : 0;  // logits this lane holds
         first = v * VEC;
         unpack(rg, hg);
@@ -792,28 +792,34 @@ __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, dou
     if (wave == (found ? wsel : wlast)) {
         const unsigned long long over = __ballot(found && start + incl_l > target), pm = __ballot(ls > 0.0);
         const int L = over ? first_lane(over) : (pm ? 63 - __clzll((long long)pm) : 0);
-        if (ONE_SCAN) log2Z = mass_log2<PLAIN>(a, at.Estar, at.total);
+        // Lane L's last term with any mass stands if none reaches the target (the chunk's largest logit is within one unit of Ec, so one
+        // exists unless the row holds something that is not a number; the index is valid then too).
         double cum = wave_shift_up_f64(incl_l) + start;
-        if (lane == L) {
-            int at = 0;
-            bool done = false;
-            float tg = hg[0], tp = hp[0], tm = hm[0];
+        int at_i = 0;
+        float term = 0.f;
+        bool done = false;
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) {
-                cum += (double)p[i] * sc;
-                if (!done && p[i] > 0.f) {  // the last of them stands if none reaches the target
-                    at = i;
-                    tg = hg[i];
-                    tp = hp[i];
-                    tm = hm[i];
-                    done = found && cum > target;
-                }
+        for (int i = 0; i < VEC; ++i) {
+            cum += (double)p[i] * sc;
+            if (!done && p[i] > 0.f) {
+                at_i = i;
+                term = p[i];
+                done = found && cum > target;
             }
-            const double y = pm ? (PLAIN ? (double)tg * a.c : rec_y(tg, tp, tm, a.c, a.bc)) : dE;
+        }
+        // The token's exponent is taken back from its term, whose rounding the masses hold too: where one token carries the row it
+        // drops out of the difference, which the logits' own exponent would leave in the log-prob (1e-7).
+        double lg;
+        if (ONE_SCAN) {  // one logarithm for both, in lane L and beside it
+            lg = log2(lane == L ? (term > 0.f ? (double)term : 1.0) : at.total);
+            log2Z = (double)at.Estar + wave_readlane_f64(lg, L ^ 1) + (PLAIN ? a.rho : 0.0) * (double)at.Estar;
+        } else {
+            lg = log2(term > 0.f ? (double)term : 1.0);
+        }
+        if (lane == L) {
+            const double y_hi = dE + lg, y = PLAIN ? y_hi + a.rho * y_hi : y_hi;
             a.accepted_len[b] = n;
-            // the chunk's largest logit is within one unit of Ec, so a positive term always exists unless the row holds
-            // something that is not a number; keep the index valid then
-            a.next_token[b] = (int32_t)min(max(first + at - head, 0l), (long)a.V - 1);
+            a.next_token[b] = (int32_t)min(max(first + at_i - head, 0l), (long)a.V - 1);
             if (a.next_token_logprob) a.next_token_logprob[b] = (float)(kLn2 * (y - log2Z));
         }
     }

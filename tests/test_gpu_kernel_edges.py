@@ -132,6 +132,24 @@ def test_greedy_picks_the_first_of_the_largest(binding, dtype, vocab, beta):
     assert out["token"].tolist() == [*edges, 0]
 
 
+# Rows that one token carries: its term and the row's mass hold the same rounded exponential (1.2e-7), which has to drop out of the
+# log-prob.  40 others at e^-22 of it are 1.1e-8 of the mass, less than half a unit of the fp32 sums, and may be lost: 1.1e-8 + the store.
+@pytest.mark.parametrize("beta", [0.0, 0.8])
+@pytest.mark.parametrize("dtype,batch,vocab", [("bf16", 64, 40000), ("bf16", 300, 9000), ("f32", 64, 40001), ("f32", 5, 200000)])
+def test_logprob_of_a_token_that_carries_its_row(binding, dtype, batch, vocab, beta):
+    gen = torch.Generator("cuda").manual_seed(batch + vocab)
+    top = (torch.rand(batch, generator=gen, device="cuda") * 20 - 10).to(W.torch_dtype(dtype))
+    at = torch.randint(0, vocab, (batch,), generator=gen, device="cuda")
+    G = torch.full((batch, vocab), float("-inf"), device="cuda", dtype=top.dtype)
+    G[:, ::vocab // 40] = (top.float() - 22).to(top.dtype)[:, None]
+    G[torch.arange(batch), at] = top
+    S = torch.zeros_like(G)
+    out = binding.steer_rows(G, S, S, torch.full((batch,), 0.5, device="cuda"), beta=beta, temperature=0.7)
+    lp = torch.log_softmax(G.double() / 0.7, -1)[torch.arange(batch), at]
+    assert torch.equal(out["token"].long(), at)
+    assert (out["token_logprob"].double() - lp).abs().max() <= 2e-8
+
+
 # The draw reads its chunk by four waves, a vector a lane: a token at the first and last logit of a lane, a wave's quarter and
 # a chunk and among the logits past the last vector, each with a uniform in the middle of its interval; uniforms of 0, of 1 and not
 # a number, where the last token with positive probability (`keep` - 1) lies in an earlier quarter than the chunk's last.
