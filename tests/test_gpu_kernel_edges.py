@@ -200,6 +200,23 @@ def test_draft_logits_at_the_edges_of_vectors_groups_and_slices(binding, dtype, 
             assert (out["draft_logprobs"][b, :n, x].double() - lp).abs().max() <= 1e-5
 
 
+# A block that fits the static scratch only without the space of the draft tokens' logits: they are gathered from the rows.
+def test_draft_logits_are_gathered_where_there_is_no_space_for_them(binding, oracle):
+    w = recipe("c4", "bf16", batch=400, k_max=1000, vocab=40)
+    inp = W.generate(w, "cuda", seq_chunk=50)
+    p = binding.make_params(400, 1000, 40, torch.bfloat16, lam=w.lam, beta=w.beta, temperature=w.temperature)
+    need = binding.workspace_bytes(p)
+    assert need <= binding.STATIC_SCRATCH_BYTES < need + 400 * 1000 * 8
+    inp["draft_len"] = torch.tensor([(37 * i) % 1001 for i in range(400)], dtype=torch.int32, device="cuda")
+    inp["draft"][2, 0] = 40  # flagged
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam, beta=w.beta,
+                               temperature=w.temperature, draft_len=inp["draft_len"], want_draft_logprobs=True)
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, want_recovery_logprobs=False,
+                            num_threads=8)
+    parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
+    assert out["accepted_len"][2].item() == -1
+
+
 # A ragged batch's rows are looked up 64 sequences at a time from the last row's on: runs of 61 .. 129 sequences without a row
 # between two that have some, at the start and at the end; rows of one slice and of several, fewer of them than waves and more.
 @pytest.mark.parametrize("vocab", [40, 33 * 2048 + 3])
