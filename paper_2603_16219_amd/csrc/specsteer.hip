@@ -182,6 +182,9 @@ struct RowWindow {
     int kmax, t_lo, t_hi;
 };
 
+// In the place of a draft token's logit: its id is outside the vocabulary.  A NaN that no bf16 logit is widened to.
+constexpr unsigned kNoToken = 0x7FC0BAD1u;
+
 // What the verdict kernel leaves per sequence: its first-rejection index (>= 0; final, Algorithm 1 has left its
 // loop), or one of
 constexpr int kInPlay = -1;   // nothing rejected so far and positions left to test
@@ -243,7 +246,7 @@ struct LseArgs {
     const int32_t* row_off;    // else: the row list, [B+1], of a batch too large for the one in LDS
     Partial* partial;          // [B][win.t_hi - win.t_lo][2][NS]
     const int32_t* draft;
-    float* draft_logit;        // [B][kmax][2] the draft token's logit in each tensor; NULL: gathered by who needs it
+    float* draft_logit;        // [B][kmax][2] the draft token's logit in each tensor, or kNoToken; NULL: gathered by who needs it
     long sb, st;               // element strides
     int B, kmax, V, NS;
     int slice_vecs;            // 16-byte vectors per slice
@@ -260,6 +263,7 @@ struct LseArgs {
 // The wave that meets the draft token's vector leaves its logit beside the partials: it is in registers here, while the
 // ratio test would gather it from HBM behind the load of the draft id, a round trip that every sequence of that launch
 // waits for.  The id itself is looked at behind the item's first loads: before them it cost 300 ragged sequences 2 us.
+// For an id outside the vocabulary the first slice leaves kNoToken, so that the ratio test needs no ids at all.
 template <int DT, int VEC, int kUnroll>
 __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
     extern __shared__ int lds_off[];
@@ -324,6 +328,7 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
         const auto find_y = [&]() {
             const int y = __builtin_amdgcn_readfirstlane(y_load);
             ye = y >= 0 && y < a.V ? y + head : -1;
+            if (ye < 0 && a.draft_logit && k == 0 && lane == 0) *y_out = __uint_as_float(kNoToken);
             yv = ye >= 0 && ye / VEC < v1 ? ye / VEC - (int)v0 : -1;
         };
 
@@ -384,7 +389,7 @@ struct RecArgs {
     const int32_t* draft_len;
     const float* uniforms;
     const Partial* partial;  // slice partials of the window this launch tests, [B][t_hi - t_lo][2][NS]
-    const float* draft_logit;  // [B][kmax][2] the draft tokens' logits, or NULL: gathered from the rows
+    const float* draft_logit;  // [B][kmax][2] the draft tokens' logits (kNoToken: not in the vocabulary), or NULL: gathered from the rows
     int NS;                  // slices per row
     int t_lo, t_hi;          // the window; t_hi == k_max for the last one
     int32_t* state;          // several windows: what the verdicts so far have found; else NULL
@@ -852,9 +857,9 @@ __device__ __forceinline__ const Partial* partials_of(const RecArgs& a, int b, i
 // Returns the first rejected position, Kt if none, to every thread; kFlagged if a draft id among those positions is outside
 // the vocabulary or `bad` is set in any thread.  sh: kRatioWords<NT> words of LDS.
 //
-// What bounds it is its chain of memory round trips, while nothing else runs on the compute unit: everything that does not depend
-// on the length is loaded before the length is known (rows past it hold leftovers, which are not used), and the draft tokens' logits
-// lie beside the partials.  With the logits gathered behind the ids behind the length the first rejection of a block was known
+// What bounds it is its chain of memory round trips, while nothing else runs on the compute unit: everything in the workspace is
+// loaded before the length is known (past it there are leftovers, which are not used), the draft tokens' logits among it, which
+// lie beside the partials.  Draft slots and rows past the length belong to the caller and are never read.  With the logits gathered behind the ids behind the length the first rejection of a block was known
 // 2.6 us after the launch's first workgroup; the recovery kernel of one sequence of V = 32000 fp32 takes 8.4 us now (9.0 before), of 8 of V = 151936 9.7
 // (10.7), a step of the first 10.6 (11.1), of 64 sequences 0.3 to 0.5 less.
 template <int NT>
@@ -866,23 +871,24 @@ __device__ __forceinline__ int ratio_test_block(const RecArgs& a, int b, int T0,
     const float* un = a.uniforms + (long)b * (kmax + 1);
     const float u0 = T0 + lane < Tend ? un[T0 + lane] : 0.f;  // wave 0's first block, on its way while the rows are merged
     const int* draft = a.draft + (long)b * kmax;
-    const auto logit = [&](int q, int y) {  // of the draft token at (position, tensor) pair q
-        if (a.draft_logit) return a.draft_logit[(long)b * kmax * 2 + q];
+    const auto gather = [&](int q) {  // the draft token's logit at (position, tensor) pair q < 2 * Kt, or kNoToken
+        const int y = draft[q >> 1];
         const long off = (long)b * a.sb + (long)(q >> 1) * a.st;
-        return y >= 0 && y < V ? ld_elem<DT>(row_ptr<DT>(q & 1 ? a.Sm : a.G, off), y) : 0.f;
+        return y >= 0 && y < V ? ld_elem<DT>(row_ptr<DT>(q & 1 ? a.Sm : a.G, off), y) : __uint_as_float(kNoToken);
     };
+    const float* left = a.draft_logit ? a.draft_logit + (long)b * kmax * 2 : nullptr;
+    const auto no_token = [](float h) { return __float_as_uint(h) == kNoToken; };
     const auto logprob = [&](float h, Partial row) { return kLn2 * ((double)h * a.c - row_log2(row, a.rho)); };
     const int q0 = 2 * T0 + (tid >> 4);
     if (2 * (Tend - T0) <= NT / 16) {
-        int y = 0;
+        float h = 0.f;
         double v = 0.0;
         if (q0 < 2 * Tend) {
-            y = draft[q0 >> 1];
-            const float h = logit(q0, y);
+            if (left) h = left[q0]; else if (q0 < 2 * Kt) h = gather(q0);
             v = logprob(h, merge_partials_row16(partials_of(a, b, q0 >> 1, q0 & 1), a.NS, l));
         }
         if (q0 < 2 * Kt) {
-            bad = bad || y < 0 || y >= V;
+            bad = bad || no_token(h);  // not before the slices are on their way
             if (l == 0) lp[q0] = v;
         }
     } else {
@@ -897,9 +903,9 @@ __device__ __forceinline__ int ratio_test_block(const RecArgs& a, int b, int T0,
         __syncthreads();
         for (int q = 2 * T0 + tid; q < 2 * Kt; q += NT) {
             const Partial m{__double2hiint(lp[q]), __int_as_float(__double2loint(lp[q]))};
-            const int y = draft[q >> 1];
-            bad = bad || y < 0 || y >= V;
-            lp[q] = logprob(logit(q, y), m);
+            const float h = left ? left[q] : gather(q);
+            bad = bad || no_token(h);
+            lp[q] = logprob(h, m);
         }
     }
     const bool any = __ballot(bad) != 0ull;

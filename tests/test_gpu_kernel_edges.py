@@ -217,6 +217,38 @@ def test_draft_logits_are_gathered_where_there_is_no_space_for_them(binding, ora
     assert out["accepted_len"][2].item() == -1
 
 
+# Draft slots and rows behind a sequence's length are the caller's: ids there are outside the vocabulary, rows not a number.  Ids outside
+# the vocabulary at the first and the last valid slot flag their sequence.  With a pair of lanes' groups to every position and
+# with rounds, in one window and two, with the space of the draft tokens' logits and (24000 sequences) without it.
+@pytest.mark.parametrize("batch,k_max,vocab", [(3, 1, 5), (5, 8, 3001), (5, 9, 3001), (3, 32, 40001), (6, 33, 3001), (300, 16, 801),
+                                               (300, 17, 801), (64, 20, 104900), (24000, 16, 40), (24000, 16, 700)])
+def test_slots_behind_the_length_are_ignored_and_ids_outside_the_vocabulary_flag(binding, oracle, batch, k_max, vocab):
+    w = recipe("c4", "bf16", batch=batch, k_max=k_max, vocab=vocab)
+    inp = W.generate(w, "cuda", seq_chunk=16 if vocab > 4000 else 600)
+    gen = torch.Generator("cuda").manual_seed(batch + k_max)
+    lens = torch.randint(0, k_max + 1, (batch,), generator=gen, device="cuda", dtype=torch.int32)
+    lens[0], lens[1], lens[2] = k_max, k_max, 1
+    behind = torch.arange(k_max, device="cuda") >= lens[:, None]
+    odd = torch.tensor([-1, vocab, -2**31, 2**31 - 1, vocab + 1], dtype=torch.int32, device="cuda")
+    inp["draft"] = torch.where(behind, odd.repeat(batch * k_max // 5 + 1)[:batch * k_max].view(batch, k_max), inp["draft"])
+    for k in ("G", "S_ctx", "S_noctx"):
+        for t in range(1, k_max + 1):
+            inp[k][lens < t, t] = float("nan")
+    inp["draft"][1, k_max - 1], inp["draft"][2, 0] = vocab, -1
+    inp["draft_len"] = lens
+    if batch == 24000:
+        p = binding.make_params(batch, k_max, vocab, torch.bfloat16, lam=w.lam, beta=w.beta, temperature=w.temperature)
+        assert binding.workspace_bytes(p) <= binding.STATIC_SCRATCH_BYTES < binding.workspace_bytes(p) + batch * k_max * 8
+        assert binding.first_window(p) == (4 if vocab == 700 else 16)
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam, beta=w.beta,
+                               temperature=w.temperature, draft_len=lens)
+    assert out["accepted_len"][1:3].tolist() == [-1, -1]
+    assert (out["accepted_len"] >= 0).sum().item() == batch - 2
+    seqs = torch.arange(0, batch, max(1, batch // 300), device="cuda")
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, seqs=seqs, want_recovery_logprobs=False)
+    parity.compare(out, ora, inp["uniforms"], lens, seqs=seqs)
+
+
 # A ragged batch's rows are looked up 64 sequences at a time from the last row's on: runs of 61 .. 129 sequences without a row
 # between two that have some, at the start and at the end; rows of one slice and of several, fewer of them than waves and more.
 @pytest.mark.parametrize("vocab", [40, 33 * 2048 + 3])
