@@ -1383,7 +1383,14 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     RecShape shape = recovery_shape(B, ra.NC, kmax, device_cu_count(), pl.split);
     if (kmax == 0 && shape.part_chunks < ra.NC && rows_in_one_launch(B, ra.NC, DT, ra.plain != 0, ra.greedy != 0)) shape = RecShape{1024, ra.NC};
     const bool rows_inside = recovery_logprobs && logprobs_in_recovery(B, kmax, V, DT == SS_BF16 ? 2 : 4);
-    if (rows_inside && shape.part_chunks < ra.NC) shape = RecShape{1024, ra.NC};
+    // Log-prob rows that lie on the logits (fp32 rows without drafts, in place): the token is drawn before any of them is written
+    const size_t esz = DT == SS_BF16 ? 2 : 4, span = ((size_t)(B - 1) * ra.sb + (size_t)kmax * ra.st + V) * esz;
+    const auto on_rows = [&](const void* t) {
+        const uintptr_t in = reinterpret_cast<uintptr_t>(t), out = reinterpret_cast<uintptr_t>(recovery_logprobs);
+        return out < in + span && in < out + (size_t)B * V * sizeof(float);
+    };
+    const bool in_place = recovery_logprobs && (on_rows(ra.G) || on_rows(ra.recSp) || on_rows(ra.recSm));
+    if ((rows_inside || in_place) && shape.part_chunks < ra.NC) shape = RecShape{1024, ra.NC};
     ra.recovery_logprobs = rows_inside ? recovery_logprobs : nullptr;
     ra.log2z = recovery_logprobs && !rows_inside ? reinterpret_cast<double*>(ws + pl.off_log2z) : nullptr;
     ra.part_chunks = shape.part_chunks;

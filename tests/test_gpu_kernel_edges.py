@@ -68,6 +68,25 @@ def test_logprob_rows_beside_the_draw(binding, oracle, dtype, batch, vocab, gree
     assert out["accepted_len"][1].item() == -1
 
 
+# fp32 rows without a draft, their log-probs written over the generalist's or a specialist's logits: the token is drawn first, whether
+# the rows come from the recovery launch (16384) or later.
+@pytest.mark.parametrize("over", ["G", "S_ctx", "S_noctx"])
+@pytest.mark.parametrize("batch,vocab,beta", [(5, 16384, 0.8), (8, 70000, 0.8), (100, 200001, 0.8), (8, 200001, 0.0)])
+def test_logprob_rows_in_place(binding, batch, vocab, beta, over):
+    gen = torch.Generator("cuda").manual_seed(batch)
+    rows = {k: torch.randn(batch, 1, vocab, generator=gen, device="cuda") for k in ("G", "S_ctx", "S_noctx")}
+    u = torch.rand(batch, 1, generator=gen, device="cuda")
+    none = torch.empty(batch, 0, dtype=torch.int32, device="cuda")
+    want = binding.verify_block(*rows.values(), none, u, beta=beta, want_recovery_logprobs=True)
+    p = binding.make_params(batch, 0, vocab, torch.float32, lam=0.5, beta=beta, temperature=1.0)
+    ws = torch.empty(binding.workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    out = {k: torch.empty_like(want[k]) for k in ("accepted_len", "next_token", "next_token_logprob")}
+    binding.verify_block_raw(*rows.values(), None, None, u, p, *out.values(), rows[over], None, ws)
+    assert torch.equal(out["next_token"], want["next_token"]) and torch.equal(out["accepted_len"], want["accepted_len"])
+    assert torch.allclose(out["next_token_logprob"], want["next_token_logprob"], rtol=0, atol=2e-6)
+    assert torch.allclose(rows[over][:, 0], want["recovery_logprobs"], rtol=0, atol=4e-6)
+
+
 # The recovery launch: 4-wave workgroups of one chunk a wave while batch x chunks <= 8 x 256 (a single workgroup of 16 waves
 # for 5 .. 8 chunks), then 16-wave parts of
 # equal rounds up to 128 sequences, then one workgroup of 16 waves per sequence up to 256 and of 8 beyond.  A chunk is
