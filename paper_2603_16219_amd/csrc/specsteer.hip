@@ -283,9 +283,13 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
     constexpr long kGroup = (long)kWave * kUnroll;
 
     // The wave's items are waves_total apart: slice and row go on from those before without a division, and the sequence of
-    // a ragged batch's row is looked up from the last one on, 64 at a time.  Divisions in 64 bits and a search by halves, eight
+    // a ragged batch's row is looked up from the last one on, first among the next 64, then among 64 places that part all
+    // that are left.  Divisions in 64 bits and a search by halves, eight
     // dependent reads of LDS, stood before the first load of every item, which counts where items are short: 16 sequences of up to
-    // 8 positions 26.2 -> 25.1 us a step, 40 ragged ones 31.6 -> 30.4, 300 131.5 -> 129.5, 256 of V = 128256 168.5 -> 166.6.
+    // 8 positions 26.2 -> 25.1 us a step, 40 ragged ones 31.6 -> 30.4, 300 131.5 -> 129.5, 256 of V = 128256 164.2 -> 162.7.  64 at a
+    // time to the end lost to halves where the rows of a wave lie thousands of sequences apart (the list in global memory; by halves,
+    // 64 at a time, now): 58940 sequences of up to 16 positions, V = 2398 2658, 3146 and 2204 us, 27250 of 2, V = 7168 647, 717, 604,
+    // 8000 of 16, V = 8000 625, 629, 599.
     const unsigned NS = (unsigned)a.NS;
     unsigned k_ = (unsigned)wave_global % NS, rx = (unsigned)wave_global / NS;
     const unsigned dk = (unsigned)waves_total % NS, drx = (unsigned)waves_total / NS;
@@ -298,13 +302,20 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
         const int k = (int)k_, x = (int)(rx & 1u), r = (int)(rx >> 1);
         int t;
         if (ragged) {
-            for (;;) {  // the largest b with off[b] <= r; off[B] = R > r
-                const int o = off[min(b + 1 + lane, a.B)];
+            // the largest b with off[b] <= r; off[B] = R > r.  Beyond the next 64, the 64 places that part what is left evenly
+            int hi = a.B, step = 1;
+            for (;;) {
+                const int o = off[min(b + step * (1 + lane), hi)];
                 const int n = __popcll(__ballot(o <= r));
-                if (n == 0) break;
-                b += n;
-                off_b = __builtin_amdgcn_readlane(o, n - 1);
-                if (n < kWave) break;
+                if (n) {
+                    b += n * step;
+                    off_b = __builtin_amdgcn_readlane(o, n - 1);
+                }
+                if (n < kWave) {
+                    if (step == 1) break;
+                    hi = min(b + step, hi);
+                }
+                step = (hi - b + kWave - 1) / kWave;
             }
             t = a.win.t_lo + (r - off_b);
         } else {

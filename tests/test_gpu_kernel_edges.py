@@ -285,6 +285,24 @@ def test_row_lookup_over_sequences_without_rows(binding, oracle, vocab, full):
     parity.compare(out, ora, inp["uniforms"], lens)
 
 
+# The same over thousands of sequences without rows, in LDS (up to 8192 sequences) and in global memory: runs of 63 .. 65 x 64 sequences
+# and one more or less, rows that only the first or the last sequence has.
+@pytest.mark.parametrize("batch", [8192, 8193, 20011])
+@pytest.mark.parametrize("full", [(0, 64, 65, 4096, 4160, 4161, 8191), (0,), (-1,), (63, 4095, 4097, -2), (1, 128, 129, -65, -64, -1)])
+def test_row_lookup_over_thousands_of_sequences_without_rows(binding, oracle, batch, full):
+    w = recipe("c4", "bf16", batch=batch, k_max=2, vocab=9)
+    inp = W.generate(w, "cuda", seq_chunk=4096)
+    at = torch.tensor([b % batch for b in full], device="cuda")
+    lens = torch.zeros(batch, dtype=torch.int32, device="cuda")
+    lens[at] = torch.arange(len(full), dtype=torch.int32, device="cuda") % 2 + 1
+    inp["draft_len"] = lens
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam, beta=w.beta,
+                               temperature=w.temperature, draft_len=lens, want_draft_logprobs=True)
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, seqs=at, want_recovery_logprobs=False)
+    parity.compare(out, ora, inp["uniforms"], lens, seqs=at)
+    assert torch.all((out["draft_logprobs"] == 0).all(-1) == (torch.arange(2, device="cuda") >= lens[:, None]))
+
+
 # Shared rows whose parts have 1 .. 9 chunks over after whole rounds of 16, dealt out in quarters (1 .. 4), halves (5 .. 8) or whole: of
 # the last part, which may have fewer, the logits past the last vector and a last chunk of one vector among them.
 @pytest.mark.parametrize("greedy,beta", [(False, 0.8), (True, 0.8), (False, 0.0)])
