@@ -135,7 +135,10 @@ size_t specsteer_workspace_bytes(const ss_params *params);
  *   workspace          device scratch, 256-byte aligned, at least
  *                      specsteer_workspace_bytes(params) bytes; contents need no
  *                      initialisation and are garbage afterwards.  Calls that
- *                      may overlap in time need distinct workspaces.
+ *                      may overlap in time need distinct workspaces.  (A block of
+ *                      more than 512 draft positions also runs, with the same
+ *                      outputs, in a workspace that lacks the 8 bytes a position,
+ *                      rounded up to 256, which keep the draft tokens' logits.)
  *   stream             a hipStream_t passed as void*; NULL is the default stream.
  *
  * Errors.  Argument errors are detected on the host before anything is

@@ -294,4 +294,17 @@ inline Plan make_plan(const ss_params* p) {
     return small.bytes <= (size_t)SS_STATIC_SCRATCH_BYTES ? small : whole;
 }
 
+// The plan for a workspace of `bytes`, the richest that fits it; make_plan's, which the caller has to refuse, if none does.  Where
+// only a plan without the draft tokens' logits fits the static scratch a larger block asks for less than a smaller one (349
+// sequences of 1000 drafts, V = 40: 8.0 MiB, 350: 5.3), and a caller that holds what the larger needs can run the smaller without them too.
+// Up to kDraftLogitsAsked positions a block lies too far below the static scratch's limit (at most 3.1 MiB) for that, and
+// what make_plan says is what it takes.
+constexpr long kDraftLogitsAsked = 512;
+inline Plan make_plan(const ss_params* p, size_t bytes) {
+    const Plan pl = make_plan(p);
+    if (bytes >= pl.bytes || !pl.draft_logit || (long)p->batch * p->k_max <= kDraftLogitsAsked) return pl;
+    const Plan lean = lay_out(p, true, false);
+    return lean.bytes <= bytes ? lean : pl;
+}
+
 }  // namespace

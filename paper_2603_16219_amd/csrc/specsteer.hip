@@ -1502,11 +1502,10 @@ ss_status verify_block_impl(const void* G, const void* S_ctx, const void* S_noct
     if (((reinterpret_cast<uintptr_t>(G) | reinterpret_cast<uintptr_t>(S_ctx) | reinterpret_cast<uintptr_t>(S_noctx)) &
          (esz - 1)) != 0)
         return SS_ERR_STRIDE;
-    const Plan pl = make_plan(params);
+    const Plan pl = make_plan(params, workspace_bytes);
     if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 || workspace_bytes < pl.bytes)
         return SS_ERR_WORKSPACE;
     if (params->batch == 0) return SS_OK;
-
 
     char* ws = static_cast<char*>(workspace);
 

@@ -548,3 +548,29 @@ def test_topk_of_equal_logits_fills_its_buffers(binding, dtype, count, spread):
     value, index = torch.sort(h, dim=-1, descending=True, stable=True)
     got_i, got_v = binding.cloud_topk(G, M, torch.zeros(2, dtype=torch.int32, device="cuda"), beta=0.5, topk=k)
     assert torch.equal(got_i.long(), index[:, :k]) and torch.equal(got_v, value[:, :k].float())
+
+
+# A workspace that lacks the space of the draft tokens' logits (more than 512 positions): they are gathered, with the same outputs bit
+# for bit, and nothing is written behind it; in one window and several, with shared recovery rows and with one workgroup each.
+@pytest.mark.parametrize("batch,k_max,vocab", [(1, 513, 3001), (27, 19, 40001), (128, 5, 70000), (300, 17, 801), (64, 20, 104900)])
+def test_a_workspace_without_space_for_the_draft_logits(binding, batch, k_max, vocab):
+    w = recipe("c4", "bf16", batch=batch, k_max=k_max, vocab=vocab)
+    inp = W.generate(w, "cuda", seq_chunk=16)
+    lens = torch.randint(0, k_max + 1, (batch,), generator=torch.Generator("cuda").manual_seed(batch), device="cuda", dtype=torch.int32)
+    lens[0] = k_max
+    if batch > 2:
+        inp["draft"][0, k_max - 1] = vocab  # flagged by its last position
+    p = binding.make_params(batch, k_max, vocab, torch.bfloat16, lam=w.lam, beta=w.beta, temperature=w.temperature)
+    need = binding.workspace_bytes(p)
+    lean = need - (8 * batch * k_max + 255) // 256 * 256
+    outs = []
+    for n in (need, lean):
+        ws = torch.full((need + 256,), 0xAB, dtype=torch.uint8, device="cuda")
+        out = [torch.full((batch,), -7, dtype=dt, device="cuda") for dt in (torch.int32, torch.int32, torch.float32)]
+        binding.verify_block_raw(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], lens, inp["uniforms"], p, *out, None, None, ws[:n])
+        assert torch.all(ws[n:] == 0xAB)
+        outs.append(out)
+    assert all(torch.equal(torch.nan_to_num(a), torch.nan_to_num(b)) for a, b in zip(*outs))
+    assert (outs[0][0] >= 0).sum().item() == batch - (batch > 2)
+    with pytest.raises(binding.SpecSteerError):
+        binding.verify_block_raw(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], lens, inp["uniforms"], p, *outs[1], None, None, ws[:lean - 256])

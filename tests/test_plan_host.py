@@ -35,6 +35,13 @@ int main() {
         ss_params p = {};  // B kmax V dtype flags lambda, then what is asked
         if (std::scanf("%d %d %d %d %u %f", &p.batch, &p.k_max, &p.vocab, &p.dtype, &p.flags, &p.lambda) != 6) return 1;
         p.beta = p.temperature = 1.f;
+        if (!std::strcmp(what, "within")) {  // bytes of the workspace: whether they will do, and with the draft tokens' logits
+            long bytes;
+            if (std::scanf("%ld", &bytes) != 1) return 1;
+            const Plan pl = make_plan(&p, (size_t)bytes);
+            std::printf("%d %d\n", pl.bytes <= (size_t)bytes ? 1 : 0, pl.draft_logit ? 1 : 0);
+            continue;
+        }
         const Plan pl = make_plan(&p);
         if (!std::strcmp(what, "parts")) {  // cus odd
             int cus, odd;
