@@ -523,7 +523,11 @@ def test_split_recovery_shapes(binding, oracle, name, batch, vocab, dtype):
     w = dataclasses.replace(W.scaled(W.WORKLOADS[name], batch=batch, vocab=vocab, name=f"split-{name}-{batch}"),
                             dtype=dtype)
     inp = W.generate(w, "cuda")
-    run_both(binding, oracle, w, inp)
+    with_rows, _, _ = run_both(binding, oracle, w, inp)  # with log-prob rows the parts only deliver, without them the last part draws
+    out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam,
+                               beta=w.beta, temperature=w.temperature, draft_len=inp["draft_len"])
+    for k in ("accepted_len", "next_token", "next_token_logprob"):
+        assert torch.equal(out[k], with_rows[k]), k
     out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam,
                                beta=w.beta, temperature=w.temperature, draft_len=inp["draft_len"], greedy=True)
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, greedy=True,
@@ -533,37 +537,38 @@ def test_split_recovery_shapes(binding, oracle, name, batch, vocab, dtype):
 
 
 def test_split_recovery_reuses_one_workspace(binding, oracle):
-    """Back-to-back calls on one workspace, the arrival counters of the parts start from zero
-    every time; sampled, greedy and draft-free calls interleaved, with flagged sequences."""
+    """Back-to-back calls on one workspace: without log-prob rows the arrival counters of the parts start from zero every
+    time and the part that arrives last draws; with them the parts only deliver and a launch of its own draws.  The two
+    follow each other in either order, sampled and greedy, with flagged sequences, whose parts never arrive."""
     w = W.scaled(W.WORKLOADS["c4"], batch=12, vocab=128256, name="split-ws")
     p = binding.make_params(w.batch, w.k_max, w.vocab, torch.bfloat16, lam=w.lam, beta=w.beta, temperature=w.temperature)
     ws = torch.empty(binding.workspace_bytes(p), dtype=torch.uint8, device="cuda")
     ws.fill_(0xAB)
-    for rnd in range(4):
+    for rnd, (greedy, flagged) in enumerate([(False, False), (False, True), (True, True), (True, False), (False, False)]):
         inp = W.generate(w, "cuda", seed_shift=rnd)
-        greedy = rnd == 2
-        if rnd == 1:
+        if flagged:
             inp["draft_len"][3] = w.k_max + 1
             inp["draft"][7, 0] = w.vocab
-        out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam,
-                                   beta=w.beta, temperature=w.temperature, draft_len=inp["draft_len"],
-                                   want_recovery_logprobs=True, greedy=greedy, workspace=ws)
         ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, greedy=greedy,
                                 num_threads=16)
-        rep = parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
-        print(f"\n[split-ws {rnd}] {rep}", flush=True)
-        if rnd == 1:
-            assert out["accepted_len"][3].item() == -1 and out["accepted_len"][7].item() == -1
+        for rows in (False, True, False) if rnd % 2 == 0 else (True, False):
+            out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam,
+                                       beta=w.beta, temperature=w.temperature, draft_len=inp["draft_len"],
+                                       want_recovery_logprobs=rows, greedy=greedy, workspace=ws)
+            rep = parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
+            print(f"\n[split-ws {rnd} rows={rows}] {rep}", flush=True)
+            assert not flagged or (out["accepted_len"][3].item() == -1 and out["accepted_len"][7].item() == -1)
     # rows without drafts (k_max = 0) have no row pass in front of the recovery
     w0 = W.scaled(W.WORKLOADS["c2"], batch=5, vocab=100000, k_max=0, name="split-k0")
     p0 = binding.make_params(w0.batch, 0, w0.vocab, torch.bfloat16, lam=w0.lam, beta=w0.beta, temperature=w0.temperature)
     ws0 = torch.full((binding.workspace_bytes(p0),), 0xCD, dtype=torch.uint8, device="cuda")
     for rnd in range(2):
         inp = W.generate(w0, "cuda", seed_shift=rnd)
-        out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w0.lam,
-                                   beta=w0.beta, temperature=w0.temperature, want_recovery_logprobs=True, workspace=ws0)
         ora = parity.oracle_run(oracle, inp, lam=w0.lam, beta=w0.beta, temperature=w0.temperature, num_threads=16)
-        parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
+        for rows in (False, True):
+            out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w0.lam,
+                                       beta=w0.beta, temperature=w0.temperature, want_recovery_logprobs=rows, workspace=ws0)
+            parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
 
 
 # ------------------------------------------------------------------ every benchmark mode at the size and launch shape bench.py times
