@@ -41,6 +41,10 @@ def test_static_scratch_entry_point_matches_the_workspace_one(binding_mod):
     _both(binding, W.scaled(W.WORKLOADS["c2"], batch=3, vocab=151936, name="static-split"), greedy=True)
     _both(binding, W.scaled(W.WORKLOADS["c2"], batch=3, vocab=151936, name="static-split-again"))
     _both(binding, W.scaled(W.WORKLOADS["c1"], batch=9, vocab=4000, k_max=0, name="static-rows"))
+    # longer rows without drafts: a launch for the chunk masses and one for the draw, masses and candidates in the scratch
+    _both(binding, W.scaled(W.WORKLOADS["c2"], batch=9, vocab=77 * 2048 + 1, k_max=0, name="static-long-rows"))
+    _both(binding, W.scaled(W.WORKLOADS["c1"], batch=5, vocab=60000, k_max=0, name="static-long-rows-f32"), want_rows=True)
+    _both(binding, W.scaled(W.WORKLOADS["c2"], batch=3, vocab=151936, k_max=0, name="static-long-rows-greedy"), greedy=True)
 
 
 def test_static_scratch_entry_point_refuses_blocks_beyond_its_limit(binding_mod):
