@@ -175,6 +175,12 @@ __device__ __forceinline__ void unpack(const float4& r, float (&h)[4]) {
     h[0] = r.x; h[1] = r.y; h[2] = r.z; h[3] = r.w;
 }
 
+// A word that no launch in flight writes, at an address the same in all lanes: by the scalar unit, whose loads are waited for apart
+// from those and the stores of the vector memory.
+__device__ __forceinline__ int ld_uniform(const int* p) {
+    return *reinterpret_cast<const __attribute__((address_space(4))) int*>(reinterpret_cast<uintptr_t>(p));
+}
+
 // element e of a vector, e the same in all lanes
 __device__ __forceinline__ float elem_of(uint4 r, int e) {
     const unsigned w = e < 4 ? (e < 2 ? r.x : r.y) : (e < 6 ? r.z : r.w);

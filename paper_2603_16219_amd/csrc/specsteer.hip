@@ -52,6 +52,9 @@ constexpr float kEClamp = 5.0e8f;           // keeps (int)ceil(h*c) inside int32
 constexpr double kLn2 = 0.693147180559945309417232121458;
 constexpr double kLog2e = 1.442695040888963407359924681002;
 
+// every memory operation this wave has issued so far has completed: s_waitcnt vmcnt(0) lgkmcnt(0)
+__device__ __forceinline__ void wait_stores() { __builtin_amdgcn_s_waitcnt(0x0070); }
+
 // ------------------------------------------------------------------ online sum of exponentials
 
 struct Acc {
@@ -264,6 +267,12 @@ struct LseArgs {
 // ratio test would gather it from HBM behind the load of the draft id, a round trip that every sequence of that launch
 // waits for.  The id itself is looked at behind the item's first loads: before them it cost 300 ragged sequences 2 us.
 // For an id outside the vocabulary the first slice leaves kNoToken, so that the ratio test needs no ids at all.
+// Loads and stores of the vector memory are counted together, so that an item which begins with a wait for a load begins with one for
+// the stores of the item before: with the id as a vector load, or the row list behind one pointer to LDS or global memory, all did.
+// Slices of one group of loads are done sooner without it (64 sequences of 8 drafts, V = 32000 28.0 -> 26.8 us a step, 128 45.1 ->
+// 42.9, 13 of 16 in fp32, V = 38784 24.7 -> 23.2, 64 ragged ones of 16, V = 32000 30.6 -> 29.4), and where a wave has few items (8 of V =
+// 151936 19.0 -> 18.7).  Else rows stream faster with it, in the order that it keeps the waves in (without -> with: 64 of V = 151936
+// 67.8 -> 66.8, of 100000 50.5 -> 49.8, 256 ragged ones of V = 50257 63.8 -> 63.4, 512 of 256000 601.5 -> 596.8), and wait as a rule.
 template <int DT, int VEC, int kUnroll>
 __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
     extern __shared__ int lds_off[];
@@ -271,14 +280,11 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
     const int wave_global = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (kLseThreads / kWave) + (threadIdx.x >> 6)));
     const int waves_total = gridDim.x * (kLseThreads / kWave);
     const bool ragged = a.uniform_rows <= 0;
-    const int* off = a.row_off;
-    if (ragged && a.list_in_lds) {
-        block_scan_rows(a.win, a.B, lds_off, kLseThreads);
-        off = lds_off;
-    }
+    if (ragged && a.list_in_lds) block_scan_rows(a.win, a.B, lds_off, kLseThreads);
+    const auto* const lds_list = (const __attribute__((address_space(3))) int*)lds_off;
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < a.zero_n; i += kLseThreads) a.zero_ptr[(long)i * kArriveStride] = 0u;
-    const int R = ragged ? __builtin_amdgcn_readfirstlane(off[a.B]) : a.B * a.uniform_rows;
+    const int R = ragged ? __builtin_amdgcn_readfirstlane(a.list_in_lds ? lds_off[a.B] : a.row_off[a.B]) : a.B * a.uniform_rows;
     const long slice_units = a.slice_vecs;
     constexpr long kGroup = (long)kWave * kUnroll;
 
@@ -293,6 +299,7 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
     const unsigned NS = (unsigned)a.NS;
     unsigned k_ = (unsigned)wave_global % NS, rx = (unsigned)wave_global / NS;
     const unsigned dk = (unsigned)waves_total % NS, drx = (unsigned)waves_total / NS;
+    const bool in_order = slice_units > kGroup && 2u * (unsigned)R >= 4u * drx;  // more than one group of loads, four items a wave
     int b = 0, off_b = 0;  // ragged: the sequence of the row before, and its first row
     for (; rx < 2u * (unsigned)R; k_ += dk, rx += drx) {
         if (k_ >= NS) {
@@ -300,17 +307,20 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
             if (++rx >= 2u * (unsigned)R) break;
         }
         const int k = (int)k_, x = (int)(rx & 1u), r = (int)(rx >> 1);
+        if (in_order) wait_stores();
         int t;
         if (ragged) {
             // the largest b with off[b] <= r; off[B] = R > r.  Beyond the next 64, the 64 places that part what is left evenly
             int hi = a.B, step = 1;
             for (;;) {
-                const int o = off[min(b + step * (1 + lane), hi)];
-                const int n = __popcll(__ballot(o <= r));
-                if (n) {
-                    b += n * step;
-                    off_b = __builtin_amdgcn_readlane(o, n - 1);
-                }
+                int n;
+                const auto look = [&](const auto* list) {
+                    const int o = list[min(b + step * (1 + lane), hi)];
+                    n = __popcll(__ballot(o <= r));
+                    if (n) off_b = __builtin_amdgcn_readlane(o, n - 1);
+                };
+                if (a.list_in_lds) look(lds_list); else look(a.row_off);
+                b += n * step;
                 if (n < kWave) {
                     if (step == 1) break;
                     hi = min(b + step, hi);
@@ -323,7 +333,7 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
             t = a.win.t_lo + (r - b * a.uniform_rows);
         }
         const long elem_off = (long)b * a.sb + (long)t * a.st;
-        const int y_load = a.draft_logit ? a.draft[(long)b * a.kmax + t] : -1;  // looked at behind the first loads of the row
+        const int y = a.draft_logit ? ld_uniform(a.draft + ((long)b * a.kmax + t)) : -1;  // looked at behind the first loads of the row
         float* const y_out = a.draft_logit + ((long)b * a.kmax + t) * 2 + x;
         const void* row = row_ptr<DT>(x ? a.Sm : a.G, elem_off);
         const int head = __builtin_amdgcn_readfirstlane(odd_head<DT>(row, elem_off));
@@ -337,7 +347,6 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
         // the draft token's element in the row as it is read, and its vector counted from the slice's start, < 0 if none of this slice
         int ye = -1, yv = -1;
         const auto find_y = [&]() {
-            const int y = __builtin_amdgcn_readfirstlane(y_load);
             ye = y >= 0 && y < a.V ? y + head : -1;
             if (ye < 0 && a.draft_logit && k == 0 && lane == 0) *y_out = __uint_as_float(kNoToken);
             yv = ye >= 0 && ye / VEC < v1 ? ye / VEC - (int)v0 : -1;
@@ -448,8 +457,6 @@ __device__ __forceinline__ Partial ld_dev_partial(const Partial* p) {
     const unsigned long long w = ld_dev(reinterpret_cast<const unsigned long long*>(p));
     return Partial{(int)(unsigned)(w & 0xFFFFFFFFull), __uint_as_float((unsigned)(w >> 32))};
 }
-// every memory operation this wave has issued so far has completed: s_waitcnt vmcnt(0) lgkmcnt(0)
-__device__ __forceinline__ void wait_stores() { __builtin_amdgcn_s_waitcnt(0x0070); }
 
 // The slice partials of one row merged by the 16 lanes of one DPP row (`l` is the lane's index in it, every lane
 // returns the pair): lane l takes slices l, l+16, ..., four loads in flight, and the 16
