@@ -265,9 +265,7 @@ struct LseArgs {
 // (every workgroup repeats the same small scan), so no separate launch is needed.
 // The wave that meets the draft token's vector leaves its logit beside the partials: it is in registers here, while the
 // ratio test would gather it from HBM behind the load of the draft id, a round trip that every sequence of that launch
-// waits for.  The id itself is looked at behind the sum over the item's first loads: before the loads it cost 300 ragged sequences
-// 2 us, between loads and sum, where few waves have more than one item, an access that may take longer than theirs (one sequence of 128
-// drafts, V = 40000 21.1 -> 20.5 us a step, 20.3 without the logits).
+// waits for.  The id itself is looked at behind the item's first loads: before them it cost 300 ragged sequences 2 us.
 // For an id outside the vocabulary the first slice leaves kNoToken, so that the ratio test needs no ids at all.
 // Loads and stores of the vector memory are counted together, so that an item which begins with a wait for a load begins with one for
 // the stores of the item before: with the id as a vector load, or the row list behind one pointer to LDS or global memory, all did.
@@ -335,7 +333,7 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
             t = a.win.t_lo + (r - b * a.uniform_rows);
         }
         const long elem_off = (long)b * a.sb + (long)t * a.st;
-        const int y = a.draft_logit ? ld_uniform(a.draft + ((long)b * a.kmax + t)) : -1;  // looked at behind the first sum
+        const int y = a.draft_logit ? ld_uniform(a.draft + ((long)b * a.kmax + t)) : -1;  // looked at behind the first loads of the row
         float* const y_out = a.draft_logit + ((long)b * a.kmax + t) * 2 + x;
         const void* row = row_ptr<DT>(x ? a.Sm : a.G, elem_off);
         const int head = __builtin_amdgcn_readfirstlane(odd_head<DT>(row, elem_off));
@@ -360,17 +358,6 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
             typename RawT<DT, VEC>::type raw[kUnroll];
 #pragma unroll
             for (int j = 0; j < kUnroll; ++j) raw[j] = ld_raw<DT, VEC>(row, v + (long)kWave * j);
-            if (masked && g == 0 && lane == 0) raw[0] = set_first(raw[0], kBf16NegInf);
-            float h[kUnroll * VEC];
-#pragma unroll
-            for (int j = 0; j < kUnroll; ++j) {
-                float hj[VEC];
-                unpack(raw[j], hj);
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) h[j * VEC + i] = hj[i];
-            }
-            acc_add_f32<kUnroll * VEC>(acc, h, a.c_hi);
-            asm volatile("" : "+v"(acc.s));  // the sum stays before the wait for the id
             if (g == 0) find_y();
             if (yv >= 0 && yv / (int)kGroup == (int)g) {
                 float hy = 0.f;
@@ -381,6 +368,16 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
                 }
                 if (yv % kWave == lane) *y_out = hy;
             }
+            if (masked && g == 0 && lane == 0) raw[0] = set_first(raw[0], kBf16NegInf);
+            float h[kUnroll * VEC];
+#pragma unroll
+            for (int j = 0; j < kUnroll; ++j) {
+                float hj[VEC];
+                unpack(raw[j], hj);
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) h[j * VEC + i] = hj[i];
+            }
+            acc_add_f32<kUnroll * VEC>(acc, h, a.c_hi);
         }
         if (nfull == 0) find_y();
         for (; v < v1; v += kWave) {
