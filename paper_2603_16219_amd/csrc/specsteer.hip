@@ -720,12 +720,14 @@ constexpr int kDrawWaves = 4;  // a chunk is one vector of each of the first 4 w
 // Inverse-CDF draw for one sequence by a workgroup, from the chunk masses `tab` (LDS) of its recovery row: a
 // double-precision scan over the masses finds the chunk holding u*Z, and only that chunk is read again to pick the token,
 // a vector a lane of the first four waves.  Every one of them scans the masses for itself, so that they meet only once, over the sums
-// of their quarters; with ONE_SCAN, in the workgroups of many rows that share a unit's vector ALUs, one does it for all and the
-// normaliser's logarithm is left to the wave that needs it (1290 sampled rows of V = 42298 24.4 -> 23.7 us, 1224 of V = 56960 27.7 -> 27.1).
+// of their quarters; with ONE_SCAN, in the workgroups of many rows that share a unit's vector ALUs, one does it for all
+// (1290 sampled rows of V = 42298 24.4 -> 23.7 us, 1224 of V = 56960 27.7 -> 27.1).  The normaliser's logarithm is taken with the token's by the wave
+// that picks it; by all four while the chunk was on its way, it took longer than the chunk (32 sampled rows of V = 24576 6.07 -> 5.92 us
+// on the GPU, of V = 32768 6.63 -> 6.45, 8 sequences of V = 151936 18.75 -> 18.62 a step).
 // What bounds it is the chain of dependent steps, in which the chip is idle: by one wave, with four vectors a lane, the part
 // behind the table took 3.6 us (8 sequences of V = 151936), now 2.9.  512 steered rows of V = 128256 67.0 -> 66.1 us, 4352 of them
 // 501 -> 498.
-// Returns log2 Z to the first four waves; one lane writes the per-sequence outputs.
+// Returns log2 Z to wave 0 where a.log2z or a.recovery_logprobs asks for it; one lane writes the per-sequence outputs.
 template <int DT, int VEC, bool PLAIN, bool ONE_SCAN>
 __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, double us, int wave, int lane, const Partial* tab,
                                              const RecRow<DT, VEC>& row, double* sh_sum, int* sh_any, Found* sh_found) {
@@ -767,7 +769,6 @@ __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, dou
                 rm = ld_raw<DT, VEC>(sm, v);
             }
         }
-        if (!ONE_SCAN) log2Z = mass_log2<PLAIN>(a, at.Estar, at.total);  // while the chunk is on its way
         float hg[VEC], hp[VEC], hm[VEC];
         int have = full ? VEC : 0;  // logits this lane holds
         first = v * VEC;
@@ -832,13 +833,9 @@ __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, dou
         }
         // The token's exponent is taken back from its term, whose rounding the masses hold too: where one token carries the row it
         // drops out of the difference, which the logits' own exponent would leave in the log-prob (1e-7).
-        double lg;
-        if (ONE_SCAN) {  // one logarithm for both, in lane L and beside it
-            lg = log2(lane == L ? (term > 0.f ? (double)term : 1.0) : at.total);
-            log2Z = (double)at.Estar + wave_readlane_f64(lg, L ^ 1) + (PLAIN ? a.rho : 0.0) * (double)at.Estar;
-        } else {
-            lg = log2(term > 0.f ? (double)term : 1.0);
-        }
+        // One logarithm for both, in lane L and beside it
+        const double lg = log2(lane == L ? (term > 0.f ? (double)term : 1.0) : at.total);
+        log2Z = (double)at.Estar + wave_readlane_f64(lg, L ^ 1) + (PLAIN ? a.rho : 0.0) * (double)at.Estar;
         if (lane == L) {
             const double y_hi = dE + lg, y = PLAIN ? y_hi + a.rho * y_hi : y_hi;
             a.accepted_len[b] = n;
@@ -846,7 +843,7 @@ __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, dou
             if (a.next_token_logprob) a.next_token_logprob[b] = (float)(kLn2 * (y - log2Z));
         }
     }
-    return ONE_SCAN && wave == 0 && (a.log2z || a.recovery_logprobs) ? mass_log2<PLAIN>(a, at.Estar, at.total) : log2Z;
+    return wave == 0 && (a.log2z || a.recovery_logprobs) ? mass_log2<PLAIN>(a, at.Estar, at.total) : log2Z;
 }
 
 // The same for greedy decoding, by one wave: the token is known, only the normaliser is needed.
