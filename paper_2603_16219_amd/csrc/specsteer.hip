@@ -602,31 +602,52 @@ __device__ __forceinline__ Partial chunk_mass(const RecRow<DT, VEC>& row, long c
     return wave_combine(acc);
 }
 
-// The masses of two full chunks of a row without steering, with the loads of both on their way at once.  Bound by latency: a wave with
-// one chunk has 4 loads in flight, and sixteen such waves draw 33 GB/s through a compute unit.  64 rows of V = 151936 bf16 in
-// one 16-wave workgroup each: 14.3 us a call with single chunks, 13.4 with pairs, V = 131072 13.3 -> 12.2.  Not with 8
-// waves, two workgroups to a unit (512 rows: 28.8 -> 29.3).
-template <int DT, int VEC, bool GREEDY>
+// The masses of two chunks of a bf16 row without steering, with the loads of both on their way at once; the first is whole, the second
+// with WHOLE, else as far as the row goes.  Bound by latency: a wave with
+// one chunk has 4 loads in flight, and sixteen such waves draw 33 GB/s through a compute unit.  64 rows of V = 151936 in
+// one 16-wave workgroup each: 14.3 us a call with single chunks, 13.4 with pairs, V = 131072 13.3 -> 12.2.  A wave left with the row's last,
+// partial chunk for a round of its own is the last of its workgroup (256 rows of V = 50256 8.52 us on the GPU, 8.12 with that chunk
+// paired too, of V = 128256 14.9 -> 14.5).  Not with 8 waves, two workgroups to a unit (512 rows: 28.8 -> 29.3), and not in fp32, whose
+// chunks are half the logits: the arithmetic of the others covers their latency (64 rows of V = 50257 9.63 us in pairs, 9.01 without, 256 of V =
+// 32768 9.04, 8.54).
+template <int DT, int VEC, bool GREEDY, bool WHOLE>
 __device__ __forceinline__ void chunk_pair_mass(const RecRow<DT, VEC>& row, const long (&c)[2], int lane, float c_hi, Best& best, Partial (&out)[2]) {
     typename RawT<DT, VEC>::type r[2][kChunkSteps];
+    const long end = WHOLE ? 0 : row.nvec;
 #pragma unroll
     for (int q = 0; q < 2; ++q)
 #pragma unroll
-        for (int j = 0; j < kChunkSteps; ++j) r[q][j] = ld_raw<DT, VEC>(row.g, (c[q] * kChunkSteps + j) * kWave + lane);
+        for (int j = 0; j < kChunkSteps; ++j) {
+            const long v = (c[q] * kChunkSteps + j) * kWave + lane;
+            if (WHOLE || q == 0 || v < end) r[q][j] = ld_raw<DT, VEC>(row.g, v);
+        }
     if (row.head && c[0] == 0 && lane == 0) r[0][0] = set_first(r[0][0], kBf16NegInf);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         Acc acc{kEInit, 0.f};
-        float h[kChunkSteps * VEC];
+        const long v0 = c[q] * kChunkSteps * kWave + lane;
+        if (WHOLE || q == 0 || v0 + (kChunkSteps - 1) * kWave < end) {
+            float h[kChunkSteps * VEC];
 #pragma unroll
-        for (int j = 0; j < kChunkSteps; ++j) {
-            float hj[VEC];
-            unpack(r[q][j], hj);
-            if (GREEDY) best_of<VEC>(best, hj, (int)((c[q] * kChunkSteps + j) * kWave + lane) * VEC);
+            for (int j = 0; j < kChunkSteps; ++j) {
+                float hj[VEC];
+                unpack(r[q][j], hj);
+                if (GREEDY) best_of<VEC>(best, hj, (int)((c[q] * kChunkSteps + j) * kWave + lane) * VEC);
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) h[j * VEC + i] = hj[i];
+                for (int i = 0; i < VEC; ++i) h[j * VEC + i] = hj[i];
+            }
+            acc_add_f32<kChunkSteps * VEC>(acc, h, c_hi);
+        } else {
+#pragma unroll
+            for (int j = 0; j < kChunkSteps; ++j) {
+                if (v0 + j * kWave < end) {
+                    float hj[VEC];
+                    unpack(r[q][j], hj);
+                    if (GREEDY) best_of<VEC>(best, hj, (int)(v0 + j * kWave) * VEC);
+                    acc_add_f32<VEC>(acc, hj, c_hi);
+                }
+            }
         }
-        acc_add_f32<kChunkSteps * VEC>(acc, h, c_hi);
         out[q] = wave_combine(acc);
     }
 }
@@ -1117,15 +1138,16 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     const int ways = over == 0 || 2 * over > NW ? 1 : 4 * over > NW ? 2 : 4;
     const int cw = ways > 1 ? c1 - over : c1;  // whole chunks end here
     int c = c0 + wave;
-    if (PLAIN && NT == 1024) {
+    if (PLAIN && DT == SS_BF16 && NT == 1024) {
+        Partial p[2];
         for (; c + NW < cw && (long)(c + NW + 1) * (kWave * kChunkSteps) <= row.nvec; c += 2 * NW) {
-            Partial p[2];
-            const long pair[2] = {c, c + NW};
-            chunk_pair_mass<DT, VEC, GREEDY>(row, pair, lane, a.c_hi, best, p);
-            if (lane == 0) {
-                tab[c] = p[0];
-                tab[c + NW] = p[1];
-            }
+            chunk_pair_mass<DT, VEC, GREEDY, true>(row, {c, c + NW}, lane, a.c_hi, best, p);
+            if (lane == 0) tab[c] = p[0], tab[c + NW] = p[1];
+        }
+        if (c + NW < cw && c + NW < row.nch) {
+            chunk_pair_mass<DT, VEC, GREEDY, false>(row, {c, c + NW}, lane, a.c_hi, best, p);
+            if (lane == 0) tab[c] = p[0], tab[c + NW] = p[1];
+            c += 2 * NW;
         }
     }
     for (; c < cw; c += NW) {

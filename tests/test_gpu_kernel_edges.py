@@ -111,12 +111,15 @@ def test_recovery_launch_shapes(binding, oracle, dtype, batch, vocab, greedy, be
 
 # Up to 128 rows without a draft: one launch while a 16-wave workgroup takes its row fast enough, with pairs of chunks where there is no
 # steering term, else a launch for the chunk masses, four chunks a workgroup, and one for the draw.  Whole chunks and
-# workgroups, pairs with and without a chunk over, one logit more, odd rows, a row that has a length (flagged).
+# workgroups, pairs with and without a chunk over, whose second chunk is partial (one vector, a third, a half), one logit more, odd
+# rows, a row that has a length (flagged).
 @pytest.mark.parametrize("greedy,beta", [(False, 0.8), (True, 0.8), (False, 0.0), (True, 0.0)])
 @pytest.mark.parametrize("dtype,batch,vocab", [("bf16", 1, 20 * 2048), ("bf16", 3, 16 * 2048 + 1), ("bf16", 128, 17 * 2048 + 9),
                                                ("bf16", 4, 32 * 2048), ("bf16", 9, 76 * 2048), ("bf16", 9, 77 * 2048 - 3),
                                                ("f32", 9, 104 * 1024 + 1), ("bf16", 9, 33 * 2048 + 1),
-                                               ("f32", 2, 17 * 1024), ("f32", 37, 300 * 1024 + 3), ("bf16", 64, 75 * 2048 - 5)])
+                                               ("f32", 2, 17 * 1024), ("f32", 37, 300 * 1024 + 3), ("bf16", 64, 75 * 2048 - 5),
+                                               ("bf16", 9, 16 * 2048 + 9), ("bf16", 9, 20 * 2048 + 700), ("bf16", 130, 24 * 2048 + 1031),
+                                               ("bf16", 3, 55 * 2048 - 1001)])
 def test_rows_without_drafts_in_one_launch_and_in_two(binding, oracle, dtype, batch, vocab, greedy, beta):
     w = recipe("c4", dtype, batch=batch, k_max=0, vocab=vocab)
     inp = W.generate(w, "cuda", seq_chunk=64)
