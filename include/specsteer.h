@@ -141,6 +141,11 @@ size_t specsteer_workspace_bytes(const ss_params *params);
  *                      rounded up to 256, which keep the draft tokens' logits.)
  *   stream             a hipStream_t passed as void*; NULL is the default stream.
  *
+ * Rows without drafts (k_max == 0, up to 128 of them): a call outside stream capture is
+ * shaped for a caller bound by the host's time and takes rows of medium length in one
+ * launch, where two would take the GPU as little as half the time; under capture, where
+ * launches cost no host time, only the GPU's counts.  The outputs are the same.
+ *
  * Errors.  Argument errors are detected on the host before anything is
  * enqueued and leave every output untouched.  Data errors that only the GPU
  * can see -- draft_len[b] outside [0, k_max], or draft[b][t] outside [0, V)

@@ -96,9 +96,18 @@ inline RecShape recovery_shape(int B, int NC, int kmax, int cus, bool split) {
 }
 
 // Whether rows without a draft that recovery_shape would cut into parts are taken whole by one 16-wave workgroup each.  Parts
-// cost a second launch, and of calls this small the host's 2.3 us for it and what it spends on the way are what bounds them: 14.3 us in
+// cost a second launch, 2.3 us of the host's time, and spread a row over the chip.
+//   In a captured graph launches cost the host nothing, and the GPU's time decides (us on the GPU in two launches -> in one, bf16 rows
+// without a steering term: 1 of 17 chunks 6.2 -> 6.6, of 76 6.0 -> 11.9; 32 of 20 7.3 -> 7.1, of 24 7.5 -> 7.8; 64 of 20 7.8 -> 7.6, of 75 9.8 ->
+// 13.0; 96 of 28 8.5 -> 8.4, of 36 8.9 -> 9.2; 128 of 36 9.5 -> 9.2, of 44 10.2 -> 10.2; fp32: 1 of 24 5.3 -> 5.2, of 32 5.4 -> 5.7; 64 of 32
+// 7.6 -> 7.6, of 40 7.8 -> 8.2; 128 of 40 9.2 -> 8.6, of 64 10.9 -> 11.4; with one, fp32: 96 of 17 9.6 -> 10.3, 128 of 17 11.2 -> 10.7, of 24
+// 12.7 -> 12.9; bf16: 128 of 17 12.3 -> 12.5).
+//   Outside of one the lines are where back-to-back calls through this repository's Python binding (some 9 us of host time beside the
+// launches) are as fast either way: they are bound by the host, 14.3 us in
 // two launches whatever the size, 11.4 in one until the rate of one compute unit (or, with a steering term, its
-// arithmetic) takes over.  Us a call in two launches -> in one, by chunks of a row:
+// arithmetic) takes over.  A caller with less host time of its own, or whose host runs ahead of the GPU, pays up to twice the GPU's
+// time for it between these lines and those above; it gets the other shape by capturing the call.  Us a call in two launches -> in
+// one, by chunks of a row:
 //   - sampled rows, bf16: 32 rows of 64 chunks 14.2 -> 11.7, of 76 13.4 -> 13.3, of 80 14.2 -> 14.5; 64 of 75 (V = 151936) 14.6 ->
 //     13.4; 128 of 76 14.1 -> 14.0, of 80 14.3 -> 15.1; 8 of 80 13.6 -> 13.4, of 88 14.3 -> 14.2.
 //   - sampled rows, fp32: 8 of 112 14.2 -> 12.4, of 149 14.2 -> 15.2; 32 of 100 14.3 -> 12.9, of 112 14.2 -> 14.2; 64 of 100
@@ -109,7 +118,8 @@ inline RecShape recovery_shape(int B, int NC, int kmax, int cus, bool split) {
 //   - greedy, where every logit is compared too: bf16 rows without a steering term 8 of 52 13.4 -> 12.2, 128 of 52 14.2 -> 13.1,
 //     32 of 60 13.5 -> 13.8; fp32 64 of 92 14.3 -> 13.9, of 104 14.2 -> 14.8; steered bf16 128 of 20 14.3 -> 13.9, 32 of 22 14.2 ->
 //     14.5; steered fp32 as sampled.
-inline bool rows_in_one_launch(int B, int NC, int dtype, bool plain, bool greedy) {
+inline bool rows_in_one_launch(int B, int NC, int dtype, bool plain, bool greedy, bool captured) {
+    if (captured) return plain ? NC <= (dtype == SS_BF16 ? 11 + B / 5 : 24 + B / 8) : dtype == SS_F32 && B > 112 && NC <= 20;
     if (greedy && plain) return NC <= (dtype == SS_BF16 ? 56 : B <= 64 ? 92 : 84);
     if (greedy) return NC <= (dtype == SS_BF16 ? 20 : B <= 32 ? 32 : 28);
     if (plain) return NC <= (dtype == SS_BF16 ? (B <= 8 ? 84 : 76) : B <= 8 ? 120 : B <= 64 ? 104 : 92);

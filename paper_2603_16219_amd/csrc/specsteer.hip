@@ -1392,6 +1392,16 @@ void launch_row_pass(LseArgs la, const Window& w, const RowWindow& win, int unif
                        stream, la);
 }
 
+// Whether what is enqueued on the stream goes into a graph.
+bool being_captured(hipStream_t stream) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+        (void)hipGetLastError();  // the launches will tell
+        return false;
+    }
+    return status == hipStreamCaptureStatusActive;
+}
+
 template <int DT>
 unsigned elem_parity(const void* p) { return (unsigned)(reinterpret_cast<uintptr_t>(p) / (DT == SS_BF16 ? 2 : 4)) & 1u; }
 
@@ -1421,7 +1431,8 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     const unsigned bases[3] = {elem_parity<DT>(ra.G), elem_parity<DT>(ra.recSp), elem_parity<DT>(ra.recSm)};
     ra.NC = chunks_per_row(V, VEC, odd_rows_possible(VEC, bases, B, kmax, ra.sb, ra.st));
     RecShape shape = recovery_shape(B, ra.NC, kmax, device_cu_count(), pl.split);
-    if (kmax == 0 && shape.part_chunks < ra.NC && rows_in_one_launch(B, ra.NC, DT, ra.plain != 0, ra.greedy != 0)) shape = RecShape{1024, ra.NC};
+    if (kmax == 0 && shape.part_chunks < ra.NC && rows_in_one_launch(B, ra.NC, DT, ra.plain != 0, ra.greedy != 0, being_captured(stream)))
+        shape = RecShape{1024, ra.NC};
     const bool rows_inside = recovery_logprobs && logprobs_in_recovery(B, kmax, V, DT == SS_BF16 ? 2 : 4);
     // Log-prob rows that lie on the logits (fp32 rows without drafts, in place): the token is drawn before any of them is written
     const size_t esz = DT == SS_BF16 ? 2 : 4, span = ((size_t)(B - 1) * ra.sb + (size_t)kmax * ra.st + V) * esz;

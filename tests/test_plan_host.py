@@ -26,6 +26,12 @@ int main() {
             std::printf("%d\n", logprobs_in_recovery(B, k, V, esz) ? 1 : 0);
             continue;
         }
+        if (!std::strcmp(what, "one")) {  // B chunks dtype plain greedy captured
+            int a[6];
+            if (std::scanf("%d %d %d %d %d %d", a, a + 1, a + 2, a + 3, a + 4, a + 5) != 6) return 1;
+            std::printf("%d\n", rows_in_one_launch(a[0], a[1], a[2], a[3], a[4], a[5]) ? 1 : 0);
+            continue;
+        }
         if (!std::strcmp(what, "odd")) {  // vec base base base B kmax sb st
             unsigned a[3]; int vec, B, k; long sb, st;
             if (std::scanf("%d %u %u %u %d %d %ld %ld", &vec, a, a + 1, a + 2, &B, &k, &sb, &st) != 8) return 1;
@@ -115,6 +121,22 @@ def test_recovery_of_few_chunks_is_spread_only_where_that_pays(planner, chunks, 
     (600, 16, 16384, 2, 1), (600, 4, 20000, 2, 0), (16, 8, 151936, 2, 0)])
 def test_short_logprob_rows_come_without_a_launch_of_their_own(planner, batch, k_max, vocab, esz, inside):
     assert planner([f"rows {batch} {k_max} {vocab} {esz}"]) == [(inside,)]
+
+
+# Rows without a draft in one launch up to a number of chunks, by what is measured beside the rule: outside a graph, and captured (0:
+# never, whatever the row).
+@pytest.mark.parametrize("dtype,plain,greedy,captured,most", [
+    ("bf16", 1, 0, 0, {1: 84, 8: 84, 9: 76, 128: 76}), ("f32", 1, 0, 0, {1: 120, 8: 120, 9: 104, 64: 104, 65: 92, 128: 92}),
+    ("bf16", 0, 0, 0, {1: 28, 8: 28, 9: 24, 128: 24}), ("f32", 0, 0, 0, {1: 34, 32: 34, 33: 28, 128: 28}),
+    ("bf16", 1, 1, 0, {1: 56, 128: 56}), ("f32", 1, 1, 0, {1: 92, 64: 92, 65: 84, 128: 84}),
+    ("bf16", 0, 1, 0, {1: 20, 128: 20}), ("f32", 0, 1, 0, {1: 32, 32: 32, 33: 28, 128: 28}),
+    ("bf16", 1, 0, 1, {1: 11, 32: 17, 64: 23, 96: 30, 128: 36}), ("f32", 1, 0, 1, {1: 24, 32: 28, 64: 32, 128: 40}),
+    ("bf16", 1, 1, 1, {1: 11, 128: 36}), ("f32", 1, 1, 1, {1: 24, 128: 40}),
+    ("bf16", 0, 0, 1, {1: 0, 128: 0}), ("f32", 0, 0, 1, {1: 0, 112: 0, 113: 20, 128: 20}), ("f32", 0, 1, 1, {112: 0, 113: 20})])
+def test_rows_without_drafts_are_taken_whole_while_that_pays(planner, dtype, plain, greedy, captured, most):
+    for batch, chunks in most.items():
+        tail = f"{BF16 if dtype == 'bf16' else 0} {plain} {greedy} {captured}"
+        assert planner([f"one {batch} {max(chunks, 1)} {tail}", f"one {batch} {chunks + 1} {tail}"]) == [(int(chunks > 0),), (0,)]
 
 
 def test_a_row_read_from_one_element_before_may_have_a_chunk_more(planner):

@@ -97,3 +97,43 @@ def test_static_scratch_entry_point_inside_a_hip_graph(binding_mod):
         torch.cuda.synchronize()
         assert torch.equal(acc, acc2) and torch.equal(tok, tok2) and torch.equal(lp, lp2), rnd
         assert torch.all(acc >= 0)
+
+
+@pytest.mark.parametrize("rows", [False, True])
+@pytest.mark.parametrize("greedy,beta", [(False, 0.0), (False, 0.8), (True, 0.8)])
+@pytest.mark.parametrize("batch,vocab", [(4, 76 * 2048), (64, 151936), (9, 20 * 2048 + 1), (37, 130 * 2048 - 3), (300, 9000)])
+def test_rows_without_drafts_inside_a_hip_graph(binding_mod, batch, vocab, greedy, beta, rows):
+    """Rows without drafts captured in a HIP graph, where the launches are shaped for the GPU's time alone, against direct
+    calls, which weigh the host's too: the same outputs bit for bit on every replay, log-prob rows among them."""
+    binding = binding_mod
+    w = W.scaled(W.WORKLOADS["c2"], batch=batch, vocab=vocab, k_max=0, name="graph-rows")
+    inp = W.generate(w, "cuda")
+    p = binding.make_params(batch, 0, vocab, W.torch_dtype(w.dtype), lam=w.lam, beta=beta, temperature=w.temperature,
+                            flags=binding.SS_FLAG_GREEDY if greedy else 0)
+    lens = torch.zeros(batch, dtype=torch.int32, device="cuda")
+    lens[1] = 1  # flagged
+    mk = lambda dt, *shape: torch.full(shape, -7, dtype=dt, device="cuda")
+    outs = [[mk(torch.int32, batch), mk(torch.int32, batch), mk(torch.float32, batch),
+             mk(torch.float32, batch, vocab) if rows else None, None] for _ in range(2)]
+    args = (inp["G"], inp["S_ctx"], inp["S_noctx"], None, lens, inp["uniforms"], p)
+    ws = torch.full((binding.workspace_bytes(p),), 0xAB, dtype=torch.uint8, device="cuda")
+    binding.verify_block_static_raw(*args, *outs[0])  # first call on the device: outside any capture
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        binding.verify_block_static_raw(*args, *outs[0])
+    for rnd in range(3):
+        fresh = W.generate(w, "cuda", seed_shift=rnd + 1)
+        for k in ("G", "S_ctx", "S_noctx", "uniforms"):
+            inp[k].copy_(fresh[k])
+        for o in outs:
+            for t in o:
+                if t is not None:
+                    t.fill_(-7)
+        g.replay()
+        torch.cuda.synchronize()
+        binding.verify_block_raw(*args, *outs[1], ws)
+        torch.cuda.synchronize()
+        for a, b in zip(*outs):
+            assert a is None or torch.equal(torch.nan_to_num(a), torch.nan_to_num(b)), rnd
+        assert (outs[0][0] == 0).sum().item() == batch - 1 and outs[0][0][1].item() == -1
