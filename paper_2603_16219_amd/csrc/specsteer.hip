@@ -934,15 +934,17 @@ __device__ __forceinline__ int ratio_test_block(const RecArgs& a, int b, int T0,
         // More pairs than groups of sixteen lanes: only the merging goes in rounds, its result waits in the pair's slot of
         // lp, and the logits and logarithms follow once, a lane to every pair.  With all of it in the rounds each of
         // them cost 0.9 us of dependent loads: 27 positions tested by 4 waves took 4, and one sequence of 128 positions,
-        // V = 40000, 24.1 us a step where it takes 20.7.
+        // V = 40000, 24.1 us a step where it takes 20.6 (20.8 with the logits that the row pass left asked for behind the merging).
+        const int qa = 2 * T0 + tid;
+        const float ha = left && qa < 2 * Tend ? left[qa] : 0.f;  // on its way while the rows are merged
         for (int q = q0; q < 2 * Kt; q += NT / 16) {
             const Partial m = merge_partials_row16(partials_of(a, b, q >> 1, q & 1), a.NS, l);
             if (l == 0) lp[q] = __hiloint2double(m.E, __float_as_int(m.s));
         }
         __syncthreads();
-        for (int q = 2 * T0 + tid; q < 2 * Kt; q += NT) {
+        for (int q = qa; q < 2 * Kt; q += NT) {
             const Partial m{__double2hiint(lp[q]), __int_as_float(__double2loint(lp[q]))};
-            const float h = left ? left[q] : gather(q);
+            const float h = !left ? gather(q) : q == qa ? ha : left[q];
             bad = bad || no_token(h);
             lp[q] = logprob(h, m);
         }
