@@ -121,14 +121,6 @@ __device__ __forceinline__ double wave_readlane_f64(double x, int lane) {  // `l
 }
 __device__ __forceinline__ double wave_last_f64(double incl) { return wave_readlane_f64(incl, 63); }
 
-// What this wave's lanes wrote to LDS is visible to its other lanes: LDS operations of one wave complete in
-// order, so only the compiler has to keep them in place.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 __device__ __forceinline__ int first_lane(unsigned long long mask) { return __ffsll((long long)mask) - 1; }
 
 // ------------------------------------------------------------------ logit loads

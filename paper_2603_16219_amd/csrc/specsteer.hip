@@ -746,8 +746,7 @@ constexpr int kDrawWaves = 4;  // a chunk is one vector of each of the first 4 w
 // that picks it; by all four while the chunk was on its way, it took longer than the chunk (32 sampled rows of V = 24576 6.07 -> 5.92 us
 // on the GPU, of V = 32768 6.63 -> 6.45, 8 sequences of V = 151936 18.75 -> 18.62 a step).
 // What bounds it is the chain of dependent steps, in which the chip is idle: by one wave, with four vectors a lane, the part
-// behind the table took 3.6 us (8 sequences of V = 151936), now 2.9.  512 steered rows of V = 128256 67.0 -> 66.1 us, 4352 of them
-// 501 -> 498.
+// behind the table took 3.6 us (8 sequences of V = 151936), now 2.9.  512 steered rows of V = 128256 67.0 -> 66.1 us.
 // Returns log2 Z to wave 0 where a.log2z or a.recovery_logprobs asks for it; one lane writes the per-sequence outputs.
 template <int DT, int VEC, bool PLAIN, bool ONE_SCAN>
 __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, double us, int wave, int lane, const Partial* tab,
@@ -1066,8 +1065,8 @@ __device__ __forceinline__ void write_logprobs(const void* g, const void* sp, co
 }
 
 // Everything after the row pass in one launch, a workgroup of NT threads per sequence:
-//   2a  every (position, tensor) pair gets 16 lanes: merge its slice partials, gather the draft
-//       token's logit, leave log P(y_t) in LDS            (two memory round trips in all)
+//   2a  every (position, tensor) pair gets 16 lanes: merge its slice partials, take the draft token's
+//       logit that the row pass left, log P(y_t) into LDS  (one memory round trip, see ratio_test_block)
 //   2b  wave 0: Eq. 7 on every position, first rejection by ballot
 //   3   all waves stream the three rows at the rejected (or bonus) position once, one (E, s)
 //       mass per 2048-logit chunk into LDS
