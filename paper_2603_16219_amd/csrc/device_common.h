@@ -186,6 +186,12 @@ template <int DT>
 __device__ __forceinline__ int odd_head(const void* row, long elem_off) {
     return DT == SS_BF16 && elem_off > 0 ? (int)((reinterpret_cast<uintptr_t>(row) >> 1) & 1) : 0;
 }
+// a vector of logits that are not there
+template <int DT, int VEC>
+__device__ __forceinline__ typename RawT<DT, VEC>::type neg_inf_raw() {
+    if constexpr (DT == SS_BF16) return make_uint4(0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u);
+    else return make_float4(-__builtin_huge_valf(), -__builtin_huge_valf(), -__builtin_huge_valf(), -__builtin_huge_valf());
+}
 // the vector that starts with such an element, with another value in its place
 __device__ __forceinline__ uint4 set_first(uint4 r, unsigned bf16) { r.x = (r.x & 0xFFFF0000u) | bf16; return r; }
 __device__ __forceinline__ float4 set_first(float4 r, unsigned) { return r; }  // fp32 rows have no such element

@@ -191,6 +191,46 @@ inline bool shape_ok(const ss_params* p) {
     return true;
 }
 
+// Small blocks in one launch (block_once_kernel): a wave forms the slice partials and the recovery mass of one chunk of one position, so
+// that nothing is left behind the ratio test but the draw.  Parts of kOnceWaves chunks.  In the workspace, per sequence and in 8-byte
+// words: the claim, then for each part its partials (four words, a draft's position) or that it has arrived (one, the bonus
+// position), its greedy candidate (two), and a mass for each chunk of every position.
+constexpr int kOnceWaves = 4;
+constexpr int kOnceMaxDrafts = 16;
+constexpr int kOnceMaxParts = 16;  // of a position: a lane each of the sixteen that merge it
+struct OnceSpace {
+    int parts;  // of a position
+    long flags, best, masses, words;
+};
+inline OnceSpace once_space(int kmax, int NC, bool greedy) {
+    OnceSpace s;
+    s.parts = (NC + kOnceWaves - 1) / kOnceWaves;
+    const long positions = (long)kmax + 1;
+    s.flags = 2 + 4l * kmax * s.parts;  // the partials lie before them, from word 2 on
+    s.best = s.flags + s.parts;
+    s.masses = s.best + (greedy ? 2 * positions * s.parts : 0);
+    s.words = s.masses + positions * NC;
+    return s;
+}
+
+// Its LDS: the masses, the drafts' log-probs, the partials and the candidates of a sequence.
+inline size_t once_lds(int kmax, int NC, bool greedy) {
+    const size_t positions = (size_t)kmax + 1, parts = (size_t)(NC + kOnceWaves - 1) / kOnceWaves;
+    return positions * NC * sizeof(Partial) + 2 * kmax * sizeof(double) + 4 * kmax * parts * sizeof(unsigned) +
+           (greedy ? positions * parts * (sizeof(double) + sizeof(int)) : 0);
+}
+
+// Which blocks: up to two workgroups a compute unit.  The third rows of all positions are read and summed for one of them, which costs
+// nothing while units are idle; beyond, a row pass and a recovery that share the chip's arithmetic take less (us a step by graph
+// replays, two launches -> one; by workgroups: 40 (1 sequence of 4 drafts, V = 32000 fp32) 10.5 -> 8.4, 144 (1 of 8, V = 128256 bf16) 13.9 ->
+// 11.5, 252 (4 of 8, V = 50257) 14.3 -> 11.8, 288 (8 of 8, V = 32000) 14.1 -> 13.7, 504 (8 of 8, V = 50257) 15.5 -> 14.8, 512 (16 of 1, V = 65536
+// fp32) 13.7 -> 12.3; 544 (8 of 16, V = 32000) 16.4 -> 17.0, 576 (4 of 8, V = 128256) 15.7 -> 16.4, 1152 18.5 -> 22.1).  Greedy with a steering
+// term, one: it compares every logit in double (224 (16 of 1, V = 50257) 15.0 -> 12.7; 312 (8 of 2, V = 100352) 14.8 -> 15.8).
+inline bool block_in_one_launch(int B, int kmax, int NC, bool plain, bool greedy, int cus) {
+    if (kmax < 1 || kmax > kOnceMaxDrafts || NC > kOnceMaxParts * kOnceWaves) return false;
+    return (long)B * (kmax + 1) * ((NC + kOnceWaves - 1) / kOnceWaves) <= (greedy && !plain ? 1l : 2l) * cus;
+}
+
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 inline int chunks_of(int elems, int vec) {

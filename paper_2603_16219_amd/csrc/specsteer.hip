@@ -28,7 +28,9 @@
 //                  several workgroups; the one that delivers its chunk masses last
 //                  draws the token (see accept_recover_kernel; hand-over by write-through
 //                  stores and an arrival counter, without cache-wide fences).
-//   row_mass, row_draw  the same without drafts, for rows too long for one workgroup each: the chunk masses, and the draw;
+//   block_once     small blocks in one launch: the row pass's partials and the recovery masses of every position, and the rest by the
+//                  workgroup that delivers last
+//   row_mass, row_draw  accept_recover without drafts, for rows too long for one workgroup each: the chunk masses, and the draw;
 //                  row_draw also writes the full log-prob rows beside the draw, on request
 //   recovery_logprob  the full log-prob rows where no workgroup shares a recovery row, a second sweep over the rows at n_b
 //
@@ -37,6 +39,7 @@
 // (log-sum-exp combine, log-probs, alpha, CDF walk across chunks) is double.
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cmath>
 #include <cstdint>
 
@@ -1249,6 +1252,297 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
         write_logprobs<DT, VEC, PLAIN>(g, sp, sm, a.recovery_logprobs + (long)b * V, V, v, NT, v == tid ? tid : kNoTail, a.c, a.bc, [&] { return sh_log2z; });
 }
 
+// ------------------------------------------------------------------ kernel: small blocks in one launch
+
+// Words that say themselves that they are there: 32 bits of the call's tag beside 32 of what is handed over, written and read with
+// device-scope atomics.  Whoever finds every word of a sequence with its tag has all that was delivered, without a
+// counter that someone would have had to clear before.  The words are cleared by whoever goes on, so that a graph that is replayed, whose
+// calls carry the same tag each time, meets none of the last replay; what else may lie in the space matches by accident only.
+struct Words {
+    unsigned long long* w;
+    unsigned tag;
+    // A different tag for every word, so that a space filled with one pattern matches one of them at most.
+    __device__ __forceinline__ unsigned tag_of(int i) const { return tag + (unsigned)i * 0x9E3779B1u; }
+    __device__ __forceinline__ void put(int i, unsigned v) const { st_dev(w + i, (unsigned long long)tag_of(i) << 32 | v); }
+    __device__ __forceinline__ bool get(int i, unsigned& v) const {
+        const unsigned long long x = ld_dev(w + i);
+        v = (unsigned)x;
+        return (unsigned)(x >> 32) == tag_of(i);
+    }
+    // A greedy candidate in words i and i + 1: 64 bits of the value, 21 of the token (up to SS_MAX_VOCAB, for none), and the tags'
+    // upper 21 and 22 bits.
+    __device__ __forceinline__ void put_best(int i, double v, int idx) const {
+        const unsigned long long x = (unsigned long long)__double_as_longlong(v);
+        st_dev(w + i, (unsigned long long)(tag_of(i) >> 11) << 43 | x >> 21);
+        st_dev(w + i + 1, (unsigned long long)(tag_of(i + 1) >> 10) << 42 | (x & 0x1FFFFFull) << 21 | (unsigned long long)idx);
+    }
+    __device__ __forceinline__ bool get_best(int i, double& v, int& idx) const {
+        const unsigned long long x = ld_dev(w + i), y = ld_dev(w + i + 1);
+        v = __longlong_as_double((long long)(x << 21 | (y >> 21 & 0x1FFFFFull)));
+        idx = (int)(y & 0x1FFFFFull);
+        return (unsigned)(x >> 43) == tag_of(i) >> 11 && (unsigned)(y >> 42) == tag_of(i + 1) >> 10;
+    }
+    __device__ __forceinline__ void clear(int i) const { st_dev(w + i, 0ull); }
+};
+
+struct OnceArgs {
+    RecArgs rec;
+    unsigned long long* words;  // [B][word_stride], see once_space
+    long word_stride;
+    unsigned tag;               // of this call's words
+    OnceSpace once;
+};
+
+// The row pass's sum over a chunk of full vectors, those that are not there -inf.
+template <int DT, int VEC>
+__device__ __forceinline__ void lse_chunk(Acc& acc, const typename RawT<DT, VEC>::type (&r)[kChunkSteps], float c_hi) {
+    float h[kChunkSteps * VEC];
+#pragma unroll
+    for (int j = 0; j < kChunkSteps; ++j) {
+        float hj[VEC];
+        unpack(r[j], hj);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) h[j * VEC + i] = hj[i];
+    }
+    acc_add_f32<kChunkSteps * VEC>(acc, h, c_hi);
+}
+
+// The whole block for small batches, without log-prob rows: a workgroup for kOnceWaves chunks of one position of one sequence, a chunk a wave.
+//   1  the chunk's slice partials in G and S_noctx (a draft's position) and its recovery mass, from one reading of the three rows;
+//      the workgroup's partials merged
+//   2  hand-over: the masses, and behind them, as words that say that they are there, the partials (the bonus position: only that)
+//   3  the part that finds the words of all parts: ratio test, first rejection, draw from the masses of that position
+// What bounds such a block is its chain of memory round trips and launches.  By a row pass, and a recovery whose parts each test, sweep the
+// rows of one position and hand over, there were eight round trips and a launch between; the masses of every position, formed beside
+// the partials on units that are idle, leave five: logits, hand-over (two), the other parts' masses, and the chunk that the token is in.  One
+// sequence of 4 drafts, V = 32000 fp32 10.55 -> 8.46 us a step (a launch less of host time, and 8.4 on the GPU instead of 10.5), 1 of 8
+// drafts, V = 128256 bf16 13.9 -> 11.5, 4 of 8, V = 50257 14.3 -> 11.8.
+// Parts end together, so that several find all words; the claim, an exchange on its way beside the masses, leaves one of them (should another
+// come behind its clearing, both draw, from the same words, the same token).  Nobody waits for anybody.
+template <int DT, int VEC, bool GREEDY, bool PLAIN>
+__global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const OnceArgs o) {
+    const RecArgs& a = o.rec;
+    static_assert(kOnceWaves == kDrawWaves, "a vector a lane of the drawing waves");
+    extern __shared__ double smem_d[];
+    __shared__ Partial sh_lse[kOnceWaves][2];
+    __shared__ double sh_best_v[kOnceWaves], sh_sum[kDrawWaves];
+    __shared__ int sh_best_i[kOnceWaves], sh_any[kDrawWaves], sh_missing[kOnceWaves], sh_mine;
+    __shared__ float sh_h[2 * kOnceMaxDrafts];
+    const int kmax = a.kmax, V = a.V, NC = a.NC, PP = o.once.parts;
+    const int per = (kmax + 1) * PP, b = (int)blockIdx.x / per, part = (int)blockIdx.x - b * per, t = part / PP, pp = part - t * PP;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    Partial* const mass = reinterpret_cast<Partial*>(smem_d);                                     // [kmax + 1][NC]
+    double* const lp = smem_d + (kmax + 1) * NC;                                                 // [kmax][2]
+    unsigned* const parts = reinterpret_cast<unsigned*>(lp + 2 * kmax);                          // [kmax][PP][2][E, s]
+    double* const cand_v = lp + 2 * kmax + 2 * kmax * PP;                                        // [kmax + 1][PP]
+    int* const cand_i = reinterpret_cast<int*>(cand_v + (GREEDY ? (kmax + 1) * PP : 0));
+
+    const int K = a.draft_len ? a.draft_len[b] : kmax;
+    const float u = lane <= kmax ? a.uniforms[(long)b * (kmax + 1) + lane] : 0.f;  // of the tests and, in lane kmax, of the draw
+    const auto flag = [&]() {
+        const float nanv = __int_as_float(0x7FC00000);
+        if (a.draft_logprobs && tid < 2 * kmax) a.draft_logprobs[(long)b * kmax * 2 + tid] = nanv;
+        if (tid == 0) {
+            a.accepted_len[b] = -1;
+            a.next_token[b] = -1;
+            if (a.next_token_logprob) a.next_token_logprob[b] = nanv;
+        }
+    };
+    if (K < 0 || K > kmax) {
+        if (part == 0) flag();
+        return;
+    }
+    if (t > K) return;
+    unsigned long long* const w = o.words + (long)b * o.word_stride;
+    const Words words{w, o.tag};
+    unsigned long long* const gmass = w + o.once.masses;
+
+    // ---- one chunk of this position
+    const int y = tid < 2 * K ? a.draft[(long)b * kmax + (tid >> 1)] : 0;
+    const int c = pp * kOnceWaves + wave;
+    const RecRow<DT, VEC> row(a, b, t);
+    const void* const sm = row_ptr<DT>(a.Sm, (long)b * a.sb + (long)t * a.st - row.head);  // row.sm, but with PLAIN
+    const long vbase = (long)c * (kChunkSteps * kWave) + lane;
+    const bool whole = c < row.nch, last = c == row.nch && lane < row.tailc;  // full vectors, or one logit past them
+    typename RawT<DT, VEC>::type rg[kChunkSteps], rp[kChunkSteps], rm[kChunkSteps];
+    float tg[1] = {0.f}, tp[1] = {0.f}, tm[1] = {0.f};
+    if (whole) {
+#pragma unroll
+        for (int j = 0; j < kChunkSteps; ++j) {
+            const long v = vbase + (long)j * kWave;
+            rg[j] = rp[j] = rm[j] = neg_inf_raw<DT, VEC>();  // past the row: adds nothing, and has no steering
+            if (v < row.nvec) {
+                rg[j] = ld_raw<DT, VEC>(row.g, v);
+                if (!PLAIN) rp[j] = ld_raw<DT, VEC>(row.sp, v);
+                if (!PLAIN || t < K) rm[j] = ld_raw<DT, VEC>(sm, v);
+            }
+        }
+    } else if (last) {
+        const long e = row.nvec * VEC + lane;
+        tg[0] = ld_elem<DT>(row.g, e);
+        tp[0] = ld_steer<DT, PLAIN>(row.sp, e);
+        tm[0] = ld_elem<DT>(sm, e);
+    }
+    float hy = 0.f;
+    if (tid < 2 * K) {  // the draft tokens' logits, on their way beside the rows
+        const long off = (long)b * a.sb + (long)(tid >> 1) * a.st;
+        hy = y >= 0 && y < V ? ld_elem<DT>(row_ptr<DT>(tid & 1 ? a.Sm : a.G, off), y) : __uint_as_float(kNoToken);
+    }
+    Acc g{kEInit, 0.f}, m{kEInit, 0.f}, rec{kEInit, 0.f};
+    Best best{-__builtin_huge_val(), kNoBest};
+    const bool first = row.head && vbase == 0;  // this lane's first vector starts with the element before the row
+    if (first) {
+        rg[0] = set_first(rg[0], kBf16NegInf);
+        rm[0] = set_first(rm[0], kBf16NegInf);
+    }
+    if (whole) {
+        if (t < K || PLAIN) lse_chunk<DT, VEC>(g, rg, a.c_hi);
+        if (t < K) lse_chunk<DT, VEC>(m, rm, a.c_hi);
+    } else if (last) {
+        acc_add_f32<1>(g, tg, a.c_hi);
+        acc_add_f32<1>(m, tm, a.c_hi);
+    }
+    // the recovery mass, as chunk_mass has it
+    if (first) {
+        rp[0] = set_first(rp[0], 0u);
+        rm[0] = set_first(rm[0], 0u);
+    }
+    if (whole) {
+#pragma unroll
+        for (int j = 0; j < kChunkSteps; ++j) {
+            const int at = (int)(vbase + (long)j * kWave) * VEC;
+            float hg[VEC], hp[VEC], hm[VEC];
+            unpack(rg[j], hg);
+            unpack_steer<DT, VEC, PLAIN>(rp[j], rm[j], hp, hm);
+            if (!PLAIN) acc_add_rec<DT, VEC, GREEDY>(rec, hg, hp, hm, a.c, a.bc, (float)a.c, (float)a.bc, a.beta, at, best);
+            if (PLAIN && GREEDY) best_of<VEC>(best, hg, at);
+            if (PLAIN && vbase + (long)j * kWave < row.nvec) acc_add_f32<VEC>(rec, hg, a.c_hi);
+        }
+        if (PLAIN && vbase + (long)(kChunkSteps - 1) * kWave < row.nvec) rec = g;
+    } else if (last) {
+        const int at = (int)(row.nvec * VEC) + lane;
+        if (!PLAIN) acc_add_rec<DT, 1, GREEDY>(rec, tg, tp, tm, a.c, a.bc, (float)a.c, (float)a.bc, a.beta, at, best);
+        if (PLAIN && GREEDY) best_of<1>(best, tg, at);
+        if (PLAIN) rec = g;
+    }
+    if (t < K) {
+        const Partial pg = wave_combine(g), pm = wave_combine(m);
+        if (lane == 0) {
+            sh_lse[wave][0] = pg;
+            sh_lse[wave][1] = pm;
+        }
+    }
+    const Partial p = wave_combine(rec);
+    if (c < row.NC && lane == 0) st_dev_partial(reinterpret_cast<Partial*>(gmass) + (long)t * NC + c, p);
+    if (GREEDY) {
+        wave_best(best);
+        if (lane == 0) {
+            sh_best_v[wave] = best.v;
+            sh_best_i[wave] = best.idx <= V ? best.idx - row.head : best.idx;
+        }
+    }
+    if (tid < 2 * K) sh_h[tid] = hy;
+    wait_stores();  // the masses have reached memory before the words that tell of them
+    __syncthreads();
+    if (wave == 0) {
+        if (t < K) {
+            const int x = lane >> 1 & 1;
+            int E = sh_lse[0][x].E;
+#pragma unroll
+            for (int i = 1; i < kOnceWaves; ++i) E = max(E, sh_lse[i][x].E);
+            float s = 0.f;
+#pragma unroll
+            for (int i = 0; i < kOnceWaves; ++i) s += ldexpf(sh_lse[i][x].s, sh_lse[i][x].E - E);
+            if (lane < 4) words.put(2 + 4 * part + lane, lane & 1 ? __float_as_uint(s) : (unsigned)E);
+        } else if (lane == 0) {
+            words.put((int)o.once.flags + pp, 0u);
+        }
+        if (GREEDY) {
+            best.v = lane < kOnceWaves ? sh_best_v[lane] : -__builtin_huge_val();
+            best.idx = lane < kOnceWaves ? sh_best_i[lane] : kNoBest;
+            wave_best(best);
+            if (lane == 0) words.put_best((int)o.once.best + 2 * part, best.v, min(best.idx, V));
+        }
+        wait_stores();
+    }
+    __syncthreads();
+
+    // ---- whether all parts have delivered.  One that ends a moment before the last may find so too: the claim leaves one of them.
+    bool all = true;
+    const int nlse = 4 * K * PP, nflag = nlse + PP, ncand = GREEDY ? (K + 1) * PP : 0;
+    for (int i = tid; i < nflag; i += kOnceWaves * kWave) {
+        unsigned v;
+        all = words.get(i < nlse ? 2 + i : (int)o.once.flags + (i - nlse), v) && all;
+        if (i < nlse) parts[i] = v;
+    }
+    if (GREEDY)
+        for (int i = tid; i < ncand; i += kOnceWaves * kWave) all = words.get_best((int)o.once.best + 2 * i, cand_v[i], cand_i[i]) && all;
+    const unsigned long long missing = __ballot(!all);
+    if (lane == 0) sh_missing[wave] = missing != 0ull;
+    __syncthreads();
+    if (sh_missing[0] | sh_missing[1] | sh_missing[2] | sh_missing[3]) return;
+    const unsigned long long claim = (unsigned long long)~o.tag << 32 | o.tag;
+    unsigned long long before = 0ull;
+    if (tid == 0) before = __hip_atomic_exchange(w, claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+
+    // ---- the ratio test, while the masses and the claim are on their way
+    constexpr int kHeld = 5;
+    unsigned long long held[kHeld];
+    const int nmass = (K + 1) * NC;
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) {
+        const int at = tid + i * kOnceWaves * kWave;
+        held[i] = at < nmass ? ld_dev(gmass + at) : 0ull;
+    }
+    const int l = tid & 15;
+    for (int q = tid >> 4; q < 2 * K; q += kOnceWaves * kWave / 16) {
+        const unsigned* const e = parts + (((q >> 1) * PP + l) * 2 + (q & 1)) * 2;
+        const Partial p = l < PP ? Partial{(int)e[0], __uint_as_float(e[1])} : Partial{kEInit, 0.f};
+        const int E = row_max_i32(p.E);
+        const Partial m{E, row_sum_f32(ldexpf(p.s, p.E - E))};
+        if (l == 0) lp[q] = kLn2 * ((double)sh_h[q] * a.c - row_log2(m, a.rho));
+    }
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) {
+        const int at = tid + i * kOnceWaves * kWave;
+        if (at < nmass) mass[at] = Partial{(int)(unsigned)held[i], __uint_as_float((unsigned)(held[i] >> 32))};
+    }
+    for (int at = tid + kHeld * kOnceWaves * kWave; at < nmass; at += kOnceWaves * kWave) mass[at] = ld_dev_partial(reinterpret_cast<Partial*>(gmass) + at);
+    if (tid == 0) sh_mine = before != claim;
+    __syncthreads();
+    if (!sh_mine) return;
+    for (int i = tid; i < nflag; i += kOnceWaves * kWave) words.clear(i < nlse ? 2 + i : (int)o.once.flags + (i - nlse));
+    for (int i = tid; i < 2 * ncand; i += kOnceWaves * kWave) words.clear((int)o.once.best + i);
+    if (tid == 0) words.clear(0);
+    bool rej = false, none = false;
+    if (lane < K) {
+        const double alpha = fmin(1.0, exp(lp[2 * lane] - lp[2 * lane + 1] - a.ln_lambda));  // Eq. 7
+        rej = !((double)u <= alpha);
+        none = __float_as_uint(sh_h[2 * lane]) == kNoToken || __float_as_uint(sh_h[2 * lane + 1]) == kNoToken;
+    }
+    if (__ballot(none)) {
+        flag();
+        return;
+    }
+    const unsigned long long rmask = __ballot(rej);
+    const int n = rmask ? first_lane(rmask) : K;
+    if (a.draft_logprobs && tid < 2 * kmax) a.draft_logprobs[(long)b * kmax * 2 + tid] = tid < 2 * K ? (float)lp[tid] : 0.f;
+
+    // ---- the draw
+    const RecRow<DT, VEC> at(a, b, n);
+    const Partial* const tab = mass + n * NC;
+    if (GREEDY) {
+        if (wave > 0) return;
+        best.v = lane < PP ? cand_v[n * PP + lane] : -__builtin_huge_val();
+        best.idx = lane < PP ? cand_i[n * PP + lane] : kNoBest;
+        wave_best(best);
+        greedy_token<PLAIN>(a, b, n, lane, tab, at.NC, best);
+    } else {
+        const double us = (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(u), kmax));
+        draw_token<DT, VEC, PLAIN, false>(a, b, n, us, wave, lane, tab, at, sh_sum, sh_any, nullptr);
+    }
+}
+
 // ------------------------------------------------------------------ kernels: few rows without drafts
 
 // k_max == 0 and the row in several parts: with no row pass to clear arrival counters, the masses and the draw are two
@@ -1393,6 +1687,12 @@ void launch_row_pass(LseArgs la, const Window& w, const RowWindow& win, int unif
                        stream, la);
 }
 
+// A tag for the words of a call (Words): another one for each of 2^32 calls, begun anywhere.
+unsigned next_tag() {
+    static std::atomic<unsigned> n{(unsigned)std::chrono::steady_clock::now().time_since_epoch().count()};
+    return n.fetch_add(0x85EBCA6Bu, std::memory_order_relaxed);
+}
+
 // Whether what is enqueued on the stream goes into a graph.
 bool being_captured(hipStream_t stream) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -1456,6 +1756,20 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     la.zero_n = split ? B : 0;
     const size_t smem = (size_t)2 * kmax * sizeof(double) + (size_t)ra.NC * sizeof(Partial);
 
+    const int kind = (ra.greedy ? 1 : 0) | (ra.plain ? 2 : 0);
+    // The call whose stages are timed has them one behind the other.
+    if (!ev && windows == 1 && !recovery_logprobs && block_in_one_launch(B, kmax, ra.NC, ra.plain != 0, ra.greedy != 0, device_cu_count())) {
+        const OnceArgs oa{ra, reinterpret_cast<unsigned long long*>(ws + pl.off_partial),
+                          (long)((pl.bytes - pl.off_partial) / sizeof(uint64_t) / B), next_tag(), once_space(kmax, ra.NC, ra.greedy != 0)};
+        if (oa.once.words <= oa.word_stride) {
+            static void (*const once[4])(OnceArgs) = {block_once_kernel<DT, VEC, false, false>, block_once_kernel<DT, VEC, true, false>,
+                                                      block_once_kernel<DT, VEC, false, true>, block_once_kernel<DT, VEC, true, true>};
+            launch(once[kind], dim3((unsigned)(B * (kmax + 1) * oa.once.parts)), dim3(kOnceWaves * kWave),
+                   once_lds(kmax, ra.NC, ra.greedy != 0), stream, oa);
+            return hipGetLastError();
+        }
+    }
+
     mark(0);
     for (int i = 0; i < windows; ++i) {
         const Window& w = wins[i];
@@ -1486,7 +1800,6 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
          accept_recover_kernel<DT, VEC, false, true, 512>, accept_recover_kernel<DT, VEC, true, true, 512>},
         {accept_recover_kernel<DT, VEC, false, false, 1024>, accept_recover_kernel<DT, VEC, true, false, 1024>,
          accept_recover_kernel<DT, VEC, false, true, 1024>, accept_recover_kernel<DT, VEC, true, true, 1024>}};
-    const int kind = (ra.greedy ? 1 : 0) | (ra.plain ? 2 : 0);
     const long per = kLogprobThreads * kLogprobUnroll;  // vectors of a segment of a log-prob row
     const int segs = V / VEC > per ? (int)((V / VEC + per - 1) / per) : 1;
     const bool rows_apart = recovery_logprobs && !rows_inside;

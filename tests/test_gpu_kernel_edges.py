@@ -532,6 +532,85 @@ def test_recovery_launch_by_chunks_and_drafts(binding, oracle, dtype, k_max, chu
     parity.compare(out, ora, inp["uniforms"], None)
 
 
+# Small blocks in one launch: a wave a chunk of 256 vectors, four to a workgroup.  Rows shorter than a vector, of one chunk and one logit more
+# and less, of whole workgroups and a chunk over, the longest (64 chunks) and, beyond and where the space does not suffice (16 greedy
+# drafts), two launches; rows at odd elements; lengths of 0, ids and lengths that flag.  On a space of garbage that the calls before
+# have left, direct and as the stages of the timed call, whose tokens are the same.
+@pytest.mark.parametrize("greedy,beta", [(False, 0.8), (True, 0.8), (False, 0.0), (True, 0.0)])
+@pytest.mark.parametrize("dtype,batch,k_max,vocab", [
+    ("bf16", 3, 2, 5), ("bf16", 5, 16, 7), ("bf16", 5, 3, 2047), ("bf16", 5, 4, 2048), ("bf16", 5, 1, 2049), ("bf16", 3, 4, 4 * 2048 + 9),
+    ("bf16", 3, 16, 17 * 2048 - 3), ("bf16", 6, 4, 32000), ("bf16", 1, 8, 64 * 2048), ("bf16", 4, 2, 64 * 2048 - 1), ("bf16", 2, 3, 64 * 2048 + 1),
+    ("bf16", 40, 2, 3 * 2048 + 1), ("f32", 1, 4, 32000), ("f32", 4, 4, 1025), ("f32", 3, 16, 33 * 1024 + 2), ("f32", 2, 2, 64 * 1024)])
+def test_small_blocks_in_one_launch(binding, oracle, dtype, batch, k_max, vocab, greedy, beta):
+    w = recipe("c4", dtype, batch=batch, k_max=k_max, vocab=vocab)
+    inp = W.generate(w, "cuda")
+    gen = torch.Generator("cuda").manual_seed(batch + vocab)
+    lens = torch.randint(0, k_max + 1, (batch,), generator=gen, device="cuda", dtype=torch.int32)
+    lens[0] = k_max
+    if batch > 3:
+        lens[1], lens[2], lens[3] = k_max + 1, 0, 1
+        inp["draft"][3, 0] = vocab
+    inp["draft_len"] = lens
+    p = binding.make_params(batch, k_max, vocab, W.torch_dtype(dtype), lam=w.lam, beta=beta, temperature=w.temperature,
+                            flags=binding.SS_FLAG_GREEDY if greedy else 0)
+    ws = torch.full((binding.workspace_bytes(p),), 0xAB, dtype=torch.uint8, device="cuda")
+    names = ("accepted_len", "next_token", "next_token_logprob", "recovery_logprobs", "draft_logprobs")
+
+    def call(timed):
+        mk = lambda dt, *shape: torch.full(shape, -7, dtype=dt, device="cuda")
+        o = [mk(torch.int32, batch), mk(torch.int32, batch), mk(torch.float32, batch), None, mk(torch.float32, batch, k_max, 2)]
+        binding.verify_block_raw(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], lens, inp["uniforms"], p, *o, ws, timed=timed)
+        torch.cuda.synchronize()
+        return dict(zip(names, o))
+
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=beta, temperature=w.temperature, greedy=greedy, want_recovery_logprobs=False)
+    first = call(False)
+    parity.compare(first, ora, inp["uniforms"], lens)
+    staged, again = call(True), call(False)
+    for k in ("accepted_len", "next_token", "next_token_logprob"):
+        assert torch.equal(torch.nan_to_num(first[k]), torch.nan_to_num(staged[k])), k
+    assert all(first[k] is None or torch.equal(torch.nan_to_num(first[k]), torch.nan_to_num(again[k])) for k in names)
+
+
+@pytest.mark.parametrize("greedy", [False, True])
+@pytest.mark.parametrize("dtype,batch,k_max,vocab", [("f32", 1, 4, 32000), ("bf16", 4, 4, 50257)])
+def test_small_blocks_in_one_launch_inside_a_hip_graph(binding, dtype, batch, k_max, vocab, greedy):
+    """The words of a captured call carry the same tag on every replay: replays on new drafts, lengths and uniforms, one behind the
+    other and with direct calls on the same workspace between them, equal the direct calls."""
+    w = recipe("c4", dtype, batch=batch, k_max=k_max, vocab=vocab)
+    inp = W.generate(w, "cuda")
+    inp["draft_len"] = torch.full((batch,), k_max, dtype=torch.int32, device="cuda")
+    p = binding.make_params(batch, k_max, vocab, W.torch_dtype(dtype), lam=w.lam, beta=w.beta, temperature=w.temperature,
+                            flags=binding.SS_FLAG_GREEDY if greedy else 0)
+    ws = torch.full((binding.workspace_bytes(p),), 0x5A, dtype=torch.uint8, device="cuda")
+    outs = [[torch.empty(batch, dtype=dt, device="cuda") for dt in (torch.int32, torch.int32, torch.float32)] for _ in range(2)]
+
+    def call(out):
+        binding.verify_block_raw(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["draft_len"], inp["uniforms"], p,
+                                 *out, None, None, ws)
+
+    call(outs[0])
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call(outs[0])
+    for rnd in range(24):
+        gen = torch.Generator("cuda").manual_seed(rnd)
+        inp["uniforms"].uniform_(generator=gen)
+        inp["draft_len"].random_(0, k_max + 1, generator=gen)
+        inp["draft"].copy_(inp["draft"].roll(1, 1))
+        inp["S_noctx"].copy_(inp["S_noctx"].roll(1, 2))
+        for t in outs[0]:
+            t.fill_(-7)
+        g.replay()
+        if rnd % 3:  # else the next replay follows this one's clearing with nothing between
+            torch.cuda.synchronize()
+            call(outs[1])
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, b) for a, b in zip(*outs)), rnd
+        assert torch.all(outs[0][0] >= 0)
+
+
 # The cloud top-k queues what reaches its bound wave by wave: as many equal largest logits as its buffers hold (256 in registers,
 # 1024 candidates, 2048 vectors) and one more or less, next to each other, a vector apart and all in the lanes of one wave.
 @pytest.mark.parametrize("spread", ["dense", "vectors", "one wave"])

@@ -32,6 +32,14 @@ int main() {
             std::printf("%d\n", rows_in_one_launch(a[0], a[1], a[2], a[3], a[4], a[5]) ? 1 : 0);
             continue;
         }
+        if (!std::strcmp(what, "once")) {  // B kmax chunks plain greedy cus: whether in one launch, and its space and LDS
+            int a[6];
+            if (std::scanf("%d %d %d %d %d %d", a, a + 1, a + 2, a + 3, a + 4, a + 5) != 6) return 1;
+            const OnceSpace s = once_space(a[1], a[2], a[4]);
+            std::printf("%d %d %ld %ld %ld %ld %ld\n", block_in_one_launch(a[0], a[1], a[2], a[3], a[4], a[5]) ? 1 : 0, s.parts, s.flags,
+                        s.best, s.masses, s.words, (long)once_lds(a[1], a[2], a[4]));
+            continue;
+        }
         if (!std::strcmp(what, "odd")) {  // vec base base base B kmax sb st
             unsigned a[3]; int vec, B, k; long sb, st;
             if (std::scanf("%d %u %u %u %d %d %ld %ld", &vec, a, a + 1, a + 2, &B, &k, &sb, &st) != 8) return 1;
@@ -137,6 +145,25 @@ def test_rows_without_drafts_are_taken_whole_while_that_pays(planner, dtype, pla
     for batch, chunks in most.items():
         tail = f"{BF16 if dtype == 'bf16' else 0} {plain} {greedy} {captured}"
         assert planner([f"one {batch} {max(chunks, 1)} {tail}", f"one {batch} {chunks + 1} {tail}"]) == [(int(chunks > 0),), (0,)]
+
+
+# Small blocks in one launch: up to two workgroups a unit, one for greedy decoding with a steering term.
+@pytest.mark.parametrize("batch,k_max,chunks,plain,greedy,one", [
+    (1, 4, 32, 0, 0, 1), (1, 0, 32, 0, 0, 0), (32, 1, 32, 0, 0, 1), (33, 1, 32, 0, 0, 0), (32, 1, 33, 0, 0, 0), (1, 16, 64, 0, 0, 1),
+    (1, 17, 4, 0, 0, 0), (1, 1, 65, 0, 0, 0), (256, 1, 4, 0, 0, 1), (257, 1, 1, 1, 0, 0), (16, 1, 32, 0, 1, 1), (17, 1, 32, 0, 1, 0),
+    (32, 1, 32, 1, 1, 1), (33, 1, 32, 1, 1, 0)])
+def test_small_blocks_take_one_launch_while_units_are_idle(planner, batch, k_max, chunks, plain, greedy, one):
+    assert planner([f"once {batch} {k_max} {chunks} {plain} {greedy} {CUS}"])[0][0] == one
+
+
+def test_the_space_of_a_block_in_one_launch_holds_what_its_parts_deliver(planner):
+    for k in range(1, 17):
+        for chunks in (1, 3, 4, 5, 32, 63, 64):
+            for greedy in (0, 1):
+                _, parts, flags, best, masses, words, lds = planner([f"once 1 {k} {chunks} 0 {greedy} {CUS}"])[0]
+                assert parts == -(-chunks // 4) and flags == 2 + 4 * k * parts and best == flags + parts
+                assert masses == best + greedy * 2 * (k + 1) * parts and words == masses + (k + 1) * chunks
+                assert lds == 8 * (k + 1) * chunks + 16 * k + 16 * k * parts + greedy * 12 * (k + 1) * parts < 32768
 
 
 def test_a_row_read_from_one_element_before_may_have_a_chunk_more(planner):
