@@ -193,6 +193,7 @@ ss_status specsteer_verify_block_static(const void *G, const void *S_ctx, const 
  * Eq. 7, Eq. 8; same arguments, same outputs, same errors).  It brackets each kernel with
  * HIP events recorded on `stream`, WAITS for the last one, and writes the elapsed
  * milliseconds of each stage to the host array stage_ms[SS_NUM_STAGES]:
+ * (a small block that the other entry points take in one launch has its stages one behind the other here)
  *   [SS_STAGE_ROW_PASS1] log-sum-exp pass over G and S_noctx, positions [0, first window),
  *   [SS_STAGE_VERDICT]   ratio test on those positions (0 in the one-pass schedule),
  *   [SS_STAGE_ROW_PASS2] log-sum-exp passes over the remaining positions of the sequences still in

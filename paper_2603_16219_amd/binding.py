@@ -1,4 +1,7 @@
-"""ctypes binding of the C-ABI library: argument marshalling only.
+"""Binding of the C-ABI library: argument marshalling only.
+
+The wrappers hand arguments that need nothing done to them to native code (csrc/calls.cpp), which makes the outputs and calls the
+library; what has to be converted, copied or refused, and the raw calls, go through ctypes here.
 
 Every step of the block runs inside ``libspecsteer.so`` (hand-written HIP for
 gfx950); PyTorch supplies device memory and the stream.  There is no CPU or
@@ -7,6 +10,7 @@ PyTorch fallback: if the library cannot be loaded or a call fails, this raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 from typing import Optional
 
@@ -45,11 +49,12 @@ class SpecSteerError(RuntimeError):
 
 
 _lib = None
+_calls = None  # the native wrappers, once the library is loaded
 
 
 def library() -> ctypes.CDLL:
     """Load libspecsteer.so from the package directory (building it only if absent)."""
-    global _lib
+    global _lib, _calls
     if _lib is None:
         path = _build.LIBRARY
         if not os.path.exists(path):
@@ -77,8 +82,23 @@ def library() -> ctypes.CDLL:
         lib.specsteer_status_string.restype = ctypes.c_char_p
         lib.specsteer_status_string.argtypes = [ctypes.c_int]
         lib.specsteer_version.restype = ctypes.c_int
-        _lib = lib
+        if not os.path.exists(_build.CALLS):
+            _build.build_calls()
+        spec = importlib.util.spec_from_file_location(__package__ + "._calls", _build.CALLS)
+        calls = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(calls)
+        calls.use(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            lib.specsteer_workspace_bytes, lib.specsteer_verify_block_unbound, lib.specsteer_cloud_topk, lib.specsteer_edge_resample)),
+            torch._C._cuda_getCurrentRawStream)
+        _lib, _calls = lib, calls
     return _lib
+
+
+def _done(out):
+    """What a native wrapper returned: the result, or the status of a call that failed."""
+    if type(out) is int:
+        raise SpecSteerError(out, status_string(out))
+    return out
 
 
 def status_string(status: int) -> str:
@@ -187,6 +207,11 @@ def verify_block(G: torch.Tensor, S_ctx: torch.Tensor, S_noctx: torch.Tensor, dr
     """specsteer_verify_block on device tensors G/S_ctx/S_noctx [B, k_max+1, V] (vocab stride 1),
     draft [B, k_max] int32, uniforms [B, k_max+1] float32.  Allocates the outputs (and a workspace
     unless one is given) with torch and returns them in a dict; runs on torch's current stream."""
+    if _calls is not None:
+        out = _calls.verify_block(G, S_ctx, S_noctx, draft, uniforms, lam, beta, temperature, draft_len, want_recovery_logprobs,
+                                  want_draft_logprobs, workspace, greedy, full_rows)
+        if out is not None:
+            return _done(out)
     if not (G.shape == S_ctx.shape == S_noctx.shape) or G.dim() != 3:
         raise ValueError("logit tensors must share a [B, k_max+1, V] shape")
     if not (G.dtype == S_ctx.dtype == S_noctx.dtype):
@@ -240,6 +265,10 @@ def steer_rows(G: torch.Tensor, S_ctx: torch.Tensor, S_noctx: torch.Tensor, unif
     one uniform per row) -- the per-token fusion the paper compares against.  This is the same entry
     point with no drafted positions (k_max = 0): each row is a one-row sequence whose bonus token is
     drawn from softmax((G + beta (S_ctx - S_noctx)) / T)."""
+    if _calls is not None:
+        out = _calls.steer_rows(G, S_ctx, S_noctx, uniforms, beta, temperature, greedy, want_logprobs)
+        if out is not None:
+            return _done(out)
     if G.dim() != 2 or uniforms.numel() != G.shape[0]:
         raise ValueError("rows must be [N, V] with one uniform per row")
     n, v = G.shape
@@ -294,6 +323,10 @@ def _split_params(T: torch.Tensor, beta: float, temperature: float, greedy: bool
 def cloud_topk(G: torch.Tensor, S_noctx: torch.Tensor, row: torch.Tensor, *, beta: float = 1.0,
                topk: int = 32):
     """specsteer_cloud_topk on device tensors: returns (index [B, topk] int32, value [B, topk] float32)."""
+    if _calls is not None:
+        out = _calls.cloud_topk(G, S_noctx, row, beta, topk)
+        if out is not None:
+            return _done(out)
     if G.dim() != 3 or G.shape != S_noctx.shape or G.stride() != S_noctx.stride() or G.stride(2) != 1:
         raise ValueError("G and S_noctx must share one [B, k_max+1, V] shape and stride, vocabulary contiguous")
     B = G.shape[0]
@@ -316,6 +349,10 @@ def edge_resample(index: torch.Tensor, value: torch.Tensor, S_ctx: torch.Tensor,
                   uniform: torch.Tensor, *, beta: float = 1.0, temperature: float = 1.0,
                   greedy: bool = False) -> dict:
     """specsteer_edge_resample on device tensors."""
+    if _calls is not None:
+        out = _calls.edge_resample(index, value, S_ctx, row, uniform, beta, temperature, greedy)
+        if out is not None:
+            return _done(out)
     if S_ctx.dim() != 3 or S_ctx.stride(2) != 1:
         raise ValueError("S_ctx must be [B, k_max+1, V] with the vocabulary contiguous")
     B = S_ctx.shape[0]

@@ -46,6 +46,7 @@
 #include "device_common.h"
 #include "plan.h"
 #include "specsteer.h"
+#include "unbound.h"
 
 namespace {
 
@@ -1707,7 +1708,7 @@ template <int DT>
 unsigned elem_parity(const void* p) { return (unsigned)(reinterpret_cast<uintptr_t>(p) / (DT == SS_BF16 ? 2 : 4)) & 1u; }
 
 template <int DT, int VEC>
-hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* recovery_logprobs, hipStream_t stream,
+hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* recovery_logprobs, bool unbound, hipStream_t stream,
                       hipEvent_t* ev) {
     const int B = ra.B, kmax = ra.kmax, V = ra.V;
     int32_t* lists[2] = {reinterpret_cast<int32_t*>(ws), reinterpret_cast<int32_t*>(ws + pl.off_list2)};
@@ -1732,7 +1733,7 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     const unsigned bases[3] = {elem_parity<DT>(ra.G), elem_parity<DT>(ra.recSp), elem_parity<DT>(ra.recSm)};
     ra.NC = chunks_per_row(V, VEC, odd_rows_possible(VEC, bases, B, kmax, ra.sb, ra.st));
     RecShape shape = recovery_shape(B, ra.NC, kmax, device_cu_count(), pl.split);
-    if (kmax == 0 && shape.part_chunks < ra.NC && rows_in_one_launch(B, ra.NC, DT, ra.plain != 0, ra.greedy != 0, being_captured(stream)))
+    if (kmax == 0 && shape.part_chunks < ra.NC && rows_in_one_launch(B, ra.NC, DT, ra.plain != 0, ra.greedy != 0, unbound || being_captured(stream)))
         shape = RecShape{1024, ra.NC};
     const bool rows_inside = recovery_logprobs && logprobs_in_recovery(B, kmax, V, DT == SS_BF16 ? 2 : 4);
     // Log-prob rows that lie on the logits (fp32 rows without drafts, in place): the token is drawn before any of them is written
@@ -1836,7 +1837,7 @@ ss_status verify_block_impl(const void* G, const void* S_ctx, const void* S_noct
                             const int32_t* draft_len, const float* uniforms, const ss_params* params,
                             int32_t* accepted_len, int32_t* next_token, float* next_token_logprob,
                             float* recovery_logprobs, float* draft_logprobs, void* workspace,
-                            size_t workspace_bytes, void* stream, hipEvent_t* ev) {
+                            size_t workspace_bytes, void* stream, hipEvent_t* ev, bool unbound = false) {
     if (!params) return SS_ERR_NULL;
     if (params->dtype != SS_F32 && params->dtype != SS_BF16) return SS_ERR_DTYPE;
     if (!shape_ok(params)) return SS_ERR_SHAPE;
@@ -1893,9 +1894,9 @@ ss_status verify_block_impl(const void* G, const void* S_ctx, const void* S_noct
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipError_t err;
     if (params->dtype == SS_BF16) {
-        err = launch_all<SS_BF16, 8>(la, ra, pl, ws, recovery_logprobs, s, ev);
+        err = launch_all<SS_BF16, 8>(la, ra, pl, ws, recovery_logprobs, unbound, s, ev);
     } else {
-        err = launch_all<SS_F32, 4>(la, ra, pl, ws, recovery_logprobs, s, ev);
+        err = launch_all<SS_F32, 4>(la, ra, pl, ws, recovery_logprobs, unbound, s, ev);
     }
     return err == hipSuccess ? SS_OK : SS_ERR_DEVICE;
 }
@@ -1940,6 +1941,16 @@ ss_status specsteer_verify_block(const void* G, const void* S_ctx, const void* S
     return verify_block_impl(G, S_ctx, S_noctx, draft, draft_len, uniforms, params, accepted_len, next_token,
                              next_token_logprob, recovery_logprobs, draft_logprobs, workspace, workspace_bytes,
                              stream, nullptr);
+}
+
+ss_status specsteer_verify_block_unbound(const void* G, const void* S_ctx, const void* S_noctx, const int32_t* draft,
+                                         const int32_t* draft_len, const float* uniforms, const ss_params* params,
+                                         int32_t* accepted_len, int32_t* next_token, float* next_token_logprob,
+                                         float* recovery_logprobs, float* draft_logprobs, void* workspace,
+                                         size_t workspace_bytes, void* stream) {
+    return verify_block_impl(G, S_ctx, S_noctx, draft, draft_len, uniforms, params, accepted_len, next_token,
+                             next_token_logprob, recovery_logprobs, draft_logprobs, workspace, workspace_bytes,
+                             stream, nullptr, true);
 }
 
 ss_status specsteer_verify_block_timed(const void* G, const void* S_ctx, const void* S_noctx, const int32_t* draft,
