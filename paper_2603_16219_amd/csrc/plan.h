@@ -102,8 +102,9 @@ inline RecShape recovery_shape(int B, int NC, int kmax, int cus, bool split) {
 // 13.0; 96 of 28 8.5 -> 8.4, of 36 8.9 -> 9.2; 128 of 36 9.5 -> 9.2, of 44 10.2 -> 10.2; fp32: 1 of 24 5.3 -> 5.2, of 32 5.4 -> 5.7; 64 of 32
 // 7.6 -> 7.6, of 40 7.8 -> 8.2; 128 of 40 9.2 -> 8.6, of 64 10.9 -> 11.4; with one, fp32: 96 of 17 9.6 -> 10.3, 128 of 17 11.2 -> 10.7, of 24
 // 12.7 -> 12.9; bf16: 128 of 17 12.3 -> 12.5).
-//   Outside of one the lines are where back-to-back calls through this repository's Python binding (some 9 us of host time beside the
-// launches) are as fast either way: they are bound by the host, 14.3 us in
+//   Outside of one, but for the binding's native wrappers (csrc/calls.cpp), whose host time is less than the GPU's, the lines are where
+// back-to-back calls with some 9 us of host time beside the launches (marshalling and three allocations in Python) are as fast either way:
+// they are bound by the host, 14.3 us in
 // two launches whatever the size, 11.4 in one until the rate of one compute unit (or, with a steering term, its
 // arithmetic) takes over.  A caller with less host time of its own, or whose host runs ahead of the GPU, pays up to twice the GPU's
 // time for it between these lines and those above; it gets the other shape by capturing the call.  Us a call in two launches -> in
