@@ -453,7 +453,7 @@ struct RecArgs {
     double c;        // log2(e) / T
     double bc;       // beta * log2(e) / T
     double beta;     // beta itself, for the greedy argmax of Eq. 8
-    double ln_lambda;
+    double lambda;
     double rho;      // (c - fl32(c)) / fl32(c): first-order repair of sums formed with the rounded scale
     float c_hi;      // fl32(c)
     int greedy;      // SS_FLAG_GREEDY
@@ -912,10 +912,28 @@ __device__ __forceinline__ const Partial* partials_of(const RecArgs& a, int b, i
     return a.partial + (((long)b * (a.t_hi - a.t_lo) + (t - a.t_lo)) * 2 + x) * a.NS;
 }
 
+// What the ratio test knows of a (position, tensor) pair, in LDS: the row's merged partials and the draft token's logit (kNoToken: none).
+struct Pairs {
+    Partial* row;  // [2 * kmax], pair 2 * t + x
+    float* h;
+    // log P(y_t), for who asks for it
+    __device__ __forceinline__ double logprob(const RecArgs& a, int q) const { return kLn2 * ((double)h[q] * a.c - row_log2(row[q], a.rho)); }
+    __device__ __forceinline__ bool unknown(int t) const { return __float_as_uint(h[2 * t]) == kNoToken || __float_as_uint(h[2 * t + 1]) == kNoToken; }
+    // Eq. 7 at position t against the uniform u: P_LLM / (lambda * P_SLM^-) is 2^((h_LLM - h_SLM^-) * c) times the rows' sums the other way
+    // round, so that one exponential decides.  By the two log-probs a logarithm, and a division by the acceptance probability's form, stood
+    // in the chain before the first rejection, where nothing else runs (one sequence of 64 drafts, V = 40000 17.4 -> 16.5 us a step, of 4,
+    // V = 32000 fp32 8.4 -> 7.95 in one launch; 64 of 8, V = 151936 66.5 -> 66.2).  Not a number on the right accepts, as a minimum with 1 does.
+    __device__ __forceinline__ bool rejects(const RecArgs& a, int t, double u) const {
+        const Partial g = row[2 * t], m = row[2 * t + 1];
+        const double d = ((double)h[2 * t] - (double)h[2 * t + 1]) * a.c - ((double)g.E - (double)m.E) * (1.0 + a.rho);
+        return !(u <= 1.0) || u * ((double)g.s * a.lambda) > exp2(d) * (double)m.s;
+    }
+};
+
 // Phase 2 for one sequence by a workgroup of NT threads, on the positions [T0, Kt) of the window (those before T0
 // are known to have been accepted):
 //   2a  every (position, tensor) pair gets 16 lanes: merge the row's slice partials, take the draft
-//       token's logit, leave log P(y_t) in lp[2t + x]
+//       token's logit, leave both in LDS
 //   2b  wave 0: Eq. 7 on every position, first rejection by ballot
 // Returns the first rejected position, Kt if none, to every thread; kFlagged if a draft id among those positions is outside
 // the vocabulary or `bad` is set in any thread.  sh: kRatioWords<NT> words of LDS.
@@ -923,12 +941,11 @@ __device__ __forceinline__ const Partial* partials_of(const RecArgs& a, int b, i
 // What bounds it is its chain of memory round trips, while nothing else runs on the compute unit: everything in the workspace is
 // loaded before the length is known (past it there are leftovers, which are not used), the draft tokens' logits among it, which
 // lie beside the partials.  Draft slots and rows past the length belong to the caller and are never read.  With the logits gathered behind the ids behind the length the first rejection of a block was known
-// 2.6 us after the launch's first workgroup; the recovery kernel of one sequence of V = 32000 fp32 takes 8.4 us now (9.0 before), of 8 of V = 151936 9.7
-// (10.7), a step of the first 10.6 (11.1), of 64 sequences 0.3 to 0.5 less.
+// 2.6 us after the launch's first workgroup; the recovery kernel of 8 sequences of V = 151936 took 10.7 us and 9.7 since.
 template <int NT>
 constexpr int kRatioWords = NT / kWave + 1;
 template <int DT, int NT>
-__device__ __forceinline__ int ratio_test_block(const RecArgs& a, int b, int T0, int Kt, bool bad, double* lp, int* sh) {
+__device__ __forceinline__ int ratio_test_block(const RecArgs& a, int b, int T0, int Kt, bool bad, const Pairs& pairs, int* sh) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l = tid & 15;
     const int kmax = a.kmax, V = a.V, Tend = a.t_hi;
     const float* un = a.uniforms + (long)b * (kmax + 1);
@@ -940,59 +957,50 @@ __device__ __forceinline__ int ratio_test_block(const RecArgs& a, int b, int T0,
         return y >= 0 && y < V ? ld_elem<DT>(row_ptr<DT>(q & 1 ? a.Sm : a.G, off), y) : __uint_as_float(kNoToken);
     };
     const float* left = a.draft_logit ? a.draft_logit + (long)b * kmax * 2 : nullptr;
-    const auto no_token = [](float h) { return __float_as_uint(h) == kNoToken; };
-    const auto logprob = [&](float h, Partial row) { return kLn2 * ((double)h * a.c - row_log2(row, a.rho)); };
     const int q0 = 2 * T0 + (tid >> 4);
     // One round for the whole window, loaded ahead of the length, or where the length makes it one (2 ragged sequences of up to 9 drafts,
     // V = 55616, in rounds by the window 14.8 us a step, by the length 14.4; longer ones within 1 % either way).
     const int top = 2 * (Tend - T0) <= NT / 16 ? Tend : Kt;
     if (2 * (top - T0) <= NT / 16) {
         float h = 0.f;
-        double v = 0.0;
+        Partial m{0, 0.f};
         if (q0 < 2 * top) {
             if (left) h = left[q0]; else if (q0 < 2 * Kt) h = gather(q0);
-            v = logprob(h, merge_partials_row16(partials_of(a, b, q0 >> 1, q0 & 1), a.NS, l));
+            m = merge_partials_row16(partials_of(a, b, q0 >> 1, q0 & 1), a.NS, l);
         }
-        if (q0 < 2 * Kt) {
-            bad = bad || no_token(h);  // not before the slices are on their way
-            if (l == 0) lp[q0] = v;
+        if (q0 < 2 * Kt && l == 0) {
+            pairs.row[q0] = m;
+            pairs.h[q0] = h;
         }
     } else {
-        // More pairs than groups of sixteen lanes: only the merging goes in rounds, its result waits in the pair's slot of
-        // lp, and the logits and logarithms follow once, a lane to every pair.  With all of it in the rounds each of
-        // them cost 0.9 us of dependent loads: 27 positions tested by 4 waves took 4, and one sequence of 128 positions,
-        // V = 40000, 24.1 us a step where it takes 20.6 (20.8 with the logits that the row pass left asked for behind the merging).
+        // More pairs than groups of sixteen lanes: only the merging goes in rounds, and the logits come meanwhile, a lane to every
+        // pair.  With all of it in the rounds each of them cost 0.9 us of dependent loads: 27 positions tested by 4 waves took 4, and one
+        // sequence of 128 positions, V = 40000, 24.1 us a step where it took 20.6 (20.8 with the logits asked for behind the merging).
         const int qa = 2 * T0 + tid;
-        const float ha = left && qa < 2 * Tend ? left[qa] : 0.f;  // on its way while the rows are merged
+        const float ha = left && qa < 2 * Tend ? left[qa] : 0.f;
         for (int q = q0; q < 2 * Kt; q += NT / 16) {
             const Partial m = merge_partials_row16(partials_of(a, b, q >> 1, q & 1), a.NS, l);
-            if (l == 0) lp[q] = __hiloint2double(m.E, __float_as_int(m.s));
+            if (l == 0) pairs.row[q] = m;
         }
-        __syncthreads();
-        for (int q = qa; q < 2 * Kt; q += NT) {
-            const Partial m{__double2hiint(lp[q]), __int_as_float(__double2loint(lp[q]))};
-            const float h = !left ? gather(q) : q == qa ? ha : left[q];
-            bad = bad || no_token(h);
-            lp[q] = logprob(h, m);
-        }
+        for (int q = qa; q < 2 * Kt; q += NT) pairs.h[q] = !left ? gather(q) : q == qa ? ha : left[q];
     }
     const bool any = __ballot(bad) != 0ull;
     if (lane == 0) sh[1 + wave] = any;
     __syncthreads();
     if (wave == 0) {
         int first_rej = Kt;
+        bool unknown = lane < NT / kWave && sh[1 + (lane < NT / kWave ? lane : 0)] != 0;
         for (int t0 = T0; t0 < Kt; t0 += kWave) {
             const int t = t0 + lane;
             bool rej = false;
             if (t < Kt) {
-                const double u = (double)(t0 == T0 ? u0 : un[t]);
-                const double alpha = fmin(1.0, exp(lp[2 * t] - lp[2 * t + 1] - a.ln_lambda));  // Eq. 7
-                rej = !(u <= alpha);
+                rej = pairs.rejects(a, t, (double)(t0 == T0 ? u0 : un[t]));
+                unknown = unknown || pairs.unknown(t);
             }
             const unsigned long long rmask = __ballot(rej);
             if (rmask && first_rej == Kt) first_rej = t0 + first_lane(rmask);
         }
-        const bool flagged = __ballot(lane < NT / kWave && sh[1 + (lane < NT / kWave ? lane : 0)] != 0) != 0ull;
+        const bool flagged = __ballot(unknown) != 0ull;
         if (lane == 0) sh[0] = flagged ? kFlagged : first_rej;
     }
     __syncthreads();
@@ -1025,7 +1033,8 @@ __global__ __launch_bounds__(NT) void verdict_kernel(const RecArgs a) {
             bad = bad || y < 0 || y >= V;
         }
     }
-    const int n = ratio_test_block<DT, NT>(a, b, a.t_lo, Kt, bad, smem_d, sh_ratio);
+    const Pairs pairs{reinterpret_cast<Partial*>(smem_d), reinterpret_cast<float*>(smem_d + 2 * kmax)};
+    const int n = ratio_test_block<DT, NT>(a, b, a.t_lo, Kt, bad, pairs, sh_ratio);
     if (tid == 0) a.state[b] = n == Kt && K > a.t_hi ? kInPlay : n;
 }
 
@@ -1125,8 +1134,8 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     constexpr int NW = NT / kWave;
     const int kmax = a.kmax, V = a.V;
-    double* lp = smem_d;                                            // [kmax][2] log P_LLM, log P_SLM^-
-    Partial* tab = reinterpret_cast<Partial*>(smem_d + 2 * kmax);   // [NC] chunk masses
+    const Pairs pairs{reinterpret_cast<Partial*>(smem_d), reinterpret_cast<float*>(smem_d + 2 * kmax)};
+    Partial* tab = reinterpret_cast<Partial*>(smem_d + 3 * kmax);   // [NC] chunk masses
 
     const double us = GREEDY ? 0.0 : (double)a.uniforms[(long)b * (kmax + 1) + kmax];  // read here, where nothing waits for it
     // Several windows: a sequence a verdict kernel saw rejected (or at its end) keeps that first-rejection
@@ -1138,13 +1147,15 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
         const int K = a.draft_len ? a.draft_len[b] : kmax;
         const bool bad_len = K < 0 || K > kmax;
         Kt = bad_len ? 0 : K;
-        n = kmax > 0 ? ratio_test_block<DT, NT>(a, b, a.t_lo, Kt, bad_len, lp, sh_ratio) : bad_len ? kFlagged : 0;
+        n = kmax > 0 ? ratio_test_block<DT, NT>(a, b, a.t_lo, Kt, bad_len, pairs, sh_ratio) : bad_len ? kFlagged : 0;
     }
     const bool bad = n < 0;
-    if (a.draft_logprobs && part == 0) {  // valid positions from LDS, padded slots 0, a flagged sequence NaN throughout
+    // Valid positions' log-probs, padded slots 0, a flagged sequence NaN throughout; up to 32 drafts by the wave that has the fewest chunks
+    const bool one_wave = 2 * kmax <= kWave;
+    if (a.draft_logprobs && part == S - 1 && (!one_wave || wave == NW - 1)) {
         const float nanv = __int_as_float(0x7FC00000);
-        for (int i = tid; i < kmax * 2; i += NT)
-            a.draft_logprobs[(long)b * kmax * 2 + i] = bad ? nanv : (i < 2 * Kt ? (float)lp[i] : 0.f);
+        for (int i = one_wave ? lane : tid; i < kmax * 2; i += one_wave ? kWave : NT)
+            a.draft_logprobs[(long)b * kmax * 2 + i] = bad ? nanv : (i < 2 * Kt ? (float)pairs.logprob(a, i) : 0.f);
     }
     if (bad) {
         if (tid == 0 && part == 0) {
@@ -1342,6 +1353,8 @@ __device__ __forceinline__ void lse_chunk(Acc& acc, const typename RawT<DT, VEC>
 // the partials on units that are idle, leave five: logits, hand-over (two), the other parts' masses, and the chunk that the token is in.  One
 // sequence of 4 drafts, V = 32000 fp32 10.55 -> 8.46 us a step (a launch less of host time, and 8.4 on the GPU instead of 10.5), 1 of 8
 // drafts, V = 128256 bf16 13.9 -> 11.5, 4 of 8, V = 50257 14.3 -> 11.8.
+// Nothing waits that need not: the masses go to memory while the partials are formed, and Eq. 7 is evaluated by every wave while the other
+// parts' masses come (behind them it was 7.95 us on the GPU for the first of those, 7.65 now, 11.4 for the third, 10.5 now).
 // Parts end together, so that several find all words; the claim, an exchange on its way beside the masses, leaves one of them (should another
 // come behind its clearing, both draw, from the same words, the same token).  Nobody waits for anybody.
 template <int DT, int VEC, bool GREEDY, bool PLAIN>
@@ -1357,9 +1370,9 @@ __global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const On
     const int per = (kmax + 1) * PP, b = (int)blockIdx.x / per, part = (int)blockIdx.x - b * per, t = part / PP, pp = part - t * PP;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     Partial* const mass = reinterpret_cast<Partial*>(smem_d);                                     // [kmax + 1][NC]
-    double* const lp = smem_d + (kmax + 1) * NC;                                                 // [kmax][2]
-    unsigned* const parts = reinterpret_cast<unsigned*>(lp + 2 * kmax);                          // [kmax][PP][2][E, s]
-    double* const cand_v = lp + 2 * kmax + 2 * kmax * PP;                                        // [kmax + 1][PP]
+    const Pairs pairs{mass + (kmax + 1) * NC, sh_h};                                              // [kmax][2]
+    unsigned* const parts = reinterpret_cast<unsigned*>(pairs.row + 2 * kmax);                   // [kmax][PP][2][E, s]
+    double* const cand_v = smem_d + (kmax + 1) * NC + 2 * kmax + 2 * kmax * PP;                  // [kmax + 1][PP]
     int* const cand_i = reinterpret_cast<int*>(cand_v + (GREEDY ? (kmax + 1) * PP : 0));
 
     const int K = a.draft_len ? a.draft_len[b] : kmax;
@@ -1420,25 +1433,21 @@ __global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const On
         rg[0] = set_first(rg[0], kBf16NegInf);
         rm[0] = set_first(rm[0], kBf16NegInf);
     }
+    // the recovery mass, as chunk_mass has it, on its way to memory while the partials are formed
+    const auto take_g = [&]() {
+        if (whole) lse_chunk<DT, VEC>(g, rg, a.c_hi);
+        else if (last) acc_add_f32<1>(g, tg, a.c_hi);
+    };
+    if (PLAIN) take_g();
     if (whole) {
-        if (t < K || PLAIN) lse_chunk<DT, VEC>(g, rg, a.c_hi);
-        if (t < K) lse_chunk<DT, VEC>(m, rm, a.c_hi);
-    } else if (last) {
-        acc_add_f32<1>(g, tg, a.c_hi);
-        acc_add_f32<1>(m, tm, a.c_hi);
-    }
-    // the recovery mass, as chunk_mass has it
-    if (first) {
-        rp[0] = set_first(rp[0], 0u);
-        rm[0] = set_first(rm[0], 0u);
-    }
-    if (whole) {
+        if (first) rp[0] = set_first(rp[0], 0u);
+        const auto m0 = first ? set_first(rm[0], 0u) : rm[0];
 #pragma unroll
         for (int j = 0; j < kChunkSteps; ++j) {
             const int at = (int)(vbase + (long)j * kWave) * VEC;
             float hg[VEC], hp[VEC], hm[VEC];
             unpack(rg[j], hg);
-            unpack_steer<DT, VEC, PLAIN>(rp[j], rm[j], hp, hm);
+            unpack_steer<DT, VEC, PLAIN>(rp[j], j == 0 ? m0 : rm[j], hp, hm);
             if (!PLAIN) acc_add_rec<DT, VEC, GREEDY>(rec, hg, hp, hm, a.c, a.bc, (float)a.c, (float)a.bc, a.beta, at, best);
             if (PLAIN && GREEDY) best_of<VEC>(best, hg, at);
             if (PLAIN && vbase + (long)j * kWave < row.nvec) acc_add_f32<VEC>(rec, hg, a.c_hi);
@@ -1450,15 +1459,18 @@ __global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const On
         if (PLAIN && GREEDY) best_of<1>(best, tg, at);
         if (PLAIN) rec = g;
     }
+    const Partial p = wave_combine(rec);
+    if (c < row.NC && lane == 0) st_dev_partial(reinterpret_cast<Partial*>(gmass) + (long)t * NC + c, p);
     if (t < K) {
+        if (!PLAIN) take_g();
+        if (whole) lse_chunk<DT, VEC>(m, rm, a.c_hi);
+        else if (last) acc_add_f32<1>(m, tm, a.c_hi);
         const Partial pg = wave_combine(g), pm = wave_combine(m);
         if (lane == 0) {
             sh_lse[wave][0] = pg;
             sh_lse[wave][1] = pm;
         }
     }
-    const Partial p = wave_combine(rec);
-    if (c < row.NC && lane == 0) st_dev_partial(reinterpret_cast<Partial*>(gmass) + (long)t * NC + c, p);
     if (GREEDY) {
         wave_best(best);
         if (lane == 0) {
@@ -1510,7 +1522,7 @@ __global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const On
     unsigned long long before = 0ull;
     if (tid == 0) before = __hip_atomic_exchange(w, claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
-    // ---- the ratio test, while the masses and the claim are on their way
+    // ---- the ratio test, by every wave, while the masses and the claim are on their way
     constexpr int kHeld = 5;
     unsigned long long held[kHeld];
     const int nmass = (K + 1) * NC;
@@ -1525,8 +1537,16 @@ __global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const On
         const Partial p = l < PP ? Partial{(int)e[0], __uint_as_float(e[1])} : Partial{kEInit, 0.f};
         const int E = row_max_i32(p.E);
         const Partial m{E, row_sum_f32(ldexpf(p.s, p.E - E))};
-        if (l == 0) lp[q] = kLn2 * ((double)sh_h[q] * a.c - row_log2(m, a.rho));
+        if (l == 0) pairs.row[q] = m;
     }
+    __syncthreads();
+    bool rej = false, none = false;
+    if (lane < K) {
+        rej = pairs.rejects(a, lane, (double)u);
+        none = pairs.unknown(lane);
+    }
+    const unsigned long long rmask = __ballot(rej), nmask = __ballot(none);
+    const int n = rmask ? first_lane(rmask) : K;
 #pragma unroll
     for (int i = 0; i < kHeld; ++i) {
         const int at = tid + i * kOnceWaves * kWave;
@@ -1539,19 +1559,11 @@ __global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const On
     for (int i = tid; i < nflag; i += kOnceWaves * kWave) words.clear(i < nlse ? 2 + i : (int)o.once.flags + (i - nlse));
     for (int i = tid; i < 2 * ncand; i += kOnceWaves * kWave) words.clear((int)o.once.best + i);
     if (tid == 0) words.clear(0);
-    bool rej = false, none = false;
-    if (lane < K) {
-        const double alpha = fmin(1.0, exp(lp[2 * lane] - lp[2 * lane + 1] - a.ln_lambda));  // Eq. 7
-        rej = !((double)u <= alpha);
-        none = __float_as_uint(sh_h[2 * lane]) == kNoToken || __float_as_uint(sh_h[2 * lane + 1]) == kNoToken;
-    }
-    if (__ballot(none)) {
+    if (nmask) {
         flag();
         return;
     }
-    const unsigned long long rmask = __ballot(rej);
-    const int n = rmask ? first_lane(rmask) : K;
-    if (a.draft_logprobs && tid < 2 * kmax) a.draft_logprobs[(long)b * kmax * 2 + tid] = tid < 2 * K ? (float)lp[tid] : 0.f;
+    if (a.draft_logprobs && tid < 2 * kmax) a.draft_logprobs[(long)b * kmax * 2 + tid] = tid < 2 * K ? (float)pairs.logprob(a, tid) : 0.f;
 
     // ---- the draw
     const RecRow<DT, VEC> at(a, b, n);
@@ -1779,7 +1791,7 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     ra.chunk_tab = reinterpret_cast<Partial*>(ws + pl.off_chunk_tab);
     la.zero_ptr = ra.arrive;
     la.zero_n = split ? B : 0;
-    const size_t smem = (size_t)2 * kmax * sizeof(double) + (size_t)ra.NC * sizeof(Partial);
+    const size_t ratio = (size_t)2 * kmax * (sizeof(Partial) + sizeof(float)), smem = ratio + (size_t)ra.NC * sizeof(Partial);
 
     const int kind = (ra.greedy ? 1 : 0) | (ra.plain ? 2 : 0);
     // The call whose stages are timed has them one behind the other.
@@ -1810,7 +1822,7 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
         if (i + 1 < windows) {
             const bool few = w.t_hi - w.t_lo <= 8;
             launch(few ? verdict_kernel<DT, 128> : verdict_kernel<DT, 512>, dim3((unsigned)B), dim3(few ? 128 : 512),
-                               (size_t)2 * kmax * sizeof(double), stream, ra);
+                               ratio, stream, ra);
         }
         if (i == 0) mark(2);
     }
@@ -1906,7 +1918,7 @@ ss_status verify_block_impl(const void* G, const void* S_ctx, const void* S_noct
     ra.next_token_logprob = next_token_logprob;
     ra.draft_logprobs = draft_logprobs; ra.sb = sb; ra.st = st; ra.B = params->batch; ra.kmax = params->k_max;
     ra.V = params->vocab; ra.NS = 0; ra.NC = 0; ra.c = c;
-    ra.bc = (double)params->beta * c; ra.ln_lambda = std::log((double)params->lambda);
+    ra.bc = (double)params->beta * c; ra.lambda = (double)params->lambda;
     ra.rho = (c - (double)c_hi) / (double)c_hi;
     ra.beta = (double)params->beta;
     ra.greedy = (params->flags & SS_FLAG_GREEDY) ? 1 : 0;
