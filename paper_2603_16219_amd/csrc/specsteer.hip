@@ -689,11 +689,11 @@ __device__ __forceinline__ double mass_log2(const RecArgs& a, int Estar, double 
 }
 
 // The chunk masses of a recovery row (`tab`, LDS) as one wave sees them: lane l owns a run of `per` consecutive chunks,
-// the first kHeld of them in registers, which is all of them up to V = 524288 bf16.
+// the first HELD of them in registers.
+template <int HELD>
 struct ChunkScan {
-    static constexpr int kHeld = 4;
     int lo, hi, Estar;
-    double held[kHeld];      // masses of chunks lo .. lo + 3 on the scale 2^Estar; 0 past the run
+    double held[HELD];       // masses of chunks lo, lo + 1, ... on the scale 2^Estar; 0 past the run
     double incl, total;      // mass up to the end of this lane's run, and of the row
     const Partial* tab;
 
@@ -702,22 +702,22 @@ struct ChunkScan {
         const int per = (NC + kWave - 1) / kWave;
         lo = min(lane * per, NC);
         hi = min(lo + per, NC);
-        Partial p[kHeld];
+        Partial p[HELD];
         int Em = kEInit;
 #pragma unroll
-        for (int i = 0; i < kHeld; ++i) {
+        for (int i = 0; i < HELD; ++i) {
             p[i] = lo + i < hi ? tab[lo + i] : Partial{kEInit, 0.f};
             Em = max(Em, p[i].E);
         }
-        for (int c = lo + kHeld; c < hi; ++c) Em = max(Em, tab[c].E);
+        for (int c = lo + HELD; c < hi; ++c) Em = max(Em, tab[c].E);
         Estar = wave_max_i32(Em);
         double sum = 0.0;
 #pragma unroll
-        for (int i = 0; i < kHeld; ++i) {
+        for (int i = 0; i < HELD; ++i) {
             held[i] = ldexp((double)p[i].s, p[i].E - Estar);
             sum += held[i];
         }
-        for (int c = lo + kHeld; c < hi; ++c) sum += mass(c);
+        for (int c = lo + HELD; c < hi; ++c) sum += mass(c);
         incl = wave_incl_scan_f64(sum);
         total = wave_last_f64(incl);
     }
@@ -728,8 +728,9 @@ struct Found {
     int c, Estar, last;          // last: u is not below the total (u >= 1 or not a number); c is then the last chunk with any mass
     double base, target, total;  // mass before the chunk, u's share and all of it, on the scale 2^Estar
 };
-__device__ __forceinline__ Found find_chunk(const Partial* tab, int NC, int lane, double us) {
-    const ChunkScan cs(tab, NC, lane);
+template <int HELD>
+__device__ __forceinline__ Found find_chunk_held(const Partial* tab, int NC, int lane, double us) {
+    const ChunkScan<HELD> cs(tab, NC, lane);
     Found f;
     f.Estar = cs.Estar;
     f.total = cs.total;
@@ -748,9 +749,9 @@ __device__ __forceinline__ Found find_chunk(const Partial* tab, int NC, int lane
         cum = cum2;
     };
 #pragma unroll
-    for (int i = 0; i < ChunkScan::kHeld; ++i)
+    for (int i = 0; i < HELD; ++i)
         if (cs.lo + i < cs.hi) meet(cs.lo + i, cs.held[i]);
-    for (int c = cs.lo + ChunkScan::kHeld; c < cs.hi; ++c) meet(c, cs.mass(c));
+    for (int c = cs.lo + HELD; c < cs.hi; ++c) meet(c, cs.mass(c));
     const unsigned long long fmask = __ballot(cfound >= 0);
     if (fmask) {
         const int L = first_lane(fmask);
@@ -761,6 +762,13 @@ __device__ __forceinline__ Found find_chunk(const Partial* tab, int NC, int lane
         f.last = 1;
     }
     return f;
+}
+
+// Two chunks a lane are all there are up to V = 262144 bf16; two more that are not there took the scan 0.15 us (8 sequences of V = 151936 18.4 -> 18.2 us a
+// step on the GPU, 16 25.9 -> 25.65, 200 steered rows of V = 128256 30.3 -> 30.0).  Beyond, four: with two held and the rest from LDS 8 sampled rows of
+// V = 250000 fp32 took 6.4 us instead of 6.2.
+__device__ __forceinline__ Found find_chunk(const Partial* tab, int NC, int lane, double us) {
+    return NC <= 2 * kWave ? find_chunk_held<2>(tab, NC, lane, us) : find_chunk_held<4>(tab, NC, lane, us);
 }
 
 constexpr int kMassWaves = 4;
@@ -832,10 +840,11 @@ __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, dou
             }
         }
 #pragma unroll
-        for (int i = 0; i < VEC; ++i)
-            if (i < have)
-                p[i] = PLAIN ? __builtin_amdgcn_exp2f(fmaf(hg[i], a.c_hi, nE))
-                             : __builtin_amdgcn_exp2f((float)(rec_y(hg[i], hp[i], hm[i], a.c, a.bc) - dE));
+        for (int i = 0; i < VEC; ++i) {
+            const float term = PLAIN ? __builtin_amdgcn_exp2f(fmaf(hg[i], a.c_hi, nE))
+                                     : __builtin_amdgcn_exp2f((float)(rec_y(hg[i], hp[i], hm[i], a.c, a.bc) - dE));
+            p[i] = i < have ? term : 0.f;
+        }
         if (head && first == 0) p[0] = 0.f;  // the element before the row
 #pragma unroll
         for (int i = 0; i < VEC; i += 2) ls += (double)p[i] + (double)p[i + 1];
@@ -897,7 +906,7 @@ __device__ __forceinline__ double draw_token(const RecArgs& a, int b, int n, dou
 // The same for greedy decoding, by one wave: the token is known, only the normaliser is needed.
 template <bool PLAIN>
 __device__ __forceinline__ double greedy_token(const RecArgs& a, int b, int n, int lane, const Partial* tab, int NC, Best pick) {
-    const ChunkScan cs(tab, NC, lane);
+    const ChunkScan<4> cs(tab, NC, lane);
     const double log2Z = mass_log2<PLAIN>(a, cs.Estar, cs.total);
     if (lane == 0) {
         a.accepted_len[b] = n;
@@ -1640,7 +1649,7 @@ __global__ __launch_bounds__(kLogprobThreads) void row_draw_kernel(const RecArgs
         write_logprobs<DT, VEC, PLAIN>(row_ptr<DT>(a.G, off), row_ptr<DT>(a.recSp, off), row_ptr<DT>(a.recSm, off),
                                        a.recovery_logprobs + (long)b * a.V, a.V, (long)seg * (kLogprobThreads * kLogprobUnroll) + tid,
                                        kLogprobThreads, seg == a.segs - 1 ? tid : kNoTail, a.c, a.bc, [&] {
-                                           const ChunkScan cs(a.chunk_tab + at, row.NC, lane);
+                                           const ChunkScan<4> cs(a.chunk_tab + at, row.NC, lane);
                                            return mass_log2<PLAIN>(a, cs.Estar, cs.total);
                                        });
         return;
