@@ -384,11 +384,12 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
             acc_add_f32<kUnroll * VEC>(acc, h, a.c_hi);
         }
         if (nfull == 0) find_y();
-        // Less than a group, the end of a row, where slices are one group: all its loads in flight at once, those past it -inf.  A vector at
-        // a time they were up to three round trips behind each other in one item of sixteen (96 sequences of 8 drafts, V = 32000 35.0 -> 30.9
-        // us a step, 64 of 4 19.7 -> 18.2, 20 of 8, V = 50257 18.7 -> 18.3, 16 of 4, V = 128256 18.6 -> 18.1).  Behind the groups of longer
-        // slices other waves cover them, and the sums over logits that are not there cost more (256 ragged of V = 50257 61.7 -> 62.6).
-        if (slice_units <= kGroup && nfull == 0) {
+        // Less than a group, the end of a row, where slices are one group or two: all its loads in flight at once, those past it -inf.  A vector
+        // at a time they were up to three round trips behind each other in one item of eight or sixteen (96 sequences of 8 drafts, V = 32000
+        // 35.0 -> 30.9 us a step, 64 of 4 19.7 -> 18.2, 500 of 4 69.3 -> 64.7, 160 ragged of 8 32.6 -> 31.0, 20 of 8, V = 50257 18.7 -> 18.3).  Behind
+        // the groups of longer slices other waves cover them, and the sums over logits that are not there cost more (256 ragged of V = 50257
+        // 61.7 -> 62.6), as they do for a single load a lane.
+        if (slice_units <= 2 * kGroup && v1 - v0 - nfull * kGroup > kWave) {
             typename RawT<DT, VEC>::type raw[kUnroll];
             float h[kUnroll * VEC];
 #pragma unroll
@@ -399,7 +400,7 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
 #pragma unroll
             for (int j = 0; j < kUnroll; ++j) {
                 if (yv >= 0 && v + (long)kWave * j == v0 + yv) *y_out = elem_of(raw[j], ye % VEC);
-                if (j == 0 && masked && lane == 0) raw[0] = set_first(raw[0], kBf16NegInf);
+                if (j == 0 && masked && v == 0) raw[0] = set_first(raw[0], kBf16NegInf);
                 float hj[VEC];
                 unpack(raw[j], hj);
 #pragma unroll

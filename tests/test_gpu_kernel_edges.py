@@ -532,13 +532,14 @@ def test_recovery_launch_by_chunks_and_drafts(binding, oracle, dtype, k_max, chu
     parity.compare(out, ora, inp["uniforms"], None)
 
 
-# Row pass in slices of one group of loads (256 vectors), of which a row's last holds 1 to 255 vectors: at the edges of its four loads, with
-# logits past the last vector and without, rows at odd elements, and the draft tokens' logits in that slice.
+# Row pass in slices of one group of loads (256 vectors), of which a row's last holds 1 to 255 vectors, and of two (500 sequences, the first two sizes): at the edges
+# of its four loads, with logits past the last vector and without, rows at odd elements, and the draft tokens' logits in that slice.
+@pytest.mark.parametrize("batch", [200, 500])
 @pytest.mark.parametrize("dtype,vocab", [(dt, (8 if dt == "bf16" else 4) * (256 * groups + more) + rest) for dt, groups, more, rest in (
-    ("bf16", 3, 1, 0), ("bf16", 3, 63, 3), ("bf16", 3, 64, 0), ("bf16", 3, 65, 0), ("bf16", 0, 130, 1), ("bf16", 1, 192, 0), ("bf16", 2, 255, 7),
+    ("bf16", 15, 160, 0), ("bf16", 14, 66, 1), ("bf16", 3, 1, 0), ("bf16", 3, 63, 3), ("bf16", 3, 64, 0), ("bf16", 3, 65, 0), ("bf16", 0, 130, 1), ("bf16", 1, 192, 0), ("bf16", 2, 255, 7),
     ("f32", 3, 1, 0), ("f32", 2, 64, 3), ("f32", 0, 129, 0), ("f32", 1, 255, 1))])
-def test_row_pass_at_the_end_of_one_group_slices(binding, oracle, dtype, vocab):
-    batch, k_max = 200, 4
+def test_row_pass_at_the_end_of_short_slices(binding, oracle, dtype, vocab, batch):
+    k_max = 4
     w = recipe("c4", dtype, batch=batch, k_max=k_max, vocab=vocab)
     inp = W.generate(w, "cuda")
     last = torch.arange(batch, device="cuda", dtype=torch.int32)
@@ -546,8 +547,9 @@ def test_row_pass_at_the_end_of_one_group_slices(binding, oracle, dtype, vocab):
     out = binding.verify_block(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"], inp["uniforms"], lam=w.lam, beta=w.beta,
                                temperature=w.temperature, want_draft_logprobs=True)
     inp["draft_len"] = torch.full((batch,), k_max, dtype=torch.int32, device="cuda")
-    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, want_recovery_logprobs=False)
-    parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
+    seqs = torch.arange(0, batch, 7, device="cuda")
+    ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, seqs=seqs, want_recovery_logprobs=False)
+    parity.compare(out, ora, inp["uniforms"], inp["draft_len"], seqs=seqs)
 
 
 # Small blocks in one launch: a wave a chunk of 256 vectors, four to a workgroup.  Rows shorter than a vector, of one chunk and one logit more
