@@ -221,15 +221,22 @@ inline size_t once_lds(int kmax, int NC, bool greedy) {
            (greedy ? positions * parts * (sizeof(double) + sizeof(int)) : 0);
 }
 
-// Which blocks: up to two workgroups a compute unit.  The third rows of all positions are read and summed for one of them, which costs
-// nothing while units are idle; beyond, a row pass and a recovery that share the chip's arithmetic take less (us a step by graph
-// replays, two launches -> one; by workgroups: 40 (1 sequence of 4 drafts, V = 32000 fp32) 10.5 -> 8.4, 144 (1 of 8, V = 128256 bf16) 13.9 ->
-// 11.5, 252 (4 of 8, V = 50257) 14.3 -> 11.8, 288 (8 of 8, V = 32000) 14.1 -> 13.7, 504 (8 of 8, V = 50257) 15.5 -> 14.8, 512 (16 of 1, V = 65536
-// fp32) 13.7 -> 12.3; 544 (8 of 16, V = 32000) 16.4 -> 17.0, 576 (4 of 8, V = 128256) 15.7 -> 16.4, 1152 18.5 -> 22.1).  Greedy with a steering
-// term, one: it compares every logit in double (224 (16 of 1, V = 50257) 15.0 -> 12.7; 312 (8 of 2, V = 100352) 14.8 -> 15.8).
-inline bool block_in_one_launch(int B, int kmax, int NC, bool plain, bool greedy, int cus) {
+// Which blocks, by workgroups a compute unit.  The third rows of all positions are read and summed for one of them, which costs nothing while
+// units are idle; beyond, a row pass and a recovery that share the chip's arithmetic take less.  Us a step by graph replays, two
+// launches -> one, by workgroups on 256 units:
+//   - bf16, up to 2 1/8: 144 (1 sequence of 8 drafts, V = 128256) 13.5 -> 10.4, 252 (4 of 8, V = 50257) 14.3 -> 10.5, 504 (8 of 8, V = 50257) 15.4 ->
+//     13.3, 544 (2 of 16, V = 128256) 15.6 -> 14.6; 576 (16 of 8, V = 32000) 14.7 -> 15.1, 640 (8 of 4, V = 128256) 14.8 -> 15.3, 864 16.1 -> 17.6.
+//   - bf16 with lengths, of whose workgroups some have nothing to do, or without a steering term, up to 3: lengths 576 14.8 -> 13.1, 768 15.4
+//     -> 14.3 (all of full length 768 15.9 -> 15.95, 702 15.3 -> 15.5); without 576 12.6 -> 11.9, 768 13.5 -> 12.1.
+//   - fp32, whose chunks are half the logits, up to 4: 40 (1 of 4, V = 32000) 10.1 -> 7.7, 512 (16 of 1, V = 65536) 13.4 -> 11.7, 624 (6 of 12, V = 32000)
+//     14.3 -> 12.9, 768 13.8 -> 13.2, 832 (4 of 12, V = 65536) 15.8 -> 15.0, 1024 15.75 -> 15.6.
+//   - Greedy with a steering term compares every logit in double: bf16 up to 1 (224 15.0 -> 12.7; 336 14.8 -> 15.5), fp32 up to 1 1/2 (384 13.4
+//     -> 12.75); without one up to 2 (512 14.2 -> 12.6).
+inline bool block_in_one_launch(int B, int kmax, int NC, int dtype, bool plain, bool greedy, bool ragged, int cus) {
     if (kmax < 1 || kmax > kOnceMaxDrafts || NC > kOnceMaxParts * kOnceWaves) return false;
-    return (long)B * (kmax + 1) * ((NC + kOnceWaves - 1) / kOnceWaves) <= (greedy && !plain ? 1l : 2l) * cus;
+    const bool bf16 = dtype == SS_BF16;
+    const int eighths = greedy ? (plain ? 16 : bf16 ? 8 : 12) : !bf16 ? 32 : plain || ragged ? 24 : 17;
+    return 8l * B * (kmax + 1) * ((NC + kOnceWaves - 1) / kOnceWaves) <= (long)eighths * cus;
 }
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }

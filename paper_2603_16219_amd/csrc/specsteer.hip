@@ -1361,8 +1361,8 @@ __device__ __forceinline__ void lse_chunk(Acc& acc, const typename RawT<DT, VEC>
 // What bounds such a block is its chain of memory round trips and launches.  By a row pass, and a recovery whose parts each test, sweep the
 // rows of one position and hand over, there were eight round trips and a launch between; the masses of every position, formed beside
 // the partials on units that are idle, leave five: logits, hand-over (two), the other parts' masses, and the chunk that the token is in.  One
-// sequence of 4 drafts, V = 32000 fp32 10.55 -> 8.46 us a step (a launch less of host time, and 8.4 on the GPU instead of 10.5), 1 of 8
-// drafts, V = 128256 bf16 13.9 -> 11.5, 4 of 8, V = 50257 14.3 -> 11.8.
+// sequence of 4 drafts, V = 32000 fp32 10.55 -> 7.9 us a step (a launch less of host time, and 7.7 on the GPU instead of 10.1), 1 of 8
+// drafts, V = 128256 bf16 13.5 -> 10.4, 4 of 8, V = 50257 14.3 -> 10.5.
 // Nothing waits that need not: the masses go to memory while the partials are formed, and Eq. 7 is evaluated by every wave while the other
 // parts' masses come (behind them it was 7.95 us on the GPU for the first of those, 7.65 now, 11.4 for the third, 10.5 now).
 // Parts end together, so that several find all words; the claim, an exchange on its way beside the masses, leaves one of them (should another
@@ -1805,7 +1805,7 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
 
     const int kind = (ra.greedy ? 1 : 0) | (ra.plain ? 2 : 0);
     // The call whose stages are timed has them one behind the other.
-    if (!ev && windows == 1 && !recovery_logprobs && block_in_one_launch(B, kmax, ra.NC, ra.plain != 0, ra.greedy != 0, device_cu_count())) {
+    if (!ev && windows == 1 && !recovery_logprobs && block_in_one_launch(B, kmax, ra.NC, DT, ra.plain != 0, ra.greedy != 0, ragged, device_cu_count())) {
         const OnceArgs oa{ra, reinterpret_cast<unsigned long long*>(ws + pl.off_partial),
                           (long)((pl.bytes - pl.off_partial) / sizeof(uint64_t) / B), next_tag(), once_space(kmax, ra.NC, ra.greedy != 0)};
         if (oa.once.words <= oa.word_stride) {

@@ -560,7 +560,8 @@ def test_row_pass_at_the_end_of_short_slices(binding, oracle, dtype, vocab, batc
 @pytest.mark.parametrize("dtype,batch,k_max,vocab", [
     ("bf16", 3, 2, 5), ("bf16", 5, 16, 7), ("bf16", 5, 3, 2047), ("bf16", 5, 4, 2048), ("bf16", 5, 1, 2049), ("bf16", 3, 4, 4 * 2048 + 9),
     ("bf16", 3, 16, 17 * 2048 - 3), ("bf16", 6, 4, 32000), ("bf16", 1, 8, 64 * 2048), ("bf16", 4, 2, 64 * 2048 - 1), ("bf16", 2, 3, 64 * 2048 + 1),
-    ("bf16", 40, 2, 3 * 2048 + 1), ("f32", 1, 4, 32000), ("f32", 4, 4, 1025), ("f32", 3, 16, 33 * 1024 + 2), ("f32", 2, 2, 64 * 1024)])
+    ("bf16", 40, 2, 3 * 2048 + 1), ("f32", 1, 4, 32000), ("f32", 4, 4, 1025), ("f32", 3, 16, 33 * 1024 + 2), ("f32", 2, 2, 64 * 1024),
+    ("f32", 25, 3, 40000), ("bf16", 24, 3, 32 * 2048)])
 def test_small_blocks_in_one_launch(binding, oracle, dtype, batch, k_max, vocab, greedy, beta):
     w = recipe("c4", dtype, batch=batch, k_max=k_max, vocab=vocab)
     inp = W.generate(w, "cuda")

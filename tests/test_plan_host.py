@@ -32,12 +32,12 @@ int main() {
             std::printf("%d\n", rows_in_one_launch(a[0], a[1], a[2], a[3], a[4], a[5]) ? 1 : 0);
             continue;
         }
-        if (!std::strcmp(what, "once")) {  // B kmax chunks plain greedy cus: whether in one launch, and its space and LDS
-            int a[6];
-            if (std::scanf("%d %d %d %d %d %d", a, a + 1, a + 2, a + 3, a + 4, a + 5) != 6) return 1;
-            const OnceSpace s = once_space(a[1], a[2], a[4]);
-            std::printf("%d %d %ld %ld %ld %ld %ld\n", block_in_one_launch(a[0], a[1], a[2], a[3], a[4], a[5]) ? 1 : 0, s.parts, s.flags,
-                        s.best, s.masses, s.words, (long)once_lds(a[1], a[2], a[4]));
+        if (!std::strcmp(what, "once")) {  // B kmax chunks dtype plain greedy ragged cus: whether in one launch, and its space and LDS
+            int a[8];
+            if (std::scanf("%d %d %d %d %d %d %d %d", a, a + 1, a + 2, a + 3, a + 4, a + 5, a + 6, a + 7) != 8) return 1;
+            const OnceSpace s = once_space(a[1], a[2], a[5]);
+            std::printf("%d %d %ld %ld %ld %ld %ld\n", block_in_one_launch(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7]) ? 1 : 0, s.parts, s.flags,
+                        s.best, s.masses, s.words, (long)once_lds(a[1], a[2], a[5]));
             continue;
         }
         if (!std::strcmp(what, "odd")) {  // vec base base base B kmax sb st
@@ -147,20 +147,28 @@ def test_rows_without_drafts_are_taken_whole_while_that_pays(planner, dtype, pla
         assert planner([f"one {batch} {max(chunks, 1)} {tail}", f"one {batch} {chunks + 1} {tail}"]) == [(int(chunks > 0),), (0,)]
 
 
-# Small blocks in one launch: up to two workgroups a unit, one for greedy decoding with a steering term.
-@pytest.mark.parametrize("batch,k_max,chunks,plain,greedy,one", [
-    (1, 4, 32, 0, 0, 1), (1, 0, 32, 0, 0, 0), (32, 1, 32, 0, 0, 1), (33, 1, 32, 0, 0, 0), (32, 1, 33, 0, 0, 0), (1, 16, 64, 0, 0, 1),
-    (1, 17, 4, 0, 0, 0), (1, 1, 65, 0, 0, 0), (256, 1, 4, 0, 0, 1), (257, 1, 1, 1, 0, 0), (16, 1, 32, 0, 1, 1), (17, 1, 32, 0, 1, 0),
-    (32, 1, 32, 1, 1, 1), (33, 1, 32, 1, 1, 0)])
-def test_small_blocks_take_one_launch_while_units_are_idle(planner, batch, k_max, chunks, plain, greedy, one):
-    assert planner([f"once {batch} {k_max} {chunks} {plain} {greedy} {CUS}"])[0][0] == one
+# Small blocks in one launch up to a number of workgroups (of 4 chunks of a position) on 256 units; the first batch that is beyond.
+@pytest.mark.parametrize("dtype,plain,greedy,ragged,most", [
+    (BF16, 0, 0, 0, 544), (BF16, 0, 0, 1, 768), (BF16, 1, 0, 0, 768), (0, 0, 0, 0, 1024), (0, 0, 0, 1, 1024), (0, 1, 0, 0, 1024),
+    (BF16, 0, 1, 0, 256), (BF16, 0, 1, 1, 256), (0, 0, 1, 0, 384), (BF16, 1, 1, 0, 512), (0, 1, 1, 1, 512)])
+def test_small_blocks_take_one_launch_while_that_pays(planner, dtype, plain, greedy, ragged, most):
+    for k_max, chunks in ((1, 1), (1, 4), (3, 32), (16, 64), (7, 5)):
+        per = (k_max + 1) * -(-chunks // 4)
+        for batch in (max(most // per, 1), most // per + 1):
+            got = planner([f"once {batch} {k_max} {chunks} {dtype} {plain} {greedy} {ragged} {CUS}"])[0][0]
+            assert got == int(batch * per <= most), (k_max, chunks, batch)
+
+
+@pytest.mark.parametrize("k_max,chunks", [(0, 32), (17, 4), (1, 65)])
+def test_blocks_without_drafts_with_many_or_of_long_rows_do_not(planner, k_max, chunks):
+    assert planner([f"once 1 {k_max} {chunks} 0 0 0 0 {CUS}"])[0][0] == 0
 
 
 def test_the_space_of_a_block_in_one_launch_holds_what_its_parts_deliver(planner):
     for k in range(1, 17):
         for chunks in (1, 3, 4, 5, 32, 63, 64):
             for greedy in (0, 1):
-                _, parts, flags, best, masses, words, lds = planner([f"once 1 {k} {chunks} 0 {greedy} {CUS}"])[0]
+                _, parts, flags, best, masses, words, lds = planner([f"once 1 {k} {chunks} 0 0 {greedy} 0 {CUS}"])[0]
                 assert parts == -(-chunks // 4) and flags == 2 + 4 * k * parts and best == flags + parts
                 assert masses == best + greedy * 2 * (k + 1) * parts and words == masses + (k + 1) * chunks
                 assert lds == 8 * (k + 1) * chunks + 16 * k + 16 * k * parts + greedy * 12 * (k + 1) * parts < 32768
