@@ -1307,8 +1307,9 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
 struct Words {
     unsigned long long* w;
     unsigned tag;
-    // A different tag for every word, so that a space filled with one pattern matches one of them at most.
-    __device__ __forceinline__ unsigned tag_of(int i) const { return tag + (unsigned)i * 0x9E3779B1u; }
+    // A different tag for every word, so that a space filled with one pattern matches one of them at most, and none that a cleared word
+    // has, whole or cut to its upper bits.
+    __device__ __forceinline__ unsigned tag_of(int i) const { return (tag + (unsigned)i * 0x9E3779B1u) | 0x80000001u; }
     __device__ __forceinline__ void put(int i, unsigned v) const { st_dev(w + i, (unsigned long long)tag_of(i) << 32 | v); }
     __device__ __forceinline__ bool get(int i, unsigned& v) const {
         const unsigned long long x = ld_dev(w + i);
