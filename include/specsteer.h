@@ -134,7 +134,10 @@ size_t specsteer_workspace_bytes(const ss_params *params);
  *                      (also past the first rejection); 0 in padded slots.
  *   workspace          device scratch, 256-byte aligned, at least
  *                      specsteer_workspace_bytes(params) bytes; contents need no
- *                      initialisation and are garbage afterwards.  Calls that
+ *                      initialisation and are garbage afterwards.  (Small blocks in one
+ *                      launch tell delivered data from leftovers by 62 or more bits of a
+ *                      tag of the call for each of their workgroups: what lies there passes
+ *                      for a workgroup's data with a chance of 2^-62.)  Calls that
  *                      may overlap in time need distinct workspaces.  (A block of
  *                      more than 512 draft positions also runs, with the same
  *                      outputs, in a workspace that lacks the 8 bytes a position,

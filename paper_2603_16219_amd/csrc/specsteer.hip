@@ -39,7 +39,6 @@
 // (log-sum-exp combine, log-probs, alpha, CDF walk across chunks) is double.
 #include <hip/hip_runtime.h>
 
-#include <chrono>
 #include <cmath>
 #include <cstdint>
 
@@ -47,6 +46,7 @@
 #include "plan.h"
 #include "specsteer.h"
 #include "unbound.h"
+#include "words.h"
 
 namespace {
 
@@ -1300,34 +1300,24 @@ __global__ __launch_bounds__(NT) void accept_recover_kernel(const RecArgs a) {
 
 // ------------------------------------------------------------------ kernel: small blocks in one launch
 
-// Words that say themselves that they are there: 32 bits of the call's tag beside 32 of what is handed over, written and read with
-// device-scope atomics.  Whoever finds every word of a sequence with its tag has all that was delivered, without a
-// counter that someone would have had to clear before.  The words are cleared by whoever goes on, so that a graph that is replayed, whose
-// calls carry the same tag each time, meets none of the last replay; what else may lie in the space matches by accident only.
+// The words of words.h in memory, written and read with device-scope atomics: whoever finds every word of a sequence has all that was
+// delivered, without a counter that someone would have had to clear before.
 struct Words {
     unsigned long long* w;
-    unsigned tag;
-    // A different tag for every word, so that a space filled with one pattern matches one of them at most, and none that a cleared word
-    // has, whole or cut to its upper bits.
-    __device__ __forceinline__ unsigned tag_of(int i) const { return (tag + (unsigned)i * 0x9E3779B1u) | 0x80000001u; }
-    __device__ __forceinline__ void put(int i, unsigned v) const { st_dev(w + i, (unsigned long long)tag_of(i) << 32 | v); }
-    __device__ __forceinline__ bool get(int i, unsigned& v) const {
-        const unsigned long long x = ld_dev(w + i);
-        v = (unsigned)x;
-        return (unsigned)(x >> 32) == tag_of(i);
-    }
-    // A greedy candidate in words i and i + 1: 64 bits of the value, 21 of the token (up to SS_MAX_VOCAB, for none), and the tags'
-    // upper 21 and 22 bits.
+    CallTag tag;
+    __device__ __forceinline__ void put(int i, unsigned v) const { st_dev(w + i, (unsigned long long)value_word(tag, i, v)); }
+    __device__ __forceinline__ void arrive(int i) const { st_dev(w + i, (unsigned long long)arrival_word(tag, i)); }
+    __device__ __forceinline__ unsigned long long load(int i) const { return ld_dev(w + i); }
     __device__ __forceinline__ void put_best(int i, double v, int idx) const {
         const unsigned long long x = (unsigned long long)__double_as_longlong(v);
-        st_dev(w + i, (unsigned long long)(tag_of(i) >> 11) << 43 | x >> 21);
-        st_dev(w + i + 1, (unsigned long long)(tag_of(i + 1) >> 10) << 42 | (x & 0x1FFFFFull) << 21 | (unsigned long long)idx);
+        st_dev(w + i, (unsigned long long)best_word(tag, i, x));
+        st_dev(w + i + 1, (unsigned long long)best_word2(tag, i, x, (unsigned)idx));
     }
     __device__ __forceinline__ bool get_best(int i, double& v, int& idx) const {
         const unsigned long long x = ld_dev(w + i), y = ld_dev(w + i + 1);
-        v = __longlong_as_double((long long)(x << 21 | (y >> 21 & 0x1FFFFFull)));
-        idx = (int)(y & 0x1FFFFFull);
-        return (unsigned)(x >> 43) == tag_of(i) >> 11 && (unsigned)(y >> 42) == tag_of(i + 1) >> 10;
+        v = __longlong_as_double((long long)best_value(x, y));
+        idx = (int)best_token(y);
+        return are_best_words(tag, i, x, y);
     }
     __device__ __forceinline__ void clear(int i) const { st_dev(w + i, 0ull); }
 };
@@ -1336,7 +1326,7 @@ struct OnceArgs {
     RecArgs rec;
     unsigned long long* words;  // [B][word_stride], see once_space
     long word_stride;
-    unsigned tag;               // of this call's words
+    CallTag tag;                // of this call's words
     OnceSpace once;
 };
 
@@ -1503,7 +1493,7 @@ __global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const On
             for (int i = 0; i < kOnceWaves; ++i) s += ldexpf(sh_lse[i][x].s, sh_lse[i][x].E - E);
             if (lane < 4) words.put(2 + 4 * part + lane, lane & 1 ? __float_as_uint(s) : (unsigned)E);
         } else if (lane == 0) {
-            words.put((int)o.once.flags + pp, 0u);
+            words.arrive((int)o.once.flags + pp);
         }
         if (GREEDY) {
             best.v = lane < kOnceWaves ? sh_best_v[lane] : -__builtin_huge_val();
@@ -1518,10 +1508,11 @@ __global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const On
     // ---- whether all parts have delivered.  One that ends a moment before the last may find so too: the claim leaves one of them.
     bool all = true;
     const int nlse = 4 * K * PP, nflag = nlse + PP, ncand = GREEDY ? (K + 1) * PP : 0;
+    const auto word = [&](int i) { return i < nlse ? 2 + i : (int)o.once.flags + (i - nlse); };
     for (int i = tid; i < nflag; i += kOnceWaves * kWave) {
-        unsigned v;
-        all = words.get(i < nlse ? 2 + i : (int)o.once.flags + (i - nlse), v) && all;
-        if (i < nlse) parts[i] = v;
+        const unsigned long long x = words.load(word(i));
+        all = is_word(o.tag, word(i), i < nlse, x) && all;
+        if (i < nlse) parts[i] = (unsigned)x;
     }
     if (GREEDY)
         for (int i = tid; i < ncand; i += kOnceWaves * kWave) all = words.get_best((int)o.once.best + 2 * i, cand_v[i], cand_i[i]) && all;
@@ -1529,7 +1520,7 @@ __global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const On
     if (lane == 0) sh_missing[wave] = missing != 0ull;
     __syncthreads();
     if (sh_missing[0] | sh_missing[1] | sh_missing[2] | sh_missing[3]) return;
-    const unsigned long long claim = (unsigned long long)~o.tag << 32 | o.tag;
+    const unsigned long long claim = (unsigned long long)claim_word(o.tag);
     unsigned long long before = 0ull;
     if (tid == 0) before = __hip_atomic_exchange(w, claim, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
@@ -1567,7 +1558,7 @@ __global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const On
     if (tid == 0) sh_mine = before != claim;
     __syncthreads();
     if (!sh_mine) return;
-    for (int i = tid; i < nflag; i += kOnceWaves * kWave) words.clear(i < nlse ? 2 + i : (int)o.once.flags + (i - nlse));
+    for (int i = tid; i < nflag; i += kOnceWaves * kWave) words.clear(word(i));
     for (int i = tid; i < 2 * ncand; i += kOnceWaves * kWave) words.clear((int)o.once.best + i);
     if (tid == 0) words.clear(0);
     if (nmask) {
@@ -1735,12 +1726,6 @@ void launch_row_pass(LseArgs la, const Window& w, const RowWindow& win, int unif
                        stream, la);
 }
 
-// A tag for the words of a call (Words): another one for each of 2^32 calls, begun anywhere.
-unsigned next_tag() {
-    static std::atomic<unsigned> n{(unsigned)std::chrono::steady_clock::now().time_since_epoch().count()};
-    return n.fetch_add(0x85EBCA6Bu, std::memory_order_relaxed);
-}
-
 // Whether what is enqueued on the stream goes into a graph.
 bool being_captured(hipStream_t stream) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
@@ -1808,7 +1793,7 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
     // The call whose stages are timed has them one behind the other.
     if (!ev && windows == 1 && !recovery_logprobs && block_in_one_launch(B, kmax, ra.NC, DT, ra.plain != 0, ra.greedy != 0, ragged, device_cu_count())) {
         const OnceArgs oa{ra, reinterpret_cast<unsigned long long*>(ws + pl.off_partial),
-                          (long)((pl.bytes - pl.off_partial) / sizeof(uint64_t) / B), next_tag(), once_space(kmax, ra.NC, ra.greedy != 0)};
+                          (long)((pl.bytes - pl.off_partial) / sizeof(uint64_t) / B), next_call_tag(), once_space(kmax, ra.NC, ra.greedy != 0)};
         if (oa.once.words <= oa.word_stride) {
             static void (*const once[4])(OnceArgs) = {block_once_kernel<DT, VEC, false, false>, block_once_kernel<DT, VEC, true, false>,
                                                       block_once_kernel<DT, VEC, false, true>, block_once_kernel<DT, VEC, true, true>};
