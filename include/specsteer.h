@@ -112,7 +112,8 @@ size_t specsteer_workspace_bytes(const ss_params *params);
  * The block (Algorithm 1 phases 2-3, Eq. 7, Eq. 8; see the top of this file).
  *
  *   G, S_ctx, S_noctx  device, [B, k_max+1, V] logits of params->dtype.  With beta == 0 the
- *                      recovery distribution is Softmax(G/T) and S_ctx is not read.  Pointers
+ *                      recovery distribution is Softmax(G/T), and neither S_ctx nor S_noctx
+ *                      at row K_b is read.  Pointers
  *                      need element alignment only (SS_ERR_STRIDE otherwise) and any V works;
  *                      rows that start on 16-byte boundaries (base pointers 16-byte aligned,
  *                      strides multiples of 16 bytes) stream fastest, others take up to a

@@ -1401,6 +1401,7 @@ __global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const On
     const int c = pp * kOnceWaves + wave;
     const RecRow<DT, VEC> row(a, b, t);
     const void* const sm = row_ptr<DT>(a.Sm, (long)b * a.sb + (long)t * a.st - row.head);  // row.sm, but with PLAIN
+    const bool with_m = !PLAIN || t < K;  // without steering nothing asks for S_noctx at the bonus position
     const long vbase = (long)c * (kChunkSteps * kWave) + lane;
     const bool whole = c < row.nch, last = c == row.nch && lane < row.tailc;  // full vectors, or one logit past them
     typename RawT<DT, VEC>::type rg[kChunkSteps], rp[kChunkSteps], rm[kChunkSteps];
@@ -1413,14 +1414,14 @@ __global__ __launch_bounds__(kOnceWaves * kWave) void block_once_kernel(const On
             if (v < row.nvec) {
                 rg[j] = ld_raw<DT, VEC>(row.g, v);
                 if (!PLAIN) rp[j] = ld_raw<DT, VEC>(row.sp, v);
-                if (!PLAIN || t < K) rm[j] = ld_raw<DT, VEC>(sm, v);
+                if (with_m) rm[j] = ld_raw<DT, VEC>(sm, v);
             }
         }
     } else if (last) {
         const long e = row.nvec * VEC + lane;
         tg[0] = ld_elem<DT>(row.g, e);
         tp[0] = ld_steer<DT, PLAIN>(row.sp, e);
-        tm[0] = ld_elem<DT>(sm, e);
+        if (with_m) tm[0] = ld_elem<DT>(sm, e);
     }
     float hy = 0.f;
     if (tid < 2 * K) {  // the draft tokens' logits, on their way beside the rows

@@ -593,6 +593,23 @@ def test_small_blocks_in_one_launch(binding, oracle, dtype, batch, k_max, vocab,
     assert all(first[k] is None or torch.equal(torch.nan_to_num(first[k]), torch.nan_to_num(again[k])) for k in names)
 
 
+# Without steering the bonus position asks for nothing but the generalist's row: S_noctx ends behind its k_max rows here (what follows
+# belongs to someone else), with logits past the last vector of a row and without, all drafts accepted.
+@pytest.mark.parametrize("greedy", [False, True])
+@pytest.mark.parametrize("dtype,vocab", [("bf16", 5), ("bf16", 2 * 2048 + 9), ("bf16", 4096), ("f32", 1027), ("f32", 32000)])
+def test_without_steering_the_bonus_row_of_the_specialist_is_not_asked_for(binding, oracle, dtype, vocab, greedy):
+    w = recipe("c4", dtype, batch=1, k_max=3, vocab=vocab)
+    inp = W.generate(w, "cuda")
+    inp["uniforms"][:, :3] = 0.0
+    inp["draft_len"] = None
+    want = parity.oracle_run(oracle, inp, lam=w.lam, beta=0.0, temperature=w.temperature, greedy=greedy, want_recovery_logprobs=False)
+    inp["S_noctx"][:, 3] = float("nan")
+    kw = dict(lam=w.lam, beta=0.0, temperature=w.temperature, greedy=greedy)
+    got = binding.verify_block(*(inp[k] for k in ("G", "S_ctx", "S_noctx", "draft", "uniforms")), want_draft_logprobs=True, **kw)
+    assert got["accepted_len"].item() == 3
+    parity.compare(got, want, inp["uniforms"], None)
+
+
 @pytest.mark.parametrize("greedy", [False, True])
 @pytest.mark.parametrize("dtype,batch,k_max,vocab", [("f32", 1, 4, 32000), ("bf16", 4, 4, 50257)])
 def test_small_blocks_in_one_launch_inside_a_hip_graph(binding, dtype, batch, k_max, vocab, greedy):
