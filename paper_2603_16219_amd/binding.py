@@ -1,7 +1,8 @@
 """Binding of the C-ABI library: argument marshalling only.
 
 The wrappers hand arguments that need nothing done to them to native code (csrc/calls.cpp), which makes the outputs and calls the
-library; what has to be converted, copied or refused, and the raw calls, go through ctypes here.
+library; what has to be converted, copied or refused, and the raw calls, go through ctypes here, as does everything where that code
+cannot be built or loaded.
 
 Every step of the block runs inside ``libspecsteer.so`` (hand-written HIP for
 gfx950); PyTorch supplies device memory and the stream.  There is no CPU or
@@ -12,6 +13,7 @@ from __future__ import annotations
 import ctypes
 import importlib.util
 import os
+import warnings
 from typing import Optional
 
 import torch  # imported before the library so both share one HIP runtime
@@ -49,7 +51,7 @@ class SpecSteerError(RuntimeError):
 
 
 _lib = None
-_calls = None  # the native wrappers, once the library is loaded
+_calls = None  # the native wrappers, once the library is loaded and if they can be
 
 
 def library() -> ctypes.CDLL:
@@ -58,7 +60,7 @@ def library() -> ctypes.CDLL:
     if _lib is None:
         path = _build.LIBRARY
         if not os.path.exists(path):
-            _build.build()
+            _build.build_library()
         lib = ctypes.CDLL(path)
         lib.specsteer_workspace_bytes.restype = ctypes.c_size_t
         lib.specsteer_workspace_bytes.argtypes = [ctypes.POINTER(SSParams)]
@@ -82,16 +84,30 @@ def library() -> ctypes.CDLL:
         lib.specsteer_status_string.restype = ctypes.c_char_p
         lib.specsteer_status_string.argtypes = [ctypes.c_int]
         lib.specsteer_version.restype = ctypes.c_int
-        if not os.path.exists(_build.CALLS):
+        _lib = lib
+        _calls = _native_wrappers(lib)
+    return _lib
+
+
+def _native_wrappers(lib: ctypes.CDLL):
+    """The native wrappers of this library (built only if absent), or None with a warning: the general path answers everything
+    without them, small calls with more host time."""
+    try:
+        path = _build.calls_path()
+        if not os.path.exists(path):
+            if not os.access(os.path.dirname(path), os.W_OK):
+                raise OSError(f"{path} is not there and cannot be built there")
             _build.build_calls()
-        spec = importlib.util.spec_from_file_location(__package__ + "._calls", _build.CALLS)
+        spec = importlib.util.spec_from_file_location(__package__ + "._calls", path)
         calls = importlib.util.module_from_spec(spec)
         spec.loader.exec_module(calls)
         calls.use(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
             lib.specsteer_workspace_bytes, lib.specsteer_verify_block_unbound, lib.specsteer_cloud_topk, lib.specsteer_edge_resample)),
             torch._C._cuda_getCurrentRawStream)
-        _lib, _calls = lib, calls
-    return _lib
+        return calls
+    except Exception as e:  # no compiler or headers, a file that does not load, a library from before the wrappers
+        warnings.warn(f"the binding's native wrappers are not available, small calls take more host time: {e}", RuntimeWarning, stacklevel=3)
+        return None
 
 
 def _done(out):

@@ -1,8 +1,15 @@
-"""The binding's native wrappers against its general path: what they take they answer alike, everything else they leave to it."""
+"""The binding's native wrappers against its general path: what they take they answer alike, everything else they leave to it, and
+without them it answers everything."""
+import os
+import shutil
+import subprocess
+import warnings
+
 import pytest
 import torch
 
 from paper_2603_16219_amd import binding
+from paper_2603_16219_amd import build as binding_build
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -24,6 +31,66 @@ def test_host_tensors_and_other_objects_are_left_to_the_general_path():
     assert c.steer_rows() is None and c.cloud_topk(x) is None  # another number of arguments
     with pytest.raises(ValueError, match="device"):
         binding.steer_rows(x[:, 0], x[:, 0], x[:, 0], u)
+
+
+@pytest.fixture
+def not_loaded(monkeypatch):
+    """The binding as it is before its first call; as it was afterwards."""
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_calls", None)
+    return monkeypatch
+
+
+def loads_without_wrappers(because):
+    p = binding.make_params(2, 3, 1000, torch.float32, lam=0.5, beta=1.0, temperature=1.0)
+    with pytest.warns(RuntimeWarning, match=because):
+        assert binding.version() >= 100
+    assert binding._lib is not None and binding._calls is None
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")  # one warning, not one a call
+        assert binding.first_window(p) == 3 and binding.workspace_bytes(p) > 0
+
+
+@pytest.mark.parametrize("compiler", ["/nonexistent/g++", "false"])
+def test_the_library_loads_where_the_wrappers_cannot_be_built(not_loaded, tmp_path, compiler):
+    not_loaded.setattr(binding_build, "calls_path", lambda: str(tmp_path / "_calls.so"))
+    not_loaded.setenv("CXX", compiler)
+    loads_without_wrappers("not available")
+    assert os.listdir(tmp_path) == []
+
+
+def test_the_library_loads_where_the_wrappers_do_not(not_loaded, tmp_path):
+    (tmp_path / "_calls.so").write_bytes(b"no shared object")
+    not_loaded.setattr(binding_build, "calls_path", lambda: str(tmp_path / "_calls.so"))
+    loads_without_wrappers("_calls.so")
+
+
+def test_a_library_from_before_the_wrappers_loads(not_loaded, tmp_path):
+    names = ("workspace_bytes", "verify_block", "verify_block_timed", "verify_block_static", "cloud_topk", "edge_resample")
+    src = "".join(f"int specsteer_{n}(void) {{ return 1; }}\n" for n in names)
+    src += "int specsteer_first_window(void) { return 3; }\nint specsteer_version(void) { return 100; }\nconst char *specsteer_status_string(int s) { return s ? \"\" : 0; }\n"
+    (tmp_path / "old.c").write_text(src)
+    old = str(tmp_path / "old.so")
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", old, str(tmp_path / "old.c")], check=True)
+    not_loaded.setattr(binding_build, "LIBRARY", old)
+    loads_without_wrappers("specsteer_verify_block_unbound")
+
+
+def test_wrappers_of_another_torch_or_other_sources_are_not_loaded(monkeypatch, tmp_path):
+    """Their file's name says what they were built against."""
+    here = binding_build.calls_path()
+    assert os.path.exists(here) and binding_build.calls_path() == here
+    with monkeypatch.context() as m:
+        m.setattr(torch, "__version__", "2.99.0")
+        assert binding_build.calls_path() != here
+    for i in range(len(binding_build.CALLS_SOURCES)):
+        copies = [shutil.copy(p, tmp_path / os.path.basename(p)) for p in binding_build.CALLS_SOURCES]
+        monkeypatch.setattr(binding_build, "CALLS_SOURCES", copies)
+        assert binding_build.calls_path() == here
+        with open(copies[i], "a") as f:
+            f.write("\n")
+        assert binding_build.calls_path() != here
+        monkeypatch.undo()
 
 
 def logits(dtype, B, k1, V, pad, odd):
