@@ -352,6 +352,24 @@ inline Plan make_plan(const ss_params* p) {
     return small.bytes <= (size_t)SS_STATIC_SCRATCH_BYTES ? small : whole;
 }
 
+// Whether a block takes one launch, in the workspace of a plan: its words begin where the slice partials would, `stride` of them for each
+// sequence.  The workspace's size is that of two launches, which is what callers hold, so space is a second gate behind the lines above.
+// From V = 32000 on sampled blocks always fit.  Greedy ones, whose candidates take two words a part, do not from 3 to 6 drafts on in
+// fp32 (4 sequences of 3, V = 62209: 586 words, 584 there; 8 of 4, V = 32000: 378, 376) and 4 to 7 in bf16 (3 of 4, V = 100352: 598, 597).  Short rows of more than 128
+// sequences, where there are no tables of shared rows, do not.
+struct OncePlan {
+    bool taken;
+    long stride;
+    OnceSpace space;
+};
+inline OncePlan once_plan(const Plan& pl, int B, int kmax, int NC, int dtype, bool plain, bool greedy, bool ragged, int cus) {
+    OncePlan o;
+    o.space = once_space(kmax, NC, greedy);
+    o.stride = B > 0 ? (long)((pl.bytes - pl.off_partial) / sizeof(uint64_t)) / B : 0;
+    o.taken = block_in_one_launch(B, kmax, NC, dtype, plain, greedy, ragged, cus) && o.space.words <= o.stride;
+    return o;
+}
+
 // The plan for a workspace of `bytes`, the richest that fits it; make_plan's, which the caller has to refuse, if none does.  Where
 // only a plan without the draft tokens' logits fits the static scratch a larger block asks for less than a smaller one (349
 // sequences of 1000 drafts, V = 40: 8.0 MiB, 350: 5.3), and a caller that holds what the larger needs can run the smaller without them too.

@@ -1792,16 +1792,14 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
 
     const int kind = (ra.greedy ? 1 : 0) | (ra.plain ? 2 : 0);
     // The call whose stages are timed has them one behind the other.
-    if (!ev && windows == 1 && !recovery_logprobs && block_in_one_launch(B, kmax, ra.NC, DT, ra.plain != 0, ra.greedy != 0, ragged, device_cu_count())) {
-        const OnceArgs oa{ra, reinterpret_cast<unsigned long long*>(ws + pl.off_partial),
-                          (long)((pl.bytes - pl.off_partial) / sizeof(uint64_t) / B), next_call_tag(), once_space(kmax, ra.NC, ra.greedy != 0)};
-        if (oa.once.words <= oa.word_stride) {
-            static void (*const once[4])(OnceArgs) = {block_once_kernel<DT, VEC, false, false>, block_once_kernel<DT, VEC, true, false>,
-                                                      block_once_kernel<DT, VEC, false, true>, block_once_kernel<DT, VEC, true, true>};
-            launch(once[kind], dim3((unsigned)(B * (kmax + 1) * oa.once.parts)), dim3(kOnceWaves * kWave),
-                   once_lds(kmax, ra.NC, ra.greedy != 0), stream, oa);
-            return hipGetLastError();
-        }
+    const OncePlan once = once_plan(pl, B, kmax, ra.NC, DT, ra.plain != 0, ra.greedy != 0, ragged, device_cu_count());
+    if (once.taken && !ev && windows == 1 && !recovery_logprobs) {
+        static void (*const kernels[4])(OnceArgs) = {block_once_kernel<DT, VEC, false, false>, block_once_kernel<DT, VEC, true, false>,
+                                                     block_once_kernel<DT, VEC, false, true>, block_once_kernel<DT, VEC, true, true>};
+        const OnceArgs oa{ra, reinterpret_cast<unsigned long long*>(ws + pl.off_partial), once.stride, next_call_tag(), once.space};
+        launch(kernels[kind], dim3((unsigned)(B * (kmax + 1) * once.space.parts)), dim3(kOnceWaves * kWave),
+               once_lds(kmax, ra.NC, ra.greedy != 0), stream, oa);
+        return hipGetLastError();
     }
 
     mark(0);

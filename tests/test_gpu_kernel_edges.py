@@ -553,15 +553,20 @@ def test_row_pass_at_the_end_of_short_slices(binding, oracle, dtype, vocab, batc
 
 
 # Small blocks in one launch: a wave a chunk of 256 vectors, four to a workgroup.  Rows shorter than a vector, of one chunk and one logit more
-# and less, of whole workgroups and a chunk over, the longest (64 chunks) and, beyond and where the space does not suffice (16 greedy
-# drafts), two launches; rows at odd elements; lengths of 0, ids and lengths that flag.  On a space of garbage that the calls before
-# have left, direct and as the stages of the timed call, whose tokens are the same.
+# and less, of whole workgroups and a chunk over, the longest (64 chunks, the last one whole, partial or of logits past the last vector)
+# and, beyond and where the space does not suffice (16 greedy drafts), two launches; rows at odd elements; lengths of 0, ids and
+# lengths that flag.  On a space of garbage that the calls before have left, direct and as the stages of the timed call, whose tokens are the
+# same.  Behind each size the modes that take one launch: sampled, greedy, and both without steering; a CPU test holds them against the rule.
+ONCE_SIZES = [
+    ("bf16", 3, 2, 5, "sgSG"), ("bf16", 5, 16, 7, "sgSG"), ("bf16", 5, 3, 2047, "sgSG"), ("bf16", 5, 4, 2048, "sgSG"), ("bf16", 5, 1, 2049, "sgSG"),
+    ("bf16", 3, 4, 4 * 2048 + 9, "sgSG"), ("bf16", 3, 16, 17 * 2048 - 3, "sS"), ("bf16", 6, 4, 32000, "sgSG"), ("bf16", 1, 8, 64 * 2048, "sgSG"),
+    ("bf16", 4, 2, 64 * 2048 - 1, ""), ("bf16", 4, 2, 64 * 2048 - 8, "sgSG"), ("bf16", 4, 2, 63 * 2048 + 5, "sgSG"), ("bf16", 2, 3, 64 * 2048 + 1, ""),
+    ("bf16", 40, 2, 3 * 2048 + 1, "sgSG"), ("f32", 1, 4, 32000, "sgSG"), ("f32", 4, 4, 1025, "sgSG"), ("f32", 3, 16, 33 * 1024 + 2, "sS"),
+    ("f32", 2, 2, 64 * 1024, "sgSG"), ("f32", 25, 3, 40000, "sS"), ("bf16", 24, 3, 32 * 2048, "sS")]
+
+
 @pytest.mark.parametrize("greedy,beta", [(False, 0.8), (True, 0.8), (False, 0.0), (True, 0.0)])
-@pytest.mark.parametrize("dtype,batch,k_max,vocab", [
-    ("bf16", 3, 2, 5), ("bf16", 5, 16, 7), ("bf16", 5, 3, 2047), ("bf16", 5, 4, 2048), ("bf16", 5, 1, 2049), ("bf16", 3, 4, 4 * 2048 + 9),
-    ("bf16", 3, 16, 17 * 2048 - 3), ("bf16", 6, 4, 32000), ("bf16", 1, 8, 64 * 2048), ("bf16", 4, 2, 64 * 2048 - 1), ("bf16", 2, 3, 64 * 2048 + 1),
-    ("bf16", 40, 2, 3 * 2048 + 1), ("f32", 1, 4, 32000), ("f32", 4, 4, 1025), ("f32", 3, 16, 33 * 1024 + 2), ("f32", 2, 2, 64 * 1024),
-    ("f32", 25, 3, 40000), ("bf16", 24, 3, 32 * 2048)])
+@pytest.mark.parametrize("dtype,batch,k_max,vocab", [c[:4] for c in ONCE_SIZES])
 def test_small_blocks_in_one_launch(binding, oracle, dtype, batch, k_max, vocab, greedy, beta):
     w = recipe("c4", dtype, batch=batch, k_max=k_max, vocab=vocab)
     inp = W.generate(w, "cuda")
@@ -610,8 +615,11 @@ def test_without_steering_the_bonus_row_of_the_specialist_is_not_asked_for(bindi
     parity.compare(got, want, inp["uniforms"], None)
 
 
+ONCE_GRAPH_SIZES = [("f32", 1, 4, 32000, "sg"), ("bf16", 4, 4, 50257, "sg")]
+
+
 @pytest.mark.parametrize("greedy", [False, True])
-@pytest.mark.parametrize("dtype,batch,k_max,vocab", [("f32", 1, 4, 32000), ("bf16", 4, 4, 50257)])
+@pytest.mark.parametrize("dtype,batch,k_max,vocab", [c[:4] for c in ONCE_GRAPH_SIZES])
 def test_small_blocks_in_one_launch_inside_a_hip_graph(binding, dtype, batch, k_max, vocab, greedy):
     """The words of a captured call carry the same tag on every replay: replays on new drafts, lengths and uniforms, one behind the
     other and with direct calls on the same workspace between them, equal the direct calls."""

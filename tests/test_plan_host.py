@@ -57,7 +57,12 @@ int main() {
             continue;
         }
         const Plan pl = make_plan(&p);
-        if (!std::strcmp(what, "parts")) {  // cus odd
+        if (!std::strcmp(what, "route")) {  // plain ragged odd cus: whether in one launch, the words it needs and has, and whether in one window
+            int a[4];
+            if (std::scanf("%d %d %d %d", a, a + 1, a + 2, a + 3) != 4) return 1;
+            const OncePlan o = once_plan(pl, p.batch, p.k_max, chunks_per_row(p.vocab, pl.vec, a[2] != 0), p.dtype, a[0], p.flags & SS_FLAG_GREEDY, a[1], a[3]);
+            std::printf("%d %ld %ld %d\n", o.taken ? 1 : 0, o.space.words, o.stride, pl.windows == 1 ? 1 : 0);
+        } else if (!std::strcmp(what, "parts")) {  // cus odd
             int cus, odd;
             if (std::scanf("%d %d", &cus, &odd) != 2) return 1;
             const int nc = chunks_per_row(p.vocab, pl.vec, odd != 0);
@@ -162,6 +167,40 @@ def test_small_blocks_take_one_launch_while_that_pays(planner, dtype, plain, gre
 @pytest.mark.parametrize("k_max,chunks", [(0, 32), (17, 4), (1, 65)])
 def test_blocks_without_drafts_with_many_or_of_long_rows_do_not(planner, k_max, chunks):
     assert planner([f"once 1 {k_max} {chunks} 0 0 0 0 {CUS}"])[0][0] == 0
+
+
+def route(planner, dtype, batch, k_max, vocab, plain=0, greedy=0, ragged=0):
+    """(whether in one launch, the words a sequence it needs, those it has, whether in one window), dense rows"""
+    return planner([f"route {batch} {k_max} {vocab} {BF16 if dtype == 'bf16' else 0} {greedy} 0.5 {plain} {ragged} {int(dtype == 'bf16' and vocab % 2)} {CUS}"])[0]
+
+
+def test_the_blocks_meant_for_one_launch_take_it(planner):
+    """The sizes of the GPU tests of that launch, which could not tell: two launches give the same answers."""
+    import test_gpu_kernel_edges as edges
+
+    for ragged, sizes in ((1, edges.ONCE_SIZES), (1, edges.ONCE_GRAPH_SIZES)):
+        for dtype, batch, k_max, vocab, modes in sizes:
+            got = "".join(m for m, plain, greedy in (("s", 0, 0), ("g", 0, 1), ("S", 1, 0), ("G", 1, 1))
+                          if route(planner, dtype, batch, k_max, vocab, plain, greedy, ragged)[0])
+            assert got == modes if sizes is edges.ONCE_SIZES else set(modes) <= set(got), (dtype, batch, k_max, vocab, got)
+    assert {m for c in edges.ONCE_SIZES for m in c[4]} == set("sgSG")
+
+
+# One user and a few, as the benchmark and serving have them; and what is beyond the lines or the space.
+@pytest.mark.parametrize("dtype,batch,k_max,vocab,greedy,one", [
+    ("f32", 1, 4, 32000, 0, 1), ("f32", 1, 4, 32000, 1, 1), ("bf16", 1, 8, 128256, 0, 1), ("bf16", 4, 8, 50257, 0, 1), ("bf16", 1, 4, 151936, 0, 0),
+    ("bf16", 8, 8, 151936, 0, 0), ("bf16", 8, 4, 128256, 0, 0), ("bf16", 1, 8, 128256, 1, 0)])
+def test_which_blocks_of_few_users_take_one_launch(planner, dtype, batch, k_max, vocab, greedy, one):
+    taken, _, _, one_window = route(planner, dtype, batch, k_max, vocab, greedy=greedy)
+    assert (taken, one_window) == (one, 1)
+
+
+# Within the lines, but a word or two more than the space of two launches (and just within it).
+@pytest.mark.parametrize("dtype,batch,k_max,vocab,greedy,words,there", [
+    ("f32", 4, 3, 62209, 1, 586, 584), ("f32", 8, 4, 32000, 1, 378, 376), ("bf16", 3, 4, 100352, 1, 598, 597), ("f32", 3, 3, 62209, 1, 586, 597)])
+def test_space_is_a_second_gate_for_one_launch(planner, dtype, batch, k_max, vocab, greedy, words, there):
+    taken, need, got, _ = route(planner, dtype, batch, k_max, vocab, greedy=greedy)
+    assert need == words and got == there and taken == int(need <= got)
 
 
 def test_the_space_of_a_block_in_one_launch_holds_what_its_parts_deliver(planner):
