@@ -232,10 +232,23 @@ inline size_t once_lds(int kmax, int NC, bool greedy) {
 //     14.3 -> 12.9, 768 13.8 -> 13.2, 832 (4 of 12, V = 65536) 15.8 -> 15.0, 1024 15.75 -> 15.6.
 //   - Greedy with a steering term compares every logit in double: bf16 up to 1 (224 15.0 -> 12.7; 336 14.8 -> 15.5), fp32 up to 1 1/2 (384 13.4
 //     -> 12.75); without one up to 2 (512 14.2 -> 12.6).
-inline bool block_in_one_launch(int B, int kmax, int NC, int dtype, bool plain, bool greedy, bool ragged, int cus) {
+// Rows of up to 8 chunks, which a recovery takes in one workgroup a sequence without a hand-over, gain less:
+//   - Greedy ones of less than 5 whole chunks nothing, but for fp32 without a steering term: one wave forms all the sums of its chunk, those in double and
+//     those past the row's end among them. bf16, 160 (32 of 4, V = 40) 9.2 -> 11.4, 15 (3 of 4, V = 1000) 9.2 -> 11.2, 95 (19 of 4, V = 8192) 11.6
+//     -> 12.5, without a steering term 255 (51 of 4, V = 1000) 9.2 -> 9.8; fp32, 255 (51 of 4, V = 40) 8.4 -> 9.6, 45 (9 of 4, V = 4096) 9.7 -> 10.1.
+//   - Other greedy ones gain up to 1, bf16 without a steering term (250, V = 16384 11.2 -> 10.6; 380 11.8 -> 12.3) and fp32 with one (250, V = 8192 11.7 ->
+//     10.9; 380 12.4 -> 12.6).
+//   - Sampled bf16 up to 2 (480, V = 10240 13.4 -> 12.9; 540 13.7 -> 14.4, V = 9000 13.2 -> 14.6, V = 8192 13.6 -> 15.1), and no further with lengths or
+//     without a steering term either from 4 chunks on (lengths 510, V = 9000 13.5 -> 12.9; 640 13.8 -> 15.1).
+//   - Sampled fp32 up to 3 (760, V = 8192 14.4 -> 13.1, V = 6166 13.4 -> 13.3; 890 13.7 -> 14.4, 1020 14.3 -> 15.4), with lengths or without a steering term as
+//     far as longer rows.
+inline bool block_in_one_launch(int B, int kmax, int V, int NC, int dtype, bool plain, bool greedy, bool ragged, int cus) {
     if (kmax < 1 || kmax > kOnceMaxDrafts || NC > kOnceMaxParts * kOnceWaves) return false;
-    const bool bf16 = dtype == SS_BF16;
-    const int eighths = greedy ? (plain ? 16 : bf16 ? 8 : 12) : !bf16 ? 32 : plain || ragged ? 24 : 17;
+    const bool bf16 = dtype == SS_BF16, brief = NC <= 8, reduced = plain || ragged;
+    if (greedy && (bf16 || !plain) && V < 5 * kChunkSteps * kWave * (bf16 ? 8 : 4)) return false;
+    const int eighths = greedy ? (bf16 ? (plain && !brief ? 16 : 8) : plain ? 16 : brief ? 8 : 12)
+                        : bf16 ? (brief ? (reduced && NC < 4 ? 24 : 16) : reduced ? 24 : 17)
+                               : (brief && !reduced ? 24 : 32);
     return 8l * B * (kmax + 1) * ((NC + kOnceWaves - 1) / kOnceWaves) <= (long)eighths * cus;
 }
 
@@ -362,11 +375,11 @@ struct OncePlan {
     long stride;
     OnceSpace space;
 };
-inline OncePlan once_plan(const Plan& pl, int B, int kmax, int NC, int dtype, bool plain, bool greedy, bool ragged, int cus) {
+inline OncePlan once_plan(const Plan& pl, int B, int kmax, int V, int NC, int dtype, bool plain, bool greedy, bool ragged, int cus) {
     OncePlan o;
     o.space = once_space(kmax, NC, greedy);
     o.stride = B > 0 ? (long)((pl.bytes - pl.off_partial) / sizeof(uint64_t)) / B : 0;
-    o.taken = block_in_one_launch(B, kmax, NC, dtype, plain, greedy, ragged, cus) && o.space.words <= o.stride;
+    o.taken = block_in_one_launch(B, kmax, V, NC, dtype, plain, greedy, ragged, cus) && o.space.words <= o.stride;
     return o;
 }
 

@@ -1792,7 +1792,7 @@ hipError_t launch_all(LseArgs la, RecArgs ra, const Plan& pl, char* ws, float* r
 
     const int kind = (ra.greedy ? 1 : 0) | (ra.plain ? 2 : 0);
     // The call whose stages are timed has them one behind the other.
-    const OncePlan once = once_plan(pl, B, kmax, ra.NC, DT, ra.plain != 0, ra.greedy != 0, ragged, device_cu_count());
+    const OncePlan once = once_plan(pl, B, kmax, V, ra.NC, DT, ra.plain != 0, ra.greedy != 0, ragged, device_cu_count());
     if (once.taken && !ev && windows == 1 && !recovery_logprobs) {
         static void (*const kernels[4])(OnceArgs) = {block_once_kernel<DT, VEC, false, false>, block_once_kernel<DT, VEC, true, false>,
                                                      block_once_kernel<DT, VEC, false, true>, block_once_kernel<DT, VEC, true, true>};

@@ -558,10 +558,10 @@ def test_row_pass_at_the_end_of_short_slices(binding, oracle, dtype, vocab, batc
 # lengths that flag.  On a space of garbage that the calls before have left, direct and as the stages of the timed call, whose tokens are the
 # same.  Behind each size the modes that take one launch: sampled, greedy, and both without steering; a CPU test holds them against the rule.
 ONCE_SIZES = [
-    ("bf16", 3, 2, 5, "sgSG"), ("bf16", 5, 16, 7, "sgSG"), ("bf16", 5, 3, 2047, "sgSG"), ("bf16", 5, 4, 2048, "sgSG"), ("bf16", 5, 1, 2049, "sgSG"),
-    ("bf16", 3, 4, 4 * 2048 + 9, "sgSG"), ("bf16", 3, 16, 17 * 2048 - 3, "sS"), ("bf16", 6, 4, 32000, "sgSG"), ("bf16", 1, 8, 64 * 2048, "sgSG"),
+    ("bf16", 3, 2, 5, "sS"), ("bf16", 5, 16, 7, "sS"), ("bf16", 5, 3, 2047, "sS"), ("bf16", 5, 4, 2048, "sS"), ("bf16", 5, 1, 2049, "sS"),
+    ("bf16", 3, 4, 4 * 2048 + 9, "sS"), ("bf16", 3, 4, 5 * 2048 + 9, "sgSG"), ("bf16", 5, 3, 7 * 2048 + 1, "sgSG"), ("bf16", 3, 16, 17 * 2048 - 3, "sS"), ("bf16", 6, 4, 32000, "sgSG"), ("bf16", 1, 8, 64 * 2048, "sgSG"),
     ("bf16", 4, 2, 64 * 2048 - 1, ""), ("bf16", 4, 2, 64 * 2048 - 8, "sgSG"), ("bf16", 4, 2, 63 * 2048 + 5, "sgSG"), ("bf16", 2, 3, 64 * 2048 + 1, ""),
-    ("bf16", 40, 2, 3 * 2048 + 1, "sgSG"), ("f32", 1, 4, 32000, "sgSG"), ("f32", 4, 4, 1025, "sgSG"), ("f32", 3, 16, 33 * 1024 + 2, "sS"),
+    ("bf16", 40, 2, 3 * 2048 + 1, "sS"), ("f32", 1, 4, 32000, "sgSG"), ("f32", 4, 4, 1025, "sSG"), ("f32", 4, 4, 5 * 1024 + 1, "sgSG"), ("f32", 3, 16, 33 * 1024 + 2, "sS"),
     ("f32", 2, 2, 64 * 1024, "sgSG"), ("f32", 25, 3, 40000, "sS"), ("bf16", 24, 3, 32 * 2048, "sS")]
 
 

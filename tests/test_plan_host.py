@@ -32,11 +32,12 @@ int main() {
             std::printf("%d\n", rows_in_one_launch(a[0], a[1], a[2], a[3], a[4], a[5]) ? 1 : 0);
             continue;
         }
-        if (!std::strcmp(what, "once")) {  // B kmax chunks dtype plain greedy ragged cus: whether in one launch, and its space and LDS
+        if (!std::strcmp(what, "once")) {  // B kmax chunks (whole) dtype plain greedy ragged cus: whether in one launch, and its space and LDS
             int a[8];
             if (std::scanf("%d %d %d %d %d %d %d %d", a, a + 1, a + 2, a + 3, a + 4, a + 5, a + 6, a + 7) != 8) return 1;
             const OnceSpace s = once_space(a[1], a[2], a[5]);
-            std::printf("%d %d %ld %ld %ld %ld %ld\n", block_in_one_launch(a[0], a[1], a[2], a[3], a[4], a[5], a[6], a[7]) ? 1 : 0, s.parts, s.flags,
+            const int V = a[2] * kChunkSteps * kWave * (a[3] == SS_BF16 ? 8 : 4);
+            std::printf("%d %d %ld %ld %ld %ld %ld\n", block_in_one_launch(a[0], a[1], V, a[2], a[3], a[4], a[5], a[6], a[7]) ? 1 : 0, s.parts, s.flags,
                         s.best, s.masses, s.words, (long)once_lds(a[1], a[2], a[5]));
             continue;
         }
@@ -60,7 +61,7 @@ int main() {
         if (!std::strcmp(what, "route")) {  // plain ragged odd cus: whether in one launch, the words it needs and has, and whether in one window
             int a[4];
             if (std::scanf("%d %d %d %d", a, a + 1, a + 2, a + 3) != 4) return 1;
-            const OncePlan o = once_plan(pl, p.batch, p.k_max, chunks_per_row(p.vocab, pl.vec, a[2] != 0), p.dtype, a[0], p.flags & SS_FLAG_GREEDY, a[1], a[3]);
+            const OncePlan o = once_plan(pl, p.batch, p.k_max, p.vocab, chunks_per_row(p.vocab, pl.vec, a[2] != 0), p.dtype, a[0], p.flags & SS_FLAG_GREEDY, a[1], a[3]);
             std::printf("%d %ld %ld %d\n", o.taken ? 1 : 0, o.space.words, o.stride, pl.windows == 1 ? 1 : 0);
         } else if (!std::strcmp(what, "parts")) {  // cus odd
             int cus, odd;
@@ -157,11 +158,26 @@ def test_rows_without_drafts_are_taken_whole_while_that_pays(planner, dtype, pla
     (BF16, 0, 0, 0, 544), (BF16, 0, 0, 1, 768), (BF16, 1, 0, 0, 768), (0, 0, 0, 0, 1024), (0, 0, 0, 1, 1024), (0, 1, 0, 0, 1024),
     (BF16, 0, 1, 0, 256), (BF16, 0, 1, 1, 256), (0, 0, 1, 0, 384), (BF16, 1, 1, 0, 512), (0, 1, 1, 1, 512)])
 def test_small_blocks_take_one_launch_while_that_pays(planner, dtype, plain, greedy, ragged, most):
-    for k_max, chunks in ((1, 1), (1, 4), (3, 32), (16, 64), (7, 5)):
+    for k_max, chunks in ((1, 9), (3, 32), (16, 64), (7, 11)):
         per = (k_max + 1) * -(-chunks // 4)
         for batch in (max(most // per, 1), most // per + 1):
             got = planner([f"once {batch} {k_max} {chunks} {dtype} {plain} {greedy} {ragged} {CUS}"])[0][0]
             assert got == int(batch * per <= most), (k_max, chunks, batch)
+
+
+# Rows of up to 8 chunks gain less: for each number of chunks the most workgroups (0: never).
+@pytest.mark.parametrize("dtype,plain,greedy,ragged,most", [
+    (BF16, 0, 0, 0, {1: 512, 8: 512, 9: 544}), (BF16, 0, 0, 1, {3: 768, 4: 512, 8: 512, 9: 768}), (BF16, 1, 0, 0, {3: 768, 4: 512, 8: 512, 9: 768}),
+    (0, 0, 0, 0, {1: 768, 8: 768, 9: 1024}), (0, 0, 0, 1, {1: 1024, 8: 1024}), (0, 1, 0, 0, {1: 1024, 8: 1024}),
+    (BF16, 0, 1, 0, {1: 0, 4: 0, 5: 256, 9: 256}), (BF16, 1, 1, 1, {1: 0, 4: 0, 5: 256, 8: 256, 9: 512}),
+    (0, 0, 1, 0, {1: 0, 4: 0, 5: 256, 8: 256, 9: 384}), (0, 1, 1, 1, {1: 512, 4: 512, 8: 512})])
+def test_small_blocks_of_short_rows_take_one_launch_less_far(planner, dtype, plain, greedy, ragged, most):
+    for chunks, limit in most.items():
+        for k_max in (1, 4, 16):
+            per = (k_max + 1) * -(-chunks // 4)
+            for batch in {1, max(limit // per, 1), limit // per + 1}:
+                got = planner([f"once {batch} {k_max} {chunks} {dtype} {plain} {greedy} {ragged} {CUS}"])[0][0]
+                assert got == int(batch * per <= limit), (k_max, chunks, batch)
 
 
 @pytest.mark.parametrize("k_max,chunks", [(0, 32), (17, 4), (1, 65)])
