@@ -24,6 +24,21 @@ def recipe(name, dtype, **size):
     return dataclasses.replace(W.scaled(W.WORKLOADS[name], name=f"{name}-{dtype}-{size}", **size), dtype=dtype)
 
 
+def in_stages(binding, inp, *, lam, beta, temperature, draft_len=None, greedy=False):
+    """The block by the timed call, which is a row pass and a recovery also for small blocks that the others take in one launch:
+    what is said below about those two kernels holds of it at every size."""
+    batch, k_max = inp["draft"].shape
+    p = binding.make_params(batch, k_max, inp["G"].shape[2], inp["G"].dtype, lam=lam, beta=beta, temperature=temperature,
+                            stride_b=inp["G"].stride(0), stride_t=inp["G"].stride(1), flags=binding.SS_FLAG_GREEDY if greedy else 0)
+    ws = torch.empty(max(256, binding.workspace_bytes(p)), dtype=torch.uint8, device="cuda")
+    out = {"accepted_len": torch.empty(batch, dtype=torch.int32, device="cuda"), "next_token": torch.empty(batch, dtype=torch.int32, device="cuda"),
+           "next_token_logprob": torch.empty(batch, device="cuda"), "recovery_logprobs": None,
+           "draft_logprobs": torch.empty(batch, k_max, 2, device="cuda")}
+    binding.verify_block_raw(inp["G"], inp["S_ctx"], inp["S_noctx"], inp["draft"] if k_max else None, draft_len, inp["uniforms"], p,
+                             *out.values(), ws, timed=True)
+    return out
+
+
 # Short log-prob rows are written by the recovery launch (5 sequences: up to 256 KiB a row, 26214 bf16 or 16384 fp32 logits),
 # longer ones by a launch of their own, cut into segments of 512 vectors (4096 bf16 or 2048 fp32 logits): whole segments,
 # one logit more and less, a last segment that holds only the logits past the last vector, less than a vector.
@@ -107,6 +122,8 @@ def test_recovery_launch_shapes(binding, oracle, dtype, batch, vocab, greedy, be
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=beta, temperature=w.temperature, greedy=greedy,
                             want_recovery_logprobs=False)
     parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
+    parity.compare(in_stages(binding, inp, lam=w.lam, beta=beta, temperature=w.temperature, draft_len=inp["draft_len"], greedy=greedy), ora,
+                   inp["uniforms"], inp["draft_len"])
 
 
 # Up to 128 rows without a draft: one launch while a 16-wave workgroup takes its row fast enough, with pairs of chunks where there is no
@@ -271,6 +288,9 @@ def test_slots_behind_the_length_are_ignored_and_ids_outside_the_vocabulary_flag
     seqs = torch.arange(0, batch, max(1, batch // 300), device="cuda")
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, seqs=seqs, want_recovery_logprobs=False)
     parity.compare(out, ora, inp["uniforms"], lens, seqs=seqs)
+    if batch < 24000:
+        staged = in_stages(binding, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, draft_len=lens)
+        parity.compare(staged, ora, inp["uniforms"], lens, seqs=seqs)
 
 
 # A ragged batch's rows are looked up 64 sequences at a time from the last row's on: runs of 61 .. 129 sequences without a row
@@ -334,6 +354,7 @@ def test_slice_merge_edges(binding, oracle, dtype, vocab):
                                beta=w.beta, temperature=w.temperature, want_draft_logprobs=True)
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, want_recovery_logprobs=False)
     parity.compare(out, ora, inp["uniforms"], None)
+    parity.compare(in_stages(binding, inp, lam=w.lam, beta=w.beta, temperature=w.temperature), ora, inp["uniforms"], None)
 
 
 # Windows of 1, 1, 2, ... positions, at the fewest bytes a position that get them (240 MiB, 280 with 4 and 5
@@ -490,6 +511,8 @@ def test_odd_bases_with_even_strides(binding, oracle, vocab, late):
                                temperature=w.temperature, draft_len=inp["draft_len"], want_draft_logprobs=True)
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, want_recovery_logprobs=False)
     parity.compare(out, ora, inp["uniforms"], inp["draft_len"])
+    staged = in_stages(binding, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, draft_len=inp["draft_len"])
+    parity.compare(staged, ora, inp["uniforms"], inp["draft_len"])
 
 
 # Ratio test: 16 lanes to a (position, tensor) pair.  As many pairs as a workgroup has such groups (8 positions with 4 waves, 32
@@ -515,6 +538,7 @@ def test_ratio_test_rounds(binding, oracle, batch, k_max, vocab):
     seqs = torch.arange(0, batch, max(1, batch // 8), device="cuda")
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, seqs=seqs, want_recovery_logprobs=False)
     parity.compare(one, ora, inp["uniforms"], lens, seqs=seqs)
+    parity.compare(in_stages(binding, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, draft_len=lens), ora, inp["uniforms"], lens, seqs=seqs)
 
 
 # The same launch by chunks and drafts: up to 16 chunks it is one workgroup or several by the number of drafts, beyond them
@@ -530,6 +554,7 @@ def test_recovery_launch_by_chunks_and_drafts(binding, oracle, dtype, k_max, chu
     ora = parity.oracle_run(oracle, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, greedy=greedy,
                             want_recovery_logprobs=False)
     parity.compare(out, ora, inp["uniforms"], None)
+    parity.compare(in_stages(binding, inp, lam=w.lam, beta=w.beta, temperature=w.temperature, greedy=greedy), ora, inp["uniforms"], None)
 
 
 # Row pass in slices of one group of loads (256 vectors), of which a row's last holds 1 to 255 vectors, and of two (500 sequences, the first two sizes): at the edges
@@ -595,7 +620,54 @@ def test_small_blocks_in_one_launch(binding, oracle, dtype, batch, k_max, vocab,
     staged, again = call(True), call(False)
     for k in ("accepted_len", "next_token", "next_token_logprob"):
         assert torch.equal(torch.nan_to_num(first[k]), torch.nan_to_num(staged[k])), k
+    # their sums are grouped by chunks here and by slices there: each is within the bound to the oracle, so twice that apart
+    assert torch.allclose(first["draft_logprobs"], staged["draft_logprobs"], rtol=0, atol=2 * parity.LOGPROB_ATOL, equal_nan=True)
     assert all(first[k] is None or torch.equal(torch.nan_to_num(first[k]), torch.nan_to_num(again[k])) for k in names)
+
+
+# The same launch on rows at odd elements of some of the three tensors (`late`: those that begin one element late; without steering S_noctx
+# is read at G's parity whatever its own), with tokens masked by the generalist, whole chunks of them, by all three models and by the
+# specialist alone, a drafted one among them, and NaN in every row that has no say: those behind a length, and S_ctx but for the recovery row.
+ONCE_FORM_SIZES = [("bf16", 4, 3, 9 * 2048 + 7, "sgSG"), ("bf16", 4, 3, 9 * 2048 + 8, "sgSG"), ("f32", 4, 3, 9 * 1024 + 3, "sgSG")]
+
+
+@pytest.mark.parametrize("greedy,beta", [(False, 0.8), (True, 0.8), (False, 0.0), (True, 0.0)])
+@pytest.mark.parametrize("late", ["", "G", "S_noctx", "G S_ctx", "G S_noctx", "G S_ctx S_noctx"])
+@pytest.mark.parametrize("dtype,batch,k_max,vocab", [c[:4] for c in ONCE_FORM_SIZES])
+def test_small_blocks_in_one_launch_of_odd_and_masked_rows(binding, oracle, dtype, batch, k_max, vocab, late, greedy, beta):
+    w = recipe("c4", dtype, batch=batch, k_max=k_max, vocab=vocab)
+    inp = W.generate(w, "cuda")
+    lens = torch.tensor([3, 0, 2, 3], dtype=torch.int32, device="cuda")
+    inp["draft_len"] = lens
+    gen = torch.Generator("cuda").manual_seed(vocab)
+    chunk = vocab // 9
+    common, alone, spec = (torch.rand(inp["G"].shape, generator=gen, device="cuda") < x for x in (0.2, 0.2, 0.1))
+    common[:, :, chunk:2 * chunk] = True
+    alone[:, 1:, 5 * chunk:6 * chunk] = True
+    at = torch.arange(batch, device="cuda").view(-1, 1), torch.arange(k_max, device="cuda").view(1, -1), inp["draft"].long()
+    for m in (common, alone, spec):
+        m[at] = False
+    alone[0, 1, inp["draft"][0, 1]] = True
+    inp["uniforms"][0, :2] = torch.tensor([0.0, 0.5], device="cuda")  # rejected there
+    inp["uniforms"][3, :3] = 0.0                                      # all accepted
+    inp["G"][common | alone] = float("-inf")
+    for k in ("S_ctx", "S_noctx"):
+        inp[k][common | spec] = float("-inf")
+    kw = dict(lam=w.lam, beta=beta, temperature=w.temperature, greedy=greedy)
+    ora = parity.oracle_run(oracle, inp, want_recovery_logprobs=False, **kw)
+    for k in ("G", "S_ctx", "S_noctx"):
+        for b, n in enumerate(lens.tolist()):
+            inp[k][b, n + 1:] = float("nan")
+            if k == "S_ctx":
+                inp[k][b, torch.arange(k_max + 1, device="cuda") != int(ora["accepted_len"][b])] = float("nan")
+        flat = torch.full((inp[k].numel() + 8,), float("nan"), dtype=inp[k].dtype, device="cuda")
+        o = int(k in late.split())
+        flat[o:o + inp[k].numel()] = inp[k].flatten()
+        inp[k] = flat[o:o + inp[k].numel()].view_as(inp[k])
+    one = binding.verify_block(*(inp[k] for k in ("G", "S_ctx", "S_noctx", "draft", "uniforms")), draft_len=lens, want_draft_logprobs=True, **kw)
+    assert one["accepted_len"].tolist()[::3] == [1, 3]
+    parity.compare(one, ora, inp["uniforms"], lens)
+    parity.compare(in_stages(binding, inp, draft_len=lens, **kw), ora, inp["uniforms"], lens)
 
 
 # Without steering the bonus position asks for nothing but the generalist's row: S_noctx ends behind its k_max rows here (what follows

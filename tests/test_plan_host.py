@@ -194,7 +194,7 @@ def test_the_blocks_meant_for_one_launch_take_it(planner):
     """The sizes of the GPU tests of that launch, which could not tell: two launches give the same answers."""
     import test_gpu_kernel_edges as edges
 
-    for ragged, sizes in ((1, edges.ONCE_SIZES), (1, edges.ONCE_GRAPH_SIZES)):
+    for ragged, sizes in ((1, edges.ONCE_SIZES), (1, edges.ONCE_GRAPH_SIZES), (1, edges.ONCE_FORM_SIZES)):
         for dtype, batch, k_max, vocab, modes in sizes:
             got = "".join(m for m, plain, greedy in (("s", 0, 0), ("g", 0, 1), ("S", 1, 0), ("G", 1, 1))
                           if route(planner, dtype, batch, k_max, vocab, plain, greedy, ragged)[0])
