@@ -41,6 +41,7 @@
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "device_common.h"
 #include "plan.h"
@@ -388,17 +389,20 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
         // at a time they were up to three round trips behind each other in one item of eight or sixteen (96 sequences of 8 drafts, V = 32000
         // 35.0 -> 30.9 us a step, 64 of 4 19.7 -> 18.2, 500 of 4 69.3 -> 64.7, 160 ragged of 8 32.6 -> 31.0, 20 of 8, V = 50257 18.7 -> 18.3).  Behind
         // the groups of longer slices other waves cover them, and the sums over logits that are not there cost more (256 ragged of V = 50257
-        // 61.7 -> 62.6), as they do for a single load a lane.
-        if (slice_units <= 2 * kGroup && v1 - v0 - nfull * kGroup > kWave) {
-            typename RawT<DT, VEC>::type raw[kUnroll];
-            float h[kUnroll * VEC];
+        // 61.7 -> 62.6), as they do for a single load a lane.  Two loads a lane are a group of two: as one of four, half of
+        // it not there, they took many short rows longer than a vector at a time did (us a step a vector at a time, as a group of four, of two:
+        // 296 sequences of 34 drafts, V = 545 26.1, 28.0, 25.4, 397 of 63, V = 976 48.6, 50.9, 44.9, 211 of 32, V = 4648 37.7, 39.1, 37.2).
+        const auto take_end = [&](auto loads) {
+            constexpr int N = decltype(loads)::value;
+            typename RawT<DT, VEC>::type raw[N];
+            float h[N * VEC];
 #pragma unroll
-            for (int j = 0; j < kUnroll; ++j) {
+            for (int j = 0; j < N; ++j) {
                 raw[j] = neg_inf_raw<DT, VEC>();
                 if (v + (long)kWave * j < v1) raw[j] = ld_raw<DT, VEC>(row, v + (long)kWave * j);
             }
 #pragma unroll
-            for (int j = 0; j < kUnroll; ++j) {
+            for (int j = 0; j < N; ++j) {
                 if (yv >= 0 && v + (long)kWave * j == v0 + yv) *y_out = elem_of(raw[j], ye % VEC);
                 if (j == 0 && masked && v == 0) raw[0] = set_first(raw[0], kBf16NegInf);
                 float hj[VEC];
@@ -406,8 +410,13 @@ __global__ __launch_bounds__(kLseThreads) void row_lse_kernel(const LseArgs a) {
 #pragma unroll
                 for (int i = 0; i < VEC; ++i) h[j * VEC + i] = hj[i];
             }
-            acc_add_f32<kUnroll * VEC>(acc, h, a.c_hi);
+            acc_add_f32<N * VEC>(acc, h, a.c_hi);
             v = v1;
+        };
+        const long rest = v1 - v0 - nfull * kGroup;
+        if (slice_units <= 2 * kGroup && rest > kWave) {
+            if (rest <= 2 * kWave) take_end(std::integral_constant<int, 2>{});
+            else take_end(std::integral_constant<int, kUnroll>{});
         }
         for (; v < v1; v += kWave) {
             typename RawT<DT, VEC>::type raw = ld_raw<DT, VEC>(row, v);

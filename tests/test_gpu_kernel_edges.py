@@ -558,11 +558,11 @@ def test_recovery_launch_by_chunks_and_drafts(binding, oracle, dtype, k_max, chu
 
 
 # Row pass in slices of one group of loads (256 vectors), of which a row's last holds 1 to 255 vectors, and of two (500 sequences, the first two sizes): at the edges
-# of its four loads, with logits past the last vector and without, rows at odd elements, and the draft tokens' logits in that slice.
+# of its two or four loads, with logits past the last vector and without, rows at odd elements, and the draft tokens' logits in that slice.
 @pytest.mark.parametrize("batch", [200, 500])
 @pytest.mark.parametrize("dtype,vocab", [(dt, (8 if dt == "bf16" else 4) * (256 * groups + more) + rest) for dt, groups, more, rest in (
-    ("bf16", 15, 160, 0), ("bf16", 14, 66, 1), ("bf16", 3, 1, 0), ("bf16", 3, 63, 3), ("bf16", 3, 64, 0), ("bf16", 3, 65, 0), ("bf16", 0, 130, 1), ("bf16", 1, 192, 0), ("bf16", 2, 255, 7),
-    ("f32", 3, 1, 0), ("f32", 2, 64, 3), ("f32", 0, 129, 0), ("f32", 1, 255, 1))])
+    ("bf16", 15, 160, 0), ("bf16", 14, 66, 1), ("bf16", 3, 1, 0), ("bf16", 3, 63, 3), ("bf16", 3, 64, 0), ("bf16", 3, 65, 0), ("bf16", 0, 127, 5), ("bf16", 2, 128, 0), ("bf16", 0, 130, 1), ("bf16", 1, 192, 0), ("bf16", 2, 255, 7),
+    ("f32", 3, 1, 0), ("f32", 2, 64, 3), ("f32", 0, 65, 2), ("f32", 1, 128, 1), ("f32", 0, 129, 0), ("f32", 1, 255, 1))])
 def test_row_pass_at_the_end_of_short_slices(binding, oracle, dtype, vocab, batch):
     k_max = 4
     w = recipe("c4", dtype, batch=batch, k_max=k_max, vocab=vocab)
