@@ -242,13 +242,17 @@ inline size_t once_lds(int kmax, int NC, bool greedy) {
 //     without a steering term either from 4 chunks on (lengths 510, V = 9000 13.5 -> 12.9; 640 13.8 -> 15.1).
 //   - Sampled fp32 up to 3 (760, V = 8192 14.4 -> 13.1, V = 6166 13.4 -> 13.3; 890 13.7 -> 14.4, 1020 14.3 -> 15.4), with lengths or without a steering term as
 //     far as longer rows.
+//   - Sampled ones of 4 whole chunks and less than half of a fifth, where every second workgroup has little to do: fp32 up to 2 (552, V = 4344
+//     12.1 -> 12.4; 700, V = 4211 11.9 -> 12.7; 742, V = 4242 12.4 -> 13.4, 720, V = 4410 12.6 -> 13.1), with lengths or without a steering term up to 3 (750, V = 4171 11.2 -> 10.8;
+//     928, V = 4130 13.3 -> 14.3, 976, V = 4316 13.0 -> 13.9), bf16 up to 1 1/2 (408, V = 8484 12.4 -> 13.1).
 inline bool block_in_one_launch(int B, int kmax, int V, int NC, int dtype, bool plain, bool greedy, bool ragged, int cus) {
     if (kmax < 1 || kmax > kOnceMaxDrafts || NC > kOnceMaxParts * kOnceWaves) return false;
-    const bool bf16 = dtype == SS_BF16, brief = NC <= 8, reduced = plain || ragged;
-    if (greedy && (bf16 || !plain) && V < 5 * kChunkSteps * kWave * (bf16 ? 8 : 4)) return false;
+    const int chunk = kChunkSteps * kWave * (dtype == SS_BF16 ? 8 : 4);
+    const bool bf16 = dtype == SS_BF16, brief = NC <= 8, reduced = plain || ragged, barely = V > 4 * chunk && 2l * V < 9l * chunk;
+    if (greedy && (bf16 || !plain) && V < 5 * chunk) return false;
     const int eighths = greedy ? (bf16 ? (plain && !brief ? 16 : 8) : plain ? 16 : brief ? 8 : 12)
-                        : bf16 ? (brief ? (reduced && NC < 4 ? 24 : 16) : reduced ? 24 : 17)
-                               : (brief && !reduced ? 24 : 32);
+                        : bf16 ? (brief ? (reduced ? (NC < 4 ? 24 : 16) : barely ? 12 : 16) : reduced ? 24 : 17)
+                               : (barely ? (reduced ? 24 : 16) : brief && !reduced ? 24 : 32);
     return 8l * B * (kmax + 1) * ((NC + kOnceWaves - 1) / kOnceWaves) <= (long)eighths * cus;
 }
 

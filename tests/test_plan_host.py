@@ -202,6 +202,17 @@ def test_the_blocks_meant_for_one_launch_take_it(planner):
     assert {m for c in edges.ONCE_SIZES for m in c[4]} == set("sgSG")
 
 
+# Rows of 4 whole chunks and less than half of a fifth (and, in a chunk of their own, logits past the last vector), and of half and more.
+@pytest.mark.parametrize("dtype,vocab,plain,ragged,most", [
+    ("f32", 4096, 0, 0, 768), ("f32", 4100, 0, 0, 512), ("f32", 4607, 0, 0, 512), ("f32", 4608, 0, 0, 768), ("f32", 4101, 0, 1, 768), ("f32", 4607, 1, 0, 768), ("f32", 4608, 0, 1, 1024),
+    ("bf16", 8194, 0, 0, 384), ("bf16", 9215, 0, 0, 384), ("bf16", 9216, 0, 0, 512), ("bf16", 8200, 0, 1, 512), ("bf16", 8200, 1, 0, 512)])
+def test_a_short_fifth_chunk_takes_one_launch_less_far(planner, dtype, vocab, plain, ragged, most):
+    for k_max in (7, 15):
+        per = (1 if vocab == 4096 else 2) * (k_max + 1)
+        for batch in (most // per, most // per + 1):
+            assert route(planner, dtype, batch, k_max, vocab, plain=plain, ragged=ragged)[0] == int(batch * per <= most), (k_max, batch)
+
+
 # One user and a few, as the benchmark and serving have them; and what is beyond the lines or the space.
 @pytest.mark.parametrize("dtype,batch,k_max,vocab,greedy,one", [
     ("f32", 1, 4, 32000, 0, 1), ("f32", 1, 4, 32000, 1, 1), ("bf16", 1, 8, 128256, 0, 1), ("bf16", 4, 8, 50257, 0, 1), ("bf16", 1, 4, 151936, 0, 0),
