@@ -148,7 +148,9 @@ size_t specsteer_workspace_bytes(const ss_params *params);
  * Rows without drafts (k_max == 0, up to 128 of them): a call outside stream capture is
  * shaped for a caller bound by the host's time and takes rows of medium length in one
  * launch, where two would take the GPU as little as half the time; under capture, where
- * launches cost no host time, only the GPU's counts.  The outputs are the same.
+ * launches cost no host time, only the GPU's counts.  The outputs are the same.  (The Python
+ * binding takes less host time than such a call takes the GPU when its arguments need no
+ * conversion, and has rows shaped for the GPU outside of capture too.)
  *
  * Errors.  Argument errors are detected on the host before anything is
  * enqueued and leave every output untouched.  Data errors that only the GPU
@@ -197,7 +199,9 @@ ss_status specsteer_verify_block_static(const void *G, const void *S_ctx, const 
  * Eq. 7, Eq. 8; same arguments, same outputs, same errors).  It brackets each kernel with
  * HIP events recorded on `stream`, WAITS for the last one, and writes the elapsed
  * milliseconds of each stage to the host array stage_ms[SS_NUM_STAGES]:
- * (a small block that the other entry points take in one launch has its stages one behind the other here)
+ * (A small block that the other entry points take in one launch has its stages one behind the other here.  Its sums are
+ * grouped differently then: log-probs agree to their rounding, 1e-5, and only where a uniform lies within that of an
+ * acceptance probability or of an edge between tokens may the decision differ.)
  *   [SS_STAGE_ROW_PASS1] log-sum-exp pass over G and S_noctx, positions [0, first window),
  *   [SS_STAGE_VERDICT]   ratio test on those positions (0 in the one-pass schedule),
  *   [SS_STAGE_ROW_PASS2] log-sum-exp passes over the remaining positions of the sequences still in

@@ -74,6 +74,9 @@ constexpr int kSplitMaxBatch = 128;  // workspace is reserved for shared recover
 //     drafts: 17.0 -> 17.4, 32 18.4 -> 18.9); a single part of 4 waves with more than 8 drafts (V = 2000, 12 drafts: 12.1 ->
 //     12.4).  Beyond 16 chunks up to 32 drafts (V = 151936: 24 drafts 27.1 -> 24.8, 32 30.8 -> 29.1; one sequence of V = 40000,
 //     48 drafts: 17.1 -> 17.9).
+//     The blocks of up to 16 drafts in these figures take one launch now, but for calls that want log-prob rows. What still comes here,
+//     spread instead of 16 waves, as multiples of the time in the middle of some 200 calls each: 17 to 32 drafts up to 4 chunks 1.09, 5 to 8
+//     1.08 to 1.14, 9 to 12 1.03 to 1.07, 13 to 16 1.00; 9 to 16 drafts with log-prob rows up to 4 chunks 1.08.
 //   - At least two compute units per sequence: as many 16-wave parts as there are units per sequence, and no more than rounds of
 //     16 chunks (80 sequences of V = 100000, 49 chunks: 38.5 us a step in 2 equal parts of two rounds, 36.9 in 3 of 17, 36.2 with
 //     the chunk over dealt out in quarters).
@@ -214,7 +217,7 @@ inline OnceSpace once_space(int kmax, int NC, bool greedy) {
     return s;
 }
 
-// Its LDS: the masses, the drafts' log-probs, the partials and the candidates of a sequence.
+// Its LDS: the masses, the rows' merged partials, what the parts delivered of them, and the candidates of a sequence.
 inline size_t once_lds(int kmax, int NC, bool greedy) {
     const size_t positions = (size_t)kmax + 1, parts = (size_t)(NC + kOnceWaves - 1) / kOnceWaves;
     return positions * NC * sizeof(Partial) + 2 * kmax * sizeof(double) + 4 * kmax * parts * sizeof(unsigned) +
